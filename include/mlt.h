@@ -60,8 +60,8 @@ typedef enum {
  *
  * M, N or K may be 0: M == 0 or N == 0 is a no-op, K == 0 stores zeros. Any positive shape and
  * any leading dimensions/alignments are accepted; shapes and pointers that allow 16-byte vector
- * access (K, N, lda, ldb multiples of 8 and 16-byte aligned bases) take the fast kernels, others
- * a slower general kernel with identical results up to summation order.
+ * access (K, N, lda, ldb multiples of 8 and 16-byte aligned bases) take the fastest kernels, others
+ * forms of the tile kernels for any alignment, with identical results up to summation order.
  */
 int mlt_gemm(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B,
              int64_t ldb, int transB, void* C, int64_t ldc, int dtype, void* stream);

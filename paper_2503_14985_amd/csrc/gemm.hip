@@ -13,372 +13,9 @@
 // work on the same sub-block of A or B).
 #include <mutex>
 
-#include "mlt_common.h"
-#include "mlt_internal.h"
+#include "gemm_tile.h"
 
 namespace mlt {
-
-// ------------------------------------------------------------------------------------------
-// Main kernel. Requirements checked by the host: K % 8 == 0, lda % 8 == 0, ldb % 8 == 0,
-// N % 8 == 0 when B is K x N row-major, A and B 16-byte aligned. M, N and K need not be
-// multiples of the tile: out-of-range rows are clamped on load (their products land in
-// accumulator rows/columns that are never stored) and the K tail is zero-filled.
-//
-// LDS layout per stage (elements are 16-bit):
-//   A tile   [BM][BK + 8]          k contiguous; the 16-byte pad makes the row stride 36 dwords,
-//                                  so 16 consecutive rows at one k offset fall in 16 distinct
-//                                  4-bank groups of the 64 banks
-//   B tile   TRANSB:  [BN][BK + 8] same as A (global B is N x K, k contiguous)
-//            !TRANSB: [BK][BN + 32] n contiguous, as in global memory; fragments are fetched with
-//                                  the transposing LDS read; the 64-byte pad puts the 4 k-rows of
-//                                  a 16-lane read group into disjoint bank ranges
-// Two stages; global loads for step k+1 are issued before the MFMAs of step k, parked in
-// registers and written to the other stage afterwards, one barrier per step.
-// ------------------------------------------------------------------------------------------
-template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB>
-struct GemmTile {
-  static constexpr int NT = WM * WN * 64;
-  static constexpr int KC = BK / 8;                     // 16-byte chunks along k
-  static constexpr int LDA_S = BK + 8;
-  static constexpr int A_BYTES = BM * LDA_S * 2;
-  static constexpr int LDB_S = TRANSB ? BK + 8 : BN + 32;
-  static constexpr int B_BYTES = (TRANSB ? BN : BK) * LDB_S * 2;
-  static constexpr int STAGE = A_BYTES + B_BYTES;
-  static constexpr int SMEM = 2 * STAGE;
-  static constexpr int NA = BM * KC / NT;               // chunks per thread per stage
-  static constexpr int NB = BN * KC / NT;
-  static constexpr int TM = BM / WM / 32;               // MFMA tiles per wavefront
-  static constexpr int TN = BN / WN / 32;
-  static_assert(BM * KC % NT == 0 && BN * KC % NT == 0, "tile must split evenly over threads");
-  static_assert(NT % KC == 0 && NT % (BN / 8) == 0, "a thread's chunks must share their column");
-  static_assert(BK % 16 == 0 && BM % (WM * 32) == 0 && BN % (WN * 32) == 0, "MFMA tiling");
-};
-
-// K split across workgroups (part_steps > 0): the grid's y index is the part; part p takes the K
-// steps p * part_steps .. of the problem and stores its fp32 partial tile (epi = EPI_PART32) into
-// slice p of the scratch that C_ then points at (slices part_stride floats apart, row stride ldc);
-// gemm_splitk_reduce_kernel adds the slices in a fixed order and applies the real epilogue.
-template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB, int KS>
-__global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
-    int M, int N, int K_, const uint16_t* __restrict__ A_, int64_t lda,
-    const uint16_t* __restrict__ B_, int64_t ldb, uint16_t* __restrict__ C_, int64_t ldc, int nbm,
-    int nbn, int nxcd, int epi, const uint16_t* __restrict__ bias, int part_steps, int64_t part_stride) {
-  typedef GemmTile<Tag, BM, BN, BK, WM, WN, TRANSB> Cfg;
-  typedef typename Elem<Tag>::vec8 V8;
-  extern __shared__ __align__(16) char smem_all[];
-  const uint16_t* A = A_;
-  const uint16_t* B = B_;
-  uint16_t* C = C_;
-  int K = K_;
-  if (part_steps > 0) {
-    const int part = blockIdx.y;
-    const int k_begin = part * part_steps * BK;            // < K_: the host launches no empty part
-    A += k_begin;
-    B += TRANSB ? (int64_t)k_begin : (int64_t)k_begin * ldb;
-    K = K_ - k_begin < part_steps * BK ? K_ - k_begin : part_steps * BK;
-    C = reinterpret_cast<uint16_t*>(reinterpret_cast<float*>(C_) + (int64_t)part * part_stride);
-  }
-
-  // KS > 1: the workgroup holds KS groups of WM x WN wavefronts; group kg runs the whole pipeline
-  // below on its own LDS stages over its own share of the K steps, and the groups' accumulators
-  // are added through LDS at the end (see there). tid, wave: inside the group.
-  const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / Cfg::NT);
-  const int tid = KS == 1 ? (int)threadIdx.x : (int)threadIdx.x % Cfg::NT;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WN, wn = wave % WN;
-  char* const smem = smem_all + kg * Cfg::SMEM;
-  int tile_m, tile_n;
-  tile_of_block<8>(blockIdx.x, nbm, nbn, nxcd, tile_m, tile_n);
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-
-  // ---- per-thread staging assignments (fixed for the whole K loop)
-  // Chunk c = tid + i*NT of a [rows][KC] tile is (row c / KC, k chunk c % KC). NT is a multiple of
-  // KC, so the k chunk is the same for every i and row_i = row_0 + i * (NT / KC): LDS offsets
-  // differ by compile-time constants and only the clamped global row pointers are per-i values.
-  constexpr int RSTEP = Cfg::NT / Cfg::KC;              // tile rows between a thread's chunks
-  const int st_row = tid / Cfg::KC, st_k = (tid % Cfg::KC) * 8;
-  const uint16_t* a_src[Cfg::NA];
-#pragma unroll
-  for (int i = 0; i < Cfg::NA; ++i) {
-    int grow = m0 + st_row + i * RSTEP;
-    grow = grow < M ? grow : M - 1;
-    a_src[i] = A + (int64_t)grow * lda + st_k;
-  }
-  const int a_dst = (st_row * Cfg::LDA_S + st_k) * 2;
-  constexpr int A_DST_STEP = RSTEP * Cfg::LDA_S * 2;
-
-  const uint16_t* b_src[TRANSB ? Cfg::NB : 1];
-  int b_dst, b_k;
-  constexpr int NC = BN / 8;                            // 16-byte chunks along n (row-major B)
-  constexpr int KSTEP = Cfg::NT / NC;                   // k rows between a thread's chunks
-  constexpr int B_DST_STEP = (TRANSB ? RSTEP : KSTEP) * Cfg::LDB_S * 2;
-  if (TRANSB) {
-#pragma unroll
-    for (int i = 0; i < Cfg::NB; ++i) {
-      int grow = n0 + st_row + i * RSTEP;
-      grow = grow < N ? grow : N - 1;
-      b_src[i] = B + (int64_t)grow * ldb + st_k;
-    }
-    b_dst = Cfg::A_BYTES + (st_row * Cfg::LDB_S + st_k) * 2;
-    b_k = st_k;
-  } else {
-    const int krow = tid / NC, nc = tid % NC;
-    const int gcol = n0 + nc * 8;
-    // N % 8 == 0: a chunk is all in or all out; an outside chunk reads column 0 instead
-    b_src[0] = B + (int64_t)krow * ldb + (gcol < N ? gcol : 0);
-    b_dst = Cfg::A_BYTES + (krow * Cfg::LDB_S + nc * 8) * 2;
-    b_k = krow;
-  }
-
-  u32x4 ga[Cfg::NA], gb[Cfg::NB];
-  const u32x4 zero4 = {0u, 0u, 0u, 0u};
-
-  // Loads never branch per element: a chunk outside the matrix re-reads a valid address (row
-  // clamp above, column 0 here). Only the last K step can run past K; it takes the second form,
-  // which re-reads k = 0 for chunks past K and zeroes them (they would pollute real outputs).
-  auto load_global_full = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < Cfg::NA; ++i) ga[i] = *reinterpret_cast<const u32x4_mem*>(a_src[i] + k0);
-#pragma unroll
-    for (int i = 0; i < Cfg::NB; ++i) {
-      if (TRANSB) gb[i] = *reinterpret_cast<const u32x4_mem*>(b_src[i] + k0);
-      else gb[i] = *reinterpret_cast<const u32x4_mem*>(b_src[0] + (int64_t)(k0 + i * KSTEP) * ldb);
-    }
-  };
-  auto load_global_tail = [&](int k0) {
-#pragma unroll
-    for (int i = 0; i < Cfg::NA; ++i) {
-      const bool ok = k0 + st_k < K;
-      const u32x4 v = *reinterpret_cast<const u32x4_mem*>(a_src[i] + (ok ? k0 : -st_k));
-      ga[i] = ok ? v : zero4;
-    }
-#pragma unroll
-    for (int i = 0; i < Cfg::NB; ++i) {
-      if (TRANSB) {
-        const bool ok = k0 + b_k < K;
-        const u32x4 v = *reinterpret_cast<const u32x4_mem*>(b_src[i] + (ok ? k0 : -b_k));
-        gb[i] = ok ? v : zero4;
-      } else {
-        const int kr = k0 + i * KSTEP;                  // + b_k = the k row of this chunk
-        const bool ok = kr + b_k < K;
-        const u32x4 v = *reinterpret_cast<const u32x4_mem*>(b_src[0] + (int64_t)(ok ? kr : -b_k) * ldb);
-        gb[i] = ok ? v : zero4;
-      }
-    }
-  };
-  auto load_global = [&](int k0, bool tail) {
-    if (tail) load_global_tail(k0); else load_global_full(k0);
-  };
-  auto store_lds = [&](int stage) {
-    char* base = smem + stage * Cfg::STAGE;
-#pragma unroll
-    for (int i = 0; i < Cfg::NA; ++i) *reinterpret_cast<u32x4_mem*>(base + a_dst + i * A_DST_STEP) = ga[i];
-#pragma unroll
-    for (int i = 0; i < Cfg::NB; ++i) *reinterpret_cast<u32x4_mem*>(base + b_dst + i * B_DST_STEP) = gb[i];
-  };
-
-  // ---- fragment addresses inside a stage
-  // A fragment: row = wavefront row offset + 32*tm + lane%32, 8 consecutive k starting at
-  // 8*(lane/32) inside each 16-wide k slice.
-  const int a_frag = ((wm * (BM / WM) + (lane & 31)) * Cfg::LDA_S + 8 * (lane >> 5)) * 2;
-  int b_frag;
-  if (TRANSB) {
-    b_frag = Cfg::A_BYTES + ((wn * (BN / WN) + (lane & 31)) * Cfg::LDB_S + 8 * (lane >> 5)) * 2;
-  } else {
-    // Transposing read: 16-lane group g = lane/16 serves columns 16*(g%2).. of the 32-wide tile
-    // and k slots 8*(g/2)..; inside the group, lane s addresses k row s/4, columns 4*(s%4)..
-    const int g = lane >> 4, s = lane & 15;
-    const int krow = 8 * (g >> 1) + (s >> 2);
-    const int col = wn * (BN / WN) + 16 * (g & 1) + 4 * (s & 3);
-    b_frag = Cfg::A_BYTES + (krow * Cfg::LDB_S + col) * 2;
-  }
-
-  f32x16 acc[Cfg::TM][Cfg::TN];
-#pragma unroll
-  for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-    for (int j = 0; j < Cfg::TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // Fragments of k slice kk of a stage: TM A operands and TN B operands.
-  auto load_frags = [&](const char* st, int kk, V8 (&af)[Cfg::TM], V8 (&bf)[Cfg::TN]) {
-#pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i)
-      af[i] = lds_read8<V8>(st, a_frag + (i * 32 * Cfg::LDA_S + kk * 16) * 2);
-#pragma unroll
-    for (int j = 0; j < Cfg::TN; ++j) {
-      if (TRANSB) {
-        bf[j] = lds_read8<V8>(st, b_frag + (j * 32 * Cfg::LDB_S + kk * 16) * 2);
-      } else {
-        const int off = b_frag + (kk * 16 * Cfg::LDB_S + j * 32) * 2;
-        s16x4 lo = lds_read_tr4(st, off);
-        s16x4 hi = lds_read_tr4(st, off + 4 * Cfg::LDB_S * 2);
-        bf[j] = join_tr<V8>(lo, hi);
-      }
-    }
-  };
-
-  const int KT = (K + BK - 1) / BK;
-  const bool ragged_k = (K % BK) != 0;                  // only the last step can be partial
-  constexpr int NKK = BK / 16;
-  static_assert(NKK == 4, "the schedule below is written for four k slices per stage");
-  // This group's K steps: kg, kg + KS, kg + 2 KS, ... (all of them when KS == 1), so that at any
-  // time the groups of a workgroup read neighbouring pieces of the same operand rows (with the
-  // operands stored k-contiguous: KS x 128 contiguous bytes of every row instead of KS pieces far
-  // apart); every group runs the loop KTG times so that all wavefronts meet at the same barriers,
-  // idle once its steps are done.
-  const int KTG = (KT + KS - 1) / KS;
-  const int kt_begin = kg;
-  const int kt_end = KT;
-  auto load_tile = [&](int t) { load_global(t * BK, ragged_k && t == KT - 1); };
-
-  // Software pipeline. Stage s holds the group's i-th tile (s = i & 1). During step kt:
-  //   slice 0: read fragments of slice 1 | MFMAs of slice 0
-  //   slice 1: read fragments of slice 2 | MFMAs of slice 1 | write tile kt+1 (already in
-  //            registers since the previous step) to the other stage | issue the global loads
-  //            of tile kt+2 into the registers just freed
-  //   slice 2: read fragments of slice 3 | MFMAs of slice 2 | barrier
-  //   slice 3: read fragments of slice 0 of tile kt+1 | MFMAs of slice 3
-  // The barrier sits where every wavefront has issued its last read of stage s and its writes
-  // of tile kt+1, so after it stage s may be overwritten (in step kt+1) and tile kt+1 may be
-  // read; its latency and that of the first fragment reads hide behind the MFMAs of slice 3.
-  const bool any = kt_begin < kt_end;
-  if (any) {
-    load_tile(kt_begin);
-    store_lds(0);
-    if (kt_begin + KS < kt_end) load_tile(kt_begin + KS);
-  }
-  __syncthreads();
-
-  V8 af[2][Cfg::TM], bf[2][Cfg::TN];
-  if (any) load_frags(smem, 0, af[0], bf[0]);
-
-  auto mfma_slice = [&](int which) {
-#pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < Cfg::TN; ++j)
-        acc[i][j] = mfma32(af[which][i], bf[which][j], acc[i][j]);
-  };
-
-  for (int it = 0; it < KTG; ++it) {
-    const int kt = kt_begin + it * KS;
-    const bool active = KS == 1 || kt < kt_end;
-    const int cur = it & 1;
-    const char* st = smem + cur * Cfg::STAGE;
-    const char* nx = smem + (cur ^ 1) * Cfg::STAGE;
-    const bool have_next = kt + KS < kt_end;
-
-    if (active) {
-      load_frags(st, 1, af[1], bf[1]);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_slice(0);
-      __builtin_amdgcn_sched_barrier(0);
-
-      load_frags(st, 2, af[0], bf[0]);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_slice(1);
-      __builtin_amdgcn_sched_barrier(0);
-      if (have_next) {
-        store_lds(cur ^ 1);
-        if (kt + 2 * KS < kt_end) load_tile(kt + 2 * KS);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-
-      load_frags(st, 3, af[1], bf[1]);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_slice(0);                                    // slice 2 lives in fragment set 0
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads();
-
-    if (active) {
-      if (have_next) load_frags(nx, 0, af[0], bf[0]);
-      __builtin_amdgcn_sched_barrier(0);
-      mfma_slice(1);                                    // slice 3 lives in fragment set 1
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-
-  // ---- KS > 1: add the groups' accumulators. Groups 1 .. KS-1 park theirs in LDS (the stages
-  // are free now), register r of MFMA tile (i, j) of wavefront w at float index
-  // ((w*TM*TN + i*TN + j)*16 + r)*64 + lane of the group's area (consecutive lanes, consecutive
-  // words); group 0 adds them in the order 1, 2, ... and goes on to the epilogue alone.
-  if (KS > 1) {
-    static_assert(KS == 1 || (KS - 1) * BM * BN * 4 <= KS * Cfg::SMEM, "reduction area fits the stages");
-    __syncthreads();
-    float* red = reinterpret_cast<float*>(smem_all);
-    const int mine = wave * Cfg::TM * Cfg::TN * 16 * 64 + lane;
-    if (kg > 0) {
-      float* dst = red + (kg - 1) * (BM * BN) + mine;
-#pragma unroll
-      for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) dst[((i * Cfg::TN + j) * 16 + r) * 64] = acc[i][j][r];
-    }
-    __syncthreads();
-    if (kg > 0) return;
-#pragma unroll
-    for (int g2 = 1; g2 < KS; ++g2) {
-      const float* src = red + (g2 - 1) * (BM * BN) + mine;
-#pragma unroll
-      for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] += src[((i * Cfg::TN + j) * 16 + r) * 64];
-    }
-  }
-
-  // ---- epilogue: fp32 -> 16-bit (RNE), guarded element stores
-  const int row_base = m0 + wm * (BM / WM) + 4 * (lane >> 5);
-  const int col_base = n0 + wn * (BN / WN) + (lane & 31);
-  // Plain 16-bit store with even N and ldc: neighbouring lanes (columns c, c+1 of the same rows)
-  // exchange two of every four values, so that the even lane holds rows 0, 1 and the odd lane
-  // rows 2, 3 of both columns of a register group: 32-bit stores, half as many.
-  if (epi == 0 && bias == nullptr && !(N & 1) && !(ldc & 1) && !(reinterpret_cast<uintptr_t>(C) & 3)) {
-    const bool odd = lane & 1;
-    auto neighbour = [](float x) {                        // the value lane l ^ 1 passes in
-      return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, true));
-    };
-    const int col0 = col_base - (odd ? 1 : 0);
-#pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < Cfg::TN; ++j) {
-        const int col = col0 + j * 32;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float got0 = neighbour(odd ? acc[i][j][4 * g] : acc[i][j][4 * g + 2]);
-          const float got1 = neighbour(odd ? acc[i][j][4 * g + 1] : acc[i][j][4 * g + 3]);
-          const uint32_t w0 = odd ? Elem<Tag>::pack2(got0, acc[i][j][4 * g + 2]) : Elem<Tag>::pack2(acc[i][j][4 * g], got0);
-          const uint32_t w1 = odd ? Elem<Tag>::pack2(got1, acc[i][j][4 * g + 3]) : Elem<Tag>::pack2(acc[i][j][4 * g + 1], got1);
-          const int row = row_base + i * 32 + 8 * g + (odd ? 2 : 0);
-          if (col < N) {
-            if (row < M) *reinterpret_cast<uint32_t*>(C + (int64_t)row * ldc + col) = w0;
-            if (row + 1 < M) *reinterpret_cast<uint32_t*>(C + (int64_t)(row + 1) * ldc + col) = w1;
-          }
-        }
-      }
-    return;
-  }
-  gemm_epilogue<Tag>([&](auto&& out) {
-#pragma unroll
-    for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < Cfg::TN; ++j) {
-        const int col = col_base + j * 32;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = row_base + i * 32 + 8 * (r >> 2) + (r & 3);
-          if (row < M && col < N) out((int64_t)row * ldc + col, col, acc[i][j][r]);
-        }
-      }
-  }, C, epi, bias);
-}
 
 // ------------------------------------------------------------------------------------------
 // General kernel: any M, N, K, leading dimensions and alignment. 64 x 64 x 32 tile, 4 wavefronts
@@ -438,34 +75,6 @@ __global__ __launch_bounds__(256) void gemm_general_kernel(
   }, C, epi, bias);
 }
 
-// Second pass of a K split across workgroups: C = epilogue(sum over parts, in the order 0, 1, ...,
-// of the fp32 partial products). One thread per four consecutive columns of a row.
-template <typename Tag>
-__global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(
-    int M, int N, int parts, const float* __restrict__ ws, int64_t part_stride,
-    uint16_t* __restrict__ C, int64_t ldc, int epi, const uint16_t* __restrict__ bias) {
-  const int nq = (N + 3) / 4;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= (int64_t)M * nq) return;
-  const int row = (int)(t / nq), col0 = (int)(t % nq) * 4;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  const float* src = ws + (int64_t)row * N + col0;
-  if (col0 + 3 < N && (N & 3) == 0) {
-    for (int p = 0; p < parts; ++p) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(src + (int64_t)p * part_stride);
-      acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
-    }
-  } else {
-    for (int p = 0; p < parts; ++p)
-      for (int e = 0; e < 4; ++e)
-        if (col0 + e < N) acc[e] += src[(int64_t)p * part_stride + e];
-  }
-  gemm_epilogue<Tag>([&](auto&& out) {
-    for (int e = 0; e < 4; ++e)
-      if (col0 + e < N) out((int64_t)row * ldc + col0 + e, col0 + e, acc[e]);
-  }, C, epi, bias);
-}
-
 // K == 0: the empty sum (only launched when C is overwritten; C += 0 is a no-op).
 __global__ void gemm_zero_kernel(int M, int N, uint16_t* __restrict__ C, int64_t ldc) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -475,44 +84,6 @@ __global__ void gemm_zero_kernel(int M, int N, uint16_t* __restrict__ C, int64_t
 // ------------------------------------------------------------------------------------------
 // Host side
 // ------------------------------------------------------------------------------------------
-template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB, int KS>
-static int launch_tile(const GemmArgs& g, hipStream_t s) {
-  typedef GemmTile<Tag, BM, BN, BK, WM, WN, TRANSB> Cfg;
-  static_assert(Cfg::NT * KS <= 1024 && KS * Cfg::SMEM <= 160 * 1024, "one workgroup, one CU's LDS");
-  auto kern = gemm_tile_kernel<Tag, BM, BN, BK, WM, WN, TRANSB, KS>;
-  static thread_local int configured_dev = -1;          // opt in to > 64 KB LDS once per device
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return MLT_ERR_DEVICE;
-  if (configured_dev != dev) {
-    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            KS * Cfg::SMEM) != hipSuccess) {
-      (void)hipGetLastError();
-      return MLT_ERR_LAUNCH;
-    }
-    configured_dev = dev;
-  }
-  const int nbm = (int)((g.M + BM - 1) / BM), nbn = (int)((g.N + BN - 1) / BN);
-  if (g.parts <= 1) {
-    hipLaunchKernelGGL(kern, dim3(nbm * nbn), dim3(Cfg::NT * KS), KS * Cfg::SMEM, s, (int)g.M, (int)g.N,
-                       (int)g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, nbm, nbn, device_xcds(), g.epi(), g.bias, 0,
-                       (int64_t)0);
-    return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
-  }
-  // K split across workgroups: fp32 partial tiles into the scratch, then the fixed-order sum
-  const int KT = (int)((g.K + BK - 1) / BK);
-  const int part_steps = (KT + g.parts - 1) / g.parts;
-  const int parts = (KT + part_steps - 1) / part_steps;    // no empty part
-  const int64_t part_stride = g.M * g.N;
-  hipLaunchKernelGGL(kern, dim3(nbm * nbn, parts), dim3(Cfg::NT * KS), KS * Cfg::SMEM, s, (int)g.M,
-                     (int)g.N, (int)g.K, g.A, g.lda, g.B, g.ldb, reinterpret_cast<uint16_t*>(g.scratch),
-                     g.N, nbm, nbn, device_xcds(), (int)EPI_PART32, (const uint16_t*)nullptr, part_steps, part_stride);
-  if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
-  const int64_t nthreads = g.M * ((g.N + 3) / 4);
-  hipLaunchKernelGGL(gemm_splitk_reduce_kernel<Tag>, dim3((unsigned)((nthreads + 255) / 256)), dim3(256),
-                     0, s, (int)g.M, (int)g.N, parts, g.scratch, part_stride, g.C, g.ldc, g.epi(), g.bias);
-  return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
-}
-
 template <typename Tag>
 static int launch_general(const GemmArgs& g, hipStream_t s) {
   dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((g.M + 63) / 64));
@@ -529,12 +100,27 @@ static bool fast_path_ok(const GemmArgs& g) {
   return true;
 }
 
+static const char* any_name(int variant, int transB) {
+  switch (variant) {
+    case GEMM_128_W8: return transB ? "gemm_general_nt_128x128x64_w2x4" : "gemm_general_nn_128x128x64_w2x4";
+    case GEMM_64X128_W8: return transB ? "gemm_general_nt_64x128x64_w2x4" : "gemm_general_nn_64x128x64_w2x4";
+    case GEMM_64_W4: return transB ? "gemm_general_nt_64x64x64_w2x2" : "gemm_general_nn_64x64x64_w2x2";
+    case GEMM_128_K2: return transB ? "gemm_general_nt_128x128x64_w2x4_k2" : "gemm_general_nn_128x128x64_w2x4_k2";
+    case GEMM_64X128_K2: return transB ? "gemm_general_nt_64x128x64_w2x4_k2" : "gemm_general_nn_64x128x64_w2x4_k2";
+    case GEMM_64_K4: return transB ? "gemm_general_nt_64x64x64_w2x2_k4" : "gemm_general_nn_64x64x64_w2x2_k4";
+  }
+  return transB ? "gemm_general_nt_256x256x64_w2x4" : "gemm_general_nn_256x256x64_w2x4";
+}
+
 GemmPlan plan_gemm(const GemmArgs& g) {
   GemmPlan p;
   // K == 0: the empty sum; with a fused epilogue C = act(bias), which the general kernel's epilogue
   // computes after zero K steps
   if (g.K == 0 && !g.fused()) { p.variant = GEMM_ZERO; p.name = "gemm_zero"; return p; }
-  if (g.K == 0 || !fast_path_ok(g) || g.forced == GEMM_GENERAL) {
+  // operands that do not allow aligned 16-byte accesses: the tile kernels in the form of gemm_any.hip;
+  // rows too short for one such access: the general kernel
+  p.aligned = g.K == 0 || g.forced == GEMM_GENERAL || fast_path_ok(g) || !gemm_any_ok(g);
+  if (g.K == 0 || g.forced == GEMM_GENERAL || (p.aligned && !fast_path_ok(g))) {
     p.variant = GEMM_GENERAL; p.name = "gemm_general_64x64x32";
     p.bm = 64; p.bn = 64; p.bk = 32; p.wm = 2; p.wn = 2;
     return p;
@@ -592,7 +178,12 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // t: ns per K step of 64; fixed: ns per round before the first and after the last step, where a
   // fit over K gave one (2048 x 2048 x K on the split 128 x 128 kernel: 0.56 us per step + 2 us)
   struct Cand { int variant; int bm, bn; int64_t t, fixed; int kgroups; };
-  const Cand big = {pp ? GEMM_256_PP16 : GEMM_256_W8, 256, 256, pp ? 1170 : 1800, 0, 1};
+  const Cand big = {pp ? GEMM_256_PP16 : GEMM_256_W8, 256, 256, pp ? 1170 : p.aligned ? 1800 : 2300, 0, 1};
+  // Operands of any alignment: a step's loads and their LDS writes weigh more than its MFMAs, and
+  // the groups of a workgroup share them, so what the K split inside the workgroup gains is small;
+  // two unsplit workgroups on a CU do as well (ns per step and tile, from 201 x 4001 x 4001, one tile
+  // per CU, and 1999 x 3001 x 1501, 384 to 1504 tiles).
+  const Cand any[] = {{GEMM_128_W8, 128, 128, 760, 0, 1}, {GEMM_64X128_K2, 64, 128, 600, 0, 2}, {GEMM_64_K4, 64, 64, 430, 0, 4}};
   const Cand split[] = {{GEMM_128_K2, 128, 128, 560, 2000, 2}, {GEMM_64X128_K2, 64, 128, 370, 0, 2}, {GEMM_64_K4, 64, 64, 220, 0, 4}};
   const Cand whole[] = {{GEMM_128_W8, 128, 128, 600, 0, 1}, {GEMM_64X128_W8, 64, 128, 410, 0, 1}, {GEMM_64_W4, 64, 64, 350, 0, 1}};
   struct Choice { int variant, parts, area; int64_t t; };
@@ -635,7 +226,7 @@ GemmPlan plan_gemm(const GemmArgs& g) {
     // every part keeps at least 8 K steps, and its partial tiles must fit the scratch allowed
     if (parts > 1 && KT < 8 * parts) break;
     if (parts > 1 && g.scratch_limit >= 0 && (int64_t)parts * g.M * g.N * 4 > g.scratch_limit) break;
-    for (const auto& c : KT / parts >= 8 ? split : whole) {
+    for (const auto& c : KT / parts < 8 ? whole : p.aligned ? split : any) {
       if (!fits(c.bm, c.bn)) continue;
       all[n_all++] = Choice{c.variant, parts, c.bm * c.bn, cost(c.bm, c.bn, c.t, c.fixed, parts, c.kgroups)};
     }
@@ -700,6 +291,7 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // a forced kernel keeps the split only if it is one of the kernels that can run it
   const bool can_split = v == GEMM_128_K2 || v == GEMM_64X128_K2 || v == GEMM_64_K4 || v == GEMM_128_W8 ||
                          v == GEMM_64X128_W8 || v == GEMM_64_W4;
+  if (!p.aligned && (v == GEMM_256 || v == GEMM_256_W8X1 || v == GEMM_256_W1X8)) v = GEMM_256_W8;
   p.parts = can_split ? best_parts : 1;
   p.scratch_bytes = p.parts > 1 ? (int64_t)p.parts * g.M * g.N * 4 : 0;
   p.variant = v;
@@ -739,19 +331,13 @@ GemmPlan plan_gemm(const GemmArgs& g) {
     default: p.variant = GEMM_256_W8; p.bm = p.bn = 256; p.wm = 2; p.wn = 4;
       p.name = g.transB ? "gemm_nt_256x256x64_w2x4" : "gemm_nn_256x256x64_w2x4"; break;
   }
+  if (!p.aligned) p.name = any_name(v, g.transB);
   return p;
-}
-
-// KS: K-split groups per workgroup when B is stored N x K, KS_NN when it is stored K x N (whose
-// padded stage is larger, so fewer groups fit the LDS).
-template <typename Tag, int BM, int BN, int BK, int WM, int WN, int KS = 1, int KS_NN = KS>
-static int launch_tile_tb(const GemmArgs& g, hipStream_t s) {
-  return g.transB ? launch_tile<Tag, BM, BN, BK, WM, WN, true, KS>(g, s)
-                  : launch_tile<Tag, BM, BN, BK, WM, WN, false, KS_NN>(g, s);
 }
 
 template <typename Tag>
 static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
+  if (!p.aligned) return run_gemm_any(g, p.variant, s);
   switch (p.variant) {
     case GEMM_ZERO: {
       if (g.acc32) return MLT_OK;
@@ -761,16 +347,9 @@ static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
       return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
     }
     case GEMM_GENERAL: return launch_general<Tag>(g, s);
-    case GEMM_256: return launch_tile_tb<Tag, 256, 256, 64, 2, 2>(g, s);
-    case GEMM_256_W8: return launch_tile_tb<Tag, 256, 256, 64, 2, 4>(g, s);
-    case GEMM_256_W8X1: return launch_tile_tb<Tag, 256, 256, 64, 8, 1>(g, s);
-    case GEMM_256_W1X8: return launch_tile_tb<Tag, 256, 256, 64, 1, 8>(g, s);
-    case GEMM_128_W8: return launch_tile_tb<Tag, 128, 128, 64, 2, 4>(g, s);
-    case GEMM_64X128_W8: return launch_tile_tb<Tag, 64, 128, 64, 2, 4>(g, s);
-    case GEMM_64_W4: return launch_tile_tb<Tag, 64, 64, 64, 2, 2>(g, s);
-    case GEMM_128_K2: return launch_tile_tb<Tag, 128, 128, 64, 2, 4, 2>(g, s);
-    case GEMM_64X128_K2: return launch_tile_tb<Tag, 64, 128, 64, 2, 4, 2>(g, s);
-    case GEMM_64_K4: return launch_tile_tb<Tag, 64, 64, 64, 2, 2, 4, 3>(g, s);
+    case GEMM_256: return launch_tile_tb<Tag, true, 256, 256, 64, 2, 2>(g, s);
+    case GEMM_256_W8X1: return launch_tile_tb<Tag, true, 256, 256, 64, 8, 1>(g, s);
+    case GEMM_256_W1X8: return launch_tile_tb<Tag, true, 256, 256, 64, 1, 8>(g, s);
     case GEMM_256_PP16: return run_gemm_pp(g, 256, 64, s);
     case GEMM_128_PP16: return run_gemm_pp(g, 128, 64, s);
     case GEMM_128_PP16_K128: return run_gemm_pp(g, 128, 128, s);
@@ -778,7 +357,8 @@ static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     case GEMM_SKINNY: return run_gemm_skinny(g, s);
     case GEMM_SKINNY_DMA: return run_gemm_skinny_dma(g, s);
   }
-  return MLT_ERR_UNSUPPORTED;
+  const int rc = launch_small_tile<Tag, true>(g, p.variant, s);
+  return rc == -1 ? MLT_ERR_UNSUPPORTED : rc;
 }
 
 // Scratch for the partial products of a K split across workgroups: one buffer per (device, stream)

@@ -49,6 +49,7 @@ struct GemmArgs {
 
 struct GemmPlan {
   int variant = GEMM_GENERAL;
+  bool aligned = true;             // false: the forms of the tile kernels for operands of any alignment
   int parts = 1;                   // > 1: K split across workgroups, partial products through a scratch
   int64_t scratch_bytes = 0;       // parts * M * N * 4 when parts > 1
   const char* name = "";
@@ -66,6 +67,8 @@ GemmPlan plan_gemm(const GemmArgs& g);
 int run_gemm(const GemmArgs& g, GemmPlan& p, hipStream_t s);
 bool gemm_pp_ok(const GemmArgs& g);            // gemm_pp.hip: can the two-group kernel take this problem?
 int run_gemm_pp(const GemmArgs& g, int tile, int kstep, hipStream_t s);   // tile: 256 or 128; K step 64 or (tile 128 only) 128
+bool gemm_any_ok(const GemmArgs& g);           // gemm_any.hip: the tile kernels on operands of any alignment
+int run_gemm_any(const GemmArgs& g, int variant, hipStream_t s);
 int run_gemm_w4(const GemmArgs& g, hipStream_t s);   // gemm_w4.hip; same operand requirements (gemm_pp_ok)
 bool gemm_skinny_ok(const GemmArgs& g);        // gemm_skinny.hip
 int run_gemm_skinny(const GemmArgs& g, hipStream_t s);
