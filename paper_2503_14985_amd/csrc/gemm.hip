@@ -178,7 +178,7 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // t: ns per K step of 64; fixed: ns per round before the first and after the last step, where a
   // fit over K gave one (2048 x 2048 x K on the split 128 x 128 kernel: 0.56 us per step + 2 us)
   struct Cand { int variant; int bm, bn; int64_t t, fixed; int kgroups; };
-  const Cand big = {pp ? GEMM_256_PP16 : GEMM_256_W8, 256, 256, pp ? 1170 : p.aligned ? 1800 : 2300, 0, 1};
+  const Cand big = {pp ? GEMM_256_PP16 : GEMM_256_W8, 256, 256, !p.aligned ? 2300 : pp ? 1170 : 1800, 0, 1};
   // Operands of any alignment: a step's loads and their LDS writes weigh more than its MFMAs, and
   // the groups of a workgroup share them, so what the K split inside the workgroup gains is small;
   // two unsplit workgroups on a CU do as well (ns per step and tile, from 201 x 4001 x 4001, one tile
@@ -197,7 +197,8 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // The two-group kernel on 128 x 128 tiles, no K split across workgroups, in its two forms (fits
   // over K at 256 and 512 tiles, kernel time without the call):
   //   K steps of 64, two workgroups per CU: 0.84 us per step for a pair of tiles + 1.9 us per pair,
-  //     0.52 us + 4 us for a tile alone on its CU;
+  //     0.52 us + 4 us for a tile alone on its CU (0.60 when K is not a multiple of 64: 2048 x 2048 x 2056
+  //     takes 27.8 us, 24.8 on the split kernel);
   //   K steps of 128, one workgroup per CU: 0.436 us per 64 of K + 4.3 us per round.
   // One tile per CU: the 128-deep form (1024 x 4096 x 4096: 35.4 us against 40.8 on the register-
   // staged split kernel and 43.3 on the 64-deep form, hipBLASLt 36.6; 2048^3: 22.9 against 25.5,
@@ -212,7 +213,7 @@ GemmPlan plan_gemm(const GemmArgs& g) {
     const int64_t arrive = wgs >= need ? base : base * need / wgs;
     const int64_t pairs = wgs / (2 * NCU), rem = wgs - pairs * 2 * NCU;
     const int64_t own64 = pairs * (KT * 840 + 1900) +
-                          (rem > NCU ? KT * 840 + 1900 : rem > 0 ? KT * 519 + 4000 : 0);
+                          (rem > NCU ? KT * 840 + 1900 : rem > 0 ? KT * (g.K % 64 ? 600 : 519) + 4000 : 0);
     // (with at most one tile per CU and K a multiple of 128 the 128-deep form is never slower, also
     // where both are bound by operand arrival: 128 x 28672 x 8192 116 against 134 us)
     if (wgs > NCU || g.K % 128 != 0)
@@ -285,9 +286,10 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   if (g.forced >= GEMM_256 && g.forced < GEMM_NUM_VARIANTS && g.forced != GEMM_SKINNY &&
       g.forced != GEMM_SKINNY_DMA)
     v = g.forced;
-  if ((v == GEMM_256_PP16 || v == GEMM_256_W4) && !gemm_pp_ok(g)) v = GEMM_256_W8;
-  if (v == GEMM_128_PP16_K128 && (!gemm_pp_ok(g) || g.K % 128)) v = GEMM_128_PP16;
-  if (v == GEMM_128_PP16 && !gemm_pp_ok(g)) v = GEMM_128_W8;
+  if (v == GEMM_256_PP16 && !gemm_pp_ok(g)) v = GEMM_256_W8;
+  if (v == GEMM_256_W4 && !gemm_w4_ok(g)) v = GEMM_256_W8;
+  if (v == GEMM_128_PP16_K128 && (!pp || g.K % 128)) v = GEMM_128_PP16;
+  if (v == GEMM_128_PP16 && !pp) v = GEMM_128_W8;
   // a forced kernel keeps the split only if it is one of the kernels that can run it
   const bool can_split = v == GEMM_128_K2 || v == GEMM_64X128_K2 || v == GEMM_64_K4 || v == GEMM_128_W8 ||
                          v == GEMM_64X128_W8 || v == GEMM_64_W4;

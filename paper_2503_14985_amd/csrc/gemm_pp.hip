@@ -28,10 +28,13 @@
 // With these, the 16 lanes that the LDS serves together hit 16 distinct 16-byte bank groups, for
 // the row reads (ds_read_b128) and for the transposing reads (ds_read_b64_tr_b16) alike.
 //
-// Requirements (checked by the host): K % 64 == 0, lda % 8 == 0, ldb % 8 == 0, N % 8 == 0 when B
-// is K x N, A and B 16-byte aligned, 256 * lda and 64 * ldb + N below 2^30 elements (32-bit
-// per-lane byte offsets). M and N need not be multiples of 256: out-of-range rows/columns are
-// clamped on load and never stored.
+// Requirements (checked by the host): K % 8 == 0, lda % 8 == 0, ldb % 8 == 0, N % 8 == 0 when B is
+// K x N, A and B 16-byte aligned, 256 * lda and 128 * ldb + N (256 * ldb with B stored N x K) below
+// 2^30 elements (32-bit per-lane byte offsets). M and N need not be multiples of the tile:
+// out-of-range rows/columns are clamped on load and never stored. Nor K of the K step: the chunks of
+// the last step that lie past K re-read valid ones, and the operand fragments they land in are
+// zeroed before its MFMAs. (1864 x 5536 x 848 in bf16: 26 us, against 38 us on the register-staged
+// 256 x 256 kernel that a ragged K took before; 4096 x 4096 x 1000 33 against 46 us.)
 #include <type_traits>
 
 #include "mlt_common.h"
@@ -84,7 +87,9 @@ __device__ __forceinline__ auto mfma_ms(V8 a, V8 b, typename std::conditional<MS
 
 }  // namespace
 
-template <typename Tag, bool TRANSB, int MS, int BT, int BK>
+// TAIL: K is not a multiple of BK (a template parameter: the checks it takes in the loop, scalar and
+// never taken, cost 8192^3 3.5 %).
+template <typename Tag, bool TRANSB, int MS, int BT, int BK, bool TAIL>
 __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_pp_kernel(
     int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
     const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc, int nbm,
@@ -106,6 +111,8 @@ __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_p
   int tile_m, tile_n;
   tile_of_block<PP_GROUP_M>(blockIdx.x, nbm, nbn, nxcd, tile_m, tile_n);
   const int m0 = tile_m * PP_BM, n0 = tile_n * PP_BN;
+  const int KT = TAIL ? (K + PP_BK - 1) / PP_BK : K / PP_BK;
+  const int k_tail = K - (KT - 1) * PP_BK;               // TAIL: k values in the last step
 
   // ---- global -> LDS assignments. A tile is 32 (16) blocks of 1 KB (64 lanes x 16 bytes). The
   // four wavefronts of group 1 fill the A tiles, those of group 0 the B tiles, NL blocks each;
@@ -119,7 +126,7 @@ __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_p
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int r = ((wave & 3) * NL + i) * RPBA + lane / CPR;  // tile row held by this slot
-      const int c = (lane % CPR) ^ T::swz(r);                   // k chunk stored in this slot
+      const int c = (lane % CPR) ^ T::swz(r);   // k chunk stored in this slot
       const int rr = (m0 + r < M) ? r : (M - 1 - m0);
       voff[i] = (uint32_t)rr * (uint32_t)lda * 2u + (uint32_t)c * 16u;
     }
@@ -145,15 +152,34 @@ __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_p
       voff[i] = (uint32_t)k * (uint32_t)ldb * 2u + (uint32_t)(col < N ? col : 0) * 2u;
     }
   }
-  const int KT = K / PP_BK;
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)smem;      // LDS byte address of the buffer
   // this wavefront's NL blocks of operand tile t (A_t for group 1, B_t for group 0) into a slot
   // (an operand that only one row or column of tiles reads is read exactly once: streaming form)
   const bool stream = grp == 1 ? nbn == 1 : nbm == 1;
+  // Bytes that chunk i of the last, partial K step moves back so that it stays inside the matrix
+  // (its values are zeroed in the fragments): to the step's first k chunk, or first k row of the K x N
+  // operand.
+  // (`ln` is the lane, hidden from the compiler by tail_lane(): it would otherwise keep all NL values in
+  // registers through the whole loop, which the 256 x 256 tile has none left for.)
+  auto tail_lane = [&]() { int ln = lane; asm volatile("" : "+v"(ln)); return ln; };
+  auto tail_back = [&](int i, int ln) -> uint32_t {
+    if (grp == 1 || TRANSB) {
+      const int r = ((wave & 3) * NL + i) * RPBA + ln / CPR;
+      const int c = (ln % CPR) ^ T::swz(r);
+      return c * 8 < k_tail ? 0u : (uint32_t)c * 16u;
+    }
+    constexpr int LPR = BT / 8, RPB = 64 / LPR;
+    const int k = ((wave & 3) * NL + i) * RPB + ln / LPR;
+    return k < k_tail ? 0u : (uint32_t)k * (uint32_t)ldb * 2u;
+  };
   auto issue_loads = [&](int t, int slot) {
     const char* gp = ld_base + (int64_t)t * ld_kstep;
     const uint32_t dst = lds0 + slot * PP_SLOT + (wave & 3) * (NL * 1024);
-    if (stream) {
+    if (TAIL && t == KT - 1) {
+      const int ln = tail_lane();
+#pragma unroll
+      for (int i = 0; i < NL; ++i) load_lds16(gp, voff[i] - tail_back(i, ln), dst + i * 1024);
+    } else if (stream) {
 #pragma unroll
       for (int i = 0; i < NL; ++i) load_lds16_stream(gp, voff[i], dst + i * 1024);
     } else {
@@ -235,7 +261,19 @@ __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_p
       }
     }
   };
-
+  // Partial last step: the 8 k values of a fragment's lane are all inside K or all past it (K % 8 ==
+  // 0); past it both operands become zeros (one alone would leave 0 * Inf).
+  auto zero_tail = [&]() {
+    const u32x4 zero4 = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int kk = 0; kk < NS; ++kk)
+      if ((CPS * kk + h) * 8 >= k_tail) {
+#pragma unroll
+        for (int i = 0; i < TA; ++i) af[kk][i] = __builtin_bit_cast(V8, zero4);
+#pragma unroll
+        for (int j = 0; j < TB; ++j) bf[kk][j] = __builtin_bit_cast(V8, zero4);
+      }
+  };
 
   // Phase p ends at workgroup barrier p. Group 0 reads tile k (A_k and B_k) in phase 2k and
   // multiplies in phase 2k+1; group 1 does the same one phase later. Operand tile number h
@@ -277,6 +315,7 @@ __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_p
         issue_loads(k + 1, slot_a + 3 >= PP_NSLOT ? slot_a + 3 - PP_NSLOT : slot_a + 3);
       __builtin_amdgcn_s_waitcnt(wait_imm(63, 0));
     }
+    if (TAIL && k == KT - 1) zero_tail();
     MLT_BARRIER();
     __builtin_amdgcn_sched_barrier(0);
     // ---- compute phase
@@ -348,20 +387,19 @@ __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_p
 bool gemm_pp_ok(const GemmArgs& g) {
   auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
   if (!al16(g.A) || !al16(g.B)) return false;
-  if (g.K < 64 || g.K % 64 || g.lda % 8 || g.ldb % 8) return false;
-  if (g.M < 1 || g.N < 1) return false;
+  if (g.K < 8 || g.K % 8 || g.lda % 8 || g.ldb % 8) return false;
   if (!g.transB && g.N % 8) return false;
+  if (g.M < 1 || g.N < 1) return false;
   const int64_t lim = (int64_t)1 << 30;
   if (256 * g.lda >= lim) return false;
   if (g.transB ? 256 * g.ldb >= lim : 128 * g.ldb + g.N >= lim) return false;
   return true;
 }
 
-template <typename Tag, bool TRANSB, int MS, int BT, int BK>
-static int launch_pp(const GemmArgs& g, hipStream_t s) {
+template <typename Tag, bool TRANSB, int MS, int BT, int BK, bool TAIL>
+static int launch_pp_k(const GemmArgs& g, hipStream_t s) {
   constexpr int PP_BM = BT, PP_BN = BT, PP_SMEM = PpTile<BT, BK>::SMEM;
-  if (g.K % BK) return MLT_ERR_UNSUPPORTED;
-  auto kern = gemm_pp_kernel<Tag, TRANSB, MS, BT, BK>;
+  auto kern = gemm_pp_kernel<Tag, TRANSB, MS, BT, BK, TAIL>;
   static thread_local int configured_dev = -1;          // opt in to > 64 KB LDS once per device
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MLT_ERR_DEVICE;
@@ -377,6 +415,13 @@ static int launch_pp(const GemmArgs& g, hipStream_t s) {
   hipLaunchKernelGGL(kern, dim3(nbm * nbn), dim3(PP_NT), PP_SMEM, s, (int)g.M, (int)g.N, (int)g.K,
                      g.A, g.lda, g.B, g.ldb, g.C, g.ldc, nbm, nbn, device_xcds(), g.epi(), g.bias);
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
+}
+
+template <typename Tag, bool TRANSB, int MS, int BT, int BK>
+static int launch_pp(const GemmArgs& g, hipStream_t s) {
+  if (g.K % BK == 0) return launch_pp_k<Tag, TRANSB, MS, BT, BK, false>(g, s);
+  if constexpr (BK == 64) return launch_pp_k<Tag, TRANSB, MS, BT, BK, true>(g, s);
+  return MLT_ERR_UNSUPPORTED;                              // (the plan takes the 64-deep form then)
 }
 
 // Only the 16x16x32 form is instantiated (MS = 16): measured on N(0,1) operands it runs 8-17 %

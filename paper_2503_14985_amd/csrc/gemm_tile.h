@@ -58,17 +58,6 @@ struct GemmTile {
 // steps p * part_steps .. of the problem and stores its fp32 partial tile (epi = EPI_PART32) into
 // slice p of the scratch that C_ then points at (slices part_stride floats apart, row stride ldc);
 // gemm_splitk_reduce_kernel adds the slices in a fixed order and applies the real epilogue.
-// 16 bytes at 2-byte alignment
-typedef u32x4 __attribute__((may_alias, aligned(2))) u32x4_mem2;
-
-// Drops the first n 16-bit elements of a chunk (n >= 8: all of them) and fills up with zeros.
-__device__ __forceinline__ u32x4 drop_elements(u32x4 v, int n) {
-  if (n & 4) v = u32x4{v[2], v[3], 0u, 0u};
-  if (n & 2) v = u32x4{v[1], v[2], v[3], 0u};
-  if (n & 1) v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
-  return n >= 8 ? u32x4{0u, 0u, 0u, 0u} : v;
-}
-
 template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB, int KS, bool AL>
 __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
     int M, int N, int K_, const uint16_t* __restrict__ A_, int64_t lda,

@@ -268,6 +268,8 @@ static int launch_w4(const GemmArgs& g, hipStream_t s) {
 }
 
 // same operand requirements as the two-group kernel (gemm_pp_ok)
+bool gemm_w4_ok(const GemmArgs& g) { return gemm_pp_ok(g) && g.K % 64 == 0; }
+
 int run_gemm_w4(const GemmArgs& g, hipStream_t s) {
   if (g.dtype == MLT_BF16)
     return g.transB ? launch_w4<bf16_tag, true>(g, s) : launch_w4<bf16_tag, false>(g, s);

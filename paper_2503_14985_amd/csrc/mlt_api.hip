@@ -221,7 +221,7 @@ int mlt_gemm_tiled(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, 
   // only; square: 2 x 2 square sub-tiles (the pipelined kernel when the operands allow it)
   if (tiling == 1) g.forced = GEMM_256_W8X1;
   if (tiling == 2) g.forced = GEMM_256_W1X8;
-  if (tiling == 3) g.forced = gemm_pp_ok(g) ? GEMM_256_W4 : GEMM_256;
+  if (tiling == 3) g.forced = gemm_w4_ok(g) ? GEMM_256_W4 : GEMM_256;
   g.forced_parts = overrides().gemm_parts;
   GemmPlan p = plan_gemm(g);
   hipStream_t s = (hipStream_t)stream;

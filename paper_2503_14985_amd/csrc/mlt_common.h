@@ -23,6 +23,17 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef u32x4 __attribute__((may_alias)) u32x4_mem;
 typedef u32x2 __attribute__((may_alias)) u32x2_mem;
 
+// 16 bytes at 2-byte alignment
+typedef u32x4 __attribute__((may_alias, aligned(2))) u32x4_mem2;
+
+// Drops the first n 16-bit elements of a chunk (n >= 8: all of them) and fills up with zeros.
+__device__ __forceinline__ u32x4 drop_elements(u32x4 v, int n) {
+  if (n & 4) v = u32x4{v[2], v[3], 0u, 0u};
+  if (n & 2) v = u32x4{v[1], v[2], v[3], 0u};
+  if (n & 1) v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+  return n >= 8 ? u32x4{0u, 0u, 0u, 0u} : v;
+}
+
 #define MLT_LDS __attribute__((address_space(3)))
 
 // Workgroup barrier of the pipelined kernels (the ones that order their direct-to-LDS loads with

@@ -69,7 +69,8 @@ bool gemm_pp_ok(const GemmArgs& g);            // gemm_pp.hip: can the two-group
 int run_gemm_pp(const GemmArgs& g, int tile, int kstep, hipStream_t s);   // tile: 256 or 128; K step 64 or (tile 128 only) 128
 bool gemm_any_ok(const GemmArgs& g);           // gemm_any.hip: the tile kernels on operands of any alignment
 int run_gemm_any(const GemmArgs& g, int variant, hipStream_t s);
-int run_gemm_w4(const GemmArgs& g, hipStream_t s);   // gemm_w4.hip; same operand requirements (gemm_pp_ok)
+bool gemm_w4_ok(const GemmArgs& g);            // gemm_w4.hip: whole K steps only
+int run_gemm_w4(const GemmArgs& g, hipStream_t s);
 bool gemm_skinny_ok(const GemmArgs& g);        // gemm_skinny.hip
 int run_gemm_skinny(const GemmArgs& g, hipStream_t s);
 bool gemm_skinny_dma_ok(const GemmArgs& g);
