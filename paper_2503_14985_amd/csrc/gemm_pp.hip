@@ -333,55 +333,25 @@ __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_p
   }
   if (grp == 0) MLT_BARRIER();
 
-  // ---- epilogue: fp32 -> 16-bit (RNE) and store, or add to the fp32 C; guarded per element
-  // accumulator register r of a 32x32 tile is row 8*(r/4) + 4*(l/32) + r%4, of a 16x16 tile row
-  // 4*(l/16) + r; the column is the lane's
-  const int row_base = m0 + wm * WTM + 4 * h;
-  const int col_base = n0 + wn * WTN + lq;
-  if constexpr (MS == 16) {
-    // Plain 16-bit store with even N and ldc: neighbouring lanes (columns c, c+1 of the same four
-    // rows) exchange two of their four values, so that the even lane holds rows 0, 1 and the odd
-    // lane rows 2, 3 of BOTH columns: two 32-bit stores per tile and lane instead of four 16-bit
-    // ones (the stores are what the epilogue spends its time on).
-    const bool pairs = epi == 0 && bias == nullptr && !(N & 1) && !(ldc & 1) &&
-                       !(reinterpret_cast<uintptr_t>(C) & 3);
-    if (pairs) {
-      const bool odd = lane & 1;
-      auto neighbour = [](float x) {                      // the value lane l ^ 1 passes in
-        return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, true));
-      };
-      const int col0 = col_base - (odd ? 1 : 0);
+  // ---- epilogue: fp32 -> 16-bit (RNE) and store, or add to the fp32 C, row-contiguous through LDS
+  // (every wavefront is past its last fragment read: the ring is free)
+  static_assert(MS == 16, "the accumulator layout below");
+  constexpr int RP = 64;                                  // rows per pass: what fits an eighth of the LDS
+  typedef RowStore<Tag, RP, WTN> Rows;
+  static_assert(8 * Rows::BYTES <= T::SMEM, "one parking area per wavefront");
+  float* park = reinterpret_cast<float*>(smem + wave * Rows::BYTES);
 #pragma unroll
-      for (int i = 0; i < TA; ++i)
+  for (int p = 0; p < WTM / RP; ++p)
+    Rows::run([&](float* lds) {
+      // accumulator register r of a 16x16 tile is row 4*(l/16) + r; the column is the lane's
 #pragma unroll
-        for (int j = 0; j < TB; ++j) {
-          const float got0 = neighbour(odd ? acc[i][j][0] : acc[i][j][2]);
-          const float got1 = neighbour(odd ? acc[i][j][1] : acc[i][j][3]);
-          const uint32_t w0 = odd ? Elem<Tag>::pack2(got0, acc[i][j][2]) : Elem<Tag>::pack2(acc[i][j][0], got0);
-          const uint32_t w1 = odd ? Elem<Tag>::pack2(got1, acc[i][j][3]) : Elem<Tag>::pack2(acc[i][j][1], got1);
-          const int row = row_base + i * 16 + (odd ? 2 : 0);
-          const int col = col0 + j * 16;
-          if (col < N) {
-            if (row < M) *reinterpret_cast<uint32_t*>(C + (int64_t)row * ldc + col) = w0;
-            if (row + 1 < M) *reinterpret_cast<uint32_t*>(C + (int64_t)(row + 1) * ldc + col) = w1;
-          }
-        }
-      return;
-    }
-  }
-  gemm_epilogue<Tag>([&](auto&& out) {
+      for (int i = 0; i < RP / 16; ++i)
 #pragma unroll
-    for (int i = 0; i < TA; ++i)
+        for (int j = 0; j < TB; ++j)
 #pragma unroll
-      for (int j = 0; j < TB; ++j) {
-        const int col = col_base + j * MS;
-#pragma unroll
-        for (int r = 0; r < (MS == 32 ? 16 : 4); ++r) {
-          const int row = row_base + i * MS + (MS == 32 ? 8 * (r >> 2) + (r & 3) : r);
-          if (row < M && col < N) out((int64_t)row * ldc + col, col, acc[i][j][r]);
-        }
-      }
-  }, C, epi, bias);
+          for (int r = 0; r < 4; ++r)
+            *reinterpret_cast<f32_mem*>(lds + (i * 16 + 4 * h + r) * Rows::STRIDE + j * 16 + lq) = acc[p * (RP / 16) + i][j][r];
+    }, park, lane, m0 + wm * WTM + p * RP, n0 + wn * WTN, M, N, C, ldc, epi, bias);
 }
 
 bool gemm_pp_ok(const GemmArgs& g) {
