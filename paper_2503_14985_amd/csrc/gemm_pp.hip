@@ -337,7 +337,7 @@ __global__ __launch_bounds__(PP_NT, (BT == 128 && BK == 64) ? 4 : 1) void gemm_p
   // (every wavefront is past its last fragment read: the ring is free)
   static_assert(MS == 16, "the accumulator layout below");
   constexpr int RP = 64;                                  // rows per pass: what fits an eighth of the LDS
-  typedef RowStore<Tag, RP, WTN> Rows;
+  typedef RowStore<Tag, RP, WTN, 4> Rows;
   static_assert(8 * Rows::BYTES <= T::SMEM, "one parking area per wavefront");
   float* park = reinterpret_cast<float*>(smem + wave * Rows::BYTES);
 #pragma unroll

@@ -138,9 +138,9 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
   const u32x4 zero4 = {0u, 0u, 0u, 0u};
 
   // Loads never branch per element: a chunk outside the matrix re-reads a valid address (row
-  // clamp above, column 0 here). Only the last K step can run past K; it takes the second form,
-  // in which a chunk past K re-reads k = 0 (AL) or the 8 elements before K (!AL), and such chunks
-  // are zeroed or shifted when they go to LDS, one step later, so that no step waits for its loads.
+  // clamp above, column 0 here). Only one K step can run past K; it takes the second form, in which
+  // a chunk past K re-reads k = 0 (AL) or the 8 elements before K (!AL), to be zeroed or shifted on
+  // the way to LDS.
   auto load_global_full = [&](int k0) {
 #pragma unroll
     for (int i = 0; i < Cfg::NA; ++i) ga[i] = *reinterpret_cast<const gmem16*>(a_src[i] + k0);
@@ -165,20 +165,21 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
       }
     }
   };
-  auto store_lds = [&](int stage, int k0, bool tail) {
+  // zeroes or shifts what a partial K step's chunks hold past K
+  auto zero_k_tail = [&](int k0) {
+    const int over = k0 + st_k + 8 - K;                  // elements of a k chunk that lie past K
+#pragma unroll
+    for (int i = 0; i < Cfg::NA; ++i) ga[i] = AL ? (over > 0 ? zero4 : ga[i]) : drop_elements(ga[i], over > 0 ? over : 0);
+#pragma unroll
+    for (int i = 0; i < Cfg::NB; ++i) {
+      if (TRANSB) gb[i] = AL ? (over > 0 ? zero4 : gb[i]) : drop_elements(gb[i], over > 0 ? over : 0);
+      else if (k0 + i * KSTEP + b_k >= K) gb[i] = zero4;
+    }
+  };
+  auto store_lds = [&](int stage) {
     if (n_edge) {
 #pragma unroll
       for (int i = 0; i < Cfg::NB; ++i) gb[i] = drop_elements(gb[i], b_drop);
-    }
-    if (tail) {
-      const int over = k0 + st_k + 8 - K;                // elements of a k chunk that lie past K
-#pragma unroll
-      for (int i = 0; i < Cfg::NA; ++i) ga[i] = AL ? (over > 0 ? zero4 : ga[i]) : drop_elements(ga[i], over > 0 ? over : 0);
-#pragma unroll
-      for (int i = 0; i < Cfg::NB; ++i) {
-        if (TRANSB) gb[i] = AL ? (over > 0 ? zero4 : gb[i]) : drop_elements(gb[i], over > 0 ? over : 0);
-        else if (k0 + i * KSTEP + b_k >= K) gb[i] = zero4;
-      }
     }
     char* base = smem + stage * Cfg::STAGE;
 #pragma unroll
@@ -241,10 +242,10 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
   const int KTG = (KT + KS - 1) / KS;
   const int kt_begin = kg;
   const int kt_end = KT;
-  auto load_tile = [&](int t) {
-    if (ragged_k && t == KT - 1) load_global_tail(t * BK); else load_global_full(t * BK);
-  };
-  auto store_tile = [&](int stage, int t) { store_lds(stage, t * BK, ragged_k && t == KT - 1); };
+  // A partial K step is taken first, by the group it belongs to, so that the loop below never asks
+  // (the question alone cost 512 x 4096 x 4096 2 %): such a group's steps are KT-1, kg, kg + KS, ...
+  const bool tail_first = ragged_k && (KT - 1) % KS == kg;
+  const int k_shift = tail_first ? KS * BK : 0;
 
   // Software pipeline. Stage s holds the group's i-th tile (s = i & 1). During step kt:
   //   slice 0: read fragments of slice 1 | MFMAs of slice 0
@@ -258,9 +259,10 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
   // read; its latency and that of the first fragment reads hide behind the MFMAs of slice 3.
   const bool any = kt_begin < kt_end;
   if (any) {
-    load_tile(kt_begin);
-    store_tile(0, kt_begin);
-    if (kt_begin + KS < kt_end) load_tile(kt_begin + KS);
+    if (tail_first) load_global_tail((KT - 1) * BK); else load_global_full(kt_begin * BK);
+    if (tail_first) zero_k_tail((KT - 1) * BK);
+    store_lds(0);
+    if (kt_begin + KS < kt_end) load_global_full((kt_begin + KS) * BK - k_shift);
   }
   __syncthreads();
 
@@ -294,8 +296,8 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
       mfma_slice(1);
       __builtin_amdgcn_sched_barrier(0);
       if (have_next) {
-        store_tile(cur ^ 1, kt + KS);
-        if (kt + 2 * KS < kt_end) load_tile(kt + 2 * KS);
+        store_lds(cur ^ 1);
+        if (kt + 2 * KS < kt_end) load_global_full((kt + 2 * KS) * BK - k_shift);
       }
       __builtin_amdgcn_sched_barrier(0);
 
@@ -314,87 +316,75 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
     }
   }
 
-  // ---- KS > 1: add the groups' accumulators. Groups 1 .. KS-1 park theirs in LDS (the stages
-  // are free now), register r of MFMA tile (i, j) of wavefront w at float index
-  // ((w*TM*TN + i*TN + j)*16 + r)*64 + lane of the group's area (consecutive lanes, consecutive
-  // words); group 0 adds them in the order 1, 2, ... and goes on to the epilogue alone.
-  if (KS > 1) {
-    static_assert(KS == 1 || (KS - 1) * BM * BN * 4 <= KS * Cfg::SMEM, "reduction area fits the stages");
-    __syncthreads();
-    float* red = reinterpret_cast<float*>(smem_all);
-    const int mine = wave * Cfg::TM * Cfg::TN * 16 * 64 + lane;
-    if (kg > 0) {
-      float* dst = red + (kg - 1) * (BM * BN) + mine;
-#pragma unroll
-      for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) dst[((i * Cfg::TN + j) * 16 + r) * 64] = acc[i][j][r];
-    }
-    __syncthreads();
-    if (kg > 0) return;
-#pragma unroll
-    for (int g2 = 1; g2 < KS; ++g2) {
-      const float* src = red + (g2 - 1) * (BM * BN) + mine;
-#pragma unroll
-      for (int i = 0; i < Cfg::TM; ++i)
-#pragma unroll
-        for (int j = 0; j < Cfg::TN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] += src[((i * Cfg::TN + j) * 16 + r) * 64];
-    }
-  }
-
-  // ---- epilogue: fp32 -> 16-bit (RNE), guarded element stores
-  const int row_base = m0 + wm * (BM / WM) + 4 * (lane >> 5);
-  const int col_base = n0 + wn * (BN / WN) + (lane & 31);
-  // Plain 16-bit store with even N and ldc: neighbouring lanes (columns c, c+1 of the same rows)
-  // exchange two of every four values, so that the even lane holds rows 0, 1 and the odd lane
-  // rows 2, 3 of both columns of a register group: 32-bit stores, half as many.
-  if (epi == 0 && bias == nullptr && !(N & 1) && !(ldc & 1) && !(reinterpret_cast<uintptr_t>(C) & 3)) {
-    const bool odd = lane & 1;
-    auto neighbour = [](float x) {                        // the value lane l ^ 1 passes in
-      return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0xB1, 0xF, 0xF, true));
-    };
-    const int col0 = col_base - (odd ? 1 : 0);
+  // ---- epilogue, row-contiguous through LDS (see RowStore)
+  if constexpr (BM * BN <= 128 * 128) {
+    // The whole tile at once: every group parks its accumulators in its own image of the tile
+    // ([row][BN + 8] floats: the two row groups of a 32x32 accumulator, 4 rows apart, in different
+    // banks), and all threads of the workgroup then add the KS images in the order 0, 1, ... and store.
+    // (The sum by group 0 alone, its partial values read one float at a time, and the store from
+    // its registers took 0.9 us longer on 512 x 4096 x 4096.)
+    constexpr int S = BN + 8, NTHR = Cfg::NT * KS;
+    static_assert(KS * BM * S * 4 <= KS * Cfg::SMEM, "the images fit the stages");
+    float* const red = reinterpret_cast<float*>(smem_all);
+    if (KS > 1) __syncthreads();                          // (KS == 1: no stage is read after the loop's last barrier)
 #pragma unroll
     for (int i = 0; i < Cfg::TM; ++i)
 #pragma unroll
-      for (int j = 0; j < Cfg::TN; ++j) {
-        const int col = col0 + j * 32;
+      for (int j = 0; j < Cfg::TN; ++j)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const float got0 = neighbour(odd ? acc[i][j][4 * g] : acc[i][j][4 * g + 2]);
-          const float got1 = neighbour(odd ? acc[i][j][4 * g + 1] : acc[i][j][4 * g + 3]);
-          const uint32_t w0 = odd ? Elem<Tag>::pack2(got0, acc[i][j][4 * g + 2]) : Elem<Tag>::pack2(acc[i][j][4 * g], got0);
-          const uint32_t w1 = odd ? Elem<Tag>::pack2(got1, acc[i][j][4 * g + 3]) : Elem<Tag>::pack2(acc[i][j][4 * g + 1], got1);
-          const int row = row_base + i * 32 + 8 * g + (odd ? 2 : 0);
-          if (col < N) {
-            if (row < M) *reinterpret_cast<uint32_t*>(C + (int64_t)row * ldc + col) = w0;
-            if (row + 1 < M) *reinterpret_cast<uint32_t*>(C + (int64_t)(row + 1) * ldc + col) = w1;
-          }
-        }
+        for (int r = 0; r < 16; ++r)
+          *reinterpret_cast<f32_mem*>(red + (kg * BM + wm * (BM / WM) + i * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * S +
+                                      wn * (BN / WN) + j * 32 + (lane & 31)) = acc[i][j][r];
+    __syncthreads();
+    if (epi & (EPI_PART32 | EPI_ACC32)) {
+      constexpr int CPT = BN / 4;                         // 4-column pieces per row
+      for (int it = threadIdx.x; it < BM * CPT; it += NTHR) {
+        const int r = it / CPT, c = it % CPT * 4;
+        f32x4 v = *reinterpret_cast<const f32x4_mem*>(red + r * S + c);
+#pragma unroll
+        for (int g2 = 1; g2 < KS; ++g2) add4(v, *reinterpret_cast<const f32x4_mem*>(red + (g2 * BM + r) * S + c));
+        if (m0 + r < M) store_row4(v, reinterpret_cast<float*>(C) + (int64_t)(m0 + r) * ldc + n0 + c, N - n0 - c, epi & EPI_ACC32);
       }
-    return;
-  }
-  gemm_epilogue<Tag>([&](auto&& out) {
+    } else {
+      constexpr int CPT = BN / 8;
+      for (int it = threadIdx.x; it < BM * CPT; it += NTHR) {
+        const int r = it / CPT, c = it % CPT * 8;
+        const float* src = red + r * S + c;
+        f32x4 lo = *reinterpret_cast<const f32x4_mem*>(src), hi = *reinterpret_cast<const f32x4_mem*>(src + 4);
+#pragma unroll
+        for (int g2 = 1; g2 < KS; ++g2) {
+          add4(lo, *reinterpret_cast<const f32x4_mem*>(src + g2 * BM * S));
+          add4(hi, *reinterpret_cast<const f32x4_mem*>(src + g2 * BM * S + 4));
+        }
+        if (m0 + r < M && n0 + c < N)
+          store_row8<Tag>(lo, hi, C + (int64_t)(m0 + r) * ldc + n0 + c, N - n0 - c, epi, bias ? bias + n0 + c : nullptr);
+      }
+    }
+  } else {
+    static_assert(KS == 1, "the large tiles have no K split inside the workgroup");
+    constexpr int TJ = Cfg::TN < 2 ? Cfg::TN : 2;         // up to 64 columns at a time
+    typedef RowStore<Tag, 32, TJ * 32, 8> Rows;
+    static_assert(WM * WN * Rows::BYTES <= Cfg::SMEM, "the parking areas fit the LDS");
+    float* park = reinterpret_cast<float*>(smem + wave * Rows::BYTES);
 #pragma unroll
     for (int i = 0; i < Cfg::TM; ++i)
 #pragma unroll
-      for (int j = 0; j < Cfg::TN; ++j) {
-        const int col = col_base + j * 32;
+      for (int j0 = 0; j0 < Cfg::TN; j0 += TJ)
+        Rows::run([&](float* lds) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = row_base + i * 32 + 8 * (r >> 2) + (r & 3);
-          if (row < M && col < N) out((int64_t)row * ldc + col, col, acc[i][j][r]);
-        }
-      }
-  }, C, epi, bias);
+          for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+              *reinterpret_cast<f32_mem*>(lds + (8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * Rows::STRIDE + j * 32 + (lane & 31)) = acc[i][j0 + j][r];
+        }, park, lane, m0 + wm * (BM / WM) + i * 32, n0 + wn * (BN / WN) + j0 * 32, M, N, C, ldc, epi, bias);
+  }
 }
+
 // Second pass of a K split across workgroups: C = epilogue(sum over parts, in the order 0, 1, ...,
-// of the fp32 partial products). One thread per four consecutive columns of a row.
-template <typename Tag>
+// of the fp32 partial products). One thread per four consecutive columns of a row;
+// every part's values are requested before the first is added (up to P of them; a serial loop over
+// the parts waits for one memory round trip after the other).
+template <typename Tag, int P>
 __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(
     int M, int N, int parts, const float* __restrict__ ws, int64_t part_stride,
     uint16_t* __restrict__ C, int64_t ldc, int epi, const uint16_t* __restrict__ bias) {
@@ -402,22 +392,49 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= (int64_t)M * nq) return;
   const int row = (int)(t / nq), col0 = (int)(t % nq) * 4;
-  float acc[4] = {0.f, 0.f, 0.f, 0.f};
   const float* src = ws + (int64_t)row * N + col0;
-  if (col0 + 3 < N && (N & 3) == 0) {
-    for (int p = 0; p < parts; ++p) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(src + (int64_t)p * part_stride);
-      acc[0] += v[0]; acc[1] += v[1]; acc[2] += v[2]; acc[3] += v[3];
-    }
+  const bool whole = col0 + 4 <= N;
+  f32x4 v[P];
+  if (whole) {
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      v[p] = *reinterpret_cast<const f32x4_mem4*>(src + (int64_t)(p < parts ? p : 0) * part_stride);
   } else {
-    for (int p = 0; p < parts; ++p)
-      for (int e = 0; e < 4; ++e)
-        if (col0 + e < N) acc[e] += src[(int64_t)p * part_stride + e];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      for (int e = 0; e < 4; ++e) v[p][e] = col0 + e < N ? src[(int64_t)(p < parts ? p : 0) * part_stride + e] : 0.f;
   }
-  gemm_epilogue<Tag>([&](auto&& out) {
+  float acc[4] = {v[0][0], v[0][1], v[0][2], v[0][3]};
+#pragma unroll
+  for (int p = 1; p < P; ++p)
+    if (p < parts) { acc[0] += v[p][0]; acc[1] += v[p][1]; acc[2] += v[p][2]; acc[3] += v[p][3]; }
+  if (epi & EPI_ACC32) {
+    store_row4(f32x4{acc[0], acc[1], acc[2], acc[3]}, reinterpret_cast<float*>(C) + (int64_t)row * ldc + col0, N - col0, true);
+    return;
+  }
+  const int act = (epi >> EPI_ACT_SHIFT) & EPI_ACT_MASK;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    if (bias && col0 + e < N) acc[e] += Elem<Tag>::to_f32(bias[col0 + e]);
+    acc[e] = epi_act(acc[e], act);
+  }
+  uint16_t* cp = C + (int64_t)row * ldc + col0;
+  if (whole) {
+    *reinterpret_cast<u32x2_mem2*>(cp) = u32x2{Elem<Tag>::pack2(acc[0], acc[1]), Elem<Tag>::pack2(acc[2], acc[3])};
+  } else {
     for (int e = 0; e < 4; ++e)
-      if (col0 + e < N) out((int64_t)row * ldc + col0 + e, col0 + e, acc[e]);
-  }, C, epi, bias);
+      if (col0 + e < N) cp[e] = Elem<Tag>::from_f32(acc[e]);
+  }
+}
+
+template <typename Tag>
+static int launch_splitk_reduce(const GemmArgs& g, int parts, int64_t part_stride, hipStream_t s) {
+  const int64_t nthreads = g.M * ((g.N + 3) / 4);
+  auto kern = parts <= 2 ? gemm_splitk_reduce_kernel<Tag, 2> : parts <= 4 ? gemm_splitk_reduce_kernel<Tag, 4>
+                                                                          : gemm_splitk_reduce_kernel<Tag, 8>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((nthreads + 255) / 256)), dim3(256), 0, s, (int)g.M, (int)g.N,
+                     parts, g.scratch, part_stride, g.C, g.ldc, g.epi(), g.bias);
+  return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 
 template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB, int KS, bool AL>
@@ -452,11 +469,9 @@ static int launch_tile(const GemmArgs& g, hipStream_t s) {
                      (int)g.N, (int)g.K, g.A, g.lda, g.B, g.ldb, reinterpret_cast<uint16_t*>(g.scratch),
                      g.N, nbm, nbn, device_xcds(), (int)EPI_PART32, (const uint16_t*)nullptr, part_steps, part_stride);
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
-  const int64_t nthreads = g.M * ((g.N + 3) / 4);
-  hipLaunchKernelGGL(gemm_splitk_reduce_kernel<Tag>, dim3((unsigned)((nthreads + 255) / 256)), dim3(256),
-                     0, s, (int)g.M, (int)g.N, parts, g.scratch, part_stride, g.C, g.ldc, g.epi(), g.bias);
-  return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
+  return launch_splitk_reduce<Tag>(g, parts, part_stride, s);
 }
+
 // KS: K-split groups per workgroup when B is stored N x K, KS_NN when it is stored K x N (whose
 // padded stage is larger, so fewer groups fit the LDS).
 template <typename Tag, bool AL, int BM, int BN, int BK, int WM, int WN, int KS = 1, int KS_NN = KS>

@@ -25,6 +25,7 @@ typedef u32x2 __attribute__((may_alias)) u32x2_mem;
 
 // 16 bytes at 2-byte alignment
 typedef u32x4 __attribute__((may_alias, aligned(2))) u32x4_mem2;
+typedef u32x2 __attribute__((may_alias, aligned(2))) u32x2_mem2;
 
 // Drops the first n 16-bit elements of a chunk (n >= 8: all of them) and fills up with zeros.
 __device__ __forceinline__ u32x4 drop_elements(u32x4 v, int n) {
@@ -202,6 +203,52 @@ typedef f32x4 __attribute__((may_alias)) f32x4_mem;
 typedef f32x4 __attribute__((may_alias, aligned(4))) f32x4_mem4;
 typedef float __attribute__((may_alias)) f32_mem;
 
+__device__ __forceinline__ void add4(f32x4& a, const f32x4& b) { a[0] += b[0]; a[1] += b[1]; a[2] += b[2]; a[3] += b[3]; }
+
+// Up to four consecutive fp32 elements of a row (`left` of them lie inside the matrix), stored or
+// added to what is there.
+__device__ __forceinline__ void store_row4(f32x4 v, float* dst, int left, bool accumulate) {
+  if (left >= 4) {
+    if (accumulate) {
+      const f32x4 old = *reinterpret_cast<const f32x4_mem4*>(dst);
+      add4(v, old);
+    }
+    *reinterpret_cast<f32x4_mem4*>(dst) = v;
+  } else {
+    for (int e = 0; e < 4; ++e)
+      if (e < left) dst[e] = accumulate ? dst[e] + v[e] : v[e];
+  }
+}
+
+// Up to eight consecutive 16-bit elements of a row (`left` >= 1 of them inside the matrix): bias and
+// activation (bias: of the first element, or null), rounding, one 16-byte store.
+template <typename Tag>
+__device__ __forceinline__ void store_row8(const f32x4& lo, const f32x4& hi, uint16_t* dst, int left, int epi, const uint16_t* bias) {
+  float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  if (bias) {
+    if (left >= 8) {
+      const u32x4 b = *reinterpret_cast<const u32x4_mem2*>(bias);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += Elem<Tag>::to_f32((uint16_t)(b[e >> 1] >> (16 * (e & 1))));
+    } else {
+      for (int e = 0; e < 8; ++e)
+        if (e < left) v[e] += Elem<Tag>::to_f32(bias[e]);
+    }
+  }
+  const int act = (epi >> EPI_ACT_SHIFT) & EPI_ACT_MASK;
+  if (act) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = epi_act(v[e], act);
+  }
+  const u32x4 w = {Elem<Tag>::pack2(v[0], v[1]), Elem<Tag>::pack2(v[2], v[3]), Elem<Tag>::pack2(v[4], v[5]), Elem<Tag>::pack2(v[6], v[7])};
+  if (left >= 8) {
+    *reinterpret_cast<u32x4_mem2*>(dst) = w;
+  } else {
+    for (int e = 0; e < 8; ++e)
+      if (e < left) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+  }
+}
+
 // One wavefront's ROWS x COLS block of the result leaves through LDS. An MFMA accumulator gives a lane
 // single elements of several rows (4 bytes of fp32, 2 of the 16-bit type per store or load
 // instruction and lane); parked in LDS and read back along the rows, a lane holds 8 (fp32: 4)
@@ -212,11 +259,12 @@ typedef float __attribute__((may_alias)) f32_mem;
 // before and after: fp32 accumulate 4096 x 4096 x 2048 115 -> 75 us, 1072 x 5960 x 872 30 -> 25 us; bias
 // and GELU 3000 x 4096 x 1024 67 -> 45 us; plain stores, 32-bit pairs before, 8192^3 +-0.)
 // `park`: LDS of this wavefront's own (nobody else reads it: a wavefront's LDS accesses are served in
-// order, so no barrier), ROWS x STRIDE floats; STRIDE = COLS + 4 keeps the four row groups of an
-// accumulator in different banks (16x16 tiles: rows 4 apart, 4 * STRIDE = 16 mod 64).
+// order, so no barrier), ROWS x STRIDE floats; the padding keeps the row groups that an accumulator
+// register holds in different banks (rows 4 apart: PAD = 4 makes 4 * STRIDE = 16 mod 64 for the four
+// groups of a 16x16 tile, PAD = 8 makes it 32 for the two of a 32x32 tile).
 // row0, col0: the block's place in C. put(park): writes the block, element (r, c) to r * STRIDE + c.
-template <typename Tag, int ROWS, int COLS> struct RowStore {
-  static constexpr int STRIDE = COLS + 4;
+template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
+  static constexpr int STRIDE = COLS + PAD;
   static constexpr int BYTES = ROWS * STRIDE * 4;
   template <typename Put>
   static __device__ __forceinline__ void run(Put&& put, float* park, int lane, int row0, int col0, int M, int N,
