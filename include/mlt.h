@@ -17,9 +17,10 @@
  *     rounded to `dtype` with round-to-nearest-even.
  *   - Return value: MLT_OK or a negative mlt_status. No C++ exception crosses the boundary and
  *     nothing aborts. On an error nothing has been enqueued.
- *   - Device memory of the library's own: the GEMM entry points (few tiles against a long K) and
- *     mlt_paged_attn_decode (few sequences x heads) may spread one result over several workgroups
- *     and then keep fp32 partial results in a scratch buffer, one per (device, stream), allocated
+ *   - Device memory of the library's own: the GEMM entry points (few tiles against a long K),
+ *     mlt_paged_attn_decode (few sequences x heads) and mlt_mha_fwd (few query tiles against many
+ *     keys; never while the stream is recording into a graph) may spread one result over several
+ *     workgroups and then keep fp32 partial results in a scratch buffer, one per (device, stream), allocated
  *     with hipMalloc at the first call that needs it, grown by doubling from 4 MiB (16 MiB covers
  *     every split the library chooses by itself) and kept until the process ends. Calls on one
  *     stream are ordered by the stream; calls on different streams use different buffers. If the

@@ -78,7 +78,7 @@ int mlt_query_tiling(int op, const int64_t dims[4], int dtype, int32_t out[10]);
  * problem (alignment, shape) falls back to one that can, as the automatic choice would.
  *   gemm_variant  "general", "256", "256w8", "256pp16", "128pp16", "128pp16k128", "256w4", "256w8x1",
  *                 "256w1x8", "128w8", "64x128", "64", "128k2", "64x128k2", "64k4", "skinny", "skinnydma"
- *   mha_variant   "pp32", "pp16", "ps"
+ *   mha_variant   "pp32", "pp16", "ps", "k2", "k4"
  * The initial values come from the environment variables MLT_GEMM_VARIANT and MLT_MHA_VARIANT,
  * which are read once, at the first call that needs them. Not synchronised with compute calls
  * running on other threads. Returns MLT_OK, or MLT_ERR_INVALID_ARG for an unknown name (nothing
@@ -98,7 +98,8 @@ int mlt_diag_force_k_parts(int parts);
 /*
  * Number of key ranges per (sequence, head) that mlt_paged_attn_decode spreads over workgroups:
  * 0 = the library's choice (the default: 1 while sequences x heads alone fill the chip, more
- * otherwise), 1..64 = that many (ranges beyond the end of a short sequence stay empty).
+ * otherwise), 1..64 = that many (ranges beyond the end of a short sequence stay empty). The same
+ * for mlt_mha_fwd where its "k2" or "k4" variant is forced.
  * Process-wide. Returns MLT_OK or MLT_ERR_INVALID_ARG.
  */
 int mlt_diag_force_key_split(int ranges);

@@ -378,8 +378,8 @@ std::mutex g_scratch_mu;
 
 }  // namespace
 
-// true while `s` records into a graph: nothing may be allocated then
-static bool stream_is_capturing(hipStream_t s) {
+// nothing may be allocated then
+bool stream_is_capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &st) != hipSuccess) { (void)hipGetLastError(); return false; }
   return st != hipStreamCaptureStatusNone;

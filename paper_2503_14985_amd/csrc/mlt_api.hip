@@ -34,7 +34,7 @@ const VariantName kGemmVariants[] = {
     {"128w8", GEMM_128_W8}, {"64x128", GEMM_64X128_W8}, {"64", GEMM_64_W4}, {"128k2", GEMM_128_K2},
     {"64x128k2", GEMM_64X128_K2}, {"64k4", GEMM_64_K4}, {"skinny", GEMM_SKINNY},
     {"skinnydma", GEMM_SKINNY_DMA}};
-const VariantName kMhaVariants[] = {{"pp32", MHA_PP32}, {"pp16", MHA_PP16}, {"ps", MHA_PS}};
+const VariantName kMhaVariants[] = {{"pp32", MHA_PP32}, {"pp16", MHA_PP16}, {"ps", MHA_PS}, {"k2", MHA_K2}, {"k4", MHA_K4}};
 
 // name -> id; "" and "auto" mean the automatic choice; -2 for an unknown name
 template <size_t N>
@@ -265,7 +265,7 @@ int mlt_mha_fwd(int64_t B, int64_t H, int64_t Sq, int64_t Sk, int64_t D, const v
   if (B == 0 || H == 0 || Sq == 0) return MLT_OK;
   if (!device_is_gfx950()) return MLT_ERR_DEVICE;
   MhaArgs a{B, H, Sq, Sk, D, (const uint16_t*)Q, (const uint16_t*)K, (const uint16_t*)V,
-            (uint16_t*)O, scale, causal ? 1 : 0, dtype, overrides().mha, overrides().ps_grid};
+            (uint16_t*)O, scale, causal ? 1 : 0, dtype, overrides().mha, overrides().ps_grid, overrides().key_split};
   MhaPlan p = plan_mha(a);
   if (!p.supported) return MLT_ERR_UNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
@@ -416,7 +416,8 @@ int mlt_query_tiling(int op, const int64_t dims[4], int dtype, int32_t out[10]) 
   if (op == 1) {
     if (dims[0] < 0 || dims[1] < 1) return MLT_ERR_INVALID_ARG;
     if (dims[2] != 64 && dims[2] != 128) return MLT_ERR_UNSUPPORTED;
-    MhaArgs a{1, 1, dims[0], dims[1], dims[2], nullptr, nullptr, nullptr, nullptr, 1.f,
+    // (batch and heads are unknown here: assume enough of them to fill the chip)
+    MhaArgs a{1, 1 << 16, dims[0], dims[1], dims[2], nullptr, nullptr, nullptr, nullptr, 1.f,
               dims[3] ? 1 : 0, dtype, overrides().mha, overrides().ps_grid};
     MhaPlan p = plan_mha(a);
     if (!p.supported) return MLT_ERR_UNSUPPORTED;

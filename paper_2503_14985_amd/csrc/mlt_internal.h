@@ -81,6 +81,8 @@ enum MhaVariant {
   MHA_PP32 = 0,   // two-group kernel, 32x32x16 MFMAs, one workgroup per (batch*head, query tile)
   MHA_PP16 = 1,   // the same on 16x16x32 MFMAs
   MHA_PS = 2,     // persistent form of the two-group kernel (unmasked, D = 128, at least two key tiles)
+  MHA_K2 = 3,     // 128 query rows per workgroup, the keys split over two groups of wavefronts
+  MHA_K4 = 4,     // 64 query rows per workgroup, the keys split over four groups
   MHA_NUM_VARIANTS
 };
 
@@ -92,6 +94,7 @@ struct MhaArgs {
   int causal, dtype;
   int forced = MHA_AUTO;   // MhaVariant or MHA_AUTO
   int ps_grid = 0;         // persistent kernel: number of workgroups (0: one per CU)
+  int forced_split = 0;    // MHA_K2 / MHA_K4: ranges of keys per item, from mlt_diag_force_key_split (0: automatic)
 };
 
 struct MhaPlan {
@@ -100,9 +103,14 @@ struct MhaPlan {
   bool supported = false;
   int mfma_size = 32;       // 32 = 32x32x16 MFMAs, 16 = 16x16x32
   bool persistent = false;  // one workgroup per CU walking through the items
+  int key_groups = 1;       // > 1: the kernels of mha_ks.hip, bm = 256 / key_groups
+  int nsplit = 1;           // > 1: their keys are split over that many workgroups as well, partial results through a scratch
 };
 bool mha_pp_ok(const MhaArgs& a);
 int run_mha_pp(const MhaArgs& a, int mfma_size, hipStream_t s);
+// mha_ks.hip; bm: 64 or 128 query rows per workgroup; nsplit > 1: scratch holds mha_ks_scratch_bytes
+int run_mha_ks(const MhaArgs& a, int bm, int nsplit, float* scratch, hipStream_t s);
+inline int64_t mha_ks_scratch_bytes(const MhaArgs& a, int nsplit) { return nsplit * a.B * a.H * a.Sq * (a.D + 2) * 4; }
 bool mha_ps_ok(const MhaArgs& a);              // mha_pp.hip: can the persistent kernel take this problem?
 int run_mha_ps(const MhaArgs& a, hipStream_t s);
 
@@ -123,7 +131,7 @@ double run_mfma_probe(int iters, int nblocks, const void* data, float* sink, int
 int run_hbm_read_probe(const void* data, int64_t bytes, uint32_t* sink, int ncu, hipStream_t s);
 
 MhaPlan plan_mha(const MhaArgs& a);
-int run_mha(const MhaArgs& a, const MhaPlan& p, hipStream_t s);
+int run_mha(const MhaArgs& a, MhaPlan& p, hipStream_t s);
 
 struct PagedArgs {
   int64_t B, H, D, block_size, max_blocks, num_blocks;
@@ -141,5 +149,6 @@ int run_paged_decode(const PagedArgs& a, hipStream_t s, int* nsplit_out);
 // (and grown by doubling) from call to call, never freed; nullptr if it cannot be had. Work of
 // one stream that uses it is ordered by the stream.
 float* cached_scratch(int64_t bytes, hipStream_t s);
+bool stream_is_capturing(hipStream_t s);   // true while `s` records into a graph
 
 }  // namespace mlt
