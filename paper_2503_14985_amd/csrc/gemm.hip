@@ -187,7 +187,7 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   const Cand split[] = {{GEMM_128_K2, 128, 128, 560, 2000, 2}, {GEMM_64X128_K2, 64, 128, 370, 0, 2}, {GEMM_64_K4, 64, 64, 220, 0, 4}};
   const Cand whole[] = {{GEMM_128_W8, 128, 128, 600, 0, 1}, {GEMM_64X128_W8, 64, 128, 410, 0, 1}, {GEMM_64_W4, 64, 64, 350, 0, 1}};
   struct Choice { int variant, parts, area; int64_t t; };
-  Choice all[20];
+  Choice all[32];
   int n_all = 0;
   // no tile taller or wider than the matrix rounded up to 64 (it would multiply padding)
   auto fits = [&](int bm, int bn) {
@@ -223,10 +223,34 @@ GemmPlan plan_gemm(const GemmArgs& g) {
       all[n_all++] = Choice{GEMM_128_PP16_K128, 1, 128 * 128, own128 > arrive ? own128 : arrive};
     }
   }
+  // The kernels with two groups on alternate K steps (gemm_kp.hip). Their step is bound by what the L2s
+  // deliver (about 17 TB/s), so it takes longer the more CUs have a workgroup (us per 64 of K, 80 / 160 / 256
+  // workgroups, call included: 256 x 128 0.56 / 0.64 / 0.73, 128 x 128 0.36 / 0.40 / 0.50, the two-group kernel
+  // with K steps of 128 0.36 / 0.43 / 0.55; below 0.8 to 0.85 of that, the scale of the other candidates).
+  // bf16, us: 1024 x 8192 x 8192 128 on the best of the other tiles, 102 here; 2048 x 4096 x 4096 60 / 55;
+  // 512 x 8192 x 8192 77 / 69; with K in two or four parts 777 x 4096 x 14336 131 / 97, 400 x 4096 x 11008
+  // 57 / 47. The 6 us per round hold the sum of the two groups' results, which is why short K stays
+  // with the others (2048^3: 21.4 on K steps of 128, 22.1 here). The scratch of a K split may take all
+  // that mlt_gemm_noalloc has and no more, so that both entry points choose alike.
+  auto cost_kp = [&](int64_t bm, int parts) {
+    const int64_t wgs = ((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * parts;
+    const int64_t rounds = (wgs + NCU - 1) / NCU, steps = (KT + parts - 1) / parts;
+    const int64_t share = wgs < NCU ? wgs * 1000 / NCU : 1000;
+    int64_t t_step = bm == 256 ? 425 + 195 * share / 1000 : 206 + 190 * share / 1000;
+    if (g.K % 64) t_step += t_step * 15 / 100;
+    const int64_t compute = rounds * (steps * t_step + (bm == 256 ? 6000 : 5700));
+    const int64_t base = (g.M + g.N) * g.K * 2 / 5200, need = 6 * NCU / 10;
+    const int64_t arrive = wgs >= need ? base : base * need / wgs;
+    return (compute > arrive ? compute : arrive) + (parts > 1 ? 4000 + 2 * parts * g.M * g.N / 1000 : 0);
+  };
   for (int parts = g.forced_parts > 0 ? g.forced_parts : 1; parts <= (g.forced_parts > 0 ? g.forced_parts : 8); parts *= 2) {
     // every part keeps at least 8 K steps, and its partial tiles must fit the scratch allowed
     if (parts > 1 && KT < 8 * parts) break;
     if (parts > 1 && g.scratch_limit >= 0 && (int64_t)parts * g.M * g.N * 4 > g.scratch_limit) break;
+    if (pp && KT >= 8 * parts && (parts == 1 || g.forced_parts > 0 || (int64_t)parts * g.M * g.N * 4 <= kStaticScratchBytes)) {
+      if (g.M > 128 && fits(64, 128)) all[n_all++] = Choice{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
+      if (fits(128, 128)) all[n_all++] = Choice{GEMM_128_KP, parts, 128 * 128, cost_kp(128, parts)};
+    }
     for (const auto& c : KT / parts < 8 ? whole : p.aligned ? split : any) {
       if (!fits(c.bm, c.bn)) continue;
       all[n_all++] = Choice{c.variant, parts, c.bm * c.bn, cost(c.bm, c.bn, c.t, c.fixed, parts, c.kgroups)};
@@ -287,12 +311,13 @@ GemmPlan plan_gemm(const GemmArgs& g) {
       g.forced != GEMM_SKINNY_DMA)
     v = g.forced;
   if (v == GEMM_256_PP16 && !gemm_pp_ok(g)) v = GEMM_256_W8;
+  if ((v == GEMM_256X128_KP || v == GEMM_128_KP) && !pp) v = v == GEMM_128_KP ? GEMM_128_W8 : GEMM_256_W8;
   if (v == GEMM_256_W4 && !gemm_w4_ok(g)) v = GEMM_256_W8;
   if (v == GEMM_128_PP16_K128 && (!pp || g.K % 128)) v = GEMM_128_PP16;
   if (v == GEMM_128_PP16 && !pp) v = GEMM_128_W8;
   // a forced kernel keeps the split only if it is one of the kernels that can run it
   const bool can_split = v == GEMM_128_K2 || v == GEMM_64X128_K2 || v == GEMM_64_K4 || v == GEMM_128_W8 ||
-                         v == GEMM_64X128_W8 || v == GEMM_64_W4;
+                         v == GEMM_64X128_W8 || v == GEMM_64_W4 || v == GEMM_256X128_KP || v == GEMM_128_KP;
   if (!p.aligned && (v == GEMM_256 || v == GEMM_256_W8X1 || v == GEMM_256_W1X8)) v = GEMM_256_W8;
   p.parts = can_split ? best_parts : 1;
   p.scratch_bytes = p.parts > 1 ? (int64_t)p.parts * g.M * g.N * 4 : 0;
@@ -310,6 +335,12 @@ GemmPlan plan_gemm(const GemmArgs& g) {
     case GEMM_256_PP16: p.bm = p.bn = 256; p.wm = 2; p.wn = 4;
       p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
       p.name = g.transB ? "gemm_nt_256x256x64_w2x4_pp16" : "gemm_nn_256x256x64_w2x4_pp16"; break;
+    case GEMM_256X128_KP: p.bm = 256; p.bn = 128; p.wm = 2; p.wn = 2;
+      p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
+      p.name = g.transB ? "gemm_nt_256x128x64_w2x2_kp2" : "gemm_nn_256x128x64_w2x2_kp2"; break;
+    case GEMM_128_KP: p.bm = p.bn = 128; p.wm = 2; p.wn = 2;
+      p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
+      p.name = g.transB ? "gemm_nt_128x128x64_w2x2_kp2" : "gemm_nn_128x128x64_w2x2_kp2"; break;
     case GEMM_128_PP16: p.bm = p.bn = 128; p.wm = 2; p.wn = 4;
       p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
       p.name = g.transB ? "gemm_nt_128x128x64_w2x4_pp16" : "gemm_nn_128x128x64_w2x4_pp16"; break;
@@ -337,6 +368,11 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   return p;
 }
 
+int run_splitk_reduce(const GemmArgs& g, int parts, int64_t part_stride, hipStream_t s) {
+  return g.dtype == MLT_BF16 ? launch_splitk_reduce<bf16_tag>(g, parts, part_stride, s)
+                             : launch_splitk_reduce<f16_tag>(g, parts, part_stride, s);
+}
+
 template <typename Tag>
 static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
   if (!p.aligned) return run_gemm_any(g, p.variant, s);
@@ -355,6 +391,8 @@ static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     case GEMM_256_PP16: return run_gemm_pp(g, 256, 64, s);
     case GEMM_128_PP16: return run_gemm_pp(g, 128, 64, s);
     case GEMM_128_PP16_K128: return run_gemm_pp(g, 128, 128, s);
+    case GEMM_256X128_KP: return run_gemm_kp(g, 256, s);
+    case GEMM_128_KP: return run_gemm_kp(g, 128, s);
     case GEMM_256_W4: return run_gemm_w4(g, s);
     case GEMM_SKINNY: return run_gemm_skinny(g, s);
     case GEMM_SKINNY_DMA: return run_gemm_skinny_dma(g, s);

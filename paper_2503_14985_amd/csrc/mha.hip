@@ -92,6 +92,7 @@ MhaPlan plan_mha(const MhaArgs& a) {
         {{"mha_fwd_d64_128x32_k2_pp", "mha_fwd_d64_causal_128x32_k2_pp"}, {"mha_fwd_d64_64x32_k4_pp", "mha_fwd_d64_causal_64x32_k4_pp"}},
         {{"mha_fwd_d128_128x32_k2_pp", "mha_fwd_d128_causal_128x32_k2_pp"}, {"mha_fwd_d128_64x32_k4_pp", "mha_fwd_d128_causal_64x32_k4_pp"}}};
     p.bm = PA_BM / p.key_groups;
+    p.waves = PA_NT / 64 / p.key_groups;                          // along the rows
     p.bn = 32;
     p.mfma_size = 32;
     p.name = names[a.D == 128][p.key_groups == 4][a.causal ? 1 : 0];

@@ -24,6 +24,8 @@ enum GemmVariant {
   GEMM_64_K4 = 19,    // 64x64x64, 4 groups of 4 wavefronts (3 when B is K x N), each group its share of the K steps
   GEMM_128_PP16 = 20, // 128x128x64, 8 wavefronts (2x4) of 64x32, two-group schedule, direct-to-LDS loads, two workgroups per CU
   GEMM_128_PP16_K128 = 21, // the same tile with K steps of 128 (one workgroup per CU, phases of twice the length)
+  GEMM_256X128_KP = 22, // 256x128x64, two groups of 4 wavefronts (2x2) of 128x64 on alternate K steps, direct-to-LDS loads
+  GEMM_128_KP = 23,   // 128x128x64, the same with 64x64 per wavefront
   GEMM_NUM_VARIANTS
 };
 
@@ -58,7 +60,7 @@ struct GemmPlan {
 };
 
 // mlt_gemm_noalloc: bytes of the fixed device array that takes the partial products of a K split
-// across workgroups (no plan the library makes by itself needs more than half of it), and that
+// across workgroups (no plan the library makes by itself needs more), and that
 // array's address on the current device (nullptr if it cannot be had)
 constexpr int64_t kStaticScratchBytes = (int64_t)32 << 20;
 float* static_scratch_of_current_device();
@@ -67,6 +69,8 @@ GemmPlan plan_gemm(const GemmArgs& g);
 int run_gemm(const GemmArgs& g, GemmPlan& p, hipStream_t s);
 bool gemm_pp_ok(const GemmArgs& g);            // gemm_pp.hip: can the two-group kernel take this problem?
 int run_gemm_pp(const GemmArgs& g, int tile, int kstep, hipStream_t s);   // tile: 256 or 128; K step 64 or (tile 128 only) 128
+int run_gemm_kp(const GemmArgs& g, int bm, hipStream_t s);   // gemm_kp.hip (where gemm_pp_ok): bm x 128, bm 256 or 128; g.parts > 1: K split across workgroups
+int run_splitk_reduce(const GemmArgs& g, int parts, int64_t part_stride, hipStream_t s);   // gemm.hip: the sum of the parts, with the epilogue
 bool gemm_any_ok(const GemmArgs& g);           // gemm_any.hip: the tile kernels on operands of any alignment
 int run_gemm_any(const GemmArgs& g, int variant, hipStream_t s);
 bool gemm_w4_ok(const GemmArgs& g);            // gemm_w4.hip: whole K steps only

@@ -7,6 +7,7 @@ import torch
 
 from paper_2503_14985_amd import inputs
 import parity_util as pu
+from test_debug_barriers_gpu import dbg, _stream  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
 BF16, FP16 = inputs.BF16, inputs.FP16
@@ -65,6 +66,32 @@ def test_automatic_choice():
     for shape, tag in (((1, 8, 200, 1000, 64, BF16, False), "64x32_k4_pp"), ((4, 16, 300, 2000, 128, BF16, False), "128x32_k2_pp"),
                        ((8, 32, 256, 256, 128, BF16, False), "256x64_pp"), ((1, 8, 5, 4096, 128, FP16, False), "64x32_k4_pp")):
         assert _go(*shape, seed=7).endswith(tag)
+
+
+@pytest.mark.parametrize("variant,split", [("k2", 0), ("k4", 0), ("k4", 3)])
+def test_agrees_with_the_debug_build(dbg, variant, split):  # noqa: F811
+    from paper_2503_14985_amd import binding
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(6)
+    try:
+        for (B, H, Sq, Sk, D, causal) in ((2, 4, 300, 1501, 128, 0), (2, 4, 700, 700, 64, 1), (1, 2, 130, 2000, 64, 0)):
+            q, k, v = (torch.randn((B, H, s, D), generator=g, device=dev).to(torch.bfloat16) for s in (Sq, Sk, Sk))
+            binding.mlt_diag_force_variant(mha=variant)
+            binding.mlt_diag_force_key_split(split)
+            dbg.mlt_diag_force_variant(None, variant.encode())
+            dbg.mlt_diag_force_key_split(split)
+            want = binding.mlt_mha_fwd(q, k, v, 0.1, causal=bool(causal))
+            for _ in range(3):
+                got = torch.full_like(want, float("nan"))
+                rc = dbg.mlt_mha_fwd(B, H, Sq, Sk, D, q.data_ptr(), k.data_ptr(), v.data_ptr(), got.data_ptr(), 0.1, causal,
+                                     0, _stream())
+                assert rc == 0
+                torch.cuda.synchronize()
+                assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    finally:
+        dbg.mlt_diag_force_variant(b"auto", b"auto")
+        dbg.mlt_diag_force_key_split(0)
 
 
 def test_captured_call_needs_no_scratch():
