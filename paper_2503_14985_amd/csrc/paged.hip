@@ -61,6 +61,33 @@ template <> struct Dot2<f16_tag> {
   }
 };
 
+// The sequence that comes `rank`-th when a batch is ordered by length, longest first (equal lengths: by
+// index). B <= PG_NT; buf: PG_NT + 1 ints of LDS. Contains workgroup barriers; afterwards buf is free.
+__device__ __forceinline__ int sequence_of_rank(const int32_t* seq_lens, int B, int rank, int* buf) {
+  const int tid = threadIdx.x;
+  const int mine = tid < B ? seq_lens[tid] : -0x7fffffff - 1;
+  buf[tid] = mine;
+  __syncthreads();
+  if (tid < B) {
+    int before = 0;
+    for (int j = 0; j < B; ++j) {
+      const int other = buf[j];
+      before += other > mine || (other == mine && j < tid) ? 1 : 0;
+    }
+    if (before == rank) buf[PG_NT] = tid;
+  }
+  __syncthreads();
+  const int b = __builtin_amdgcn_readfirstlane(buf[PG_NT]);
+  __syncthreads();
+  return b;
+}
+
+// Which workgroup takes which sequence: hardware deals the workgroups of a launch to the CUs in turn, all of
+// them at once up to 8 per CU, and with the batch in its own order the CUs' shares of keys differ by
+// chance. With ncu > 0 (a batch of 2 to PG_NT sequences, more workgroups than CUs) the pieces are dealt from the
+// longest sequence to the shortest, every second round of CUs backwards. 64 sequences of 1024 to 4096
+// keys, 32 heads, D = 128, shuffled: 456 -> 421 us (6.4 TB/s, as for equal lengths).
+//
 // SPLIT: blockIdx.y is the range of units this workgroup takes, and the result goes to `part`
 // ([pair][range][2 + D] floats: maximum (log2 domain), sum, unnormalised outputs) instead of O.
 template <typename Tag, int D, bool SPLIT>
@@ -68,18 +95,34 @@ __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc,
     const uint16_t* __restrict__ Vc, const int32_t* __restrict__ block_table,
     const int32_t* __restrict__ seq_lens, uint16_t* __restrict__ O, float* __restrict__ part, int H,
-    int block_size, int max_blocks, int num_blocks, float c) {
+    int block_size, int max_blocks, int num_blocks, int B, int ncu, float c) {
   constexpr int LPR = D / 8;                 // lanes per key row (16 bytes each)
   constexpr int RPI = 64 / LPR;              // key rows per load instruction
   constexpr int NL = PG_UNIT / RPI;          // loads per unit and matrix
   constexpr int NSPLIT = PG_NW * RPI;        // partial results per workgroup
   __shared__ float sm[NSPLIT], sl[NSPLIT];
-  __shared__ float so[NSPLIT][D];
+  __shared__ float so[NSPLIT][D];                        // (the rank search borrows it)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rgrp = lane / LPR, chunk = lane % LPR;
-  const int bh = blockIdx.x, b = bh / H, h = bh % H;
+  const int nsplit = SPLIT ? (int)gridDim.y : 1;
+  // which sequence, head and range
+  int b, h, range = 0;
+  if (ncu > 0) {
+    const int pieces = H * nsplit, total = B * pieces;
+    int id = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+    const int blk = id / ncu * ncu;
+    if ((id / ncu & 1) && blk + ncu <= total) id = blk + (ncu - 1 - (id - blk));
+    b = sequence_of_rank(seq_lens, B, id / pieces, reinterpret_cast<int*>(&so[0][0]));
+    h = id % pieces / nsplit;
+    range = id % nsplit;
+  } else {
+    b = blockIdx.x / H;
+    h = blockIdx.x % H;
+    if (SPLIT) range = blockIdx.y;
+  }
+  const int bh = b * H + h;
 
   int len = seq_lens[b];
   const int cap = max_blocks * block_size;
@@ -90,9 +133,8 @@ __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
   // equal length (a multiple of the wavefront count; the last ranges of a short sequence are empty)
   int u_begin = 0, nunits = all_units;
   if (SPLIT) {
-    const int nsplit = (int)gridDim.y;
     const int per = ((all_units + nsplit - 1) / nsplit + PG_NW - 1) / PG_NW * PG_NW;
-    u_begin = (int)blockIdx.y * per;
+    u_begin = range * per;
     nunits = u_begin + per < all_units ? u_begin + per : all_units;
   }
 
@@ -189,7 +231,7 @@ __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
       acc += so[s][tid] * wgt;
     }
     if (SPLIT) {
-      float* out = part + ((int64_t)bh * gridDim.y + blockIdx.y) * (2 + D);
+      float* out = part + ((int64_t)bh * nsplit + range) * (2 + D);
       if (tid == 0) { out[0] = M; out[1] = L; }
       out[2 + tid] = acc;
     } else {
@@ -198,68 +240,95 @@ __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
   }
 }
 
-// One workgroup of D threads per (sequence, head): the ranges' partial results, in index order.
-// Range 0 is never empty (a sequence has at least one key), so the maximum is finite.
+// One workgroup per (sequence, head), D x 4 threads: group g adds the ranges g, g + 4, ... (at most 64 in all)
+// and the four sums meet in LDS in the order 0, 1, 2, 3. A sequence has at least one key, so range 0 is never
+// empty and the maximum is finite.
+constexpr int PG_MAX_SPLIT = 64;
 template <typename Tag, int D>
-__global__ __launch_bounds__(D) void paged_merge_kernel(const float* __restrict__ part,
-                                                        uint16_t* __restrict__ O, int nsplit) {
-  // the ranges' maxima and sums go through LDS (one load each, all in flight together), the
-  // output slices are read with eight loads in flight per thread: a plain loop over the ranges
-  // would wait for one memory round trip after the other (measured 16 us for 32 ranges)
-  __shared__ float sm[64], sl[64];
-  const int bh = blockIdx.x, tid = threadIdx.x;
+__global__ __launch_bounds__(4 * D) void paged_merge_kernel(const float* __restrict__ part,
+                                                            uint16_t* __restrict__ O, int nsplit) {
+  // All of a thread's loads are requested at once: this kernel is the memory round trips that it waits
+  // for (a plain loop over 32 ranges: 16 us, eight loads in flight 3.9 us).
+  constexpr int NR = PG_MAX_SPLIT / 4;
+  __shared__ float sm[PG_MAX_SPLIT], sl[PG_MAX_SPLIT], acc4[4][D], l4[4];
+  const int bh = blockIdx.x, tid = threadIdx.x, g = tid / D, d = tid % D;
   const float* p = part + (int64_t)bh * nsplit * (2 + D);
-  if (tid < nsplit) {
-    sm[tid] = p[tid * (2 + D)];
-    sl[tid] = p[tid * (2 + D) + 1];
+  float v[NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i) v[i] = g + 4 * i < nsplit ? p[(g + 4 * i) * (2 + D) + 2 + d] : 0.f;
+  if (tid < PG_MAX_SPLIT) {
+    sm[tid] = tid < nsplit ? p[tid * (2 + D)] : -__builtin_inff();
+    sl[tid] = tid < nsplit ? p[tid * (2 + D) + 1] : 0.f;
   }
   __syncthreads();
   float M = sm[0];
-  for (int s = 1; s < nsplit; ++s) M = __builtin_fmaxf(M, sm[s]);
-  float L = 0.f, acc = 0.f;
-#pragma unroll 8
-  for (int s = 0; s < nsplit; ++s) {
-    const float wgt = __builtin_amdgcn_exp2f(sm[s] - M);           // empty ranges: exp2(-inf) = 0
-    L += sl[s] * wgt;
-    acc += p[s * (2 + D) + 2 + tid] * wgt;
+#pragma unroll
+  for (int s = 1; s < PG_MAX_SPLIT; ++s) M = __builtin_fmaxf(M, sm[s]);
+  float acc = 0.f, L = 0.f;
+#pragma unroll
+  for (int i = 0; i < NR; ++i) {
+    const float wgt = __builtin_amdgcn_exp2f(sm[g + 4 * i] - M);           // empty ranges: exp2(-inf) = 0
+    acc += v[i] * wgt;
+    L += sl[g + 4 * i] * wgt;
   }
-  O[(int64_t)bh * D + tid] = Elem<Tag>::from_f32(acc / L);
+  acc4[g][d] = acc;
+  if (d == 0) l4[g] = L;
+  __syncthreads();
+  if (g == 0)
+    O[(int64_t)bh * D + d] = Elem<Tag>::from_f32((acc4[0][d] + acc4[1][d] + acc4[2][d] + acc4[3][d]) / (l4[0] + l4[1] + l4[2] + l4[3]));
 }
 
 template <typename Tag, int D>
 int launch_paged(const PagedArgs& a, int nsplit, float* part, hipStream_t s) {
   const float c = a.scale * 1.4426950408889634f;
   const unsigned pairs = (unsigned)(a.B * a.H);
+  DeviceInfo di;
+  const int64_t ncu = device_info(di) ? di.ncu : 0;
+  const int order_ncu = a.B > 1 && a.B <= PG_NT && a.B * a.H * (nsplit > 1 ? nsplit : 1) > ncu ? (int)ncu : 0;
   if (nsplit <= 1) {
     hipLaunchKernelGGL((paged_decode_kernel<Tag, D, false>), dim3(pairs), dim3(PG_NT), 0, s,
                        a.Q, a.Kc, a.Vc, a.block_table, a.seq_lens, a.O, (float*)nullptr, (int)a.H,
-                       (int)a.block_size, (int)a.max_blocks, (int)a.num_blocks, c);
+                       (int)a.block_size, (int)a.max_blocks, (int)a.num_blocks, (int)a.B, order_ncu, c);
     return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
   }
   hipLaunchKernelGGL((paged_decode_kernel<Tag, D, true>), dim3(pairs, (unsigned)nsplit), dim3(PG_NT), 0, s,
                      a.Q, a.Kc, a.Vc, a.block_table, a.seq_lens, a.O, part, (int)a.H,
-                     (int)a.block_size, (int)a.max_blocks, (int)a.num_blocks, c);
+                     (int)a.block_size, (int)a.max_blocks, (int)a.num_blocks, (int)a.B, order_ncu, c);
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
-  hipLaunchKernelGGL((paged_merge_kernel<Tag, D>), dim3(pairs), dim3(D), 0, s, part, a.O, nsplit);
+  hipLaunchKernelGGL((paged_merge_kernel<Tag, D>), dim3(pairs), dim3(4 * D), 0, s, part, a.O, nsplit);
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 
 }  // namespace
 
-// Ranges per (sequence, head): 1 while the pairs alone give every CU a workgroup; otherwise what
-// brings the launch to two workgroups per CU, as long as a range of the longest possible sequence
-// (the table's width) keeps at least 16 units (256 keys), and at most 32 (measured on 8 to 256
-// pairs of 2k to 32k keys: more ranges than that lose to their own start and end).
+// Ranges per (sequence, head), at most 64. Up to one workgroup per CU from the pairs alone: what brings the
+// launch to two per CU, as long as a range of the longest possible sequence (the table's width) keeps 16
+// units (256 keys); twice that for one sequence whose ranges are short anyway, down to 8 units
+// (1 x 32 pairs, 4096 keys: 15.0 us with 16 ranges, 13.7 with 32). A batch, whose sequences differ in
+// length, is cut finer, up to 8 pieces per CU and 32 units, also beyond one pair per CU: the pieces are dealt out by
+// length, and the more there are the closer the CUs' shares come (us, lengths s/4 .. s, D = 128: 10 x 32, s = 4096:
+// 102 uncut, 71 in 6 ranges; 8 x 16, 32768: 238 in 4, 208 in 16; 16 x 32, 4096: 118 uncut, 111 in 4; equal lengths
+// 121 / 112, 335 / 331, 168 / 173). From three pairs per CU on the second kernel costs as much as that gains
+// (24 x 32, 2048: 83.8 uncut, 86.3 in 2), and so it does where the cache is read in less than 20 us.
 int plan_paged_split(const PagedArgs& a) {
-  if (a.forced_split > 0) return a.forced_split > 64 ? 64 : a.forced_split;
+  if (a.forced_split > 0) return a.forced_split > PG_MAX_SPLIT ? PG_MAX_SPLIT : a.forced_split;
   DeviceInfo di;
   const int64_t ncu = device_info(di) ? di.ncu : 256;
   const int64_t pairs = a.B * a.H;
-  if (pairs > ncu) return 1;
   const int64_t max_units = (a.max_blocks * a.block_size + PG_UNIT - 1) / PG_UNIT;
-  int64_t n = (2 * ncu + pairs - 1) / pairs;
-  if (n > max_units / 16) n = max_units / 16;
-  if (n > 32) n = 32;
+  int64_t n = 1;
+  if (pairs <= ncu) {
+    n = (2 * ncu + pairs - 1) / pairs;
+    if (n > max_units / 16) n = max_units / 16;
+    if (a.B == 1 && n > 1 && max_units <= 64 * n && max_units >= 16 * n) n *= 2;
+  }
+  const bool long_read = pairs <= ncu || pairs * max_units * PG_UNIT * a.D * 4 >= ((int64_t)128 << 20);
+  if (a.B > 1 && a.B <= PG_NT && pairs < 3 * ncu && long_read) {
+    int64_t fine = 8 * ncu / pairs;
+    if (fine > max_units / 32) fine = max_units / 32;
+    if (fine > n) n = fine;
+  }
+  if (n > PG_MAX_SPLIT) n = PG_MAX_SPLIT;
   return n < 1 ? 1 : (int)n;
 }
 
