@@ -278,7 +278,7 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // ---- the skinny kernels (B stored N x K, no LDS staging of A): the automatic choice for one
   // 16-row tile of A, and for two when they beat the tile kernels' estimate; B streamed through
   // an LDS ring (16 columns x 512 k per stage, the A fragments of a k stage shared by a group of
-  // column blocks) once B is well beyond the caches: measured 5.7 TB/s of B for M <= 16; for two
+  // column blocks): measured 5.7 TB/s of B for M <= 16; for two
   // row tiles 4.7-5.9 TB/s with 16384 columns or more and 3.0-4.6 TB/s with fewer (32 x 8192 x
   // 28672: 103 us, against 85 us for the tile kernels with K split four ways). The rates that
   // decide are those with B coming from memory, as the weights of a decoder do (every matrix is
@@ -289,11 +289,19 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // the streaming kernel 55 and 56 us; 32 x 65536 x 2048: 43 / 65 against 53 / 54 us). Taller A
   // goes to the tile kernels, which stage A through LDS once per tile (64 x 28672 x 8192: 99 us
   // against 160 us streaming; 64 x 14336 x 4096: 20 us against 43 us).
+  // A smaller B (kernel time, us, K split over wavefronts / streaming / small tiles): 8 x 2048 x 2048 6.0 / 5.4 /
+  // 10.2; 16 x 1024 x 8192 17.0 / 13.4 / 28; 4 x 6144 x 4096 16.4 / 12.7 / 17.6; 20 x 5120 x 5120 29 / 17.9 / 23.6;
+  // 16 x 4096 x 4096 11.8 / 11.7 / 17.6, 1 x 4096 x 4096 9.8 / 10.5 / 17: the streaming kernel, except with
+  // the one column block per CU that leaves nothing to its persistent workgroups. A fused epilogue goes
+  // with the streaming kernel only, down to where the launch is all that counts.
   const bool big_b = g.N * g.K >= ((int64_t)1 << 25);
-  const int64_t two_tile_rate = g.N >= 16384 ? 5600 : 3900;  // bytes of B per us, B from memory
+  // bytes of B per us, B from memory (N = 4096, one column block per CU, so A is read for every one: 2900)
+  const int64_t two_tile_rate = g.N >= 16384 ? 5600 : g.N >= 8192 ? 4600 : 2900;
   const bool stream_wins = g.M <= 16 || g.N * g.K * 2 / two_tile_rate < best;
-  const bool skinny_auto = g.forced == GEMM_AUTO && g.M <= 32 && (!big_b || stream_wins);
-  if ((g.forced == GEMM_SKINNY_DMA || (skinny_auto && big_b)) && gemm_skinny_dma_ok(g)) {
+  const bool skinny_auto = g.forced == GEMM_AUTO && g.M <= 32 && stream_wins &&
+                           (!g.fused() || g.N * g.K >= ((int64_t)1 << 21));
+  const bool one_block_per_cu = !big_b && !g.fused() && g.N > 14 * NCU && g.N <= 16 * NCU;
+  if ((g.forced == GEMM_SKINNY_DMA || (skinny_auto && !one_block_per_cu)) && gemm_skinny_dma_ok(g)) {
     p.variant = GEMM_SKINNY_DMA;
     p.name = "gemm_nt_skinny_16cols_stream";
     p.bm = (int)((g.M + 15) / 16) * 16; p.bn = 16; p.bk = 512;

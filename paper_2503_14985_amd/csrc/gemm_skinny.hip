@@ -9,7 +9,7 @@
 //   * a lane loads 16 bytes (8 consecutive k) of one B row straight into the register that the
 //     16x16x32 MFMA wants as its B operand (lane l: column l % 16, k slots 8*(l/16)..+7), and the
 //     matching 16 bytes of one A row as the A operand; A (M x K, at most 64 rows) stays in L2;
-//   * 16 KB of B per wavefront are in flight before the first MFMA of a batch;
+//   * two batches of chunks are in registers, one in flight while the other is multiplied;
 //   * the 8 partial 16 x 16 fp32 tiles are added through LDS and rounded to 16 bit once.
 // Requirements (host): transB, M <= 64, K % 8 == 0, lda % 8 == 0, ldb % 8 == 0, A and B 16-byte
 // aligned. N and K need not be multiples of the tile.
@@ -22,18 +22,18 @@ namespace {
 
 constexpr int SK_NW = 8;            // wavefronts per workgroup = K split
 constexpr int SK_NT = SK_NW * 64;
-constexpr int SK_U = 16;            // chunks in flight per wavefront
 constexpr int SK_MAXMT = 4;         // 16-row tiles of A (M <= 64)
 
-template <typename Tag, int MT, int NT>
-__global__ __launch_bounds__(SK_NT) void gemm_skinny_nt_kernel(
+// U: k chunks per batch; two batches are in registers, one on its way while the other is multiplied.
+template <typename Tag, int MT, int NT, int U>
+__global__ __launch_bounds__(SK_NT, MT <= 2 && U * NT <= 4 ? 4 : 2) void gemm_skinny_nt_kernel(
     int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
     const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc) {
   typedef typename Elem<Tag>::vec8 V8;
-  constexpr int U = SK_U / NT;               // chunks per batch: 16 KB of B in flight per wavefront
   __shared__ float red[SK_NW][256];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, q = lane >> 4;
   const int n0 = blockIdx.x * (16 * NT);
   const uint16_t* bp[NT];
@@ -57,42 +57,62 @@ __global__ __launch_bounds__(SK_NT) void gemm_skinny_nt_kernel(
 
   const int KC = (K + 31) / 32;                            // 32-wide chunks; K % 8 == 0
   const u32x4 zero4 = {0u, 0u, 0u, 0u};
-  for (int c0 = wave; c0 < KC; c0 += SK_NW * U) {
-    // k of this lane's 8 values in chunk u of the batch; past K (last batch only) the loads
-    // re-read k = 0 and the B values are zeroed after they have arrived
-    const bool whole = (c0 + (U - 1) * SK_NW) * 32 + 32 <= K;   // wavefront-uniform
-    u32x4 bfrag[U][NT];
+  struct Batch { u32x4 b[U][NT], a[U][MT]; };
+  // batch i of this wavefront: chunks wave + 8 * (i * U + u). k of a lane's 8 values; past K the loads re-read
+  // k = 0 and both operands are zeroed in front of the MFMAs
+  auto k_of = [&](int i, int u) { return (wave + SK_NW * (i * U + u)) * 32 + 8 * q; };
+  auto load = [&](Batch& s, int i) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int k = (c0 + u * SK_NW) * 32 + 8 * q;
+      const int k = k_of(i, u) < K ? k_of(i, u) : 0;
 #pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-        bfrag[u][nt] = load_stream16(bp[nt] + ((whole || k < K) ? k : 0));   // B is read once
+      for (int nt = 0; nt < NT; ++nt) s.b[u][nt] = load_stream16(bp[nt] + k);   // B is read once
     }
-    __builtin_amdgcn_sched_barrier(0);                     // all B loads of the batch go out first
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      u32x4 afrag[U];
+    for (int u = 0; u < U; ++u) {
+      const int k = k_of(i, u) < K ? k_of(i, u) : 0;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = (c0 + u * SK_NW) * 32 + 8 * q;
-        afrag[u] = *reinterpret_cast<const u32x4_mem*>(ap[mt] + ((whole || k < K) ? k : 0));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if (mt == 0 && !whole) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if ((c0 + u * SK_NW) * 32 + 8 * q >= K) {
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) bfrag[u][nt] = zero4;
-          }
-      }
+      for (int mt = 0; mt < MT; ++mt) s.a[u][mt] = *reinterpret_cast<const u32x4_mem*>(ap[mt] + k);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto multiply = [&](Batch& s, int i) __attribute__((always_inline)) {
+    if ((wave + SK_NW * (i * U + U - 1)) * 32 + 32 > K) {  // wavefront-uniform
 #pragma unroll
       for (int u = 0; u < U; ++u)
+        if (k_of(i, u) >= K) {
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) s.b[u][nt] = zero4;
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) s.a[u][mt] = zero4;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
-          acc[mt][nt] = mfma16(__builtin_bit_cast(V8, afrag[u]), __builtin_bit_cast(V8, bfrag[u][nt]),
-                               acc[mt][nt]);
+          acc[mt][nt] = mfma16(__builtin_bit_cast(V8, s.a[u][mt]), __builtin_bit_cast(V8, s.b[u][nt]), acc[mt][nt]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const int mine = KC > wave ? (KC - wave + SK_NW - 1) / SK_NW : 0, nb = (mine + U - 1) / U;
+  Batch s0, s1;
+  if (nb > 0) {
+    load(s0, 0);
+    int i = 0;
+    for (; i + 2 < nb; i += 2) {
+      load(s1, i + 1);
+      multiply(s0, i);
+      load(s0, i + 2);
+      multiply(s1, i + 1);
+    }
+    if (i + 1 < nb) {
+      load(s1, i + 1);
+      multiply(s0, i);
+      multiply(s1, i + 1);
+    } else {
+      multiply(s0, i);
     }
   }
 
@@ -116,21 +136,25 @@ __global__ __launch_bounds__(SK_NT) void gemm_skinny_nt_kernel(
     }
 }
 
-template <typename Tag, int MT, int NT>
+template <typename Tag, int MT, int NT, int U>
 int launch_skinny(const GemmArgs& g, hipStream_t s) {
   const unsigned nwg = (unsigned)((g.N + 16 * NT - 1) / (16 * NT));
-  hipLaunchKernelGGL((gemm_skinny_nt_kernel<Tag, MT, NT>), dim3(nwg), dim3(SK_NT), 0, s, (int)g.M,
+  hipLaunchKernelGGL((gemm_skinny_nt_kernel<Tag, MT, NT, U>), dim3(nwg), dim3(SK_NT), 0, s, (int)g.M,
                      (int)g.N, (int)g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc);
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 
 // Columns per workgroup: more columns reuse each A fragment more often (A comes from L2 once per
-// workgroup), fewer keep the chip full; at least ~2 workgroups per CU are wanted.
+// workgroup), fewer keep the chip full; at least ~2 workgroups per CU are wanted. Up to one workgroup per CU
+// (16 columns) a wavefront keeps 16 chunks in flight, with more 8: two workgroups then share a CU.
 template <typename Tag, int MT>
 int run_skinny_mt(const GemmArgs& g, hipStream_t s) {
-  if (g.N >= 64 * 512) return launch_skinny<Tag, MT, 4>(g, s);
-  if (g.N >= 32 * 512) return launch_skinny<Tag, MT, 2>(g, s);
-  return launch_skinny<Tag, MT, 1>(g, s);
+  DeviceInfo di;
+  const int64_t ncu = device_info(di) && di.ncu > 0 ? di.ncu : 256;
+  if (g.N >= 64 * 512) return launch_skinny<Tag, MT, 4, 1>(g, s);
+  if (g.N >= 32 * 512) return launch_skinny<Tag, MT, 2, 2>(g, s);
+  if (MT <= 2 && g.N <= 16 * ncu) return launch_skinny<Tag, MT, 1, MT <= 2 ? 8 : 4>(g, s);
+  return launch_skinny<Tag, MT, 1, 4>(g, s);
 }
 
 template <typename Tag>
@@ -183,7 +207,8 @@ struct SdCfg {
 template <typename Tag, int MT>
 __global__ __launch_bounds__(SK_NT) void gemm_skinny_dma_kernel(
     int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
-    const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc) {
+    const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc, int act,
+    const uint16_t* __restrict__ bias) {
   typedef typename Elem<Tag>::vec8 V8;
   typedef SdCfg L;
   constexpr int KS = L::KS, NT = L::NT, J = L::J;
@@ -364,7 +389,10 @@ __global__ __launch_bounds__(SK_NT) void gemm_skinny_dma_kernel(
 #pragma unroll
               for (int w = 0; w < 4; ++w) sum += red[(w * NT + nt) * 256 + ctid];
               const int gr = mt * 16 + (ctid >> 4), gc = n0 + nt * 16 + (ctid & 15);
-              if (gr < M && gc < N) C[(int64_t)gr * ldc + gc] = Elem<Tag>::from_f32(sum);
+              if (gr < M && gc < N) {
+                if (bias) sum += Elem<Tag>::to_f32(bias[gc]);
+                C[(int64_t)gr * ldc + gc] = Elem<Tag>::from_f32(epi_act(sum, act));
+              }
             }
           }
         }
@@ -392,7 +420,7 @@ int launch_skinny_dma(const GemmArgs& g, hipStream_t s) {
   const int64_t nblocks = (g.N + SdCfg::RPS - 1) / SdCfg::RPS;
   const unsigned nwg = (unsigned)(nblocks < ncu ? nblocks : ncu);   // one persistent workgroup per CU
   hipLaunchKernelGGL(kern, dim3(nwg), dim3(SK_NT), SD_SMEM + SD_RED, s, (int)g.M, (int)g.N, (int)g.K,
-                     g.A, g.lda, g.B, g.ldb, g.C, g.ldc);
+                     g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.act, g.bias);
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 
@@ -410,13 +438,15 @@ int run_skinny_dma_t(const GemmArgs& g, hipStream_t s) {
 }  // namespace
 
 // Worth it only when the columns alone fill the chip (one workgroup per 16 columns).
-bool gemm_skinny_ok(const GemmArgs& g) {
+static bool skinny_shape_ok(const GemmArgs& g) {
   auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  if (!g.transB || g.acc32 || g.fused() || g.M > 16 * SK_MAXMT || g.N < 1024) return false;
+  if (!g.transB || g.acc32 || g.M > 16 * SK_MAXMT || g.N < 1024) return false;
   if (!al16(g.A) || !al16(g.B)) return false;
   if (g.K % 8 || g.lda % 8 || g.ldb % 8) return false;
   return true;
 }
+
+bool gemm_skinny_ok(const GemmArgs& g) { return skinny_shape_ok(g) && !g.fused(); }
 
 int run_gemm_skinny(const GemmArgs& g, hipStream_t s) {
   return g.dtype == MLT_BF16 ? run_skinny_t<bf16_tag>(g, s) : run_skinny_t<f16_tag>(g, s);
@@ -424,7 +454,7 @@ int run_gemm_skinny(const GemmArgs& g, hipStream_t s) {
 
 // The streaming variant addresses B rows with 32-bit byte offsets from the column block's first row.
 bool gemm_skinny_dma_ok(const GemmArgs& g) {
-  return gemm_skinny_ok(g) && g.ldb * 2 * 64 + g.K * 2 < ((int64_t)1 << 32);
+  return skinny_shape_ok(g) && g.ldb * 2 * 64 + g.K * 2 < ((int64_t)1 << 32);
 }
 
 int run_gemm_skinny_dma(const GemmArgs& g, hipStream_t s) {

@@ -1,0 +1,43 @@
+"""GPU parity of the decode GEMM kernels (K split over wavefronts; streaming) around the sizes of their batches
+and rings, and of the streaming kernel's fused epilogue, against the fp64 oracle."""
+import pytest
+
+from paper_2503_14985_amd import inputs
+import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+BF16, FP16 = inputs.BF16, inputs.FP16
+
+
+@pytest.fixture(autouse=True)
+def _announce(request):
+    from paper_2503_14985_amd import binding
+    print("\n[case] %s" % request.node.name, flush=True)
+    yield
+    binding.mlt_diag_force_variant(gemm="auto")
+
+
+# fewer chunks of 32 than wavefronts, one batch (4 or 8 chunks of a wavefront), one more, two, an odd and an
+# even count, a chunk that ends inside K; up to one column block per CU, and more
+@pytest.mark.parametrize("M", [1, 16, 17, 33, 64])
+@pytest.mark.parametrize("N", [1032, 4112, 16400, 32776])
+def test_k_split_over_wavefronts(M, N):
+    from paper_2503_14985_amd import binding
+    binding.mlt_diag_force_variant(gemm="skinny")
+    for i, K in enumerate((8, 72, 256, 1024, 1056, 2048, 2088, 3104, 4128)):
+        if N > 4112 and i % 3:
+            continue
+        A, B = inputs.gemm_inputs(M, N, K, FP16 if i % 2 else BF16, i, transB=True)
+        C = pu.run_gemm(A, B, FP16 if i % 2 else BF16, transB=True)
+        pu.check_gemm(A, B, C, FP16 if i % 2 else BF16, True, seed=i)
+        assert binding.mlt_last_kernel().endswith("ksplit8")
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 2048, 1024), (16, 4104, 520), (13, 1032, 4096), (24, 14336, 2048)])
+@pytest.mark.parametrize("act", [0, 1, 2])
+def test_streaming_with_bias_and_activation(M, N, K, act):
+    from paper_2503_14985_amd import binding
+    for dtype in (BF16, FP16):
+        A, B = inputs.gemm_inputs(M, N, K, dtype, 4, transB=True)
+        pu.run_check_gemm_bias_act(A, B, inputs.bias_input(N, dtype, 4, std=4.0), act, dtype, transB=True)
+        assert binding.mlt_last_kernel().endswith("16cols_stream")
