@@ -84,13 +84,14 @@ __device__ __forceinline__ int sequence_of_rank(const int32_t* seq_lens, int B, 
 
 // Which workgroup takes which sequence: hardware deals the workgroups of a launch to the CUs in turn, all of
 // them at once up to 8 per CU, and with the batch in its own order the CUs' shares of keys differ by
-// chance. With ncu > 0 (a batch of 2 to PG_NT sequences, more workgroups than CUs) the pieces are dealt from the
+// chance. A batch of 2 to PG_NT sequences with more workgroups than CUs is therefore dealt from the
 // longest sequence to the shortest, every second round of CUs backwards. 64 sequences of 1024 to 4096
 // keys, 32 heads, D = 128, shuffled: 456 -> 421 us (6.4 TB/s, as for equal lengths).
 //
 // SPLIT: blockIdx.y is the range of units this workgroup takes, and the result goes to `part`
 // ([pair][range][2 + D] floats: maximum (log2 domain), sum, unnormalised outputs) instead of O.
-template <typename Tag, int D, bool SPLIT>
+// ORDER: by length, see above (ncu, B: only then).
+template <typename Tag, int D, bool SPLIT, bool ORDER>
 __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc,
     const uint16_t* __restrict__ Vc, const int32_t* __restrict__ block_table,
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
   const int nsplit = SPLIT ? (int)gridDim.y : 1;
   // which sequence, head and range
   int b, h, range = 0;
-  if (ncu > 0) {
+  if (ORDER) {
     const int pieces = H * nsplit, total = B * pieces;
     int id = (int)(blockIdx.y * gridDim.x + blockIdx.x);
     const int blk = id / ncu * ncu;
@@ -240,30 +241,30 @@ __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
   }
 }
 
-// One workgroup per (sequence, head), D x 4 threads: group g adds the ranges g, g + 4, ... (at most 64 in all)
+// One workgroup per (sequence, head), D x 4 threads: group g adds the ranges g, g + 4, ... (at most MAXS in all)
 // and the four sums meet in LDS in the order 0, 1, 2, 3. A sequence has at least one key, so range 0 is never
 // empty and the maximum is finite.
 constexpr int PG_MAX_SPLIT = 64;
-template <typename Tag, int D>
+template <typename Tag, int D, int MAXS>
 __global__ __launch_bounds__(4 * D) void paged_merge_kernel(const float* __restrict__ part,
                                                             uint16_t* __restrict__ O, int nsplit) {
   // All of a thread's loads are requested at once: this kernel is the memory round trips that it waits
   // for (a plain loop over 32 ranges: 16 us, eight loads in flight 3.9 us).
-  constexpr int NR = PG_MAX_SPLIT / 4;
-  __shared__ float sm[PG_MAX_SPLIT], sl[PG_MAX_SPLIT], acc4[4][D], l4[4];
+  constexpr int NR = MAXS / 4;
+  __shared__ float sm[MAXS], sl[MAXS], acc4[4][D], l4[4];
   const int bh = blockIdx.x, tid = threadIdx.x, g = tid / D, d = tid % D;
   const float* p = part + (int64_t)bh * nsplit * (2 + D);
   float v[NR];
 #pragma unroll
   for (int i = 0; i < NR; ++i) v[i] = g + 4 * i < nsplit ? p[(g + 4 * i) * (2 + D) + 2 + d] : 0.f;
-  if (tid < PG_MAX_SPLIT) {
+  if (tid < MAXS) {
     sm[tid] = tid < nsplit ? p[tid * (2 + D)] : -__builtin_inff();
     sl[tid] = tid < nsplit ? p[tid * (2 + D) + 1] : 0.f;
   }
   __syncthreads();
   float M = sm[0];
 #pragma unroll
-  for (int s = 1; s < PG_MAX_SPLIT; ++s) M = __builtin_fmaxf(M, sm[s]);
+  for (int s = 1; s < MAXS; ++s) M = __builtin_fmaxf(M, sm[s]);
   float acc = 0.f, L = 0.f;
 #pragma unroll
   for (int i = 0; i < NR; ++i) {
@@ -284,18 +285,20 @@ int launch_paged(const PagedArgs& a, int nsplit, float* part, hipStream_t s) {
   const unsigned pairs = (unsigned)(a.B * a.H);
   DeviceInfo di;
   const int64_t ncu = device_info(di) ? di.ncu : 0;
-  const int order_ncu = a.B > 1 && a.B <= PG_NT && a.B * a.H * (nsplit > 1 ? nsplit : 1) > ncu ? (int)ncu : 0;
-  if (nsplit <= 1) {
-    hipLaunchKernelGGL((paged_decode_kernel<Tag, D, false>), dim3(pairs), dim3(PG_NT), 0, s,
-                       a.Q, a.Kc, a.Vc, a.block_table, a.seq_lens, a.O, (float*)nullptr, (int)a.H,
-                       (int)a.block_size, (int)a.max_blocks, (int)a.num_blocks, (int)a.B, order_ncu, c);
-    return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
-  }
-  hipLaunchKernelGGL((paged_decode_kernel<Tag, D, true>), dim3(pairs, (unsigned)nsplit), dim3(PG_NT), 0, s,
-                     a.Q, a.Kc, a.Vc, a.block_table, a.seq_lens, a.O, part, (int)a.H,
-                     (int)a.block_size, (int)a.max_blocks, (int)a.num_blocks, (int)a.B, order_ncu, c);
+  // (the rank search costs 1 us: not for caches that are read in less than 25 us; 38 x 32 pairs of 181 keys at most
+  // 16.1 us in batch order, 17.1 by length)
+  const bool order = ncu > 0 && a.B > 1 && a.B <= PG_NT && (int64_t)pairs * (nsplit > 1 ? nsplit : 1) > ncu &&
+                     pairs * a.max_blocks * a.block_size * a.D * 4 >= ((int64_t)192 << 20);
+  auto kern = nsplit > 1 ? (order ? paged_decode_kernel<Tag, D, true, true> : paged_decode_kernel<Tag, D, true, false>)
+                         : (order ? paged_decode_kernel<Tag, D, false, true> : paged_decode_kernel<Tag, D, false, false>);
+  hipLaunchKernelGGL(kern, dim3(pairs, nsplit > 1 ? (unsigned)nsplit : 1u), dim3(PG_NT), 0, s, a.Q, a.Kc, a.Vc,
+                     a.block_table, a.seq_lens, a.O, nsplit > 1 ? part : (float*)nullptr, (int)a.H, (int)a.block_size,
+                     (int)a.max_blocks, (int)a.num_blocks, (int)a.B, (int)ncu, c);
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
-  hipLaunchKernelGGL((paged_merge_kernel<Tag, D>), dim3(pairs), dim3(4 * D), 0, s, part, a.O, nsplit);
+  if (nsplit <= 1) return MLT_OK;
+  auto merge = nsplit <= 8 ? paged_merge_kernel<Tag, D, 8> : nsplit <= 32 ? paged_merge_kernel<Tag, D, 32>
+                                                                          : paged_merge_kernel<Tag, D, PG_MAX_SPLIT>;
+  hipLaunchKernelGGL(merge, dim3(pairs), dim3(4 * D), 0, s, part, a.O, nsplit);
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 

@@ -25,4 +25,6 @@ def test_every_sequence_is_taken_once(B, H, ranges):
     binding.mlt_diag_force_key_split(ranges)
     rng = np.random.default_rng(B)
     lens = [int(x) for x in rng.choice([1, 16, 17, 40, 40, 96, 100], B)]
-    _check(B, H, 64, 16, lens, inputs.BF16, B)
+    # one sequence so long that the table's width is that of a cache of 192 MiB, where the ordering begins
+    lens[B // 2] = (192 << 20) // (B * H * 128 * 4) + 40
+    _check(B, H, 128, 16, lens, inputs.BF16, B)
