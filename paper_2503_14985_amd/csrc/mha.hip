@@ -42,8 +42,9 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
     const int64_t rounds = (wgs + ncu - 1) / ncu;
     int64_t t;
     if (rounds <= 1) t = longest + 7000;
-    else if (a.D == 128) t = a.causal ? wgs * (avg + 7000) / ncu : rounds * (longest + 7000);
-    else t = rounds * ((a.causal && rounds > 2 ? avg * 5 / 4 : avg) + 3000) + 4000;
+    else if (a.D == 128) t = a.causal ? wgs * (avg * 5 / 4) / ncu + rounds * 7000 : rounds * (longest + 7000);
+    else if (a.causal) t = wgs * (rounds > 2 ? avg * 5 / 4 : avg) / ncu + (rounds + 1) / 2 * 6000 + 4000;
+    else t = rounds * (avg + 3000) + 4000;
     if (t < longest + 7000) t = longest + 7000;
     t = (int64_t)std::sqrt((double)t * t + arrive * arrive);       // the two overlap in part
     // the partial results' second kernel: a launch, and writing and reading them at 4 TB/s
@@ -56,12 +57,12 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
     if (t + t / 20 < best) { best = t; p.key_groups = groups; }
   }
   // Few workgroups against many keys: the keys split over workgroups as well, as long as all of them fit one
-  // round and a range keeps 8 steps (1 x 8 heads, 1 x 4096, D = 128: 37 us, 16 in four ranges; 4 x 32: the
-  // operands' arrival takes as long either way, 40.6 against 44 us).
+  // round and a range keeps 4 steps (1 x 8 heads, 1 x 4096, D = 128: 37 us, 16 in four ranges; 3 x 16, 2 x 2831, D = 64:
+  // 21.5 us, 11.8 in four ranges; 4 x 32, 1 x 4096: the operands' arrival takes as long either way, 40.6 against 44).
   if (p.key_groups != 4 || a.causal) return;
   const int64_t w64 = heads * ((a.Sq + 63) / 64);
   for (int n = 2; n <= 16; ++n) {
-    if (w64 * n > ncu || tiles < 4 * 8 * n) break;
+    if (w64 * n > ncu || tiles < 4 * 4 * n) break;
     const int64_t t = cost(4, n);
     if (t + t / 20 < best) { best = t; p.nsplit = n; }
   }
