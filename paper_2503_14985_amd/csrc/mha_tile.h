@@ -58,11 +58,12 @@ __device__ __forceinline__ void block_map(int bid, int total, int nq, int nxcd, 
 }
 
 // The same for the masked problem on two workgroups per CU when all of them are resident at once
-// (cus: CUs per XCD, 0 for any other launch): a CU then keeps the items i and i + cus of its XCD's range,
-// and with the plain map both can be last tiles. Every second block of `cus` items is walked backwards, so
-// that a long item shares its CU with a short one (D = 64, 8 x 32 heads, 512 x 512: 24.2 -> 21.8 us;
-// 1 x 32, 2048 x 2048 on 128-row tiles: 43.5 -> 32.3 us).
-__device__ __forceinline__ void block_map_paired(int bid, int total, int nq, int nxcd, int cus, int& bh, int& qt) {
+// (cus: CUs per XCD, in bits 8 and up of nxcd_cus; 0 for any other launch): a CU then keeps the items
+// i and i + cus of its XCD's range, and with the plain map both can be last tiles. Every second block of
+// `cus` items is walked backwards, so that a long item shares its CU with a short one (D = 64, 8 x 32
+// heads, 512 x 512: 24.2 -> 21.8 us; 1 x 32, 2048 x 2048 on 128-row tiles: 43.5 -> 32.3 us).
+__device__ __forceinline__ void block_map_paired(int bid, int total, int nq, int nxcd_cus, int& bh, int& qt) {
+  const int nxcd = nxcd_cus & 255, cus = nxcd_cus >> 8;
   int logical = logical_block(bid, total, nxcd);
   if (cus > 0) {
     const int first = logical_block(bid % nxcd, total, nxcd), i = logical - first;   // place in the XCD's range
@@ -73,11 +74,11 @@ __device__ __forceinline__ void block_map_paired(int bid, int total, int nq, int
   bh = logical / nq;
   qt = nq - 1 - logical % nq;
 }
-// `cus` of that map for a launch of `total` workgroups
+// what a launch of `total` workgroups adds to the XCD count for that map
 inline int paired_cus(int total, bool causal, int D) {
   DeviceInfo di;
   if (D != 64 || !causal || !device_info(di) || di.ncu <= 0 || di.nxcd <= 0) return 0;
-  return total > di.ncu && total <= 2 * di.ncu ? di.ncu / di.nxcd : 0;
+  return total > di.ncu && total <= 2 * di.ncu ? di.ncu / di.nxcd << 8 : 0;
 }
 
 template <int D> struct PaCfg {

@@ -249,7 +249,7 @@ template <typename Tag, int D, int MAXS>
 __global__ __launch_bounds__(4 * D) void paged_merge_kernel(const float* __restrict__ part,
                                                             uint16_t* __restrict__ O, int nsplit) {
   // All of a thread's loads are requested at once: this kernel is the memory round trips that it waits
-  // for (a plain loop over 32 ranges: 16 us, eight loads in flight 3.9 us).
+  // for (a plain loop over 32 ranges: 16 us, eight loads in flight 3.9; 64 ranges here: 4.5).
   constexpr int NR = MAXS / 4;
   __shared__ float sm[MAXS], sl[MAXS], acc4[4][D], l4[4];
   const int bh = blockIdx.x, tid = threadIdx.x, g = tid / D, d = tid % D;
