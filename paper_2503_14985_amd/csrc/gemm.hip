@@ -230,8 +230,7 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // bf16, us: 1024 x 8192 x 8192 128 on the best of the other tiles, 102 here; 2048 x 4096 x 4096 60 / 55;
   // 512 x 8192 x 8192 77 / 69; with K in two or four parts 777 x 4096 x 14336 131 / 97, 400 x 4096 x 11008
   // 57 / 47. The 6 us per round hold the sum of the two groups' results, which is why short K stays
-  // with the others (2048^3: 21.4 on K steps of 128, 22.1 here). The scratch of a K split may take all
-  // that mlt_gemm_noalloc has and no more, so that both entry points choose alike.
+  // with the others (2048^3: 21.4 on K steps of 128, 22.1 here).
   auto cost_kp = [&](int64_t bm, int parts) {
     const int64_t wgs = ((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * parts;
     const int64_t rounds = (wgs + NCU - 1) / NCU, steps = (KT + parts - 1) / parts;
@@ -244,10 +243,11 @@ GemmPlan plan_gemm(const GemmArgs& g) {
     return (compute > arrive ? compute : arrive) + (parts > 1 ? 4000 + 2 * parts * g.M * g.N / 1000 : 0);
   };
   for (int parts = g.forced_parts > 0 ? g.forced_parts : 1; parts <= (g.forced_parts > 0 ? g.forced_parts : 8); parts *= 2) {
-    // every part keeps at least 8 K steps, and its partial tiles must fit the scratch allowed
+    // every part keeps at least 8 K steps, and all parts' tiles fit the scratch that mlt_gemm_noalloc has
+    // (a forced split may ask for more: mlt_gemm allocates it, mlt_gemm_noalloc refuses)
     if (parts > 1 && KT < 8 * parts) break;
-    if (parts > 1 && g.scratch_limit >= 0 && (int64_t)parts * g.M * g.N * 4 > g.scratch_limit) break;
-    if (pp && KT >= 8 * parts && (parts == 1 || g.forced_parts > 0 || (int64_t)parts * g.M * g.N * 4 <= kStaticScratchBytes)) {
+    if (parts > 1 && g.forced_parts == 0 && parts * g.M * g.N * 4 > kStaticScratchBytes) break;
+    if (pp && KT >= 8 * parts) {
       if (g.M > 128 && fits(64, 128)) all[n_all++] = Choice{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
       if (fits(128, 128)) all[n_all++] = Choice{GEMM_128_KP, parts, 128 * 128, cost_kp(128, parts)};
     }

@@ -43,7 +43,6 @@ struct GemmArgs {
   // and the number of parts the plan asks for; run_gemm fills both in.
   float* scratch = nullptr;
   int parts = 1;
-  int64_t scratch_limit = -1;      // plan_gemm: largest scratch (bytes) a split may use; -1 = no limit
   int forced_parts = 0;            // plan_gemm: 0 = the cost model's choice, 1 / 2 / 4 / 8 = forced
   int epi() const { return acc32 ? 1 : (act << 1); }   // the kernels' epilogue word
   bool fused() const { return bias != nullptr || act != 0; }

@@ -1,0 +1,33 @@
+// Prints what the library's planning functions choose, without a device (they then assume 256 CUs, 8
+// XCDs). One problem per line on stdin, one answer per line on stdout:
+//   gemm M N K transB lda ldb fp32_accumulate fused noncontiguous_base   ->  name parts scratch_bytes
+// (noncontiguous_base != 0: A starts on an odd element)
+#include <stdio.h>
+#include <string.h>
+
+#include "../../paper_2503_14985_amd/csrc/mlt_internal.h"
+
+using namespace mlt;
+
+int main() {
+  char op[16];
+  while (scanf("%15s", op) == 1) {
+    if (!strcmp(op, "gemm")) {
+      long long M, N, K, lda, ldb;
+      int tb, acc, fused, odd;
+      if (scanf("%lld %lld %lld %d %lld %lld %d %d %d", &M, &N, &K, &tb, &lda, &ldb, &acc, &fused, &odd) != 9) return 1;
+      GemmArgs g{};
+      g.M = M; g.N = N; g.K = K;
+      g.A = (const uint16_t*)(0x100000 + (odd ? 2 : 0)); g.lda = lda;
+      g.B = (const uint16_t*)0x200000; g.ldb = ldb; g.transB = tb;
+      g.C = (uint16_t*)0x300000; g.ldc = N;
+      g.forced = GEMM_AUTO; g.acc32 = acc;
+      if (fused) g.bias = (const uint16_t*)0x400000;
+      const GemmPlan p = plan_gemm(g);
+      printf("%s %d %lld\n", p.name, p.parts, (long long)p.scratch_bytes);
+    } else {
+      return 1;
+    }
+  }
+  return 0;
+}

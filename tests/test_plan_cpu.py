@@ -1,0 +1,59 @@
+"""The library's choice of kernels and splits, asked on the host (tests/host/plan_driver.cpp calls the
+planning functions; no kernel runs and no device is needed)."""
+import os
+import random
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LIB_DIR = os.path.join(ROOT, "paper_2503_14985_amd")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("no hipcc")
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_driver")
+    cmd = [HIPCC, "-O1", "-std=c++17", "--offload-arch=gfx950", "-x", "hip", os.path.join(ROOT, "tests", "host", "plan_driver.cpp"),
+           "-x", "none", "-o", exe, os.path.join(LIB_DIR, "libmlt.so"), "-Wl,-rpath," + LIB_DIR]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stderr[-3000:]
+    env = {k: v for k, v in os.environ.items() if not k.startswith("MLT_")}
+
+    def ask(lines):
+        r = subprocess.run([exe], input="\n".join(lines) + "\n", capture_output=True, text=True, timeout=600, env=env)
+        assert r.returncode == 0, r.stderr[-2000:]
+        out = r.stdout.strip().split("\n")
+        assert len(out) == len(lines)
+        return out
+    return ask
+
+
+def gemm_line(M, N, K, transB, lda=None, ldb=None, acc=0, fused=0, odd=0):
+    return "gemm %d %d %d %d %d %d %d %d %d" % (M, N, K, transB, lda or K, ldb or (K if transB else N), acc, fused, odd)
+
+
+def test_no_split_of_its_own_needs_more_than_the_fixed_scratch(plan):
+    """mlt_gemm_noalloc has 32 MiB for the partial products of a K split and refuses what needs more:
+    no split that the library chooses by itself may, whatever the operands' alignment."""
+    cases = [(2056, 2056, 8193, 0), (67, 16714, 9761, 1), (2100, 2100, 16001, 0), (2111, 2111, 8191, 1),
+             (3001, 3001, 16385, 1), (3967, 4383, 24204, 0)]
+    rng = random.Random(3)
+    for _ in range(20000):
+        size = lambda lo, hi: int(lo * (hi / lo) ** rng.random())
+        cases.append((size(1, 6000), size(8, 30000), size(64, 60000), rng.randint(0, 1)))
+    lines, shapes = [], []
+    for i, (M, N, K, tb) in enumerate(cases):
+        if i % 3 == 2:                                      # aligned operands
+            N, K = N // 8 * 8, K // 8 * 8
+        lines.append(gemm_line(M, N, K, tb, acc=i % 5 == 0, odd=i % 3 == 1))
+        shapes.append((M, N, K, tb))
+    split = 0
+    for shape, ans in zip(shapes, plan(lines)):
+        name, parts, scratch = ans.split()
+        split += int(parts) > 1
+        assert int(scratch) <= 32 << 20, (shape, ans)
+        assert int(scratch) == (int(parts) * shape[0] * shape[1] * 4 if int(parts) > 1 else 0)
+    assert split > 500                                       # the question was asked of real splits

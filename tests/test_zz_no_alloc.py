@@ -90,3 +90,20 @@ def test_no_alloc_entry_point_inside_a_captured_graph():
         torch.cuda.synchronize()
         assert torch.equal(static.view(torch.int16), eager.view(torch.int16)), "replay %d" % rep
         del other
+
+
+@pytest.mark.parametrize("M,N,K,split", [(2111, 2111, 8191, False), (70, 2001, 8193, True), (300, 1111, 16001, True)])
+def test_no_alloc_entry_point_on_unaligned_operands(M, N, K, split):
+    """Odd sizes take other kernels; the split they are given has to fit the fixed array as well."""
+    from paper_2503_14985_amd import binding
+    dev = torch.device("cuda:0")
+    A, B, tA, tB = _pair(M, N, K, 90, dev)
+    want = binding.mlt_gemm(tA, tB, transB=True)
+    name = binding.mlt_last_kernel()
+    assert ("splitk" in name) == split, name
+    got = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=dev)
+    binding.mlt_gemm_noalloc(tA, tB, got, transB=True)
+    torch.cuda.synchronize()
+    assert binding.mlt_last_kernel() == name
+    assert torch.equal(got.view(torch.int16), want.view(torch.int16))
+    pu.check_gemm(A, B, got, BF16, True, seed=90)
