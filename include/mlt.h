@@ -19,14 +19,14 @@
  *     nothing aborts. On an error nothing has been enqueued.
  *   - Device memory of the library's own: the GEMM entry points (few tiles against a long K),
  *     mlt_paged_attn_decode (few sequences x heads) and mlt_mha_fwd (few query tiles against many
- *     keys; never while the stream is recording into a graph) may spread one result over several
- *     workgroups and then keep fp32 partial results in a scratch buffer, one per (device, stream), allocated
- *     with hipMalloc at the first call that needs it, grown by doubling from 4 MiB (32 MiB covers
- *     every split the library chooses by itself) and kept until the process ends. Calls on one
- *     stream are ordered by the stream; calls on different streams use different buffers. If the
- *     allocation fails, or the stream is recording into a graph and has no buffer yet, the call
- *     runs without the split (same result up to summation order). mlt_gemm_noalloc never
- *     allocates.
+ *     keys) may spread one result over several workgroups and then keep fp32 partial results in a
+ *     scratch buffer, one per (device, stream), allocated with hipMalloc at the first call that
+ *     needs it, grown by doubling from 4 MiB (32 MiB covers every split the library chooses by
+ *     itself) and kept until the process ends. Calls on one stream are ordered by the stream; calls
+ *     on different streams use different buffers. If the allocation fails, or the stream is
+ *     recording into a graph (which may be replayed at any time and on any stream, so that it must
+ *     not share the stream's buffer), the call runs without the split (same result up to summation
+ *     order). mlt_gemm_noalloc never allocates.
  */
 #ifndef MLT_H_
 #define MLT_H_

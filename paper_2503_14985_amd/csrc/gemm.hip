@@ -409,12 +409,15 @@ static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
   return rc == -1 ? MLT_ERR_UNSUPPORTED : rc;
 }
 
-// Scratch for the partial products of a K split across workgroups: one buffer per (device, stream)
+// Scratch for the partial results of a split across workgroups: one buffer per (device, stream)
 // pair, so that calls on different streams never share one; allocated at the first call that needs
 // it (hipMalloc; no device synchronisation), grown by doubling (the smaller buffer is kept until the
 // process ends: work already enqueued may still use it), used in stream order. The table is
-// small and fixed; when it is full, or an allocation fails, the call gets a stream-ordered
-// allocation of its own (or, if that fails too, runs without the split).
+// small and fixed; when it is full, or an allocation fails, a GEMM gets a stream-ordered
+// allocation of its own (or, if that fails too, runs without the split). A call that is being recorded
+// into a graph gets none, also where the stream has a buffer: the graph would go on using it whenever
+// and on whatever stream it is replayed, beside the stream's own calls and beside other graphs recorded
+// on it, in no order with either.
 namespace {
 struct ScratchSlot { int dev; hipStream_t stream; float* ptr; int64_t bytes; };
 constexpr int kScratchSlots = 32;
@@ -424,7 +427,6 @@ std::mutex g_scratch_mu;
 
 }  // namespace
 
-// nothing may be allocated then
 bool stream_is_capturing(hipStream_t s) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &st) != hipSuccess) { (void)hipGetLastError(); return false; }
@@ -434,6 +436,7 @@ bool stream_is_capturing(hipStream_t s) {
 float* cached_scratch(int64_t bytes, hipStream_t s) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
+  if (stream_is_capturing(s)) return nullptr;
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   ScratchSlot* slot = nullptr;
   for (int i = 0; i < g_scratch_used; ++i)
@@ -444,10 +447,6 @@ float* cached_scratch(int64_t bytes, hipStream_t s) {
     slot = &g_scratch[g_scratch_used];
     *slot = ScratchSlot{dev, s, nullptr, 0};
   }
-  // a buffer that is there is used under capture as well; a new one is not allocated in the
-  // middle of a capture (the call then runs without the split; mlt_gemm_noalloc is the entry point
-  // made for captured code)
-  if (stream_is_capturing(s)) return nullptr;
   int64_t want = slot->bytes > 0 ? 2 * slot->bytes : (int64_t)4 << 20;
   while (want < bytes) want *= 2;
   void* p = nullptr;

@@ -115,8 +115,7 @@ int run_mha(const MhaArgs& a, MhaPlan& p, hipStream_t s) {
   if (p.key_groups > 1) {
     float* scratch = nullptr;
     if (p.nsplit > 1) {
-      // (not under capture: a graph may be replayed while other work of the stream uses the scratch)
-      scratch = stream_is_capturing(s) ? nullptr : cached_scratch(mha_ks_scratch_bytes(a, p.nsplit), s);
+      scratch = cached_scratch(mha_ks_scratch_bytes(a, p.nsplit), s);
       if (!scratch) p.nsplit = 1;
     }
     return run_mha_ks(a, p.bm, p.nsplit, scratch, s);

@@ -149,8 +149,8 @@ struct PagedArgs {
 int run_paged_decode(const PagedArgs& a, hipStream_t s, int* nsplit_out);
 
 // The library's own scratch memory for a stream of the current device: at least `bytes`, kept
-// (and grown by doubling) from call to call, never freed; nullptr if it cannot be had. Work of
-// one stream that uses it is ordered by the stream.
+// (and grown by doubling) from call to call, never freed; nullptr if it cannot be had, and while the
+// stream records into a graph. Work of one stream that uses it is ordered by the stream.
 float* cached_scratch(int64_t bytes, hipStream_t s);
 bool stream_is_capturing(hipStream_t s);   // true while `s` records into a graph
 
