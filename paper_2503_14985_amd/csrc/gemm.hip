@@ -178,7 +178,11 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // t: ns per K step of 64; fixed: ns per round before the first and after the last step, where a
   // fit over K gave one (2048 x 2048 x K on the split 128 x 128 kernel: 0.56 us per step + 2 us)
   struct Cand { int variant; int bm, bn; int64_t t, fixed; int kgroups; };
-  const Cand big = {pp ? GEMM_256_PP16 : GEMM_256_W8, 256, 256, !p.aligned ? 2300 : pp ? 1170 : 1800, 0, 1};
+  // (fewer than 8 K steps, the last one partial: 1170 leaves out the start and end of the large tiles, and they were
+  // taken where many small ones are faster. bf16, us, 256 x 256 / 128 x 128: 2936 x 5560 x 144 with bias and GELU 46 /
+  // 31; 5117 x 1240 x 176 fp32 accumulate 26 / 19; 7029 x 1088 x 224 14.5 / 13.0)
+  const bool short_ragged = g.K % 64 && KT < 8;
+  const Cand big = {pp ? GEMM_256_PP16 : GEMM_256_W8, 256, 256, !p.aligned ? 2300 : pp && !short_ragged ? 1170 : 1800, 0, 1};
   // Operands of any alignment: a step's loads and their LDS writes weigh more than its MFMAs, and
   // the groups of a workgroup share them, so what the K split inside the workgroup gains is small;
   // two unsplit workgroups on a CU do as well (ns per step and tile, from 201 x 4001 x 4001, one tile

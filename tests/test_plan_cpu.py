@@ -57,3 +57,10 @@ def test_no_split_of_its_own_needs_more_than_the_fixed_scratch(plan):
         assert int(scratch) <= 32 << 20, (shape, ans)
         assert int(scratch) == (int(parts) * shape[0] * shape[1] * 4 if int(parts) > 1 else 0)
     assert split > 500                                       # the question was asked of real splits
+
+
+@pytest.mark.parametrize("M,N,K,transB,acc,fused", [(1094, 13928, 72, 0, 0, 1), (2936, 5560, 144, 1, 0, 1), (417, 11424, 336, 0, 0, 1),
+                                                    (5117, 1240, 176, 0, 1, 0), (2314, 2728, 176, 1, 1, 0), (7029, 1088, 224, 0, 0, 0)])
+def test_a_short_ragged_k_takes_many_small_tiles(plan, M, N, K, transB, acc, fused):
+    """Fewer than 8 K steps, the last one partial: 100 to 300 large tiles took up to 1.5 times as long."""
+    assert plan([gemm_line(M, N, K, transB, acc=acc, fused=fused)])[0].split()[0].endswith("128x128x64_w2x4")
