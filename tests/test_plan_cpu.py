@@ -63,4 +63,4 @@ def test_no_split_of_its_own_needs_more_than_the_fixed_scratch(plan):
                                                     (5117, 1240, 176, 0, 1, 0), (2314, 2728, 176, 1, 1, 0), (7029, 1088, 224, 0, 0, 0)])
 def test_a_short_ragged_k_takes_many_small_tiles(plan, M, N, K, transB, acc, fused):
     """Fewer than 8 K steps, the last one partial: 100 to 300 large tiles took up to 1.5 times as long."""
-    assert plan([gemm_line(M, N, K, transB, acc=acc, fused=fused)])[0].split()[0].endswith("128x128x64_w2x4")
+    assert "_128x128x64_w2x4" in plan([gemm_line(M, N, K, transB, acc=acc, fused=fused)])[0].split()[0]
