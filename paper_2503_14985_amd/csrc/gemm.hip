@@ -227,10 +227,14 @@ GemmPlan plan_gemm(const GemmArgs& g) {
       all[n_all++] = Choice{GEMM_128_PP16_K128, 1, 128 * 128, own128 > arrive ? own128 : arrive};
     }
   }
-  // The kernels with two groups on alternate K steps (gemm_kp.hip). Their step is bound by what the L2s
-  // deliver (about 17 TB/s), so it takes longer the more CUs have a workgroup (us per 64 of K, 80 / 160 / 256
-  // workgroups, call included: 256 x 128 0.56 / 0.64 / 0.73, 128 x 128 0.36 / 0.40 / 0.50, the two-group kernel
-  // with K steps of 128 0.36 / 0.43 / 0.55; below 0.8 to 0.85 of that, the scale of the other candidates).
+  // The kernels with two groups on alternate K steps (gemm_kp.hip). On a full chip their step is bound by what
+  // the L2s deliver (about 17 TB/s), with fewer workgroups by its own latency (us per 64 of K, 80 / 160 / 256
+  // workgroups, call included, B repeated: 256 x 128 0.56 / 0.64 / 0.73, 128 x 128 0.36 / 0.40 / 0.50; with B from
+  // memory 80 workgroups take as long per step as 256 do). Below on the scale of the other candidates, whose
+  // times come out 1.1 to 1.25 of their estimates: over 280 problems of 6 to 300 tiles with B from memory the choice
+  // is nowhere more than 8 % behind the best of the other tiles and 3 % ahead on average; rates that fall with the share
+  // of busy CUs took these kernels for 40 to 110 tiles where they are up to 1.45 times slower (352 x 3176 x 5632 fp32
+  // accumulate 37 us, 54; 245 x 4368 x 4456 30, 38; 2057 x 608 x 3200 26, 33).
   // bf16, us: 1024 x 8192 x 8192 128 on the best of the other tiles, 102 here; 2048 x 4096 x 4096 60 / 55;
   // 512 x 8192 x 8192 77 / 69; with K in two or four parts 777 x 4096 x 14336 131 / 97, 400 x 4096 x 11008
   // 57 / 47. The 6 us per round hold the sum of the two groups' results, which is why short K stays
@@ -239,7 +243,7 @@ GemmPlan plan_gemm(const GemmArgs& g) {
     const int64_t wgs = ((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * parts;
     const int64_t rounds = (wgs + NCU - 1) / NCU, steps = (KT + parts - 1) / parts;
     const int64_t share = wgs < NCU ? wgs * 1000 / NCU : 1000;
-    int64_t t_step = bm == 256 ? 425 + 195 * share / 1000 : 206 + 190 * share / 1000;
+    int64_t t_step = bm == 256 ? 615 : 345 + 50 * share / 1000;
     if (g.K % 64) t_step += t_step * 15 / 100;
     const int64_t compute = rounds * (steps * t_step + (bm == 256 ? 6000 : 5700));
     const int64_t base = (g.M + g.N) * g.K * 2 / 5200, need = 6 * NCU / 10;
@@ -252,7 +256,9 @@ GemmPlan plan_gemm(const GemmArgs& g) {
     if (parts > 1 && KT < 8 * parts) break;
     if (parts > 1 && g.forced_parts == 0 && parts * g.M * g.N * 4 > kStaticScratchBytes) break;
     if (pp && KT >= 8 * parts) {
-      if (g.M > 128 && fits(64, 128)) all[n_all++] = Choice{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
+      // (256 x 128 in up to 4 parts: 25 problems that took 8 were 6 % slower than on the other tiles with B repeated
+      // and 3 % faster with B from memory, 852 x 920 x 14784 43 -> 50 us)
+      if (g.M > 128 && parts < 8 && fits(64, 128)) all[n_all++] = Choice{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
       if (fits(128, 128)) all[n_all++] = Choice{GEMM_128_KP, parts, 128 * 128, cost_kp(128, parts)};
     }
     for (const auto& c : KT / parts < 8 ? whole : p.aligned ? split : any) {

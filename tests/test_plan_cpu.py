@@ -64,3 +64,12 @@ def test_no_split_of_its_own_needs_more_than_the_fixed_scratch(plan):
 def test_a_short_ragged_k_takes_many_small_tiles(plan, M, N, K, transB, acc, fused):
     """Fewer than 8 K steps, the last one partial: 100 to 300 large tiles took up to 1.5 times as long."""
     assert "_128x128x64_w2x4" in plan([gemm_line(M, N, K, transB, acc=acc, fused=fused)])[0].split()[0]
+
+
+@pytest.mark.parametrize("M,N,K,transB", [(2057, 608, 3200, 0), (241, 6680, 4096, 1), (245, 4368, 4456, 0), (352, 3176, 5632, 1), (2509, 704, 6744, 0),
+                                          (460, 2648, 4224, 0)])
+def test_few_tiles_are_not_left_to_the_two_k_groups_alone(plan, M, N, K, transB):
+    """40 to 110 tiles of 128 x 128: without a split across workgroups the kernels with two groups on alternate K steps
+    take up to 1.45 times as long as the best other one."""
+    name, parts, _ = plan([gemm_line(M, N, K, transB)])[0].split()
+    assert "kp2" not in name or int(parts) > 1
