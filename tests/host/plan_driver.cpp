@@ -2,6 +2,7 @@
 // XCDs). One problem per line on stdin, one answer per line on stdout:
 //   gemm M N K transB lda ldb fp32_accumulate fused noncontiguous_base   ->  name parts scratch_bytes
 // (noncontiguous_base != 0: A starts on an odd element)
+//   mha B H Sq Sk D causal   ->  name ranges
 #include <stdio.h>
 #include <string.h>
 
@@ -25,6 +26,16 @@ int main() {
       if (fused) g.bias = (const uint16_t*)0x400000;
       const GemmPlan p = plan_gemm(g);
       printf("%s %d %lld\n", p.name, p.parts, (long long)p.scratch_bytes);
+    } else if (!strcmp(op, "mha")) {
+      long long B, H, Sq, Sk, D;
+      int causal;
+      if (scanf("%lld %lld %lld %lld %lld %d", &B, &H, &Sq, &Sk, &D, &causal) != 6) return 1;
+      MhaArgs a{};
+      a.B = B; a.H = H; a.Sq = Sq; a.Sk = Sk; a.D = D;
+      a.scale = 1.f; a.causal = causal;
+      a.forced = MHA_AUTO;
+      const MhaPlan p = plan_mha(a);
+      printf("%s %d\n", p.name, p.nsplit);
     } else {
       return 1;
     }

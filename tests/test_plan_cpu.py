@@ -73,3 +73,12 @@ def test_few_tiles_are_not_left_to_the_two_k_groups_alone(plan, M, N, K, transB)
     take up to 1.45 times as long as the best other one."""
     name, parts, _ = plan([gemm_line(M, N, K, transB)])[0].split()
     assert "kp2" not in name or int(parts) > 1
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_causal_attention_is_priced_by_the_keys_it_sees(plan, D):
+    """Keys past the last query row are masked for all rows: their number changes nothing in the choice."""
+    for B, H, Sq in ((17, 8, 65), (4, 40, 67), (1, 32, 121), (1, 16, 600), (8, 32, 200)):
+        assert len(set(plan(["mha %d %d %d %d %d 1" % (B, H, Sq, Sk, D) for Sk in (Sq, 2 * Sq, 1994, 30000)]))) == 1
+    name = "mha_fwd_d%d_causal_256x64_pp 1" % D
+    assert plan(["mha 17 8 65 1994 %d 1" % D, "mha 4 8 41 41 %d 1" % D]) == [name, name]
