@@ -28,7 +28,7 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
   const int64_t heads = a.B * a.H;
   if (a.forced != MHA_AUTO || heads < 1 || a.Sq < 1) return;
   DeviceInfo di;
-  const int64_t ncu = device_info(di) && di.ncu > 0 ? di.ncu : 256;
+  const int64_t ncu = device_info(di) && di.ncu > 0 ? di.ncu : 256, nxcd = di.nxcd > 0 ? di.nxcd : 8;
   const bool one_round_of_256 = heads * ((a.Sq + 255) / 256) <= ncu;
   if (heads * ((a.Sq + 255) / 256) > 4 * ncu) return;             // enough of the large tiles
   // with the mask the last query row sees min(Sq, Sk) keys (17 x 8 heads, 65 x 1994 causal, D = 128, priced with all
@@ -51,6 +51,11 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
     else if (a.causal) t = wgs * (rounds > 2 ? avg * 5 / 4 : avg) / ncu + (rounds + 1) / 2 * 6000 + 4000;
     else t = rounds * (avg + 3000) + 4000;
     if (t < longest + 7000) t = longest + 7000;
+    // Masked items in a second, partly filled round, where the 256-row kernel needs one round: a long item may start
+    // behind another one (D = 64: shares its CU with it), unless every XCD has whole heads (D = 64: the round is
+    // full and block_map_paired evens it out). 128 / 256 rows, us: D = 128, 12 x 3403 82 / 72, 22 x 1574 42 / 38 (but 24 x
+    // 1536 30 / 37); D = 64, 29 x 1809 38 / 35.
+    if (a.causal && groups > 1 && rounds == 2 && one_round_of_256 && (a.D == 128 ? heads % nxcd != 0 : wgs < 2 * ncu)) t += longest / 2;
     t = (int64_t)std::sqrt((double)t * t + arrive * arrive);       // the two overlap in part
     // the partial results' second kernel: a launch, and writing and reading them at 4 TB/s
     if (nsplit > 1) t += 3500 + 2 * nsplit * heads * a.Sq * (a.D + 2) / 1000;

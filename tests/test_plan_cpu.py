@@ -82,3 +82,9 @@ def test_causal_attention_is_priced_by_the_keys_it_sees(plan, D):
         assert len(set(plan(["mha %d %d %d %d %d 1" % (B, H, Sq, Sk, D) for Sk in (Sq, 2 * Sq, 1994, 30000)]))) == 1
     name = "mha_fwd_d%d_causal_256x64_pp 1" % D
     assert plan(["mha 17 8 65 1994 %d 1" % D, "mha 4 8 41 41 %d 1" % D]) == [name, name]
+
+
+def test_masked_attention_avoids_a_partly_filled_second_round(plan):
+    """128-row tiles that just overflow the chip, with heads that do not divide over the XCDs, start long items late."""
+    ans = plan(["mha 1 %d %d %d %d 1" % c for c in ((12, 3403, 3403, 128), (22, 1574, 1574, 128), (29, 1809, 3928, 64), (24, 1536, 1536, 128))])
+    assert ["128x32_k2" in a for a in ans] == [False, False, False, True], ans
