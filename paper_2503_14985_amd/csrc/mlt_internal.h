@@ -145,8 +145,16 @@ struct PagedArgs {
   int dtype;
   int forced_split = 0;      // > 0: ranges of keys per (sequence, head), from mlt_diag_force_key_split
 };
+// Pieces of a paged decode dealt out by length: workgroup `id` of `total`, which the hardware puts on CU id % ncu (all are
+// resident at once), takes the piece of this rank. Every second round of CUs runs backwards, the last full one among them.
+__host__ __device__ inline int dealt_piece(int id, int total, int ncu) {
+  const int round = id / ncu, full = total / ncu;
+  return round < full && ((full - round) & 1) ? round * ncu + (ncu - 1 - (id - round * ncu)) : id;
+}
 // paged.hip; *nsplit_out: the number of key ranges per (sequence, head) that ran
 int run_paged_decode(const PagedArgs& a, hipStream_t s, int* nsplit_out);
+int plan_paged_split(const PagedArgs& a);                                       // key ranges per (sequence, head)
+bool paged_by_length(const PagedArgs& a, int64_t nsplit, int64_t ncu);   // workgroups dealt out by sequence length?
 
 // The library's own scratch memory for a stream of the current device: at least `bytes`, kept
 // (and grown by doubling) from call to call, never freed; nullptr if it cannot be had, and while the

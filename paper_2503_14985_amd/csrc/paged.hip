@@ -85,7 +85,9 @@ __device__ __forceinline__ int sequence_of_rank(const int32_t* seq_lens, int B, 
 // Which workgroup takes which sequence: hardware deals the workgroups of a launch to the CUs in turn, all of
 // them at once up to 8 per CU, and with the batch in its own order the CUs' shares of keys differ by
 // chance. A batch of 2 to PG_NT sequences with more workgroups than CUs is therefore dealt from the
-// longest sequence to the shortest, every second round of CUs backwards. 64 sequences of 1024 to 4096
+// longest sequence to the shortest, every second round of CUs backwards, the last full one among them: an odd
+// number of rounds leaves the first CUs with the shorter sequences, and they get what is over (27 x 32 of at most 9344
+// keys, D = 64: 226 us with the first round forwards, 213 so, 212 in batch order). 64 sequences of 1024 to 4096
 // keys, 32 heads, D = 128, shuffled: 456 -> 421 us (6.4 TB/s, as for equal lengths).
 //
 // SPLIT: blockIdx.y is the range of units this workgroup takes, and the result goes to `part`
@@ -113,8 +115,7 @@ __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
   if (ORDER) {
     const int pieces = H * nsplit, total = B * pieces;
     int id = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-    const int blk = id / ncu * ncu;
-    if ((id / ncu & 1) && blk + ncu <= total) id = blk + (ncu - 1 - (id - blk));
+    id = dealt_piece(id, total, ncu);
     b = sequence_of_rank(seq_lens, B, id / pieces, reinterpret_cast<int*>(&so[0][0]));
     h = id % pieces / nsplit;
     range = id % nsplit;
@@ -285,10 +286,7 @@ int launch_paged(const PagedArgs& a, int nsplit, float* part, hipStream_t s) {
   const unsigned pairs = (unsigned)(a.B * a.H);
   DeviceInfo di;
   const int64_t ncu = device_info(di) ? di.ncu : 0;
-  // (the rank search costs 1 us: not for caches that are read in less than 25 us; 38 x 32 pairs of 181 keys at most
-  // 16.1 us in batch order, 17.1 by length)
-  const bool order = ncu > 0 && a.B > 1 && a.B <= PG_NT && (int64_t)pairs * (nsplit > 1 ? nsplit : 1) > ncu &&
-                     pairs * a.max_blocks * a.block_size * a.D * 4 >= ((int64_t)192 << 20);
+  const bool order = paged_by_length(a, nsplit, ncu);
   auto kern = nsplit > 1 ? (order ? paged_decode_kernel<Tag, D, true, true> : paged_decode_kernel<Tag, D, true, false>)
                          : (order ? paged_decode_kernel<Tag, D, false, true> : paged_decode_kernel<Tag, D, false, false>);
   hipLaunchKernelGGL(kern, dim3(pairs, nsplit > 1 ? (unsigned)nsplit : 1u), dim3(PG_NT), 0, s, a.Q, a.Kc, a.Vc,
@@ -303,6 +301,19 @@ int launch_paged(const PagedArgs& a, int nsplit, float* part, hipStream_t s) {
 }
 
 }  // namespace
+
+// Whether a launch deals its workgroups by length. The rank search costs 1 to 2 us in front of the first load, so not for
+// caches that are read in less than 30 us, 25 us in smaller pieces (17 x 32 pairs of at most 800 keys 26.9 us in batch order, 29.3 by length; 167 x 4
+// of 1280, D = 64: 30, 32.6; 38 x 32 of 181: 16.1, 17.1). And every workgroup reads all
+// B lengths, 25 ps for each on the whole chip. That has to stay below what the order gains: 0.5 to 0.6 of the reading over the
+// workgroups per CU, nothing on short sequences. us in batch order / by length: 228 x 16 pairs of at most 256 keys, D = 128:
+// 51 / 72; 76 x 16 of 400: 29 / 31; 206 x 16 of 544, D = 64: 49 / 61; 254 x 1 of 3456 in 6 ranges, D = 128: 54 / 60; but
+// 246 x 4 of 1088, D = 128: 71 / 63; 208 x 4 of 608: 36 / 34; 230 x 8 of 2416, D = 64: 131 / 123.
+bool paged_by_length(const PagedArgs& a, int64_t nsplit, int64_t ncu) {
+  const int64_t wgs = a.B * a.H * nsplit, keys = a.max_blocks * a.block_size;
+  if (ncu <= 0 || a.B < 2 || a.B > PG_NT || wgs <= ncu || keys < 512) return false;
+  return a.B * a.H * keys * a.D * 4 >= ((int64_t)(nsplit > 1 ? 192 : 224) << 20) && wgs * nsplit * a.B * 10 < keys * a.D * 32;
+}
 
 // Ranges per (sequence, head), at most 64. Up to one workgroup per CU from the pairs alone: what brings the
 // launch to two per CU, as long as a range of the longest possible sequence (the table's width) keeps 16

@@ -3,6 +3,8 @@
 //   gemm M N K transB lda ldb fp32_accumulate fused noncontiguous_base   ->  name parts scratch_bytes
 // (noncontiguous_base != 0: A starts on an odd element)
 //   mha B H Sq Sk D causal   ->  name ranges
+//   paged B H D block_size max_blocks   ->  ranges dealt_by_length
+//   deal pieces CUs   ->  the rank of the piece that each workgroup takes
 #include <stdio.h>
 #include <string.h>
 
@@ -36,6 +38,18 @@ int main() {
       a.forced = MHA_AUTO;
       const MhaPlan p = plan_mha(a);
       printf("%s %d\n", p.name, p.nsplit);
+    } else if (!strcmp(op, "paged")) {
+      long long B, H, D, block_size, max_blocks;
+      if (scanf("%lld %lld %lld %lld %lld", &B, &H, &D, &block_size, &max_blocks) != 5) return 1;
+      PagedArgs a{};
+      a.B = B; a.H = H; a.D = D; a.block_size = block_size; a.max_blocks = max_blocks; a.num_blocks = B * max_blocks;
+      const int n = plan_paged_split(a);
+      printf("%d %d\n", n, paged_by_length(a, n, 256) ? 1 : 0);
+    } else if (!strcmp(op, "deal")) {
+      int total, ncu;
+      if (scanf("%d %d", &total, &ncu) != 2) return 1;
+      for (int id = 0; id < total; ++id) printf("%d ", dealt_piece(id, total, ncu));
+      printf("\n");
     } else {
       return 1;
     }

@@ -88,3 +88,24 @@ def test_masked_attention_avoids_a_partly_filled_second_round(plan):
     """128-row tiles that just overflow the chip, with heads that do not divide over the XCDs, start long items late."""
     ans = plan(["mha 1 %d %d %d %d 1" % c for c in ((12, 3403, 3403, 128), (22, 1574, 1574, 128), (29, 1809, 3928, 64), (24, 1536, 1536, 128))])
     assert ["128x32_k2" in a for a in ans] == [False, False, False, True], ans
+
+
+def test_paged_decode_searches_ranks_only_where_the_lengths_are_few_for_the_keys(plan):
+    """Every workgroup reads all B lengths: many short sequences took up to 1.4 times as long by length as in batch order."""
+    ask = lambda cases: [a.split()[1] for a in plan(["paged %d %d %d %d %d" % c for c in cases])]
+    assert ask([(228, 16, 128, 16, 16), (206, 16, 64, 32, 17), (76, 16, 128, 16, 25), (38, 32, 128, 16, 12), (300, 8, 128, 16, 256)]) == ["0"] * 5
+    assert ask([(64, 32, 128, 16, 256), (246, 4, 128, 64, 17), (230, 8, 64, 16, 151), (10, 32, 128, 16, 256)]) == ["1"] * 4
+
+
+def test_pieces_dealt_by_length_leave_the_remainder_to_the_cus_with_less(plan):
+    """Piece lengths that fall evenly with the rank to a quarter; the hardware deals workgroup i to CU i % 256. Bounds: the
+    most loaded CU over the mean, with the last full round backwards (forwards: 1.85, 1.55, 1.30, 1.18, 1.16 and 1.09
+    for the first six)."""
+    for total, bound in ((300, 1.37), (400, 1.07), (511, 1.01), (816, 1.07), (864, 1.06), (1000, 1.01), (512, 1.001), (2048, 1.001)):
+        ranks = [int(x) for x in plan(["deal %d 256" % total])[0].split()]
+        assert sorted(ranks) == list(range(total))
+        load = [0.0] * 256
+        for i, r in enumerate(ranks):
+            load[i % 256] += 1.0 - 0.75 * r / total
+        assert max(load) <= bound * sum(load) / 256, total
+
