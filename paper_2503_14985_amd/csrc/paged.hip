@@ -323,7 +323,10 @@ bool paged_by_length(const PagedArgs& a, int64_t nsplit, int64_t ncu) {
 // length, and the more there are the closer the CUs' shares come (us, lengths s/4 .. s, D = 128: 10 x 32, s = 4096:
 // 102 uncut, 71 in 6 ranges; 8 x 16, 32768: 238 in 4, 208 in 16; 16 x 32, 4096: 118 uncut, 111 in 4; equal lengths
 // 121 / 112, 335 / 331, 168 / 173). From three pairs per CU on the second kernel costs as much as that gains
-// (24 x 32, 2048: 83.8 uncut, 86.3 in 2), and so it does where the cache is read in less than 20 us.
+// (24 x 32, 2048: 83.8 uncut, 86.3 in 2), from two and a half on for caches below 448 MiB (22 x 32, 2176, D = 64: 45.5, 47.4;
+// but 83 x 8, 2816: 64, 56), and so it does where the cache is read in less than 20 us, or for a quarter more
+// ranges and less (14 x 4, 5920: 26 in 10, 29 in 11; 4 x 16, 5440: 27 in 8, 28.7 in 10). Nor do the ranges of one sequence get finer from 32 units (D = 64: 64)
+// on (1 x 32, 14848 keys: 42.8 in 16, 45.2 in 32; 7680 keys equal; D = 64, 12672 keys: 22.8, 21.5).
 int plan_paged_split(const PagedArgs& a) {
   if (a.forced_split > 0) return a.forced_split > PG_MAX_SPLIT ? PG_MAX_SPLIT : a.forced_split;
   DeviceInfo di;
@@ -334,13 +337,14 @@ int plan_paged_split(const PagedArgs& a) {
   if (pairs <= ncu) {
     n = (2 * ncu + pairs - 1) / pairs;
     if (n > max_units / 16) n = max_units / 16;
-    if (a.B == 1 && n > 1 && max_units <= 64 * n && max_units >= 16 * n) n *= 2;
+    if (a.B == 1 && n > 1 && max_units * a.D <= 4096 * n && max_units >= 16 * n) n *= 2;
   }
-  const bool long_read = pairs <= ncu || pairs * max_units * PG_UNIT * a.D * 4 >= ((int64_t)128 << 20);
+  const int64_t mib = pairs * max_units * PG_UNIT * a.D * 4 >> 20;
+  const bool long_read = pairs <= ncu || mib >= (2 * pairs <= 5 * ncu ? 128 : 448);
   if (a.B > 1 && a.B <= PG_NT && pairs < 3 * ncu && long_read) {
     int64_t fine = 8 * ncu / pairs;
     if (fine > max_units / 32) fine = max_units / 32;
-    if (fine > n) n = fine;
+    if (4 * fine > 5 * n) n = fine;
   }
   if (n > PG_MAX_SPLIT) n = PG_MAX_SPLIT;
   return n < 1 ? 1 : (int)n;

@@ -109,3 +109,11 @@ def test_pieces_dealt_by_length_leave_the_remainder_to_the_cus_with_less(plan):
             load[i % 256] += 1.0 - 0.75 * r / total
         assert max(load) <= bound * sum(load) / 256, total
 
+
+def test_paged_decode_is_cut_finer_only_where_that_gains(plan):
+    ask = lambda cases: [int(a.split()[0]) for a in plan(["paged %d %d %d %d %d" % c for c in cases])]
+    # one range, or the ranges that bring the launch to two workgroups per CU
+    assert ask([(64, 32, 128, 16, 256), (24, 32, 128, 16, 128), (22, 32, 64, 16, 136), (14, 4, 128, 32, 185), (1, 32, 128, 64, 232)]) == [1, 1, 1, 10, 16]
+    # finer
+    assert ask([(1, 8, 128, 16, 2048), (1, 32, 128, 16, 256), (10, 32, 128, 16, 256), (8, 16, 128, 16, 2048), (20, 32, 128, 16, 128), (23, 32, 64, 64, 128),
+                (6, 32, 64, 64, 36)]) == [64, 32, 6, 16, 3, 2, 4]
