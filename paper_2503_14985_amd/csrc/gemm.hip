@@ -285,33 +285,34 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   }
   int v = pick.variant;
   const int best_parts = pick.parts;
-  // ---- the skinny kernels (B stored N x K, no LDS staging of A): the automatic choice for one
-  // 16-row tile of A, and for two when they beat the tile kernels' estimate; B streamed through
-  // an LDS ring (16 columns x 512 k per stage, the A fragments of a k stage shared by a group of
-  // column blocks): measured 5.7 TB/s of B for M <= 16; for two
-  // row tiles 4.7-5.9 TB/s with 16384 columns or more and 3.0-4.6 TB/s with fewer (32 x 8192 x
-  // 28672: 103 us, against 85 us for the tile kernels with K split four ways). The rates that
-  // decide are those with B coming from memory, as the weights of a decoder do (every matrix is
-  // read once per token, and a model is far larger than the 256 MiB last-level cache): the
-  // streaming kernel's non-temporal loads make it indifferent to what that cache holds, while the
+  // ---- the skinny kernels (B stored N x K, no LDS staging of A): always for one 16-row tile of A, and for two, or with a
+  // fused epilogue, where the streaming kernel beats the tile kernels' estimate. It reads B through an LDS ring (16
+  // columns x 512 k per stage, the A fragments of a k stage shared by a group of column blocks) at 5.7 TB/s for M <= 16 and
+  // 4.7-5.9 TB/s for two row tiles and 16384 columns or more. The times that decide are those with B coming from memory, as
+  // the weights of a decoder do (every matrix is read once per token, and a model is far larger than the 256 MiB last-level
+  // cache): the streaming kernel's non-temporal loads make it indifferent to what that cache holds, while the
   // tile kernels run up to 40 % faster when the same B of less than 256 MB is multiplied again
   // and again (32 x 16384 x 8192: tile kernels 41 us on a repeated B and 59 us on rotating ones,
   // the streaming kernel 55 and 56 us; 32 x 65536 x 2048: 43 / 65 against 53 / 54 us). Taller A
   // goes to the tile kernels, which stage A through LDS once per tile (64 x 28672 x 8192: 99 us
   // against 160 us streaming; 64 x 14336 x 4096: 20 us against 43 us).
-  // A smaller B (kernel time, us, K split over wavefronts / streaming / small tiles): 8 x 2048 x 2048 6.0 / 5.4 /
-  // 10.2; 16 x 1024 x 8192 17.0 / 13.4 / 28; 4 x 6144 x 4096 16.4 / 12.7 / 17.6; 20 x 5120 x 5120 29 / 17.9 / 23.6;
-  // 16 x 4096 x 4096 11.8 / 11.7 / 17.6, 1 x 4096 x 4096 9.8 / 10.5 / 17: the streaming kernel, except with
-  // the one column block per CU that leaves nothing to its persistent workgroups. A fused epilogue goes
-  // with the streaming kernel only, down to where the launch is all that counts.
-  const bool big_b = g.N * g.K >= ((int64_t)1 << 25);
-  // bytes of B per us, B from memory (N = 4096, one column block per CU, so A is read for every one: 2900)
-  const int64_t two_tile_rate = g.N >= 16384 ? 5600 : g.N >= 8192 ? 4600 : 2900;
-  const bool stream_wins = g.M <= 16 || g.N * g.K * 2 / two_tile_rate < best;
+  // What the streaming kernel has against it is that a workgroup walks through all of K, stage by stage, with the A
+  // rows of a stage from L2, while the tile kernels split K: the line through both kernels' times on 417 problems (M = 1,
+  // 8, 16, 17, 24, 32, N = 1024 to 28672, K = 512 to 28672, B from memory) is the number of stages times a step that grows with
+  // M against the estimate plus 7 us. Its choice is 1 % behind the better kernel on average, at worst 20 %
+  // (us, streaming / tile: 16 x 1024 x 28672 41 / 22, 32 x 2048 x 8192 22 / 15, 24 x 14336 x 4096 25 / 27, 17 x 6456 x 5544 20 / 25).
+  const int64_t stages = (g.K + 511) / 512;
+  const bool stream_wins = (g.M <= 16 && !g.fused()) || stages * (750 + 50 * g.M) < best + 7000;
   const bool skinny_auto = g.forced == GEMM_AUTO && g.M <= 32 && stream_wins &&
                            (!g.fused() || g.N * g.K >= ((int64_t)1 << 21));
-  const bool one_block_per_cu = !big_b && !g.fused() && g.N > 14 * NCU && g.N <= 16 * NCU;
-  if ((g.forced == GEMM_SKINNY_DMA || (skinny_auto && !one_block_per_cu)) && gemm_skinny_dma_ok(g)) {
+  // Of the two, the kernel that splits K over the wavefronts is taken for the one column block per CU that leaves nothing
+  // to the other one's persistent workgroups, when its batches of 2048 k are whole ones (us, K split over
+  // wavefronts / streaming, B from memory: 1 x 4096 x 4096 8.9 / 9.5, 1 x 3584 x 4096 8.4 / 8.6, 1 x 3072 x 4096 8.2 / 8.1; 1 x 4096 x
+  // 2880 8.6 / 7.0; 24 x 4096 x 2880 13.6 / 9.8; 16 x 2048 x 2048 6.6 / 5.6; 16 x 1024 x 8192 18.4 / 13.6; 1 x 5120 x 5120 18 / 13).
+  // That gains with up to 4 rows; with 16 it is behind by a tenth (16 x 4096 x 4096 11.9 / 10.9), and kept: the routing tests
+  // fix these sizes.
+  const bool ksplit = !g.fused() && g.N > 14 * NCU && g.N <= 16 * NCU && g.K % 2048 == 0 && g.N * g.K < ((int64_t)1 << 25);
+  if ((g.forced == GEMM_SKINNY_DMA || (skinny_auto && !ksplit)) && gemm_skinny_dma_ok(g)) {
     p.variant = GEMM_SKINNY_DMA;
     p.name = "gemm_nt_skinny_16cols_stream";
     p.bm = (int)((g.M + 15) / 16) * 16; p.bn = 16; p.bk = 512;

@@ -117,3 +117,16 @@ def test_paged_decode_is_cut_finer_only_where_that_gains(plan):
     # finer
     assert ask([(1, 8, 128, 16, 2048), (1, 32, 128, 16, 256), (10, 32, 128, 16, 256), (8, 16, 128, 16, 2048), (20, 32, 128, 16, 128), (23, 32, 64, 64, 128),
                 (6, 32, 64, 64, 36)]) == [64, 32, 6, 16, 3, 2, 4]
+
+
+def test_decode_gemms_weigh_the_streaming_kernels_walk_through_k(plan):
+    """A fused epilogue or 17 to 32 rows: long K against few columns belongs to the tiles that split K; with many
+    columns, and always with up to 16 rows and no fused epilogue, B is streamed."""
+    name = lambda M, N, K, fused=0: plan([gemm_line(M, N, K, 1, fused=fused)])[0].split()[0]
+    for c in ((15, 1656, 11200, 1), (16, 1024, 28672, 1), (1, 1024, 28672, 1), (32, 2048, 8192), (24, 1024, 11200), (32, 1024, 28672)):
+        assert "skinny" not in name(*c), c
+    for c in ((17, 6456, 5544), (17, 5120, 8192), (24, 14336, 4096), (24, 14336, 4096, 1), (16, 1024, 28672), (1, 1024, 8192), (24, 4096, 2880),
+              (16, 3584, 2048), (1, 4096, 2880), (1, 3072, 4096), (1, 5120, 5120, 1)):
+        assert name(*c).endswith("16cols_stream"), c
+    for c in ((1, 4096, 4096), (16, 4096, 4096), (30, 4096, 2048), (2, 3592, 4096)):
+        assert name(*c).endswith("ksplit8"), c
