@@ -112,14 +112,18 @@ static const char* any_name(int variant, int transB) {
   return transB ? "gemm_general_nt_256x256x64_w2x4" : "gemm_general_nn_256x256x64_w2x4";
 }
 
-GemmPlan plan_gemm(const GemmArgs& g) {
+GemmPlan plan_gemm(const GemmArgs& g_in) {
   GemmPlan p;
+  GemmArgs g = g_in;
   // K == 0: the empty sum; with a fused epilogue C = act(bias), which the general kernel's epilogue
   // computes after zero K steps
   if (g.K == 0 && !g.fused()) { p.variant = GEMM_ZERO; p.name = "gemm_zero"; return p; }
   // operands that do not allow aligned 16-byte accesses: the tile kernels in the form of gemm_any.hip;
   // rows too short for one such access: the general kernel
   p.aligned = g.K == 0 || g.forced == GEMM_GENERAL || fast_path_ok(g) || !gemm_any_ok(g);
+  // the 256 x 256 kernels of the tiling hints exist for aligned operands only, and that tile is far too large for most
+  // others (1439 x 333 x 113 row-major: 10.6 us, the automatic choice 7)
+  if (!p.aligned && (g.forced == GEMM_256 || g.forced == GEMM_256_W8X1 || g.forced == GEMM_256_W1X8)) g.forced = GEMM_AUTO;
   if (g.K == 0 || g.forced == GEMM_GENERAL || (p.aligned && !fast_path_ok(g))) {
     p.variant = GEMM_GENERAL; p.name = "gemm_general_64x64x32";
     p.bm = 64; p.bn = 64; p.bk = 32; p.wm = 2; p.wn = 2;
@@ -337,7 +341,6 @@ GemmPlan plan_gemm(const GemmArgs& g) {
   // a forced kernel keeps the split only if it is one of the kernels that can run it
   const bool can_split = v == GEMM_128_K2 || v == GEMM_64X128_K2 || v == GEMM_64_K4 || v == GEMM_128_W8 ||
                          v == GEMM_64X128_W8 || v == GEMM_64_W4 || v == GEMM_256X128_KP || v == GEMM_128_KP;
-  if (!p.aligned && (v == GEMM_256 || v == GEMM_256_W8X1 || v == GEMM_256_W1X8)) v = GEMM_256_W8;
   p.parts = can_split ? best_parts : 1;
   p.scratch_bytes = p.parts > 1 ? (int64_t)p.parts * g.M * g.N * 4 : 0;
   p.variant = v;

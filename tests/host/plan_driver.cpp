@@ -1,7 +1,7 @@
 // Prints what the library's planning functions choose, without a device (they then assume 256 CUs, 8
 // XCDs). One problem per line on stdin, one answer per line on stdout:
 //   gemm M N K transB lda ldb fp32_accumulate fused noncontiguous_base   ->  name parts scratch_bytes
-// (noncontiguous_base != 0: A starts on an odd element)
+// (noncontiguous_base != 0: A starts on an odd element; "hint1", "hint2" instead of "gemm": with that tiling hint)
 //   mha B H Sq Sk D causal   ->  name ranges
 //   paged B H D block_size max_blocks   ->  ranges dealt_by_length
 //   deal pieces CUs   ->  the rank of the piece that each workgroup takes
@@ -15,16 +15,18 @@ using namespace mlt;
 int main() {
   char op[16];
   while (scanf("%15s", op) == 1) {
-    if (!strcmp(op, "gemm")) {
+    if (!strcmp(op, "gemm") || !strcmp(op, "hint1") || !strcmp(op, "hint2")) {
       long long M, N, K, lda, ldb;
-      int tb, acc, fused, odd;
+      int tb, acc, fused, odd, forced = GEMM_AUTO;
       if (scanf("%lld %lld %lld %d %lld %lld %d %d %d", &M, &N, &K, &tb, &lda, &ldb, &acc, &fused, &odd) != 9) return 1;
       GemmArgs g{};
       g.M = M; g.N = N; g.K = K;
       g.A = (const uint16_t*)(0x100000 + (odd ? 2 : 0)); g.lda = lda;
       g.B = (const uint16_t*)0x200000; g.ldb = ldb; g.transB = tb;
       g.C = (uint16_t*)0x300000; g.ldc = N;
-      g.forced = GEMM_AUTO; g.acc32 = acc;
+      if (!strcmp(op, "hint1")) forced = GEMM_256_W8X1;
+      if (!strcmp(op, "hint2")) forced = GEMM_256_W1X8;
+      g.forced = forced; g.acc32 = acc;
       if (fused) g.bias = (const uint16_t*)0x400000;
       const GemmPlan p = plan_gemm(g);
       printf("%s %d %lld\n", p.name, p.parts, (long long)p.scratch_bytes);

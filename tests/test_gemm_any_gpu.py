@@ -77,3 +77,39 @@ def test_epilogues_on_unaligned_operands():
     for act in (0, 1, 2):
         A, B = inputs.gemm_inputs(130, 133, 203, BF16, 5, transB=True)
         pu.run_check_gemm_bias_act(A, B, inputs.bias_input(133, BF16, 5, std=4.0), act, BF16, transB=True)
+
+
+def test_fp32_accumulate_on_unaligned_operands():
+    import numpy as np
+    import torch
+    import oracle
+    from paper_2503_14985_amd import binding
+    dev = torch.device("cuda:0")
+    for M, N, K, transB, parts in ((130, 133, 203, True, 1), (130, 133, 203, False, 1), (300, 77, 64 * 20 + 3, True, 2)):
+        binding.mlt_diag_force_k_parts(parts)
+        A, B = inputs.gemm_inputs(M, N, K, BF16, 6, transB=transB)
+        C0 = np.random.default_rng(6).standard_normal((M, N)).astype(np.float32) * 10.0
+        Ct = torch.from_numpy(C0.copy()).to(dev)
+        binding.mlt_gemm_acc(inputs.bits_to_torch(A, BF16, dev), inputs.bits_to_torch(B, BF16, dev), Ct, transB=transB)
+        torch.cuda.synchronize()
+        assert binding.mlt_last_kernel().startswith("gemm_general_n") and ("splitk" in binding.mlt_last_kernel()) == (parts > 1)
+        Cref, T = oracle.gemm(A, B, BF16, transB=transB)
+        err = np.abs(Ct.double().cpu().numpy() - (C0.astype(np.float64) + Cref))
+        # fp32 accumulation over K terms, then the final addition (as in tests/test_gemm_gpu.py)
+        bound = (K * 2.0 ** -24) * T + 2.0 ** -22 * (np.abs(C0) + T) + 1e-6
+        assert np.all(err <= bound), "worst err/bound %.3f" % float(np.max(err / bound))
+
+
+@pytest.mark.parametrize("transB", [False, True])
+def test_tiling_hints_change_nothing_on_unaligned_operands(transB):
+    import torch
+    from paper_2503_14985_amd import binding
+    dev = torch.device("cuda:0")
+    for M, N, K in ((130, 333, 203), (9, 18, 77), (40, 70, 5)):
+        A, B = (inputs.bits_to_torch(x, BF16, dev) for x in inputs.gemm_inputs(M, N, K, BF16, 4, transB=transB))
+        want = binding.mlt_gemm(A, B, transB=transB)
+        name = binding.mlt_last_kernel()
+        for tiling in (1, 2, 3):
+            got = binding.mlt_gemm_tiled(A, B, tiling, transB=transB)
+            assert binding.mlt_last_kernel() == name
+            assert torch.equal(got.view(torch.int16), want.view(torch.int16))

@@ -130,3 +130,11 @@ def test_decode_gemms_weigh_the_streaming_kernels_walk_through_k(plan):
         assert name(*c).endswith("16cols_stream"), c
     for c in ((1, 4096, 4096), (16, 4096, 4096), (30, 4096, 2048), (2, 3592, 4096)):
         assert name(*c).endswith("ksplit8"), c
+
+
+def test_a_tiling_hint_on_unaligned_operands_is_the_automatic_choice(plan):
+    for M, N, K, tb in ((1439, 333, 113, 0), (9, 18, 200, 0), (926, 10, 77, 1), (1999, 3001, 1501, 0), (64, 65, 3, 1)):
+        line = gemm_line(M, N, K, tb)
+        auto, h1, h2 = plan([line, line.replace("gemm", "hint1"), line.replace("gemm", "hint2")])
+        assert auto == h1 == h2, (M, N, K, tb)
+    assert "_w8x1" in plan([gemm_line(520, 776, 320, 0).replace("gemm", "hint1")])[0]
