@@ -201,7 +201,12 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   auto fits = [&](int bm, int bn) {
     return !(bm > 64 && bm > (g.M + 63) / 64 * 64) && !(bn > 64 && bn > (g.N + 63) / 64 * 64);
   };
-  if (g.forced_parts <= 1 && fits(256, 256)) all[n_all++] = Choice{big.variant, 1, 256 * 256, cost(256, 256, big.t, 0, 1, 1)};
+  // Fewer than 8 K steps and at most one 64 x 64 tile per CU: that tile has the least estimate by more than the 8 %
+  // that a larger one is granted (350 a step against 410 or more, and more workgroups to fetch the operands), so the others
+  // are not priced (0.2 us of a call of 6.5).
+  const bool small_tiles = KT < 8 && g.forced_parts <= 1 && ((g.M + 63) / 64) * ((g.N + 63) / 64) <= NCU;
+  if (small_tiles) all[n_all++] = Choice{GEMM_64_W4, 1, 64 * 64, cost(64, 64, 350, 0, 1, 1)};
+  else if (g.forced_parts <= 1 && fits(256, 256)) all[n_all++] = Choice{big.variant, 1, 256 * 256, cost(256, 256, big.t, 0, 1, 1)};
   // The two-group kernel on 128 x 128 tiles, no K split across workgroups, in its two forms (fits
   // over K at 256 and 512 tiles, kernel time without the call):
   //   K steps of 64, two workgroups per CU: 0.84 us per step for a pair of tiles + 1.9 us per pair,
@@ -214,7 +219,7 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   // 64-deep form, whose workgroups hide each other's start and end (2048 x 4096 x 4096: 60.0
   // against 69.6 us, 82 on the split kernel, 73 on 128 big tiles; 1024 x 8192 x 8192: 114 against
   // 132, 153 and 134).
-  if (pp && g.forced_parts <= 1 && fits(128, 128)) {
+  if (pp && !small_tiles && g.forced_parts <= 1 && fits(128, 128)) {
     const int64_t wgs = ((g.M + 127) / 128) * ((g.N + 127) / 128);
     const int64_t base = (g.M + g.N) * g.K * 2 / 5200;
     const int64_t need = 6 * NCU / 10;
@@ -254,7 +259,7 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     const int64_t arrive = wgs >= need ? base : base * need / wgs;
     return (compute > arrive ? compute : arrive) + (parts > 1 ? 4000 + 2 * parts * g.M * g.N / 1000 : 0);
   };
-  for (int parts = g.forced_parts > 0 ? g.forced_parts : 1; parts <= (g.forced_parts > 0 ? g.forced_parts : 8); parts *= 2) {
+  for (int parts = g.forced_parts > 0 ? g.forced_parts : 1; !small_tiles && parts <= (g.forced_parts > 0 ? g.forced_parts : 8); parts *= 2) {
     // every part keeps at least 8 K steps, and all parts' tiles fit the scratch that mlt_gemm_noalloc has
     // (a forced split may ask for more: mlt_gemm allocates it, mlt_gemm_noalloc refuses)
     if (parts > 1 && KT < 8 * parts) break;

@@ -27,14 +27,15 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
   }
   const int64_t heads = a.B * a.H;
   if (a.forced != MHA_AUTO || heads < 1 || a.Sq < 1) return;
+  // with the mask the last query row sees min(Sq, Sk) keys (17 x 8 heads, 65 x 1994 causal, D = 128, priced with all
+  // 1994: 64 rows, 11.8 us; 256 rows take 8.0)
+  const int64_t keys = a.causal && a.Sq < a.Sk ? a.Sq : a.Sk, tiles = (keys + 31) / 32;
+  // one key tile of the 256-row kernel and no second round: nothing to divide (64 workgroups fit any of these chips)
+  if (tiles <= 2 && heads * ((a.Sq + 255) / 256) <= 64) return;
   DeviceInfo di;
   const int64_t ncu = device_info(di) && di.ncu > 0 ? di.ncu : 256, nxcd = di.nxcd > 0 ? di.nxcd : 8;
   const bool one_round_of_256 = heads * ((a.Sq + 255) / 256) <= ncu;
   if (heads * ((a.Sq + 255) / 256) > 4 * ncu) return;             // enough of the large tiles
-  // with the mask the last query row sees min(Sq, Sk) keys (17 x 8 heads, 65 x 1994 causal, D = 128, priced with all
-  // 1994: 64 rows, 11.8 us; 256 rows take 8.0)
-  const int64_t keys = a.causal && a.Sq < a.Sk ? a.Sq : a.Sk, tiles = (keys + 31) / 32;
-  // one key tile of the 256-row kernel and no second round: nothing to divide
   if (tiles <= 2 && one_round_of_256) return;
   const double arrive = (double)heads * (a.Sq + keys) * a.D * 4 / 5500;   // every tensor once at 5.5 TB/s
   auto cost = [&](int groups, int nsplit) -> int64_t {

@@ -77,7 +77,7 @@ __device__ __forceinline__ void block_map_paired(int bid, int total, int nq, int
 // what a launch of `total` workgroups adds to the XCD count for that map
 inline int paired_cus(int total, bool causal, int D) {
   DeviceInfo di;
-  if (D != 64 || !causal || !device_info(di) || di.ncu <= 0 || di.nxcd <= 0) return 0;
+  if (D != 64 || !causal || total <= 64 || !device_info(di) || di.ncu <= 0 || di.nxcd <= 0) return 0;
   return total > di.ncu && total <= 2 * di.ncu ? di.ncu / di.nxcd << 8 : 0;
 }
 
