@@ -419,8 +419,8 @@ int launch_ks(const MhaArgs& a, int nsplit, float* scratch, hipStream_t s) {
   if (c < 1e-30f) c = 1e-30f;
   float* ps = SPLIT ? scratch + (int64_t)nsplit * rows * D : nullptr;
   hipLaunchKernelGGL(kern, dim3((unsigned)total, SPLIT ? nsplit : 1), dim3(512), L::SMEM, s, a.Q, a.K, a.V, a.O, scratch, ps,
-                     (int)a.Sq, (int)a.Sk, (int)nq, (int)total, 
-                     device_xcds() + paired_cus((int)total, a.causal, D), c, a.scale < 0 ? 1 : 0, a.causal);
+                     (int)a.Sq, (int)a.Sk, (int)nq, (int)total,
+                     mha_xcd_word((int)total, a.causal, D, 32), c, a.scale < 0 ? 1 : 0, a.causal);
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
   if (!SPLIT) return MLT_OK;
   hipLaunchKernelGGL((mha_ks_merge_kernel<Tag, D>), dim3((unsigned)((rows * (D / 8) + 255) / 256)), dim3(256), 0, s,

@@ -1220,7 +1220,7 @@ int launch_mha_pp(const MhaArgs& a, hipStream_t s) {
   float c = (a.scale < 0 ? -a.scale : a.scale) * LOG2E;
   if (c < 1e-30f) c = 1e-30f;
   hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(PA_NT), L::SMEM, s, a.Q, a.K, a.V, a.O,
-                     (int)a.Sq, (int)a.Sk, nq, (int)total, device_xcds() + paired_cus((int)total, CAUSAL, D), c, a.scale < 0 ? 1 : 0);
+                     (int)a.Sq, (int)a.Sk, nq, (int)total, mha_xcd_word((int)total, CAUSAL, D, MS), c, a.scale < 0 ? 1 : 0);
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 

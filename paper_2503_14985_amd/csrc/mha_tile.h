@@ -75,10 +75,19 @@ __device__ __forceinline__ void block_map_paired(int bid, int total, int nq, int
   qt = nq - 1 - logical % nq;
 }
 // what a launch of `total` workgroups adds to the XCD count for that map
-inline int paired_cus(int total, bool causal, int D) {
-  DeviceInfo di;
-  if (D != 64 || !causal || total <= 64 || !device_info(di) || di.ncu <= 0 || di.nxcd <= 0) return 0;
+inline int paired_cus(int total, bool causal, int D, const DeviceInfo& di) {
+  if (D != 64 || !causal || di.ncu <= 0 || di.nxcd <= 0) return 0;
   return total > di.ncu && total <= 2 * di.ncu ? di.ncu / di.nxcd << 8 : 0;
+}
+// The XCD word of a launch: their count, and for the kernels that decode it (all but the one on 16x16x32 MFMAs,
+// which uses the plain map) the paired map's CUs.
+inline int mha_xcd_word(int total, bool causal, int D, int mfma_size, const DeviceInfo& di) {
+  return (di.nxcd > 0 ? di.nxcd : 8) + (mfma_size == 32 ? paired_cus(total, causal, D, di) : 0);
+}
+inline int mha_xcd_word(int total, bool causal, int D, int mfma_size) {
+  DeviceInfo di;
+  (void)device_info(di);
+  return mha_xcd_word(total, causal, D, mfma_size, di);
 }
 
 template <int D> struct PaCfg {

@@ -4,11 +4,12 @@
 // (noncontiguous_base != 0: A starts on an odd element; "hint1", "hint2" instead of "gemm": with that tiling hint)
 //   mha B H Sq Sk D causal   ->  name ranges
 //   paged B H D block_size max_blocks   ->  ranges dealt_by_length
+//   xcdword workgroups causal D mfma_size   ->  what an attention launch passes as its XCD count
 //   deal pieces CUs   ->  the rank of the piece that each workgroup takes
 #include <stdio.h>
 #include <string.h>
 
-#include "../../paper_2503_14985_amd/csrc/mlt_internal.h"
+#include "../../paper_2503_14985_amd/csrc/mha_tile.h"
 
 using namespace mlt;
 
@@ -47,6 +48,12 @@ int main() {
       a.B = B; a.H = H; a.D = D; a.block_size = block_size; a.max_blocks = max_blocks; a.num_blocks = B * max_blocks;
       const int n = plan_paged_split(a);
       printf("%d %d\n", n, paged_by_length(a, n, 256) ? 1 : 0);
+    } else if (!strcmp(op, "xcdword")) {
+      int total, causal, D, mfma;
+      if (scanf("%d %d %d %d", &total, &causal, &D, &mfma) != 4) return 1;
+      DeviceInfo di;
+      di.ncu = 256; di.nxcd = 8; di.gfx950 = true;
+      printf("%d\n", mha_xcd_word(total, causal != 0, D, mfma, di));
     } else if (!strcmp(op, "deal")) {
       int total, ncu;
       if (scanf("%d %d", &total, &ncu) != 2) return 1;

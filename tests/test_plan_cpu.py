@@ -138,3 +138,12 @@ def test_a_tiling_hint_on_unaligned_operands_is_the_automatic_choice(plan):
         auto, h1, h2 = plan([line, line.replace("gemm", "hint1"), line.replace("gemm", "hint2")])
         assert auto == h1 == h2, (M, N, K, tb)
     assert "_w8x1" in plan([gemm_line(520, 776, 320, 0).replace("gemm", "hint1")])[0]
+
+
+def test_only_kernels_that_decode_it_get_the_paired_maps_word(plan):
+    """The masked D = 64 launches of 1 to 2 workgroups per CU carry the CUs per XCD above the XCD count; the kernel on 16x16x32
+    MFMAs takes the word for the plain count."""
+    ask = lambda *c: int(plan(["xcdword %d %d %d %d" % c])[0])
+    assert [ask(t, 1, 64, 32) for t in (256, 257, 512, 513)] == [8, 8 + (32 << 8), 8 + (32 << 8), 8]
+    assert [ask(t, 1, 64, 16) for t in (256, 257, 512, 513)] == [8] * 4
+    assert ask(300, 0, 64, 32) == ask(300, 1, 128, 32) == 8
