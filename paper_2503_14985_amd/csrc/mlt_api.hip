@@ -273,7 +273,13 @@ int mlt_mha_fwd(int64_t B, int64_t H, int64_t Sq, int64_t Sk, int64_t D, const v
     TimedRegion t(s);
     rc = run_mha(a, p, s);
   }
-  if (rc == MLT_OK) g_last_kernel = p.name;
+  if (rc == MLT_OK && p.nsplit > 1) {                      // keys split over workgroups as well: the count in the name
+    snprintf(g_name_buf, sizeof(g_name_buf), "mha_fwd_d%d%s_keysplit%d_%dx32_k%d_pp", (int)D, causal ? "_causal" : "", p.nsplit,
+             p.bm, p.key_groups);
+    g_last_kernel = g_name_buf;
+  } else if (rc == MLT_OK) {
+    g_last_kernel = p.name;
+  }
   return rc;
 }
 

@@ -3,7 +3,7 @@
 //   gemm M N K transB lda ldb fp32_accumulate fused noncontiguous_base   ->  name parts scratch_bytes
 // (noncontiguous_base != 0: A starts on an odd element; "hint1", "hint2" instead of "gemm": with that tiling hint)
 //   mha B H Sq Sk D causal   ->  name ranges
-//   paged B H D block_size max_blocks   ->  ranges dealt_by_length
+//   paged B H D block_size max_blocks   ->  ranges dealt_by_length ("paged_split": and a forced number of ranges)
 //   xcdword workgroups causal D mfma_size   ->  what an attention launch passes as its XCD count
 //   deal pieces CUs   ->  the rank of the piece that each workgroup takes
 #include <stdio.h>
@@ -41,11 +41,12 @@ int main() {
       a.forced = MHA_AUTO;
       const MhaPlan p = plan_mha(a);
       printf("%s %d\n", p.name, p.nsplit);
-    } else if (!strcmp(op, "paged")) {
+    } else if (!strcmp(op, "paged") || !strcmp(op, "paged_split")) {
       long long B, H, D, block_size, max_blocks;
       if (scanf("%lld %lld %lld %lld %lld", &B, &H, &D, &block_size, &max_blocks) != 5) return 1;
       PagedArgs a{};
       a.B = B; a.H = H; a.D = D; a.block_size = block_size; a.max_blocks = max_blocks; a.num_blocks = B * max_blocks;
+      if (op[5] == '_') scanf("%d", &a.forced_split);
       const int n = plan_paged_split(a);
       printf("%d %d\n", n, paged_by_length(a, n, 256) ? 1 : 0);
     } else if (!strcmp(op, "xcdword")) {

@@ -59,13 +59,15 @@ def test_ranges_of_keys(variant, causal, ranges):
     binding.mlt_diag_force_variant(mha=variant)
     binding.mlt_diag_force_key_split(ranges)
     for D, dtype, (Sq, Sk) in ((64, FP16, (33, 300)), (128, BF16, (70, 65)), (128, FP16, (150, 517))):
-        _go(1, 2, Sq, Sk, D, dtype, causal, Sq, rounding_aware=True)
+        assert "_keysplit%d_" % ranges in _go(1, 2, Sq, Sk, D, dtype, causal, Sq, rounding_aware=True)
 
 
 def test_automatic_choice():
     for shape, tag in (((1, 8, 200, 1000, 64, BF16, False), "64x32_k4_pp"), ((4, 16, 300, 2000, 128, BF16, False), "128x32_k2_pp"),
                        ((8, 32, 256, 256, 128, BF16, False), "256x64_pp"), ((1, 8, 5, 4096, 128, FP16, False), "64x32_k4_pp")):
-        assert _go(*shape, seed=7).endswith(tag)
+        name = _go(*shape, seed=7)
+        assert name.endswith(tag)
+        assert ("_keysplit" in name) == (shape[2] == 5), name       # few queries, few heads, many keys
 
 
 @pytest.mark.parametrize("variant,split", [("k2", 0), ("k4", 0), ("k4", 3)])
@@ -95,19 +97,24 @@ def test_agrees_with_the_debug_build(dbg, variant, split):  # noqa: F811
 
 
 def test_captured_call_needs_no_scratch():
-    """A call whose keys are spread over workgroups, captured: it runs without that (no memory of the
-    library's own), and every replay equals the oracle within its bound."""
+    """A call whose keys are spread over workgroups, captured on the stream that has the library's scratch from
+    an eager call: it runs without that, and every replay equals the oracle within its bound."""
     from paper_2503_14985_amd import binding
     Q, K, V = inputs.mha_inputs(1, 8, 9, 4096, 128, BF16, 3)
     dev = torch.device("cuda:0")
     q, k, v = (inputs.bits_to_torch(x, BF16, dev) for x in (Q, K, V))
     scale = 1.0 / math.sqrt(128)
-    binding.mlt_mha_fwd(q, k, v, scale)
     static = torch.empty_like(q)
+    side = torch.cuda.Stream(device=dev)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        binding.mlt_mha_fwd(q, k, v, scale)
+        assert "_keysplit" in binding.mlt_last_kernel()
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
+    with torch.cuda.graph(graph, stream=side):
         binding.mlt_mha_fwd(q, k, v, scale, O=static)
+        assert "_keysplit" not in binding.mlt_last_kernel()
     for _ in range(3):
         static.fill_(0)
         graph.replay()

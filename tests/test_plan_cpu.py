@@ -147,3 +147,10 @@ def test_only_kernels_that_decode_it_get_the_paired_maps_word(plan):
     assert [ask(t, 1, 64, 32) for t in (256, 257, 512, 513)] == [8, 8 + (32 << 8), 8 + (32 << 8), 8]
     assert [ask(t, 1, 64, 16) for t in (256, 257, 512, 513)] == [8] * 4
     assert ask(300, 0, 64, 32) == ask(300, 1, 128, 32) == 8
+
+
+def test_the_batches_of_the_order_test_are_dealt_by_length(plan):
+    from test_paged_order_gpu import CASES, longest
+    lines = ["paged_split %d %d %d 16 %d %d" % (B, H, D, -(-longest(B, H, ranges, D) // 16), ranges) for B, H, ranges, D, _ in CASES]
+    for (B, H, ranges, D, _), ans in zip(CASES, plan(lines)):
+        assert ans == "%d %d" % (ranges, B <= 256), (B, H, ranges, D)
