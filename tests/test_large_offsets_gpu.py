@@ -40,11 +40,12 @@ def _gemm_samples(M, N, rng):
     return r, c
 
 
-@pytest.mark.parametrize("variant", ["auto", "128pp16k128", "64k4"])
+@pytest.mark.parametrize("variant,N,K", [("auto", 53248, 128), ("128pp16k128", 53248, 128), ("64k4", 53248, 128), ("256x128kp", 53248, 128),
+                                         ("128kp", 53248, 128), ("128w8", 53249, 131), ("64x128k2", 53249, 131)])
 @pytest.mark.parametrize("transB", [False, True])
-def test_gemm_output_beyond_2_31_elements(variant, transB):
+def test_gemm_output_beyond_2_31_elements(variant, N, K, transB):
     from paper_2503_14985_amd import binding
-    M, N, K = 40960, 53248, 128                      # M * N = 2.18e9 elements, C is 4.4 GB
+    M = 40960                                        # M * N = 2.18e9 elements, C is 4.4 GB; odd sizes: any alignment
     assert M * N > 1 << 31
     A, B = inputs.gemm_inputs(M, N, K, BF16, 5, transB=transB)
     dev = torch.device("cuda:0")
@@ -72,6 +73,15 @@ def test_gemm_operand_rows_beyond_4_gib(transB):
     C = pu.run_gemm(A, B, BF16, transB=transB, lda=65536)
     st = pu.check_gemm(A, B, C, BF16, transB, seed=6)
     print("   %s" % st, flush=True)
+    # the same rows in the forms for any alignment (odd K and row stride) and with two K groups
+    from paper_2503_14985_amd import binding
+    A, B = inputs.gemm_inputs(M, 513, 255, BF16, 7, transB=transB)
+    pu.check_gemm(A, B, pu.run_gemm(A, B, BF16, transB=transB, lda=65537), BF16, transB, seed=7)
+    assert binding.mlt_last_kernel().startswith("gemm_general_n")
+    binding.mlt_diag_force_variant(gemm="256x128kp")
+    A, B = inputs.gemm_inputs(M, 512, 256, BF16, 8, transB=transB)
+    pu.check_gemm(A, B, pu.run_gemm(A, B, BF16, transB=transB, lda=65536), BF16, transB, seed=8)
+    assert "kp2" in binding.mlt_last_kernel()
 
 
 def _device_normal(shape, dev, seed, dtype):
