@@ -30,13 +30,12 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
   // with the mask the last query row sees min(Sq, Sk) keys (17 x 8 heads, 65 x 1994 causal, D = 128, priced with all
   // 1994: 64 rows, 11.8 us; 256 rows take 8.0)
   const int64_t keys = a.causal && a.Sq < a.Sk ? a.Sq : a.Sk, tiles = (keys + 31) / 32;
-  // one key tile of the 256-row kernel and no second round: nothing to divide (64 workgroups fit any of these chips)
+  // one key tile of the 256-row kernel and few workgroups: nothing to divide
   if (tiles <= 2 && heads * ((a.Sq + 255) / 256) <= 64) return;
   DeviceInfo di;
   const int64_t ncu = device_info(di) && di.ncu > 0 ? di.ncu : 256, nxcd = di.nxcd > 0 ? di.nxcd : 8;
   const bool one_round_of_256 = heads * ((a.Sq + 255) / 256) <= ncu;
   if (heads * ((a.Sq + 255) / 256) > 4 * ncu) return;             // enough of the large tiles
-  if (tiles <= 2 && one_round_of_256) return;
   const double arrive = (double)heads * (a.Sq + keys) * a.D * 4 / 5500;   // every tensor once at 5.5 TB/s
   auto cost = [&](int groups, int nsplit) -> int64_t {
     const int64_t bm = 256 / groups, nq = (a.Sq + bm - 1) / bm, wgs = heads * nq * nsplit;
@@ -46,17 +45,26 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
     // with a short one (block_map_paired)
     const int64_t avg = a.causal && a.Sk >= a.Sq ? longest * (nq + 1) / (2 * nq) : longest;
     const int64_t rounds = (wgs + ncu - 1) / ncu;
+    // start and end of a workgroup in a launch of several rounds: 256 rows of which more than half are not there cost as much
+    // as if they were (928 heads, us, 256 / 128 rows: D = 128, 9 x 41 25 / 20, 68 x 68 causal 37 / 30, but 1024 heads, 128 x 128 44 / 47;
+    // D = 64, 9 x 41 causal 13.0 / 8.5)
+    const int64_t ends = groups > 1 && a.Sq <= 96 ? 5000 : 7000;
     int64_t t;
     if (rounds <= 1) t = longest + 7000;
-    else if (a.D == 128) t = a.causal ? wgs * (avg * 5 / 4) / ncu + rounds * 7000 : rounds * (longest + 7000);
-    else if (a.causal) t = wgs * (rounds > 2 ? avg * 5 / 4 : avg) / ncu + (rounds + 1) / 2 * 6000 + 4000;
+    else if (a.D == 128) t = a.causal ? wgs * (avg * 5 / 4) / ncu + rounds * ends : rounds * (longest + ends);
+    else if (a.causal) t = wgs * (rounds > 2 ? avg * 5 / 4 : avg) / ncu + (rounds + 1) / 2 * (ends - 1000) + 4000;
     else t = rounds * (avg + 3000) + 4000;
     if (t < longest + 7000) t = longest + 7000;
-    // Masked items in a second, partly filled round, where the 256-row kernel needs one round: a long item may start
-    // behind another one (D = 64: shares its CU with it), unless every XCD has whole heads (D = 64: the round is
-    // full and block_map_paired evens it out). 128 / 256 rows, us: D = 128, 12 x 3403 82 / 72, 22 x 1574 42 / 38 (but 24 x
-    // 1536 30 / 37); D = 64, 29 x 1809 38 / 35.
-    if (a.causal && groups > 1 && rounds == 2 && one_round_of_256 && (a.D == 128 ? heads % nxcd != 0 : wgs < 2 * ncu)) t += longest / 2;
+    // Masked items in a second, partly filled round of 128-row tiles, where the 256-row kernel needs one round: a long item
+    // may start behind another one (D = 64: shares its CU with it). An XCD's range ends with the last tiles of its
+    // last head when it has whole heads; then the `extra` items behind the first round are the shorter ones of that head.
+    // 128 / 256 rows, us: D = 128, 12 heads x 3403 82 / 72, 22 x 1574 42 / 38, but 24 x 1536 30 / 37; D = 64, 29 x 1809 38 / 35, 40 x 998
+    // 26 / 23, but 16 x 2202 33 / 41. (A full second round of D = 64 is evened out by block_map_paired.)
+    if (a.causal && groups == 2 && rounds == 2 && one_round_of_256 && (a.D == 128 || wgs < 2 * ncu)) {
+      const int64_t extra = (wgs - ncu + nxcd - 1) / nxcd;
+      if (heads % nxcd != 0 || (a.D == 128 && 4 * extra >= 3 * nq)) t += longest / 2;
+      else if (a.D == 64) t += longest * (extra < nq ? extra : nq) * 7 / (10 * nq);
+    }
     t = (int64_t)std::sqrt((double)t * t + arrive * arrive);       // the two overlap in part
     // the partial results' second kernel: a launch, and writing and reading them at 4 TB/s
     if (nsplit > 1) t += 3500 + 2 * nsplit * heads * a.Sq * (a.D + 2) / 1000;

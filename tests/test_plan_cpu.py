@@ -86,8 +86,11 @@ def test_causal_attention_is_priced_by_the_keys_it_sees(plan, D):
 
 def test_masked_attention_avoids_a_partly_filled_second_round(plan):
     """128-row tiles that just overflow the chip, with heads that do not divide over the XCDs, start long items late."""
-    ans = plan(["mha 1 %d %d %d %d 1" % c for c in ((12, 3403, 3403, 128), (22, 1574, 1574, 128), (29, 1809, 3928, 64), (24, 1536, 1536, 128))])
-    assert ["128x32_k2" in a for a in ans] == [False, False, False, True], ans
+    ans = plan(["mha 1 %d %d %d %d 1" % c for c in ((12, 3403, 3403, 128), (22, 1574, 1574, 128), (29, 1809, 3928, 64), (40, 998, 998, 64),
+                                                           (24, 1536, 1536, 128), (16, 2202, 2202, 64))])
+    assert ["128x32_k2" in a for a in ans] == [False, False, False, False, True, True], ans
+    # few rows of many heads, several rounds: 128-row tiles, whose workgroups start and end sooner
+    assert ["128x32_k2" in a for a in plan(["mha 232 4 9 41 %d 1" % d for d in (64, 128)])] == [True, True]
 
 
 def test_paged_decode_searches_ranks_only_where_the_lengths_are_few_for_the_keys(plan):
