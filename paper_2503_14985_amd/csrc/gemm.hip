@@ -239,7 +239,7 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   // The kernels with two groups on alternate K steps (gemm_kp.hip). On a full chip their step is bound by what
   // the L2s deliver (about 17 TB/s), with fewer workgroups by its own latency (us per 64 of K, 80 / 160 / 256
   // workgroups, call included, B repeated: 256 x 128 0.56 / 0.64 / 0.73, 128 x 128 0.36 / 0.40 / 0.50; with B from
-  // memory 80 workgroups take as long per step as 256 do). Below on the scale of the other candidates, whose
+  // memory 80 workgroups take as long per step as 256 do, less so where K is split over more of them). Below on the scale of the other candidates, whose
   // times come out 1.1 to 1.25 of their estimates: over 280 problems of 6 to 300 tiles with B from memory the choice
   // is nowhere more than 8 % behind the best of the other tiles and 3 % ahead on average; rates that fall with the share
   // of busy CUs took these kernels for 40 to 110 tiles where they are up to 1.45 times slower (352 x 3176 x 5632 fp32
@@ -252,7 +252,7 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     const int64_t wgs = ((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * parts;
     const int64_t rounds = (wgs + NCU - 1) / NCU, steps = (KT + parts - 1) / parts;
     const int64_t share = wgs < NCU ? wgs * 1000 / NCU : 1000;
-    int64_t t_step = bm == 256 ? 615 : 345 + 50 * share / 1000;
+    int64_t t_step = parts > 1 ? (bm == 256 ? 425 + 195 * share / 1000 : 206 + 190 * share / 1000) : bm == 256 ? 615 : 345 + 50 * share / 1000;
     if (g.K % 64) t_step += t_step * 15 / 100;
     const int64_t compute = rounds * (steps * t_step + (bm == 256 ? 6000 : 5700));
     const int64_t base = (g.M + g.N) * g.K * 2 / 5200, need = 6 * NCU / 10;
@@ -265,9 +265,9 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     if (parts > 1 && KT < 8 * parts) break;
     if (parts > 1 && g.forced_parts == 0 && parts * g.M * g.N * 4 > kStaticScratchBytes) break;
     if (pp && KT >= 8 * parts) {
-      // (256 x 128 in up to 4 parts: 25 problems that took 8 were 6 % slower than on the other tiles with B repeated
-      // and 3 % faster with B from memory, 852 x 920 x 14784 43 -> 50 us)
-      if (g.M > 128 && parts < 8 && fits(64, 128)) all[n_all++] = Choice{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
+      // (256 x 128 in 8 parts for one row of tiles only: 138 x 3840 x 14928 40 us, 51 in 4 parts of 128 x 128; but 852 x 920 x
+      // 14784 50 in 8, 43 on the other tiles, 2375 x 272 x 16256 67, 60)
+      if (g.M > 128 && (parts < 8 || g.M <= 256) && fits(64, 128)) all[n_all++] = Choice{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
       if (fits(128, 128)) all[n_all++] = Choice{GEMM_128_KP, parts, 128 * 128, cost_kp(128, parts)};
     }
     for (const auto& c : KT / parts < 8 ? whole : p.aligned ? split : any) {
