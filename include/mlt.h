@@ -70,11 +70,12 @@ int mlt_gemm(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const 
 /*
  * mlt_gemm for callers that cannot allocate device memory: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc. Same arguments, same kernels and the same
- * result, bit for bit, as mlt_gemm. Where mlt_gemm splits K across workgroups (few tiles against
+ * result, bit for bit, as mlt_gemm on a stream that is not recording (there mlt_gemm leaves the
+ * split out, see above). Where mlt_gemm splits K across workgroups (few tiles against
  * a long K) and keeps the fp32 partial products in a scratch buffer it allocates, this entry point
  * keeps them in a fixed array of 32 MiB in device memory that is part of the library (one copy
  * per GPU the library runs on, held until the process ends). It calls no hipMalloc, hipFree or
- * other allocating routine. The library's own choice of a split never needs more than 16 MiB;
+ * other allocating routine. The library's own choice of a split never needs more than that;
  * a split forced through mlt_diag_force_k_parts that needs more than 32 MiB (parts * M * N * 4
  * bytes) is refused with MLT_ERR_SCRATCH and nothing is enqueued. All calls on one GPU share that
  * GPU's array: two calls of this entry point that may run at the same time on one GPU (different

@@ -87,8 +87,8 @@ int mlt_query_tiling(int op, const int64_t dims[4], int dtype, int32_t out[10]);
 int mlt_diag_force_variant(const char* gemm_variant, const char* mha_variant);
 
 /*
- * Number of parts the GEMM entry points split K into across workgroups (the small-tile kernels;
- * partial products through an fp32 scratch, added in a fixed order by a second kernel): 0 = the
+ * Number of parts the GEMM entry points split K into across workgroups (the small-tile kernels and
+ * those with two K groups; partial products through an fp32 scratch, added in a fixed order by a second kernel): 0 = the
  * cost model's choice (the default), 1 = never split, 2 / 4 / 8 = that many parts wherever every
  * part keeps at least 8 K steps of 64. Process-wide, like mlt_diag_force_variant. Returns MLT_OK
  * or MLT_ERR_INVALID_ARG.
@@ -97,9 +97,10 @@ int mlt_diag_force_k_parts(int parts);
 
 /*
  * Number of key ranges per (sequence, head) that mlt_paged_attn_decode spreads over workgroups:
- * 0 = the library's choice (the default: 1 while sequences x heads alone fill the chip, more
- * otherwise), 1..64 = that many (ranges beyond the end of a short sequence stay empty). The same
- * for mlt_mha_fwd where its "k2" or "k4" variant is forced.
+ * 0 = the library's choice (the default: by the CUs that sequences x heads leave idle and the
+ * table's width; a batch, whose sequences differ in length, also with up to three pairs per CU),
+ * 1..64 = that many (ranges beyond the end of a short sequence stay empty). The same for
+ * mlt_mha_fwd where its "k2" or "k4" variant is forced; elsewhere it takes its own choice.
  * Process-wide. Returns MLT_OK or MLT_ERR_INVALID_ARG.
  */
 int mlt_diag_force_key_split(int ranges);

@@ -117,7 +117,7 @@ def mlt_diag_force_k_parts(parts: int) -> None:
 
 
 def mlt_diag_force_key_split(ranges: int) -> None:
-    """Paged decode: 0 = the library's choice; 1..64 = key ranges per (sequence, head)."""
+    """Paged decode, and attention with "k2" or "k4" forced: 0 = the library's choice; 1..64 = key ranges."""
     rc = _lib.mlt_diag_force_key_split(int(ranges))
     if rc != MLT_OK:
         raise MltError(rc, "mlt_diag_force_key_split")

@@ -18,8 +18,9 @@
 namespace mlt {
 
 // ------------------------------------------------------------------------------------------
-// General kernel: any M, N, K, leading dimensions and alignment. 64 x 64 x 32 tile, 4 wavefronts
-// of 32 x 32, element-wise guarded loads with zero fill, B always staged as [n][k].
+// General kernel: what no 16-byte access fits (K < 8, N < 8 with row-major B), K = 0 with a fused
+// epilogue, and any problem by override. 64 x 64 x 32 tile, 4 wavefronts of 32 x 32, element-wise
+// guarded loads with zero fill, B always staged as [n][k].
 // ------------------------------------------------------------------------------------------
 template <typename Tag>
 __global__ __launch_bounds__(256) void gemm_general_kernel(

@@ -1,4 +1,4 @@
-// Pieces shared by the attention-forward kernels for gfx950 (mha_pp.hip, mha_fr.hip): tile sizes,
+// Pieces shared by the attention-forward kernels for gfx950 (mha_pp.hip, mha_ks.hip): tile sizes,
 // the direct global->LDS load, lane-pair exchanges, the workgroup->item map and the LDS layout of
 // a K/V tile (paper: arXiv 2503.14985, Section 2.5, Algorithm 1 and Table 5).
 #pragma once
