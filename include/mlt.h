@@ -103,7 +103,7 @@ int mlt_gemm_acc(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, co
  *          2  vertical: evenly along the columns only, 8 wavefronts x (256 x 32)
  *          3  square: 2 x 2 wavefronts x (128 x 128)
  * The hint applies to operands that allow 16-byte vector access (see mlt_gemm); others are
- * treated as with tiling 0, K = 0 stores zeros, and the skinny kernels (M <= 32 with B stored N x K)
+ * treated as with tiling 0, K = 0 stores zeros, and the skinny kernel (M <= 64 with B stored N x K)
  * and the smaller workgroup tiles of small aligned problems are chosen only for tiling 0. Returns as
  * mlt_gemm; MLT_ERR_INVALID_ARG also for an unknown `tiling`.
  */

@@ -130,6 +130,38 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     p.bm = 64; p.bn = 64; p.bk = 32; p.wm = 2; p.wn = 2;
     return p;
   }
+  DeviceInfo di;
+  const int64_t NCU = device_info(di) && di.ncu > 0 ? di.ncu : 256;
+  const int64_t KT = (g.K + 63) / 64;
+  // ---- short A against B stored N x K: the streaming kernel of gemm_skinny.hip (all figures with B coming from memory, as a
+  // decoder's weights do: every matrix is read once per token, and a model is far larger than the 256 MiB last-level cache).
+  // Over 135 problems of 1 to 64 rows it is 1.14 times as fast as the best of the tile kernels and its own predecessors (us:
+  // 16 x 4096 x 4096 11.6 -> 9.5, 24 x 14336 x 4096 with bias and GELU 25.9 -> 23.7, 16 x 1024 x 8192 13.2 -> 7.9, 47 x 8640 x 5376
+  // 35.5 -> 23.0). It stays behind the tile kernels where a CU's rows of A are long beside its few columns and not so
+  // long that splitting K pays for itself (64 x 4096 x 4096 12.8 on tiles, 13.9 here; 61 x 2976 x 16192 26.4, 29.5; but 64 x 1024 x 28672 24.8, 19.9),
+  // and for tall A against a few steps of K (64 x 5512 x 72 4.4, 5.8).
+  const bool tiles_win = (g.M > 48 && g.N <= 16 * NCU && KT >= 64 && KT < 256) || (g.M > 32 && KT < 8);
+  if ((g.forced == GEMM_SKINNY || g.forced == GEMM_SKINNY_DMA || (g.forced == GEMM_AUTO && !tiles_win)) && gemm_skinny_ok(g)) {
+    // K over 1, 2, 4 or 8 workgroups: B's arrival + what a CU fetches of A (at 100 GB/s) + the price of the partial
+    // results (a fit to the times of 175 problems: the choice is 1.2 % behind the best one on average, 26 % at worst)
+    auto time = [&](int64_t parts) {
+      const int64_t rows = g.M <= 4 ? 4 : (g.M + 15) / 16 * 16;
+      return g.N * g.K * 2 / 6600 + rows * g.K * 2 / (100 * parts) + (parts > 1 ? 800 + 7 * parts * g.M * g.N / 1000 : 0);
+    };
+    p.parts = g.forced_parts > 0 ? g.forced_parts : 1;
+    if (g.forced == GEMM_AUTO && g.forced_parts == 0)
+      for (int n = 2; n <= 8; n *= 2)
+        if (n * g.M * g.N * 4 <= kStaticScratchBytes && time(n) < time(p.parts)) p.parts = n;
+    p.scratch_bytes = p.parts > 1 ? (int64_t)p.parts * g.M * g.N * 4 : 0;
+    // (the first name for a single column block per workgroup and whole rounds of 128-k pieces over its wavefronts)
+    const bool one_block = !g.fused() && g.M <= 32 && g.N > 14 * NCU && g.N <= 16 * NCU && g.K % 2048 == 0 && g.N * g.K < ((int64_t)1 << 25);
+    p.variant = g.forced == GEMM_SKINNY || (g.forced == GEMM_AUTO && one_block) ? GEMM_SKINNY : GEMM_SKINNY_DMA;
+    p.name = p.variant == GEMM_SKINNY ? "gemm_nt_skinny_16cols_ksplit8" : "gemm_nt_decode_k8_16cols_stream";
+    p.bm = (int)((g.M + 15) / 16) * 16; p.bn = 16; p.bk = 128;
+    p.wm = 1; p.wn = 1;
+    p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
+    return p;
+  }
   // ---- the tile kernels: workgroup tile and K split
   // The candidate that needs the least time over the whole grid: (rounds of one workgroup per CU)
   // x (K steps of 64) x (its measured time per K step: two-group 256x256 kernel 1.17 us, older
@@ -146,9 +178,6 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   // an fp32 partial tile to a scratch and a second kernel adds the parts in a fixed order
   // (deterministic; no atomics). Its price in the same units: a launch (4 us) plus writing and
   // reading parts * M * N floats at about 4 TB/s.
-  DeviceInfo di;
-  const int64_t NCU = device_info(di) && di.ncu > 0 ? di.ncu : 256;
-  const int64_t KT = (g.K + 63) / 64;
   auto cost = [&](int64_t bm, int64_t bn, int64_t t_step, int64_t fixed, int parts, int kgroups) {
     const int64_t wgs = ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * parts;
     const int64_t rounds = (wgs + NCU - 1) / NCU;
@@ -295,50 +324,7 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   }
   int v = pick.variant;
   const int best_parts = pick.parts;
-  // ---- the skinny kernels (B stored N x K, no LDS staging of A): always for one 16-row tile of A, and for two, or with a
-  // fused epilogue, where the streaming kernel beats the tile kernels' estimate. It reads B through an LDS ring (16
-  // columns x 512 k per stage, the A fragments of a k stage shared by a group of column blocks) at 5.7 TB/s for M <= 16 and
-  // 4.7-5.9 TB/s for two row tiles and 16384 columns or more. The times that decide are those with B coming from memory, as
-  // the weights of a decoder do (every matrix is read once per token, and a model is far larger than the 256 MiB last-level
-  // cache): the streaming kernel's non-temporal loads make it indifferent to what that cache holds, while the
-  // tile kernels run up to 40 % faster when the same B of less than 256 MB is multiplied again
-  // and again (32 x 16384 x 8192: tile kernels 41 us on a repeated B and 59 us on rotating ones,
-  // the streaming kernel 55 and 56 us; 32 x 65536 x 2048: 43 / 65 against 53 / 54 us). Taller A
-  // goes to the tile kernels, which stage A through LDS once per tile (64 x 28672 x 8192: 99 us
-  // against 160 us streaming; 64 x 14336 x 4096: 20 us against 43 us).
-  // What the streaming kernel has against it is that a workgroup walks through all of K, stage by stage, with the A
-  // rows of a stage from L2, while the tile kernels split K: the line through both kernels' times on 417 problems (M = 1,
-  // 8, 16, 17, 24, 32, N = 1024 to 28672, K = 512 to 28672, B from memory) is the number of stages times a step that grows with
-  // M against the estimate plus 7 us. Its choice is 1 % behind the better kernel on average, at worst 20 %
-  // (us, streaming / tile: 16 x 1024 x 28672 41 / 22, 32 x 2048 x 8192 22 / 15, 24 x 14336 x 4096 25 / 27, 17 x 6456 x 5544 20 / 25).
-  const int64_t stages = (g.K + 511) / 512;
-  const bool stream_wins = (g.M <= 16 && !g.fused()) || stages * (750 + 50 * g.M) < best + 7000;
-  const bool skinny_auto = g.forced == GEMM_AUTO && g.M <= 32 && stream_wins &&
-                           (!g.fused() || g.N * g.K >= ((int64_t)1 << 21));
-  // Of the two, the kernel that splits K over the wavefronts is taken for the one column block per CU that leaves nothing
-  // to the other one's persistent workgroups, when its batches of 2048 k are whole ones (us, K split over
-  // wavefronts / streaming, B from memory: 1 x 4096 x 4096 8.9 / 9.5, 1 x 3584 x 4096 8.4 / 8.6, 1 x 3072 x 4096 8.2 / 8.1; 1 x 4096 x
-  // 2880 8.6 / 7.0; 24 x 4096 x 2880 13.6 / 9.8; 16 x 2048 x 2048 6.6 / 5.6; 16 x 1024 x 8192 18.4 / 13.6; 1 x 5120 x 5120 18 / 13).
-  // That gains with up to 4 rows; with 16 it is behind by a tenth (16 x 4096 x 4096 11.9 / 10.9), and kept: the routing tests
-  // fix these sizes.
-  const bool ksplit = !g.fused() && g.N > 14 * NCU && g.N <= 16 * NCU && g.K % 2048 == 0 && g.N * g.K < ((int64_t)1 << 25);
-  if ((g.forced == GEMM_SKINNY_DMA || (skinny_auto && !ksplit)) && gemm_skinny_dma_ok(g)) {
-    p.variant = GEMM_SKINNY_DMA;
-    p.name = "gemm_nt_skinny_16cols_stream";
-    p.bm = (int)((g.M + 15) / 16) * 16; p.bn = 16; p.bk = 512;
-    p.wm = 1; p.wn = 1;
-    p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
-    return p;
-  }
-  if ((skinny_auto || g.forced == GEMM_SKINNY || g.forced == GEMM_SKINNY_DMA) && gemm_skinny_ok(g)) {
-    p.variant = GEMM_SKINNY; p.name = "gemm_nt_skinny_16cols_ksplit8";
-    p.bm = (int)((g.M + 15) / 16) * 16; p.bn = 16; p.bk = 32; p.wm = 1; p.wn = 1;
-    p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
-    return p;
-  }
-  if (g.forced >= GEMM_256 && g.forced < GEMM_NUM_VARIANTS && g.forced != GEMM_SKINNY &&
-      g.forced != GEMM_SKINNY_DMA)
-    v = g.forced;
+  if (g.forced >= GEMM_256 && g.forced < GEMM_NUM_VARIANTS && g.forced != GEMM_SKINNY && g.forced != GEMM_SKINNY_DMA) v = g.forced;
   if (v == GEMM_256_PP16 && !gemm_pp_ok(g)) v = GEMM_256_W8;
   if ((v == GEMM_256X128_KP || v == GEMM_128_KP) && !pp) v = v == GEMM_128_KP ? GEMM_128_W8 : GEMM_256_W8;
   if (v == GEMM_256_W4 && !gemm_w4_ok(g)) v = GEMM_256_W8;
@@ -422,8 +408,8 @@ static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     case GEMM_256X128_KP: return run_gemm_kp(g, 256, s);
     case GEMM_128_KP: return run_gemm_kp(g, 128, s);
     case GEMM_256_W4: return run_gemm_w4(g, s);
-    case GEMM_SKINNY: return run_gemm_skinny(g, s);
-    case GEMM_SKINNY_DMA: return run_gemm_skinny_dma(g, s);
+    case GEMM_SKINNY:
+    case GEMM_SKINNY_DMA: return run_gemm_skinny(g, s);
   }
   const int rc = launch_small_tile<Tag, true>(g, p.variant, s);
   return rc == -1 ? MLT_ERR_UNSUPPORTED : rc;
@@ -453,6 +439,8 @@ bool stream_is_capturing(hipStream_t s) {
   return st != hipStreamCaptureStatusNone;
 }
 
+__global__ void zero_counters_kernel(uint32_t* counters) { counters[blockIdx.x * blockDim.x + threadIdx.x] = 0; }
+
 float* cached_scratch(int64_t bytes, hipStream_t s) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
@@ -470,9 +458,11 @@ float* cached_scratch(int64_t bytes, hipStream_t s) {
   int64_t want = slot->bytes > 0 ? 2 * slot->bytes : (int64_t)4 << 20;
   while (want < bytes) want *= 2;
   void* p = nullptr;
-  if (hipMalloc(&p, (size_t)want) != hipSuccess || !p) { (void)hipGetLastError(); return nullptr; }
+  if (hipMalloc(&p, (size_t)want + kScratchCounters * 4) != hipSuccess || !p) { (void)hipGetLastError(); return nullptr; }
+  hipLaunchKernelGGL(zero_counters_kernel, dim3(kScratchCounters / 256), dim3(256), 0, s, static_cast<uint32_t*>(p));
+  if (hipGetLastError() != hipSuccess) { (void)hipFree(p); return nullptr; }
   if (slot == &g_scratch[g_scratch_used]) ++g_scratch_used;
-  slot->ptr = static_cast<float*>(p);
+  slot->ptr = reinterpret_cast<float*>(static_cast<uint32_t*>(p) + kScratchCounters);
   slot->bytes = want;
   return slot->ptr;
 }
@@ -508,7 +498,9 @@ int run_gemm(const GemmArgs& g_in, GemmPlan& p, hipStream_t s) {
   bool own = false;
   if (p.parts > 1 && !g.scratch) {
     g.scratch = cached_scratch(p.scratch_bytes, s);
-    if (!g.scratch) {
+    if (g.scratch) {
+      g.counters = scratch_counters(g.scratch);
+    } else {
       void* ws = nullptr;
       if (!stream_is_capturing(s) && hipMallocAsync(&ws, (size_t)p.scratch_bytes, s) == hipSuccess && ws) {
         g.scratch = static_cast<float*>(ws);

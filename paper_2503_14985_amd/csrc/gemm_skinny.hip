@@ -1,18 +1,32 @@
 // Skinny GEMM C = A*B for gfx950: M <= 64 rows (next-token decode shapes, Section 4.1 of the paper
 // (arXiv 2503.14985): memory-bound GEMMs with a small m), B given as the N x K row-major array
-// (k contiguous). The whole cost is reading B once from HBM, so the kernel is built around that
-// stream and nothing is staged in LDS:
-//   * a workgroup owns 16, 32 or 64 columns of C (rows of the stored B; more when N is large, so
-//     that an A fragment fetched from L2 serves more columns) and all of K; its 8 wavefronts
-//     take the 32-wide K chunks round-robin, so at any moment the workgroup reads 512 contiguous
-//     bytes of each of its 16 B rows;
-//   * a lane loads 16 bytes (8 consecutive k) of one B row straight into the register that the
-//     16x16x32 MFMA wants as its B operand (lane l: column l % 16, k slots 8*(l/16)..+7), and the
-//     matching 16 bytes of one A row as the A operand; A (M x K, at most 64 rows) stays in L2;
-//   * two batches of chunks are in registers, one in flight while the other is multiplied;
-//   * the 8 partial 16 x 16 fp32 tiles are added through LDS and rounded to 16 bit once.
-// Requirements (host): transB, M <= 64, K % 8 == 0, lda % 8 == 0, ldb % 8 == 0, A and B 16-byte
-// aligned. N and K need not be multiples of the tile.
+// (k contiguous). The whole cost is reading B once from HBM, and the kernel is built around that stream:
+//   * one workgroup of 8 wavefronts per CU, each with its even share of the columns of C (rows of the stored B),
+//     contiguous, whatever their number, in blocks of up to 16. The wavefronts split K: wavefront w takes the
+//     pieces of 128 k numbered w, w + 8, ..., so that at any time the workgroup reads 2 KB of each of its rows;
+//   * every wavefront has an LDS ring of its own (20 KB) and is alone with it: it fetches its pieces of A and of
+//     its columns of B straight into the ring (global_load_lds_dwordx4, 4 rows x 256 contiguous bytes per
+//     instruction), several slots ahead, waits for the oldest by count, reads its MFMA fragments (16x16x32) and
+//     refills it. No barrier until the end, no wavefront that only fetches, and A, which comes from L2, arrives in the
+//     same stream as B, as far ahead (a CU's loads come back in order, so a load of A waits for the
+//     loads of B in front of it wherever it goes);
+//   * the rows of a piece are stored permuted (16-byte chunk c of row r at position c ^ r): the source
+//     address of a lane is free, its LDS position is not, and the 16 lanes that read 16 rows at one k
+//     position must hit 16 distinct bank groups;
+//   * with more than 16 columns a piece of A is fetched once for a group of up to 8 column blocks (4 from three row
+//     tiles on), whose accumulators stay in registers;
+//   * at the end the 8 partial tiles of a column block meet in LDS and are added in wavefront order.
+//
+// K may also be split over 2, 4 or 8 workgroups (PARTS): a workgroup then has that many times the columns and that part
+// of K, so every CU fetches that much less of A, which all of them fetch in full otherwise (64 rows x 4096: 512 KB a CU
+// beside 128 KB of B). The parts leave fp32 partial results in a scratch, and the one that comes last at a
+// counter adds them in the order of the parts: no second launch, no atomics on values, the same bits on every run.
+//
+// What bounds it: what a CU's memory path takes (about 64 bytes per clock, A and B together: 1 x 4096 x 4096 8.3 us,
+// 16 rows 9.2, 32 10.7, 64 13.7, where a kernel that only reads B takes 6.4 and an empty one 2.0), and for large B the
+// memory (16 x 28672 x 8192 74 us = 6.4 TB/s). The kernels before it, one with direct loads of 64 bytes per row into the
+// operand registers, one with four fetching and four computing wavefronts and a barrier per 16 KB: 16 x 4096 x 4096
+// 11.5 and 10.7 us, 16 x 28672 x 8192 123 and 83, 32 x 5120 x 5120 37 and 21.
 #include "mlt_common.h"
 #include "mlt_internal.h"
 
@@ -20,445 +34,284 @@ namespace mlt {
 
 namespace {
 
-constexpr int SK_NW = 8;            // wavefronts per workgroup = K split
+constexpr int SK_NW = 8;              // wavefronts per workgroup = K split
 constexpr int SK_NT = SK_NW * 64;
-constexpr int SK_MAXMT = 4;         // 16-row tiles of A (M <= 64)
+constexpr int SK_KP = 128;            // k values per piece
+constexpr int SK_RING = 20 * 1024;    // LDS ring of a wavefront
+constexpr int SK_SMEM = SK_NW * SK_RING;
 
-// U: k chunks per batch; two batches are in registers, one on its way while the other is multiplied.
-template <typename Tag, int MT, int NT, int U>
-__global__ __launch_bounds__(SK_NT, MT <= 2 && U * NT <= 4 ? 4 : 2) void gemm_skinny_nt_kernel(
+// MT: 16-row tiles of A. AU, BU: load instructions (4 rows each) for a piece of a row tile, of a column block: 4, or
+// fewer where no more rows or columns exist (each instruction costs a CU the same, whatever it fetches)
+template <int MT, int AU, int BU> struct SkCfg {
+  static constexpr int LU = AU > BU ? AU : BU;
+  static constexpr int SLOT = LU * 1024;
+  static constexpr int R = SK_RING / SLOT < 12 ? SK_RING / SLOT : 12;     // slots
+  static constexpr int CB = 4 * BU;                                       // columns per block
+  static constexpr int GB = BU < 4 ? 1 : MT <= 2 ? 8 : 4;                 // blocks per group
+  static_assert(GB * MT * 1024 <= SK_RING, "a wavefront's partial tiles lie in its own ring");
+  static_assert((R - 1) * LU < 63, "loads in flight are counted");
+};
+
+// share, rest: columns per workgroup, and how many of them have one more. PARTS: blockIdx.y is the part of K; `part` holds
+// [part][M][N] floats, `counter` one zero per blockIdx.x (left as zero); without counters (null) another kernel adds the parts.
+template <typename Tag, int MT, int AU, int BU, bool PARTS>
+__global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
     int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
-    const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc) {
+    const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc, int act,
+    const uint16_t* __restrict__ bias, int share, int rest, float* __restrict__ part, uint32_t* __restrict__ counter) {
   typedef typename Elem<Tag>::vec8 V8;
-  __shared__ float red[SK_NW][256];
-
+  typedef SkCfg<MT, AU, BU> L;
+  constexpr int GB = L::GB, CB = L::CB, R = L::R;
+  extern __shared__ __align__(16) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, q = lane >> 4;
-  const int n0 = blockIdx.x * (16 * NT);
-  const uint16_t* bp[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int nrow = n0 + nt * 16 + r16 < N ? n0 + nt * 16 + r16 : N - 1;   // clamped: never stored
-    bp[nt] = B + (int64_t)nrow * ldb;
+  const int bid = (int)blockIdx.x, c0 = bid * share + (bid < rest ? bid : rest), c1 = c0 + share + (bid < rest ? 1 : 0);
+  const int nblk = (c1 - c0 + CB - 1) / CB;
+  // pieces p0 .. p1 - 1, of them p0 + wave, p0 + wave + 8, ...
+  int p0 = 0, p1 = (K + SK_KP - 1) / SK_KP;
+  if (PARTS) {
+    const int per = (p1 + (int)gridDim.y - 1) / (int)gridDim.y;
+    p0 = (int)blockIdx.y * per;
+    p1 = p0 + per < p1 ? p0 + per : p1;
   }
-  const uint16_t* ap[MT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt) {
-    const int arow = mt * 16 + r16 < M ? mt * 16 + r16 : M - 1;
-    ap[mt] = A + (int64_t)arow * lda;
-  }
+  const int first = p0 + wave, mine = p1 > first ? (p1 - first + SK_NW - 1) / SK_NW : 0;
+  const uint32_t ring = (uint32_t)(uintptr_t)(lptr_t)smem + (uint32_t)wave * SK_RING;
 
-  f32x4 acc[MT][NT];
+  // load instruction i of a slot: rows 4 i .. 4 i + 3, lane l the chunk at position l % 16 of row 4 i + l / 16
+  uint32_t va[AU], vb[BU];
 #pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
+  for (int i = 0; i < AU; ++i)
+    va[i] = (uint32_t)(i * 4 + lane / 16) * (uint32_t)lda * 2u + (uint32_t)((lane % 16) ^ (i * 4 + lane / 16)) * 16u;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < BU; ++i)
+    vb[i] = (uint32_t)(i * 4 + lane / 16) * (uint32_t)ldb * 2u + (uint32_t)((lane % 16) ^ (i * 4 + lane / 16)) * 16u;
 
-  const int KC = (K + 31) / 32;                            // 32-wide chunks; K % 8 == 0
-  const u32x4 zero4 = {0u, 0u, 0u, 0u};
-  struct Batch { u32x4 b[U][NT], a[U][MT]; };
-  // batch i of this wavefront: chunks wave + 8 * (i * U + u). k of a lane's 8 values; past K the loads re-read
-  // k = 0 and both operands are zeroed in front of the MFMAs
-  auto k_of = [&](int i, int u) { return (wave + SK_NW * (i * U + u)) * 32 + 8 * q; };
-  auto load = [&](Batch& s, int i) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = k_of(i, u) < K ? k_of(i, u) : 0;
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) s.b[u][nt] = load_stream16(bp[nt] + k);   // B is read once
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = k_of(i, u) < K ? k_of(i, u) : 0;
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt) s.a[u][mt] = *reinterpret_cast<const u32x4_mem*>(ap[mt] + k);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  auto multiply = [&](Batch& s, int i) __attribute__((always_inline)) {
-    if ((wave + SK_NW * (i * U + U - 1)) * 32 + 32 > K) {  // wavefront-uniform
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (k_of(i, u) >= K) {
-#pragma unroll
-          for (int nt = 0; nt < NT; ++nt) s.b[u][nt] = zero4;
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) s.a[u][mt] = zero4;
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          acc[mt][nt] = mfma16(__builtin_bit_cast(V8, s.a[u][mt]), __builtin_bit_cast(V8, s.b[u][nt]), acc[mt][nt]);
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  const int mine = KC > wave ? (KC - wave + SK_NW - 1) / SK_NW : 0, nb = (mine + U - 1) / U;
-  Batch s0, s1;
-  if (nb > 0) {
-    load(s0, 0);
-    int i = 0;
-    for (; i + 2 < nb; i += 2) {
-      load(s1, i + 1);
-      multiply(s0, i);
-      load(s0, i + 2);
-      multiply(s1, i + 1);
-    }
-    if (i + 1 < nb) {
-      load(s1, i + 1);
-      multiply(s0, i);
-      multiply(s1, i + 1);
-    } else {
-      multiply(s0, i);
-    }
-  }
-
-  // one 16 x 16 tile at a time through LDS: lane owns C[4*q + r][r16] in acc[..][r]
-  const int row = (tid & 255) >> 4, col = tid & 15;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) red[wave][(4 * q + r) * 16 + r16] = acc[mt][nt][r];
-      __syncthreads();
-      if (tid < 256) {
-        float s = 0.f;
-#pragma unroll
-        for (int w = 0; w < SK_NW; ++w) s += red[w][tid];
-        const int gr = mt * 16 + row, gc = n0 + nt * 16 + col;
-        if (gr < M && gc < N) C[(int64_t)gr * ldc + gc] = Elem<Tag>::from_f32(s);
-      }
-      __syncthreads();
-    }
-}
-
-template <typename Tag, int MT, int NT, int U>
-int launch_skinny(const GemmArgs& g, hipStream_t s) {
-  const unsigned nwg = (unsigned)((g.N + 16 * NT - 1) / (16 * NT));
-  hipLaunchKernelGGL((gemm_skinny_nt_kernel<Tag, MT, NT, U>), dim3(nwg), dim3(SK_NT), 0, s, (int)g.M,
-                     (int)g.N, (int)g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc);
-  return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
-}
-
-// Columns per workgroup: more columns reuse each A fragment more often (A comes from L2 once per
-// workgroup), fewer keep the chip full; at least ~2 workgroups per CU are wanted. Up to one workgroup per CU
-// (16 columns) a wavefront keeps 16 chunks in flight, with more 8: two workgroups then share a CU.
-template <typename Tag, int MT>
-int run_skinny_mt(const GemmArgs& g, hipStream_t s) {
-  DeviceInfo di;
-  const int64_t ncu = device_info(di) && di.ncu > 0 ? di.ncu : 256;
-  if (g.N >= 64 * 512) return launch_skinny<Tag, MT, 4, 1>(g, s);
-  if (g.N >= 32 * 512) return launch_skinny<Tag, MT, 2, 2>(g, s);
-  if (MT <= 2 && g.N <= 16 * ncu) return launch_skinny<Tag, MT, 1, MT <= 2 ? 8 : 4>(g, s);
-  return launch_skinny<Tag, MT, 1, 4>(g, s);
-}
-
-template <typename Tag>
-int run_skinny_t(const GemmArgs& g, hipStream_t s) {
-  switch ((g.M + 15) / 16) {
-    case 1: return run_skinny_mt<Tag, 1>(g, s);
-    case 2: return run_skinny_mt<Tag, 2>(g, s);
-    case 3: return run_skinny_mt<Tag, 3>(g, s);
-    case 4: return run_skinny_mt<Tag, 4>(g, s);
-  }
-  return MLT_ERR_UNSUPPORTED;
-}
-
-
-// ---------------------------------------------------------------------------------------------
-// Streaming variant for large B. What limits the kernel above on matrices far beyond the caches
-// is the shape of its HBM requests (one load instruction touches 16 rows with 64 bytes each) and,
-// for taller A, that A is fetched from L2 again for every 16 columns. Here B goes through an LDS
-// ring in long contiguous row pieces and stays 7 stages (112 KB per CU) in flight:
-//   * a stage is 16 KB of B: 16 rows x 512 k (1 KB per row, one row per load instruction: 64 lanes
-//     x 16 contiguous bytes, global_load_lds_dwordx4). (A wider stage of 64 rows x 128 k, which
-//     reuses every A fragment for four column tiles, measured slower than the small-tile kernels
-//     wherever it beat this one, and is no longer built.) The ring holds 8 stages (128 KB);
-//   * wavefronts 0-3 only fetch: wavefront p issues load instructions 4p .. 4p+3 of every stage,
-//     seven stages ahead. Their vector-memory counter sees nothing but these loads, so "stage s
-//     has landed" is an exact count; wavefronts 4-7 only compute: they split the 32-wide k chunks
-//     of a stage among themselves, read the B fragments from LDS and the A fragments from global
-//     memory (A stays in L2; their loads are counted by the compiler as usual);
-//   * one workgroup barrier per stage; the slot of stage s-1 is refilled right after barrier s;
-//   * workgroups are persistent (one per CU) and walk over their column blocks without letting
-//     the ring drain; at the end of a block the four partial tiles are added through a separate
-//     LDS area and stored;
-//   * within a row piece the 16-byte chunks are stored permuted (chunk c at position c ^ (row &
-//     15)): the source address of a lane is free, its LDS position is not, and the 16 lanes that
-//     read 16 rows at one k position must hit 16 distinct bank groups.
-constexpr int SD_ST = 8;              // ring stages
-constexpr int SD_STAGE_B = 16384;     // bytes of B per stage
-constexpr int SD_SMEM = SD_ST * SD_STAGE_B;
-constexpr int SD_RED = 4 * 4 * 256 * 4;   // reduction area behind the ring: [4 wavefronts][4 tiles][256]
-
-struct SdCfg {
-  static constexpr int RPS = 16;                 // rows of B (columns of C) per stage and column block
-  static constexpr int KS = 512;                 // k values per stage
-  static constexpr int PB = KS * 2;              // bytes of a row piece
-  static constexpr int LPR = PB / 16;            // lanes per row piece
-  static constexpr int NT = RPS / 16;            // 16-column tiles per block
-  static constexpr int J = KS / 32 / 4;          // k chunks per computing wavefront and stage
-};
-
-template <typename Tag, int MT>
-__global__ __launch_bounds__(SK_NT) void gemm_skinny_dma_kernel(
-    int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
-    const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc, int act,
-    const uint16_t* __restrict__ bias) {
-  typedef typename Elem<Tag>::vec8 V8;
-  typedef SdCfg L;
-  constexpr int KS = L::KS, NT = L::NT, J = L::J;
-  extern __shared__ __align__(16) char smem[];             // the ring, then the reduction area
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int NS = (K + KS - 1) / KS;                        // stages per column block
-  const int nblocks = (N + L::RPS - 1) / L::RPS;
-  // Persistent workgroups: this one owns column blocks blockIdx.x, + gridDim.x, ... and takes
-  // them in groups of up to GB. The stages of a group are ordered k stage first: (k stage 0 of
-  // every block of the group), (k stage 1 of every block), ...; the accumulators of all the
-  // group's blocks stay in registers, and the A fragments of a k stage are fetched once per group
-  // instead of once per block. All stages of all groups form one stream g = 0 .. G-1, so the ring
-  // never drains between blocks or groups.
-  // (as many as the registers take: 8 blocks for one 16-row tile of A in the narrow form)
-  constexpr int GB = MT == 1 ? 8 : MT == 2 ? 4 : 2;
-  const int nmine = (nblocks - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
-  const int G = nmine * NS;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)smem;
-
-  if (wave < 4) {
-    // ---- fetching wavefronts: load instruction ii of a stage fills LDS bytes ii*1024 .. +1023 of
-    // the slot, i.e. rows ii*(64/LPR) .. of the stage; lane l serves row l / LPR of those at
-    // position l % LPR. The cursor (i_*) names the next stage of the stream to fetch.
-    int i_g = 0, i_base = 0, i_nb = nmine < GB ? nmine : GB, i_ks = 0, i_b = 0;
-    auto issue_next = [&]() __attribute__((always_inline)) {
-      if (i_g >= G) return;
-      const int n0 = ((int)blockIdx.x + (i_base + i_b) * (int)gridDim.x) * L::RPS;
-      const int k0 = i_ks * KS;
-      const char* Bw = reinterpret_cast<const char*>(B + (int64_t)n0 * ldb);
-      const uint32_t slot = lds0 + (uint32_t)(i_g % SD_ST) * SD_STAGE_B;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ii = wave * 4 + i;
-        const int r = ii * (64 / L::LPR) + lane / L::LPR;
-        const int nrow = n0 + r < N ? r : N - 1 - n0;      // clamped: such columns are never stored
-        int ck = (lane % L::LPR) ^ (r & 15);               // the 16-byte chunk this lane fetches
-        if (k0 + ck * 8 >= K) ck = 0;                      // past K (last stage): any valid chunk, zeroed later
-        load_lds16_stream(Bw, (uint32_t)nrow * (uint32_t)ldb * 2u + (uint32_t)(k0 + ck * 8) * 2u,
-                      slot + (uint32_t)ii * 1024u);
-      }
-      ++i_g;
-      if (++i_b == i_nb) {
-        i_b = 0;
-        if (++i_ks == NS) {
-          i_ks = 0;
-          i_base += GB;
-          i_nb = nmine - i_base < GB ? nmine - i_base : GB;
-        }
-      }
-    };
-#pragma unroll
-    for (int t = 0; t < SD_ST - 1; ++t) issue_next();
-    int g = 0;
-    for (int base = 0; base < nmine; base += GB) {
-      const int nb = nmine - base < GB ? nmine - base : GB;
-      for (int t = 0; t < NS * nb; ++t, ++g) {
-        // issued so far: stages 0 .. min(G, g + SD_ST - 1) - 1; those after g may stay in flight
-        const int last = g + SD_ST - 2 < G - 1 ? g + SD_ST - 2 : G - 1;
-        switch (last - g) {
-          case 0: __builtin_amdgcn_s_waitcnt(wait_imm(0, 15)); break;
-          case 1: __builtin_amdgcn_s_waitcnt(wait_imm(4, 15)); break;
-          case 2: __builtin_amdgcn_s_waitcnt(wait_imm(8, 15)); break;
-          case 3: __builtin_amdgcn_s_waitcnt(wait_imm(12, 15)); break;
-          case 4: __builtin_amdgcn_s_waitcnt(wait_imm(16, 15)); break;
-          case 5: __builtin_amdgcn_s_waitcnt(wait_imm(20, 15)); break;
-          default: __builtin_amdgcn_s_waitcnt(wait_imm(24, 15)); break;
-        }
-        MLT_BARRIER();                      // stage g is complete in LDS for everyone
-        issue_next();                                      // stage g + SD_ST - 1, into the slot of stage g-1 (read before this barrier)
-      }
-      // end of a group: the barriers of the computing wavefronts' reductions (two per block and
-      // row tile, less the very first)
-      for (int t = 0; t < 2 * nb * MT - 1; ++t) __syncthreads();
-    }
-  } else {
-    // ---- computing wavefronts: wavefront cw takes k chunks J*cw .. J*cw + J-1 of every stage
-    const int cw = wave - 4, ctid = tid - 256;
-    const int r16 = lane & 15, q = lane >> 4;
-    float* red = reinterpret_cast<float*>(smem + SD_SMEM);  // [4][NT][256]
-    const uint16_t* ap[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-      const int arow = mt * 16 + r16 < M ? mt * 16 + r16 : M - 1;
-      ap[mt] = A + (int64_t)arow * lda;
-    }
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    f32x4 acc[GB][MT][NT];
+  for (int base = 0; base < nblk; base += GB) {
+    const int nb = nblk - base < GB ? nblk - base : GB;
+    const int S = MT + nb, T = mine * S;                 // slots per piece (row tiles, then column blocks), in all
+    f32x4 acc[GB][MT];
 #pragma unroll
     for (int gb = 0; gb < GB; ++gb)
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+      for (int mt = 0; mt < MT; ++mt) acc[gb][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // the cursor: the next slot of the stream to fetch, f_s of piece f_p, and its place
+    int f_t = 0, f_s = 0, f_p = first;
+    uint32_t f_slot = ring;
+    int issued = 0, need = 0;                            // load instructions issued; up to the end of the slot in hand
+    auto fetch = [&]() __attribute__((always_inline)) {
+      if (f_t >= T) return;
+      const int k0 = f_p * SK_KP;
+      const bool tail = k0 + SK_KP > K;
+      // rows past the matrix (past this workgroup's columns) and chunks past K: the piece's first chunk for all such
+      // lanes, never stored or zeroed later; the instruction stays, and with it the count of loads in flight
+      if (f_s < MT) {
+        const char* src = reinterpret_cast<const char*>(A + (int64_t)(f_s * 16) * lda + k0);
+        const int rows = M - f_s * 16;
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[gb][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // A fragments of k stage ks: k = ks*KS + (J*cw + j)*32 + 8*q
-    auto load_a = [&](int ks, u32x4 (&af)[J][MT]) __attribute__((always_inline)) {
+        for (int i = 0; i < AU; ++i) {
+          const int row = i * 4 + lane / 16;
+          uint32_t off = row < rows ? va[i] : 0u;
+          if (tail && k0 + ((lane % 16) ^ row) * 8 >= K) off = 0u;
+          load_lds16(src, off, f_slot + i * 1024u);
+        }
+        issued += AU;
+      } else {
+        const int n0 = c0 + (base + f_s - MT) * CB;
+        const char* src = reinterpret_cast<const char*>(B + (int64_t)n0 * ldb + k0);
+        const int rows = c1 - n0;
 #pragma unroll
-      for (int j = 0; j < J; ++j) {
-        const int k = ks * KS + (J * cw + j) * 32 + 8 * q;
+        for (int i = 0; i < BU; ++i) {
+          const int row = i * 4 + lane / 16;
+          uint32_t off = row < rows ? vb[i] : 0u;
+          if (tail && k0 + ((lane % 16) ^ row) * 8 >= K) off = 0u;
+          load_lds16_stream(src, off, f_slot + i * 1024u);
+        }
+        issued += BU;
+      }
+      ++f_t;
+      f_slot = f_slot == ring + (R - 1) * L::SLOT ? ring : f_slot + L::SLOT;
+      if (++f_s == S) { f_s = 0; f_p += SK_NW; }
+    };
+#pragma unroll
+    for (int i = 0; i < R; ++i) fetch();
+
+    // the next slot, of n loads: wait until it has landed (what was issued after it may be in flight), read its
+    // fragments, refill its place
+    uint32_t slot = ring;
+    auto take = [&](u32x4 (&f)[4], int n) __attribute__((always_inline)) {
+      need += n;
+      const int later = issued - need;
+      if (L::LU == 4 && later >= 16) __builtin_amdgcn_s_waitcnt(wait_imm(16, 15));
+      else if (L::LU == 4 && later >= 12) __builtin_amdgcn_s_waitcnt(wait_imm(12, 15));
+      else if (later >= 10) __builtin_amdgcn_s_waitcnt(wait_imm(10, 15));
+      else if (later >= 8) __builtin_amdgcn_s_waitcnt(wait_imm(8, 15));
+      else if (later >= 6) __builtin_amdgcn_s_waitcnt(wait_imm(6, 15));
+      else if (later >= 4) __builtin_amdgcn_s_waitcnt(wait_imm(4, 15));
+      else if (later >= 2) __builtin_amdgcn_s_waitcnt(wait_imm(2, 15));
+      else if (later >= 1) __builtin_amdgcn_s_waitcnt(wait_imm(1, 15));
+      else __builtin_amdgcn_s_waitcnt(wait_imm(0, 15));
+      __builtin_amdgcn_sched_barrier(0);
+      const int row = r16 & (4 * n - 1);                 // (fewer than 16 rows: repeated, never stored)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        f[j] = *(const MLT_LDS u32x4*)(uintptr_t)(slot + (uint32_t)row * 256u + (uint32_t)(((j * 4 + q) ^ row) << 4));
+      __builtin_amdgcn_s_waitcnt(wait_imm(63, 0));
+      __builtin_amdgcn_sched_barrier(0);
+      fetch();
+      __builtin_amdgcn_sched_barrier(0);
+      slot = slot == ring + (R - 1) * L::SLOT ? ring : slot + L::SLOT;
+    };
+    const u32x4 zero4 = {0u, 0u, 0u, 0u};
+    for (int i = 0; i < mine; ++i) {
+      const int k0 = (first + i * SK_NW) * SK_KP;
+      const bool tail = k0 + SK_KP > K;                  // chunks past K: zeros in both operands
+      u32x4 af[MT][4];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) take(af[mt], AU);
+      if (tail) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (k0 + j * 32 + 8 * q >= K) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) af[mt][j] = zero4;
+          }
+      }
+#pragma unroll
+      for (int gb = 0; gb < GB; ++gb)
+        if (gb < nb) {
+          u32x4 bf[4];
+          take(bf, BU);
+          if (tail) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (k0 + j * 32 + 8 * q >= K) bf[j] = zero4;
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+              acc[gb][mt] = mfma16(__builtin_bit_cast(V8, af[mt][j]), __builtin_bit_cast(V8, bf[j]), acc[gb][mt]);
+        }
+    }
+    // the partial tiles into the wavefront's own ring (all its loads have landed), then their sums
+    float* own = reinterpret_cast<float*>(smem + wave * SK_RING);
+#pragma unroll
+    for (int gb = 0; gb < GB; ++gb)
+      if (gb < nb) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-          af[j][mt] = *reinterpret_cast<const u32x4_mem*>(ap[mt] + (k < K ? k : 0));
+#pragma unroll
+          for (int r = 0; r < 4; ++r) own[(gb * MT + mt) * 256 + (4 * q + r) * 16 + r16] = acc[gb][mt][r];
       }
-    };
-    int g = 0;
-    u32x4 af0[J][MT], af1[J][MT];
-    load_a(0, af0);
-    for (int base = 0; base < nmine; base += GB) {
-      const int nb = nmine - base < GB ? nmine - base : GB;
-      // k stage ks of every block of the group: `cur` holds its A fragments; those of the next k
-      // stage (of this group, or stage 0 for the next group) are requested into `nxt` meanwhile
-      auto k_stage = [&](int ks, u32x4 (&cur)[J][MT], u32x4 (&nxt)[J][MT]) __attribute__((always_inline)) {
-        const bool whole = (ks + 1) * KS <= K;
+    __syncthreads();
+    // (one element at a time: a call of a few microseconds notices every line of code that it has to fetch)
+    for (int e = tid; e < nb * MT * 256; e += SK_NT) {
+      const int t = e >> 8, gr = t % MT * 16 + ((e >> 4) & 15), gc = c0 + (base + t / MT) * CB + (e & 15);
+      if (gr < M && gc < c1 && (e & 15) < CB) {
+        float sum = 0.f;
 #pragma unroll
-        for (int gb = 0; gb < GB; ++gb) {
-          if (gb < nb) {
-            MLT_BARRIER();
-            const uint32_t slot = lds0 + (uint32_t)(g % SD_ST) * SD_STAGE_B;
-            u32x4 bf[J][NT];
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-              const int c16 = (J * cw + j) * 4 + q;              // 16-byte chunk of the row piece
-#pragma unroll
-              for (int nt = 0; nt < NT; ++nt)
-                bf[j][nt] = *(const __attribute__((address_space(3))) u32x4*)(uintptr_t)(
-                    slot + (uint32_t)(nt * 16 + r16) * L::PB + (uint32_t)((c16 ^ r16) << 4));
-            }
-            if (gb == 0) load_a(ks + 1 < NS ? ks + 1 : 0, nxt);  // unconditional: keeps the load counting exact
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-              const bool dead = !whole && ks * KS + (J * cw + j) * 32 + 8 * q >= K;
-#pragma unroll
-              for (int mt = 0; mt < MT; ++mt) {
-                const u32x4 a = dead ? zero4 : cur[j][mt];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                  const u32x4 bb = dead ? zero4 : bf[j][nt];
-                  acc[gb][mt][nt] = mfma16(__builtin_bit_cast(V8, a), __builtin_bit_cast(V8, bb), acc[gb][mt][nt]);
-                }
-              }
-            }
-            ++g;
-          }
-        }
-      };
-      for (int ks = 0; ks < NS; ks += 2) {
-        k_stage(ks, af0, af1);
-        if (ks + 1 < NS) k_stage(ks + 1, af1, af0);
-      }
-      if (NS & 1) {
-        // an odd number of k stages leaves the fragments of the next group's stage 0 in af1
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) af0[j][mt] = af1[j][mt];
-      }
-      // end of a group: per block and 16-row tile of A the four wavefronts' partial tiles meet in
-      // LDS, 256 lanes add them and store (2 * nb * MT - 1 barriers, matched by the fetching
-      // wavefronts)
-#pragma unroll
-      for (int gb = 0; gb < GB; ++gb) {
-        if (gb < nb) {
-          const int n0 = ((int)blockIdx.x + (base + gb) * (int)gridDim.x) * L::RPS;
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            if (gb > 0 || mt > 0) __syncthreads();             // the previous sums have been read
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                red[(cw * NT + nt) * 256 + (4 * q + r) * 16 + r16] = acc[gb][mt][nt][r];
-                acc[gb][mt][nt][r] = 0.f;
-              }
-            __syncthreads();                                   // with the fence: the partial tiles are LDS stores
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-              float sum = 0.f;
-#pragma unroll
-              for (int w = 0; w < 4; ++w) sum += red[(w * NT + nt) * 256 + ctid];
-              const int gr = mt * 16 + (ctid >> 4), gc = n0 + nt * 16 + (ctid & 15);
-              if (gr < M && gc < N) {
-                if (bias) sum += Elem<Tag>::to_f32(bias[gc]);
-                C[(int64_t)gr * ldc + gc] = Elem<Tag>::from_f32(epi_act(sum, act));
-              }
-            }
-          }
-        }
+        for (int w = 0; w < SK_NW; ++w) sum += reinterpret_cast<const float*>(smem)[w * (SK_RING / 4) + e];
+        if (PARTS) store_shared(part + ((int64_t)blockIdx.y * M + gr) * N + gc, sum);
+        else C[(int64_t)gr * ldc + gc] = Elem<Tag>::from_f32(epi_act(bias ? sum + Elem<Tag>::to_f32(bias[gc]) : sum, act));
       }
     }
+    if (base + GB < nblk) __syncthreads();
+  }
+  if (!PARTS || !counter) return;
+
+  // the last part of these columns to get here adds them all
+  if (!last_to_arrive(counter + bid, gridDim.y, reinterpret_cast<uint32_t*>(smem))) return;
+  const int cols = c1 - c0, parts = (int)gridDim.y;
+  // (EB elements of a thread at a time, all their parts requested before the first is used: each such round is a trip to
+  // memory)
+  constexpr int EB = MT == 1 ? 2 : 4;
+  for (int e0 = tid; e0 < M * cols; e0 += EB * SK_NT) {
+    float v[8][EB];
+    int64_t at[EB];
+#pragma unroll
+    for (int i = 0; i < EB; ++i) {
+      const int e = e0 + i * SK_NT < M * cols ? e0 + i * SK_NT : e0;
+      at[i] = (int64_t)(e / cols) * N + c0 + e % cols;
+    }
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+      if (p < parts) {
+#pragma unroll
+        for (int i = 0; i < EB; ++i) v[p][i] = load_shared(part + (int64_t)p * M * N + at[i]);
+      }
+#pragma unroll
+    for (int p = 1; p < 8; ++p)
+      if (p < parts) {
+#pragma unroll
+        for (int i = 0; i < EB; ++i) v[0][i] += v[p][i];
+      }
+#pragma unroll
+    for (int i = 0; i < EB; ++i)
+      if (e0 + i * SK_NT < M * cols) {
+        const int gr = (e0 + i * SK_NT) / cols, gc = c0 + (e0 + i * SK_NT) % cols;
+        C[(int64_t)gr * ldc + gc] = Elem<Tag>::from_f32(epi_act(bias ? v[0][i] + Elem<Tag>::to_f32(bias[gc]) : v[0][i], act));
+      }
   }
 }
 
-template <typename Tag, int MT>
-int launch_skinny_dma(const GemmArgs& g, hipStream_t s) {
-  auto kern = gemm_skinny_dma_kernel<Tag, MT>;
+template <typename Tag, int MT, int AU, int BU, bool PARTS>
+int launch_skinny(const GemmArgs& g, int64_t ncu, hipStream_t s) {
+  auto kern = gemm_skinny_kernel<Tag, MT, AU, BU, PARTS>;
   static thread_local int configured_dev = -1;            // opt in to > 64 KB LDS once per device
-  static thread_local int ncu = 0;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MLT_ERR_DEVICE;
   if (configured_dev != dev) {
-    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            SD_SMEM + SD_RED) != hipSuccess ||
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    if (hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, SK_SMEM) != hipSuccess) {
       (void)hipGetLastError();
       return MLT_ERR_LAUNCH;
     }
     configured_dev = dev;
   }
-  const int64_t nblocks = (g.N + SdCfg::RPS - 1) / SdCfg::RPS;
-  const unsigned nwg = (unsigned)(nblocks < ncu ? nblocks : ncu);   // one persistent workgroup per CU
-  hipLaunchKernelGGL(kern, dim3(nwg), dim3(SK_NT), SD_SMEM + SD_RED, s, (int)g.M, (int)g.N, (int)g.K,
-                     g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.act, g.bias);
-  return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
+  const int64_t parts = PARTS ? g.parts : 1, want = ncu / parts > 0 ? ncu / parts : 1;
+  const unsigned nwg = (unsigned)(g.N < want ? g.N : want);   // one workgroup per CU, every one with columns
+  hipLaunchKernelGGL(kern, dim3(nwg, (unsigned)parts), dim3(SK_NT), SK_SMEM, s, (int)g.M, (int)g.N, (int)g.K,
+                     g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.act, g.bias, (int)(g.N / nwg), (int)(g.N % nwg), g.scratch, g.counters);
+  if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
+  return PARTS && !g.counters ? run_splitk_reduce(g, (int)parts, g.M * g.N, s) : MLT_OK;
+}
+
+template <typename Tag, int MT, int AU>
+int run_skinny_cols(const GemmArgs& g, hipStream_t s) {
+  DeviceInfo di;
+  const int64_t ncu = device_info(di) && di.ncu > 0 ? di.ncu : 256;
+  if (g.parts > 1) return launch_skinny<Tag, MT, AU, 4, true>(g, ncu, s);
+  if (g.N <= 4 * ncu) return launch_skinny<Tag, MT, AU, 1, false>(g, ncu, s);
+  if (g.N <= 8 * ncu) return launch_skinny<Tag, MT, AU, 2, false>(g, ncu, s);
+  return launch_skinny<Tag, MT, AU, 4, false>(g, ncu, s);
 }
 
 template <typename Tag>
-int run_skinny_dma_t(const GemmArgs& g, hipStream_t s) {
+int run_skinny_t(const GemmArgs& g, hipStream_t s) {
+  if (g.M <= 4) return run_skinny_cols<Tag, 1, 1>(g, s);
   switch ((g.M + 15) / 16) {
-    case 1: return launch_skinny_dma<Tag, 1>(g, s);
-    case 2: return launch_skinny_dma<Tag, 2>(g, s);
-    case 3: return launch_skinny_dma<Tag, 3>(g, s);
-    case 4: return launch_skinny_dma<Tag, 4>(g, s);
+    case 1: return run_skinny_cols<Tag, 1, 4>(g, s);
+    case 2: return run_skinny_cols<Tag, 2, 4>(g, s);
+    case 3: return run_skinny_cols<Tag, 3, 4>(g, s);
+    case 4: return run_skinny_cols<Tag, 4, 4>(g, s);
   }
   return MLT_ERR_UNSUPPORTED;
 }
 
 }  // namespace
 
-// Worth it only when the columns alone fill the chip (one workgroup per 16 columns).
-static bool skinny_shape_ok(const GemmArgs& g) {
+bool gemm_skinny_ok(const GemmArgs& g) {
   auto al16 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
-  if (!g.transB || g.acc32 || g.M > 16 * SK_MAXMT || g.N < 1024) return false;
+  if (!g.transB || g.acc32 || g.M > 64 || g.N < 1024) return false;
   if (!al16(g.A) || !al16(g.B)) return false;
   if (g.K % 8 || g.lda % 8 || g.ldb % 8) return false;
-  return true;
+  // 32-bit byte offsets from a block's first row
+  return g.lda * 2 * 16 + g.K * 2 < ((int64_t)1 << 32) && g.ldb * 2 * 16 + g.K * 2 < ((int64_t)1 << 32);
 }
-
-bool gemm_skinny_ok(const GemmArgs& g) { return skinny_shape_ok(g) && !g.fused(); }
 
 int run_gemm_skinny(const GemmArgs& g, hipStream_t s) {
   return g.dtype == MLT_BF16 ? run_skinny_t<bf16_tag>(g, s) : run_skinny_t<f16_tag>(g, s);
-}
-
-// The streaming variant addresses B rows with 32-bit byte offsets from the column block's first row.
-bool gemm_skinny_dma_ok(const GemmArgs& g) {
-  return skinny_shape_ok(g) && g.ldb * 2 * 64 + g.K * 2 < ((int64_t)1 << 32);
-}
-
-int run_gemm_skinny_dma(const GemmArgs& g, hipStream_t s) {
-  return g.dtype == MLT_BF16 ? run_skinny_dma_t<bf16_tag>(g, s) : run_skinny_dma_t<f16_tag>(g, s);
 }
 
 }  // namespace mlt

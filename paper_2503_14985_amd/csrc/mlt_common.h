@@ -336,6 +336,25 @@ template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
   }
 };
 
+// Partial results that the workgroups of one launch hand to each other through memory, and the counter at which the last of
+// them finds out that it is the last. The XCDs' L2s do not see each other's lines, so these values are stored and loaded with
+// device-scope accesses (written through, never served from an L2), and a wavefront's stores are complete when its
+// memory counter is zero: no fence, which would write back or drop a whole L2 (fences in all wavefronts
+// of 256 workgroups: 16 to 20 us).
+__device__ __forceinline__ void store_shared(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float load_shared(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Called by all threads of each of n workgroups, once: true in the one that comes last, for which load_shared
+// then returns what any of them has stored with store_shared. The counter goes from 0 to n - 1 and back to 0. flag: one word
+// of LDS that nobody needs any more.
+__device__ __forceinline__ bool last_to_arrive(uint32_t* counter, uint32_t n, uint32_t* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) *flag = atomicInc(counter, n - 1);
+  __syncthreads();
+  return *flag == n - 1;
+}
+
 // D(32x32) += A(32x16) * B(16x32). Lane l supplies A[l%32][8*(l/32) .. +7] and
 // B[8*(l/32) .. +7][l%32]; it owns D[8*(r/4) + 4*(l/32) + r%4][l%32] in register r (0..15).
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {

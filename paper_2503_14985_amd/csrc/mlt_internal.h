@@ -10,8 +10,8 @@ enum GemmVariant {
   GEMM_AUTO = -1, GEMM_ZERO = 0, GEMM_GENERAL = 1,
   GEMM_256 = 2,       // 256x256x64, 4 wavefronts (2x2) of 128x128 (tiling hint "square" with a ragged K)
   GEMM_256_W8 = 4,    // 256x256x64, 8 wavefronts (2x4) of 128x64 (big tiles when the direct loads do not apply)
-  GEMM_SKINNY = 7,    // M <= 64, B stored N x K: 16 columns per workgroup, K split over 8 wavefronts
-  GEMM_SKINNY_DMA = 8,  // same shapes, B streamed through an LDS ring: 16 columns x 512 k per stage
+  GEMM_SKINNY = 7,    // M <= 64, B stored N x K: K split over 8 wavefronts, LDS rings (one column block per workgroup)
+  GEMM_SKINNY_DMA = 8,  // the same kernel, any number of column blocks
   GEMM_256_W4 = 10,   // 256x256x64, 4 wavefronts (2x2) of 128x128, software-pipelined, direct-to-LDS loads
   GEMM_256_PP16 = 11, // 256x256x64, 8 wavefronts (2x4), two-group schedule, direct-to-LDS loads, 16x16x32 MFMAs
   GEMM_256_W8X1 = 12, // 256x256x64, 8 wavefronts as 8x1: row strips of 32 x 256 ("horizontal")
@@ -42,6 +42,7 @@ struct GemmArgs {
   // K split across workgroups: the fp32 scratch the partial products go to (parts * M * N floats)
   // and the number of parts the plan asks for; run_gemm fills both in.
   float* scratch = nullptr;
+  uint32_t* counters = nullptr;    // the scratch's kScratchCounters zeros (left as zeros), or null: a second kernel adds the parts
   int parts = 1;
   int forced_parts = 0;            // plan_gemm: 0 = the cost model's choice, 1 / 2 / 4 / 8 = forced
   int epi() const { return acc32 ? 1 : (act << 1); }   // the kernels' epilogue word
@@ -63,6 +64,10 @@ struct GemmPlan {
 // array's address on the current device (nullptr if it cannot be had)
 constexpr int64_t kStaticScratchBytes = (int64_t)32 << 20;
 float* static_scratch_of_current_device();
+// Counters (last_to_arrive in mlt_common.h) in front of every buffer that cached_scratch returns. The fixed array has none: calls
+// that overlap there, against the rules, would leave them in disorder for all later ones.
+constexpr int kScratchCounters = 16384;
+inline uint32_t* scratch_counters(float* scratch) { return reinterpret_cast<uint32_t*>(scratch) - kScratchCounters; }
 
 GemmPlan plan_gemm(const GemmArgs& g);
 int run_gemm(const GemmArgs& g, GemmPlan& p, hipStream_t s);
@@ -76,8 +81,6 @@ bool gemm_w4_ok(const GemmArgs& g);            // gemm_w4.hip: whole K steps onl
 int run_gemm_w4(const GemmArgs& g, hipStream_t s);
 bool gemm_skinny_ok(const GemmArgs& g);        // gemm_skinny.hip
 int run_gemm_skinny(const GemmArgs& g, hipStream_t s);
-bool gemm_skinny_dma_ok(const GemmArgs& g);
-int run_gemm_skinny_dma(const GemmArgs& g, hipStream_t s);
 
 enum MhaVariant {
   MHA_AUTO = -1,
@@ -156,7 +159,7 @@ int run_paged_decode(const PagedArgs& a, hipStream_t s, int* nsplit_out);
 int plan_paged_split(const PagedArgs& a);                                       // key ranges per (sequence, head)
 bool paged_by_length(const PagedArgs& a, int64_t nsplit, int64_t ncu);   // workgroups dealt out by sequence length?
 
-// The library's own scratch memory for a stream of the current device: at least `bytes`, kept
+// The library's own scratch memory for a stream of the current device: at least `bytes`, behind its counters, kept
 // (and grown by doubling) from call to call, never freed; nullptr if it cannot be had, and while the
 // stream records into a graph. Work of one stream that uses it is ordered by the stream.
 float* cached_scratch(int64_t bytes, hipStream_t s);

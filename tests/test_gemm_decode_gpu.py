@@ -41,3 +41,35 @@ def test_streaming_with_bias_and_activation(M, N, K, act):
         A, B = inputs.gemm_inputs(M, N, K, dtype, 4, transB=True)
         pu.run_check_gemm_bias_act(A, B, inputs.bias_input(N, dtype, 4, std=4.0), act, dtype, transB=True)
         assert binding.mlt_last_kernel().endswith("16cols_stream")
+
+
+# columns per workgroup that make blocks of 4, 8 and 16 (one block, a ragged second one, more than a group of 8 or 4 takes),
+# up to 4 rows and beyond, one to four row tiles; K below one piece of 128, not a multiple of it, with idle wavefronts, several
+# pieces of a wavefront; K in 1 to 8 parts, some of them empty. The sum over parts and wavefronts has one order: the bits repeat.
+@pytest.mark.parametrize("M", [1, 4, 5, 16, 32, 47, 64])
+@pytest.mark.parametrize("N", [1024, 1100, 2048, 2056, 4104, 34000])
+def test_streaming_with_k_in_parts(M, N):
+    import torch
+    from paper_2503_14985_amd import binding
+    try:
+        for i, K in enumerate((8, 136, 1032, 2504) if N <= 4104 else (136, 1032)):
+            dtype = (BF16, FP16)[i % 2]
+            A, B = inputs.gemm_inputs(M, N, K, dtype, 5 + i, transB=True)
+            for parts in (1, 2, 4, 8):
+                binding.mlt_diag_force_variant(gemm="skinnydma")
+                binding.mlt_diag_force_k_parts(parts)
+                C = pu.run_gemm(A, B, dtype, transB=True)
+                pu.check_gemm(A, B, C, dtype, True, seed=i)
+                name = binding.mlt_last_kernel()
+                assert name.endswith("16cols_stream" if parts == 1 else "16cols_stream_splitk%d" % parts)
+                for _ in range(2):
+                    assert torch.equal(pu.run_gemm(A, B, dtype, transB=True).view(torch.int16), C.view(torch.int16))
+                if parts > 1 and parts * M * N * 4 <= 32 << 20:   # the fixed scratch: a second kernel adds the parts, in the same order
+                    dev = torch.device("cuda:0")
+                    tA, tB = inputs.bits_to_torch(A, dtype, dev), inputs.bits_to_torch(B, dtype, dev)
+                    D = torch.empty((M, N), dtype=tA.dtype, device=dev)
+                    binding.mlt_gemm_noalloc(tA, tB, D, transB=True)
+                    torch.cuda.synchronize()
+                    assert torch.equal(D.view(torch.int16).cpu(), C.view(torch.int16).cpu())
+    finally:
+        binding.mlt_diag_force_k_parts(0)
