@@ -42,7 +42,7 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
     const int64_t t_step = a.D == 128 ? (groups == 1 ? 550 : groups == 2 ? 800 : 780) : (groups == 1 ? 525 : groups == 2 ? 650 : 700);
     const int64_t steps = (tiles + groups * nsplit - 1) / (groups * nsplit), longest = steps * t_step;
     // with the mask a workgroup sees its share of the keys only; the longest start first, or share their CU
-    // with a short one (block_map_paired)
+    // with a short one (block_map_masked)
     const int64_t avg = a.causal && a.Sk >= a.Sq ? longest * (nq + 1) / (2 * nq) : longest;
     const int64_t rounds = (wgs + ncu - 1) / ncu;
     // start and end of a workgroup in a launch of several rounds: 256 rows of which more than half are not there cost as much
@@ -59,7 +59,7 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
     // may start behind another one (D = 64: shares its CU with it). An XCD's range ends with the last tiles of its
     // last head when it has whole heads; then the `extra` items behind the first round are the shorter ones of that head.
     // 128 / 256 rows, us: D = 128, 12 heads x 3403 82 / 72, 22 x 1574 42 / 38, but 24 x 1536 30 / 37; D = 64, 29 x 1809 38 / 35, 40 x 998
-    // 26 / 23, but 16 x 2202 33 / 41. (A full second round of D = 64 is evened out by block_map_paired.)
+    // 26 / 23, but 16 x 2202 33 / 41. (A full second round of D = 64 is evened out by block_map_masked.)
     if (a.causal && groups == 2 && rounds == 2 && one_round_of_256 && (a.D == 128 || wgs < 2 * ncu)) {
       const int64_t extra = (wgs - ncu + nxcd - 1) / nxcd;
       if (heads % nxcd != 0 || (a.D == 128 && 4 * extra >= 3 * nq)) t += longest / 2;

@@ -57,7 +57,7 @@ template <typename Tag, int D, int QW, bool SPLIT>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void mha_ks_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     uint16_t* __restrict__ O, float* __restrict__ po, float* __restrict__ ps, int Sq, int Sk, int nq,
-    int total, int nxcd, float c, int negate, int causal) {
+    int total, int nxcd, MaskedMap map, float c, int negate, int causal) {
   typedef KsCfg<D, QW> L;
   typedef PaCfg<D> P;                              // swizzles
   typedef typename Elem<Tag>::vec8 V8;
@@ -70,8 +70,8 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void mha_ks_kernel(
   const bool late = wave >= 4;                     // the half of a SIMD's wavefronts that runs X before C
   const int lq = lane & 31, h = lane >> 5;
   int bh, qt;
-  if (D == 64) block_map_paired(blockIdx.x, total, nq, nxcd, bh, qt);
-  else block_map(blockIdx.x, total, nq, nxcd, bh, qt);
+  if (map.chunk > 0) block_map_masked(blockIdx.x, nq, nxcd, map, bh, qt);
+  else block_map(blockIdx.x, total, nq, nxcd & 255, bh, qt);
   const int q0 = qt * L::BM + qw * 32;             // first query row of this wavefront
   const int my_q = q0 + lq;
 
@@ -418,9 +418,10 @@ int launch_ks(const MhaArgs& a, int nsplit, float* scratch, hipStream_t s) {
   float c = (a.scale < 0 ? -a.scale : a.scale) * 1.4426950408889634f;   // c > 0 always, as in launch_mha_pp
   if (c < 1e-30f) c = 1e-30f;
   float* ps = SPLIT ? scratch + (int64_t)nsplit * rows * D : nullptr;
+  const int xcds = mha_xcd_word((int)total, a.causal, D, 32);
   hipLaunchKernelGGL(kern, dim3((unsigned)total, SPLIT ? nsplit : 1), dim3(512), L::SMEM, s, a.Q, a.K, a.V, a.O, scratch, ps,
                      (int)a.Sq, (int)a.Sk, (int)nq, (int)total,
-                     mha_xcd_word((int)total, a.causal, D, 32), c, a.scale < 0 ? 1 : 0, a.causal);
+                     xcds, masked_map((int)total, (int)nq, (int)a.Sq, L::BM, a.causal, D, xcds), c, a.scale < 0 ? 1 : 0, a.causal);
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
   if (!SPLIT) return MLT_OK;
   hipLaunchKernelGGL((mha_ks_merge_kernel<Tag, D>), dim3((unsigned)((rows * (D / 8) + 255) / 256)), dim3(256), 0, s,

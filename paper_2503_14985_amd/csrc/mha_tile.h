@@ -57,22 +57,78 @@ __device__ __forceinline__ void block_map(int bid, int total, int nq, int nxcd, 
   qt = nq - 1 - logical % nq;
 }
 
-// The same for the masked problem on two workgroups per CU when all of them are resident at once
-// (cus: CUs per XCD, in bits 8 and up of nxcd_cus; 0 for any other launch): a CU then keeps the items
-// i and i + cus of its XCD's range, and with the plain map both can be last tiles. Every second block of
-// `cus` items is walked backwards, so that a long item shares its CU with a short one (D = 64, 8 x 32
-// heads, 512 x 512: 24.2 -> 21.8 us; 1 x 32, 2048 x 2048 on 128-row tiles: 43.5 -> 32.3 us).
-__device__ __forceinline__ void block_map_paired(int bid, int total, int nq, int nxcd_cus, int& bh, int& qt) {
+// The same for the masked problem, whose last query tiles take longest. An XCD's items, in the order above, are cut into chunks,
+// and a chunk's are taken longest first, the last tiles of all its heads, then the tiles before them, and so on: the launch ends
+// with short items, where whole heads, one after the other, left long items that started late to run alone (us, heads one by one / chunks, D = 128:
+// 32 x 16 x 1024 242 / 201, 3 x 16 x 1693 58 / 48, 31 x 8 x 945 112 / 98; D = 64: 32 x 32 x 1024 258 / 227, 10 x 16 x 1778 100 / 91).
+// cus (CUs per XCD, in bits 8 and up of nxcd_cus; 0 for other launches): all items are resident at once, one or two per CU, and
+// the XCD's items i and i + cus share a CU. The longest that have to share one do so with the shortest, and those
+// that do not are the longest of all (D = 64, 8 x 32 heads, 512 x 512: 24.2 -> 21.8 us).
+struct MaskedMap {
+  int per, rem;                 // items per XCD, and how many XCDs have one more
+  int chunk;                    // 0: plain order (block_map)
+  float r_nxcd, r_chunk, r_nq;  // reciprocals of the divisors
+};
+// a / b for 0 <= a < 2^20 (an integer division takes the start of a workgroup 0.1 us)
+__host__ __device__ inline int small_div(int a, int b, float r) {
+  int q = (int)((float)a * r);
+  q -= q * b > a ? 1 : 0;
+  return q + (a - q * b >= b ? 1 : 0);
+}
+__host__ __device__ inline void block_map_masked(int bid, int nq, int nxcd_cus, const MaskedMap& m, int& bh, int& qt) {
   const int nxcd = nxcd_cus & 255, cus = nxcd_cus >> 8;
-  int logical = logical_block(bid, total, nxcd);
-  if (cus > 0) {
-    const int first = logical_block(bid % nxcd, total, nxcd), i = logical - first;   // place in the XCD's range
-    const int n = total / nxcd + (bid % nxcd < total % nxcd ? 1 : 0);
-    const int blk = i / cus * cus;
-    if ((i / cus & 1) && blk + cus <= n) logical = first + blk + (cus - 1 - (i - blk));
+  int k = small_div(bid, nxcd, m.r_nxcd);
+  const int xcd = bid - k * nxcd;
+  int first = xcd * m.per + (xcd < m.rem ? xcd : m.rem), n = m.per + (xcd < m.rem ? 1 : 0);
+  if (cus > 0 && n >= cus && n <= 2 * cus) {
+    const int two = n - cus;                               // CUs with two items
+    k = k >= cus ? n - 1 - (k - cus) : k < two ? cus - two + k : k - two;
+  } else {
+    const int skip = small_div(k, m.chunk, m.r_chunk) * m.chunk;
+    k -= skip;
+    first += skip;
+    n = n - skip < m.chunk ? n - skip : m.chunk;
   }
-  bh = logical / nq;
-  qt = nq - 1 - logical % nq;
+  // the k-th of the items first .. first + n - 1 by falling tile. Item i is tile nq - 1 - j, j = i % nq, of head i / nq: `rows` or
+  // rows + 1 items of every j, one more of the n % nq values from j0 on (modulo nq)
+  const int rows = small_div(n, nq, m.r_nq), more = n - rows * nq, h0 = small_div(first, nq, m.r_nq), j0 = first - h0 * nq;
+  const int wrap = j0 + more - nq;
+  auto before = [&](int j) {                               // items with a smaller j
+    const int ext = wrap <= 0 ? (j - j0 < 0 ? 0 : j - j0 < more ? j - j0 : more) : (j < wrap ? j : wrap) + (j > j0 ? j - j0 : 0);
+    return j * rows + ext;
+  };
+  int j = small_div(k, rows + 1, 1.f / (float)(rows + 1));     // (every j before the right one has at most rows + 1 items, ...
+  if (rows > 0 && k > more) {                             // ... and all but `more` of them only `rows`)
+    const int j1 = small_div(k - more, rows, 1.f / (float)rows);
+    j = j1 > j ? j1 : j;
+  }
+  while (before(j + 1) <= k) ++j;
+  bh = h0 + (j < j0 ? 1 : 0) + (k - before(j));
+  qt = nq - 1 - j;
+}
+// Chunks of one launch's worth of resident workgroups for D = 128 and short sequences (their K and V are the 4 MB of an XCD's L2), of
+// two otherwise (us, chunks of one / two / four: D = 128, 32 x 16 x 1024 201 / 204 / 221, 16 x 16 x 2048 313 / 322 / 325, 8 x 16 x 4096 543 /
+// 537 / 550, 4 x 16 x 8192 1018 / 991 / 984; D = 64, 32 x 32 x 1024 231 / 227 / 231, 4 x 32 x 8192 1229 / 1171 / 1176; only the last two
+// launches' worth sorted, the rest head by head: 235, 345 and 253 us for the three that begin with 32 and 16).
+// The plain order stays where all items, or all but the shorter ones of the last head, are resident at once and not paired, where
+// an XCD has no two heads, for launches too large for small_div, and for two or three tiles of which the last is at most half full: half of its workgroup's
+// wavefronts have nothing to do, so the order of the tiles is not that of their lengths (11 x 16 x 640 44.8 us head by head, 52 sorted;
+// 31 x 32 x 540, D = 64, 114, 118).
+inline MaskedMap masked_map(int total, int nq, int Sq, int bm, bool causal, int D, int nxcd_cus, const DeviceInfo& di) {
+  MaskedMap m{0, 0, 0, 0.f, 0.f, 0.f};
+  const int nxcd = nxcd_cus & 255, ncu = di.ncu > 0 ? di.ncu : 256, per = total / nxcd, n = per + (total % nxcd ? 1 : 0);
+  const int slots = ncu / nxcd * (D == 64 ? 2 : 1);
+  if (!causal || nq < 2 || total >= 1 << 20 || slots < 1) return m;
+  if (nxcd_cus < 256 && (8 * (n - slots) <= 5 * nq || n < 2 * nq || (nq <= 3 && 2 * (Sq - (nq - 1) * bm) <= bm))) return m;
+  const int least = slots * (D == 128 && nq <= 8 ? 1 : 2), chunks = n >= least ? n / least : 1;
+  m.per = per; m.rem = total % nxcd; m.chunk = (n + chunks - 1) / chunks;
+  m.r_nxcd = 1.f / (float)nxcd; m.r_chunk = 1.f / (float)m.chunk; m.r_nq = 1.f / (float)nq;
+  return m;
+}
+inline MaskedMap masked_map(int total, int nq, int Sq, int bm, bool causal, int D, int nxcd_cus) {
+  DeviceInfo di;
+  (void)device_info(di);
+  return masked_map(total, nq, Sq, bm, causal, D, nxcd_cus, di);
 }
 // what a launch of `total` workgroups adds to the XCD count for that map
 inline int paired_cus(int total, bool causal, int D, const DeviceInfo& di) {
@@ -80,7 +136,7 @@ inline int paired_cus(int total, bool causal, int D, const DeviceInfo& di) {
   return total > di.ncu && total <= 2 * di.ncu ? di.ncu / di.nxcd << 8 : 0;
 }
 // The XCD word of a launch: their count, and for the kernels that decode it (all but the one on 16x16x32 MFMAs,
-// which uses the plain map) the paired map's CUs.
+// which uses the plain map) the CUs for pairs.
 inline int mha_xcd_word(int total, bool causal, int D, int mfma_size, const DeviceInfo& di) {
   return (di.nxcd > 0 ? di.nxcd : 8) + (mfma_size == 32 ? paired_cus(total, causal, D, di) : 0);
 }

@@ -5,6 +5,7 @@
 //   mha B H Sq Sk D causal   ->  name ranges
 //   paged B H D block_size max_blocks   ->  ranges dealt_by_length ("paged_split": and a forced number of ranges)
 //   xcdword workgroups causal D mfma_size   ->  what an attention launch passes as its XCD count
+//   masked workgroups query_tiles Sq D   ->  head:tile of each workgroup of a masked attention launch
 //   deal pieces CUs   ->  the rank of the piece that each workgroup takes
 #include <stdio.h>
 #include <string.h>
@@ -55,6 +56,20 @@ int main() {
       DeviceInfo di;
       di.ncu = 256; di.nxcd = 8; di.gfx950 = true;
       printf("%d\n", mha_xcd_word(total, causal != 0, D, mfma, di));
+    } else if (!strcmp(op, "masked")) {
+      int total, nq, Sq, D;
+      if (scanf("%d %d %d %d", &total, &nq, &Sq, &D) != 4) return 1;
+      DeviceInfo di;
+      di.ncu = 256; di.nxcd = 8; di.gfx950 = true;
+      const int word = mha_xcd_word(total, true, D, 32, di);
+      const MaskedMap m = masked_map(total, nq, Sq, 256, true, D, word, di);
+      if (m.chunk <= 0) printf("plain");
+      for (int b = 0; b < total && m.chunk > 0; ++b) {
+        int bh, qt;
+        block_map_masked(b, nq, word, m, bh, qt);
+        printf("%d:%d ", bh, qt);
+      }
+      printf("\n");
     } else if (!strcmp(op, "deal")) {
       int total, ncu;
       if (scanf("%d %d", &total, &ncu) != 2) return 1;

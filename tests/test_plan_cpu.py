@@ -157,3 +157,29 @@ def test_the_batches_of_the_order_test_are_dealt_by_length(plan):
     lines = ["paged_split %d %d %d 16 %d %d" % (B, H, D, -(-longest(B, H, ranges, D) // 16), ranges) for B, H, ranges, D, _ in CASES]
     for (B, H, ranges, D, _), ans in zip(CASES, plan(lines)):
         assert ans == "%d %d" % (ranges, B <= 256), (B, H, ranges, D)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("heads,Sq", [(1024, 1024), (512, 2048), (128, 8192), (300, 1280), (161, 700), (64, 4096), (100, 768), (57, 1600), (64, 2048), (71, 2000),
+                                      (29, 4096), (33, 1100), (10, 9472), (35, 512), (9, 12800), (257, 500), (86, 640), (1000, 540), (19, 999)])
+def test_masked_attention_ends_with_short_items(plan, D, heads, Sq):
+    """Every item once; and an XCD's workgroups, each started where one has ended (two per CU for D = 64), end together but for less
+    than half of the longest item (head after head it was up to all of it)."""
+    nq = -(-Sq // 256)
+    ans = plan(["masked %d %d %d %d" % (heads * nq, nq, Sq, D)])[0]
+    if ans == "plain":    # all resident at once, one per CU; no XCD has two heads; two or three tiles, the last not half full
+        assert heads * nq <= (512 if D == 64 else 256) + 5 * nq or heads < 16 or (nq <= 3 and (Sq - 1) % 256 < 128)
+        return
+    items = [tuple(map(int, x.split(":"))) for x in ans.split()]
+    assert sorted(items) == [(h, q) for h in range(heads) for q in range(nq)]
+    for xcd in range(8):
+        mine = [4 * (q + 1) for _, q in items[xcd::8]]
+        if D == 64 and heads * nq <= 512:                   # pairs: the items i and i + 32 of an XCD share a CU
+            pairs, alone = [a + b for a, b in zip(mine, mine[32:])], mine[max(0, len(mine) - 32):32]
+            assert not pairs or max(pairs) - min(pairs) <= max(mine) / 2
+            assert not alone or not pairs or min(alone) >= max(mine[:len(pairs)])
+            continue
+        load = [0] * (64 if D == 64 else 32)
+        for c in mine:
+            load[load.index(min(load))] += 2 + c
+        assert max(load) <= sum(load) / len(load) + (2 + max(mine)) / 2
