@@ -26,10 +26,11 @@ DIAG_EXPORTS = ("mlt_probe_mfma", "mlt_probe_mfma16", "mlt_probe_hbm_read", "mlt
                 "mlt_last_kernel", "mlt_query_tiling", "mlt_diag_force_variant",
                 "mlt_diag_force_k_parts", "mlt_diag_force_key_split", "mlt_diag_set_persistent_grid")
 
-if not os.path.exists(LIB_PATH):
+FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
+if not (os.path.exists(LIB_PATH) and os.path.exists(FASTCALL_PATH)):
     raise ImportError(
-        "libmlt.so is not built (%s). Run `python -c 'import __graft_entry__ as g; g.build_lib()'` "
-        "from the repository root; there is no CPU fallback." % LIB_PATH)
+        "libmlt.so and _fastcall.so are not built (%s). Run `python -c 'import __graft_entry__ as g; g.build_lib()'` "
+        "from the repository root; there is no CPU fallback." % _HERE)
 
 _lib = ctypes.CDLL(LIB_PATH)
 # What torch.cuda.current_stream(i).cuda_stream and torch.cuda.current_device() return, without the objects
@@ -75,6 +76,13 @@ _lib.mlt_diag_set_persistent_grid.argtypes = [_i32]
 _lib.mlt_status_string.restype = ctypes.c_char_p
 _lib.mlt_status_string.argtypes = [_i32]
 _lib.mlt_version.restype = ctypes.c_char_p
+
+# The usual case of a call (plain GPU tensors, an output given, no stream) goes through native code (csrc/fastcall.cpp), which returns
+# None for everything else: the functions below then marshal, allocate or raise. (us per mlt_gemm call of 16 x 64 x 64 back to back:
+# 7.5 without, 3.8 with; the library's and the runtime's own part is 3.1.)
+from . import _fastcall as _fast  # noqa: E402
+_fast.bind(*(ctypes.cast(getattr(_lib, _f), _p).value for _f in ("mlt_gemm", "mlt_gemm_bias_act", "mlt_gemm_acc", "mlt_mha_fwd",
+                                                                "mlt_paged_attn_decode")))
 
 
 class MltError(RuntimeError):
@@ -134,6 +142,9 @@ def mlt_paged_attn_decode(Q: torch.Tensor, Kc: torch.Tensor, Vc: torch.Tensor,
                           O: torch.Tensor = None) -> torch.Tensor:
     """Q [B,H,D]; Kc, Vc [num_blocks,H,block_size,D]; block_table int32 [B,max_blocks]; seq_lens
     int32 [B]; returns O [B,H,D]. All on the GPU, contiguous."""
+    done = _fast.paged_attn_decode(Q, Kc, Vc, block_table, seq_lens, scale, O)
+    if done is not None:
+        return done
     B, H, D = Q.shape
     nb, Hc, bs, Dc = Kc.shape
     if (Hc, Dc) != (H, D) or Vc.shape != Kc.shape or Vc.dtype != Q.dtype or Kc.dtype != Q.dtype:
@@ -271,6 +282,9 @@ def mlt_gemm(A: torch.Tensor, B: torch.Tensor, C: torch.Tensor | None = None, tr
     """C = A @ B (transB=False, B is [K, N]) or C = A @ B.T (transB=True, B is [N, K]).
 
     Row strides of A, B and C are passed through as lda/ldb/ldc, so row-sliced views work."""
+    done = _fast.gemm(A, B, C, transB, stream)
+    if done is not None:
+        return done
     M, N, K, lda, ldb, ldc, dt, C = _gemm_operands("mlt_gemm", A, B, C, transB)
     with _OtherDevice(A.device):
         rc = _lib.mlt_gemm(M, N, K, A.data_ptr(), lda, B.data_ptr(), ldb, int(transB),
@@ -315,6 +329,9 @@ def mlt_gemm_bias_act(A: torch.Tensor, B: torch.Tensor, bias: torch.Tensor | Non
                       stream=None) -> torch.Tensor:
     """C = act(A @ B + bias) (or A @ B.T), bias a contiguous [N] tensor of the input dtype or None,
     act one of ACT_NONE / ACT_RELU / ACT_GELU."""
+    done = _fast.gemm_bias_act(A, B, bias, act, C, transB, stream)
+    if done is not None:
+        return done
     M, N, K, lda, ldb, ldc, dt, C = _gemm_operands("mlt_gemm_bias_act", A, B, C, transB)
     if bias is not None and (not bias.is_cuda or bias.dtype != A.dtype or tuple(bias.shape) != (N,)
                              or not bias.is_contiguous()):
@@ -331,6 +348,9 @@ def mlt_gemm_bias_act(A: torch.Tensor, B: torch.Tensor, bias: torch.Tensor | Non
 def mlt_gemm_acc(A: torch.Tensor, B: torch.Tensor, C: torch.Tensor, transB: bool = False,
                  stream=None) -> torch.Tensor:
     """C += A @ B (or A @ B.T) with C an fp32 [M, N] tensor that is read and written."""
+    done = _fast.gemm_acc(A, B, C, transB, stream)
+    if done is not None:
+        return done
     if C is None:
         raise ValueError("mlt_gemm_acc needs the fp32 C it accumulates into")
     M, N, K, lda, ldb, ldc, dt, C = _gemm_operands("mlt_gemm_acc", A, B, C, transB, torch.float32)
@@ -345,6 +365,9 @@ def mlt_gemm_acc(A: torch.Tensor, B: torch.Tensor, C: torch.Tensor, transB: bool
 def mlt_mha_fwd(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, scale: float,
                 causal: bool = False, O: torch.Tensor | None = None, stream=None) -> torch.Tensor:
     """O = softmax(scale * Q K^T [+ causal mask]) V for contiguous [B, H, S, D] tensors."""
+    done = _fast.mha_fwd(Q, K, V, scale, causal, O, stream)
+    if done is not None:
+        return done
     if not (Q.is_cuda and K.is_cuda and V.is_cuda):
         raise ValueError("mlt_mha_fwd needs GPU tensors")
     dt = _dtype_code(Q)
