@@ -53,11 +53,11 @@ template <int D, int QW> struct KsCfg {
 // O (SPLIT = false), or, when blockIdx.y selects one of gridDim.y ranges of the key tiles, that range's
 // fp32 partial result: outputs not yet divided by the sum, po[range][row][D], and maximum (log2
 // domain) and sum, ps[range][row][2], with `row` counting all batch * heads * Sq rows.
-template <typename Tag, int D, int QW, bool SPLIT>
+template <typename Tag, int D, int QW, bool SPLIT, bool CAUSAL>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void mha_ks_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ V,
     uint16_t* __restrict__ O, float* __restrict__ po, float* __restrict__ ps, int Sq, int Sk, int nq,
-    int total, int nxcd, MaskedMap map, float c, int negate, int causal) {
+    int total, int nxcd, float c, int negate, MaskedMap map) {
   typedef KsCfg<D, QW> L;
   typedef PaCfg<D> P;                              // swizzles
   typedef typename Elem<Tag>::vec8 V8;
@@ -70,8 +70,8 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void mha_ks_kernel(
   const bool late = wave >= 4;                     // the half of a SIMD's wavefronts that runs X before C
   const int lq = lane & 31, h = lane >> 5;
   int bh, qt;
-  if (map.chunk > 0) block_map_masked(blockIdx.x, nq, nxcd, map, bh, qt);
-  else block_map(blockIdx.x, total, nq, nxcd & 255, bh, qt);
+  if (CAUSAL && map.chunk > 0) block_map_masked(blockIdx.x, nq, nxcd, map, bh, qt);
+  else block_map(blockIdx.x, total, nq, CAUSAL ? nxcd & 255 : nxcd, bh, qt);
   const int q0 = qt * L::BM + qw * 32;             // first query row of this wavefront
   const int my_q = q0 + lq;
 
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void mha_ks_kernel(
 
   // key tiles of this workgroup: those its last query row sees (all without the mask), or a range of them
   int kv_len = Sk;
-  if (causal) {
+  if (CAUSAL) {
     const int last_q = (qt + 1) * L::BM < Sq ? (qt + 1) * L::BM : Sq;     // exclusive
     kv_len = last_q < Sk ? last_q : Sk;
   }
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void mha_ks_kernel(
   // masked (causal, or the last tile reaches past Sk)
   int Tw = q0 < Sq ? Tg : 0;
   int t_mask = Tg - 1 >= 0 && (tb + kg + (Tg - 1) * KW + 1) * L::KEYS > Sk ? Tg - 1 : Tg;
-  if (causal) {
+  if (CAUSAL) {
     const int last = (q0 + 31) / L::KEYS - tb - kg;                // tiles up to the one of this wavefront's last row
     const int vis = last >= 0 ? last / KW + 1 : 0;
     Tw = Tw < vis ? Tw : vis;
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void mha_ks_kernel(
   // then -inf and the weights are taken against 0, which makes them exp2(-inf) = 0.
   auto softmax = [&](int t) __attribute__((always_inline)) {
     if (t >= t_mask) {
-      const int limit = causal && my_q < Sk - 1 ? my_q : Sk - 1;      // last visible key
+      const int limit = CAUSAL && my_q < Sk - 1 ? my_q : Sk - 1;      // last visible key
       const int rel = limit - ((tb + kg + t * KW) * L::KEYS + 4 * h);
 #pragma unroll
       for (int r = 0; r < 16; ++r)
@@ -399,10 +399,10 @@ __global__ __launch_bounds__(256) void mha_ks_merge_kernel(const float* __restri
             Elem<Tag>::pack2(hi[0] * inv, hi[1] * inv), Elem<Tag>::pack2(hi[2] * inv, hi[3] * inv)};
 }
 
-template <typename Tag, int D, int QW, bool SPLIT>
+template <typename Tag, int D, int QW, bool SPLIT, bool CAUSAL>
 int launch_ks(const MhaArgs& a, int nsplit, float* scratch, hipStream_t s) {
   typedef KsCfg<D, QW> L;
-  auto kern = mha_ks_kernel<Tag, D, QW, SPLIT>;
+  auto kern = mha_ks_kernel<Tag, D, QW, SPLIT, CAUSAL>;
   static thread_local int configured_dev = -1;          // opt in to > 64 KB LDS once per device
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MLT_ERR_DEVICE;
@@ -418,10 +418,10 @@ int launch_ks(const MhaArgs& a, int nsplit, float* scratch, hipStream_t s) {
   float c = (a.scale < 0 ? -a.scale : a.scale) * 1.4426950408889634f;   // c > 0 always, as in launch_mha_pp
   if (c < 1e-30f) c = 1e-30f;
   float* ps = SPLIT ? scratch + (int64_t)nsplit * rows * D : nullptr;
-  const int xcds = mha_xcd_word((int)total, a.causal, D, 32);
+  const int xcds = mha_xcd_word((int)total, CAUSAL, D, 32);
   hipLaunchKernelGGL(kern, dim3((unsigned)total, SPLIT ? nsplit : 1), dim3(512), L::SMEM, s, a.Q, a.K, a.V, a.O, scratch, ps,
                      (int)a.Sq, (int)a.Sk, (int)nq, (int)total,
-                     xcds, masked_map((int)total, (int)nq, (int)a.Sq, L::BM, a.causal, D, xcds), c, a.scale < 0 ? 1 : 0, a.causal);
+                     xcds, c, a.scale < 0 ? 1 : 0, masked_map((int)total, (int)nq, (int)a.Sq, L::BM, CAUSAL, D, xcds));
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
   if (!SPLIT) return MLT_OK;
   hipLaunchKernelGGL((mha_ks_merge_kernel<Tag, D>), dim3((unsigned)((rows * (D / 8) + 255) / 256)), dim3(256), 0, s,
@@ -429,10 +429,16 @@ int launch_ks(const MhaArgs& a, int nsplit, float* scratch, hipStream_t s) {
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 
+template <typename Tag, int D, int QW>
+int run_ks_q(const MhaArgs& a, int nsplit, float* scratch, hipStream_t s) {
+  if (a.causal) return nsplit > 1 ? launch_ks<Tag, D, QW, true, true>(a, nsplit, scratch, s) : launch_ks<Tag, D, QW, false, true>(a, 1, nullptr, s);
+  return nsplit > 1 ? launch_ks<Tag, D, QW, true, false>(a, nsplit, scratch, s) : launch_ks<Tag, D, QW, false, false>(a, 1, nullptr, s);
+}
+
 template <typename Tag, int D>
 int run_ks_t(const MhaArgs& a, int bm, int nsplit, float* scratch, hipStream_t s) {
-  if (bm == 64) return nsplit > 1 ? launch_ks<Tag, D, 2, true>(a, nsplit, scratch, s) : launch_ks<Tag, D, 2, false>(a, 1, nullptr, s);
-  return nsplit > 1 ? launch_ks<Tag, D, 4, true>(a, nsplit, scratch, s) : launch_ks<Tag, D, 4, false>(a, 1, nullptr, s);
+  if (bm == 64) return run_ks_q<Tag, D, 2>(a, nsplit, scratch, s);
+  return run_ks_q<Tag, D, 4>(a, nsplit, scratch, s);
 }
 
 }  // namespace

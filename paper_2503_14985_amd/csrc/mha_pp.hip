@@ -41,7 +41,7 @@ template <typename Tag, int D, bool CAUSAL>
 __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, uint16_t* __restrict__ O, int Sq, int Sk, int nq, int total,
-    int nxcd, MaskedMap map, float c, int negate) {
+    int nxcd, float c, int negate, MaskedMap map) {
   typedef PaCfg<D> L;
   typedef typename Elem<Tag>::vec8 V8;
   constexpr int NKK = L::NKK, NDT = L::NDT, ROWB = L::ROWB;
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp_kernel(
   const int lq = lane & 31, h = lane >> 5;
   int bh, qt;
   if (CAUSAL && map.chunk > 0) block_map_masked(blockIdx.x, nq, nxcd, map, bh, qt);
-  else block_map(blockIdx.x, total, nq, nxcd & 255, bh, qt);
+  else block_map(blockIdx.x, total, nq, CAUSAL ? nxcd & 255 : nxcd, bh, qt);
   const int q0 = qt * PA_BM + wave * 32;                 // first query row of this wavefront
   const int my_q = q0 + lq;
 
@@ -854,7 +854,7 @@ template <typename Tag, int D, bool CAUSAL>
 __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
     const uint16_t* __restrict__ V, uint16_t* __restrict__ O, int Sq, int Sk, int nq, int total,
-    int nxcd, MaskedMap, float c, int negate) {
+    int nxcd, float c, int negate, MaskedMap) {
   typedef PaCfg<D> L;
   typedef typename Elem<Tag>::vec8 V8;
   constexpr int NDS = D / 32;                            // 32-deep d slices of S^T = K Q^T
@@ -1221,7 +1221,7 @@ int launch_mha_pp(const MhaArgs& a, hipStream_t s) {
   if (c < 1e-30f) c = 1e-30f;
   const int xcds = mha_xcd_word((int)total, CAUSAL, D, MS);
   hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(PA_NT), L::SMEM, s, a.Q, a.K, a.V, a.O,
-                     (int)a.Sq, (int)a.Sk, nq, (int)total, xcds, masked_map((int)total, nq, (int)a.Sq, PA_BM, CAUSAL, D, xcds), c, a.scale < 0 ? 1 : 0);
+                     (int)a.Sq, (int)a.Sk, nq, (int)total, xcds, c, a.scale < 0 ? 1 : 0, masked_map((int)total, nq, (int)a.Sq, PA_BM, CAUSAL, D, xcds));
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 
