@@ -77,18 +77,19 @@ _lib.mlt_status_string.restype = ctypes.c_char_p
 _lib.mlt_status_string.argtypes = [_i32]
 _lib.mlt_version.restype = ctypes.c_char_p
 
-# The usual case of a call (plain GPU tensors, an output given, no stream) goes through native code (csrc/fastcall.cpp), which returns
-# None for everything else: the functions below then marshal, allocate or raise. (us per mlt_gemm call of 16 x 64 x 64 back to back:
-# 7.5 without, 3.8 with; the library's and the runtime's own part is 3.1.)
-from . import _fastcall as _fast  # noqa: E402
-_fast.bind(*(ctypes.cast(getattr(_lib, _f), _p).value for _f in ("mlt_gemm", "mlt_gemm_bias_act", "mlt_gemm_acc", "mlt_mha_fwd",
-                                                                "mlt_paged_attn_decode")))
-
 
 class MltError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
         super().__init__("%s: %s (%d)" % (where, mlt_status_string(status), status))
+
+
+# The usual case of a call (plain GPU tensors, an output given, no stream) goes through native code (csrc/fastcall.cpp), which returns
+# None for everything else: the functions below then marshal, allocate or raise. A call that the library refuses raises there.
+# (us per mlt_gemm call of 16 x 64 x 64 back to back: 7.5 without, 3.8 with; the library's and the runtime's own part is 3.1.)
+from . import _fastcall as _fast  # noqa: E402
+_fast.bind(MltError, *(ctypes.cast(getattr(_lib, _f), _p).value for _f in ("mlt_gemm", "mlt_gemm_bias_act", "mlt_gemm_acc", "mlt_mha_fwd",
+                                                                          "mlt_paged_attn_decode")))
 
 
 def raw():

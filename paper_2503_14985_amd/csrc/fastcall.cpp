@@ -1,8 +1,10 @@
 // The entry points' usual case in native code: what binding.py does with the tensors of a call (their sizes, strides, types and
 // addresses, the current stream) took 3.5 of the 7.3 us of a small one, as much as the library and the runtime; here 0.4.
 // A function looks at its arguments as binding.py passes them on. Where they are plain tensors on the current GPU of the shapes and types that
-// the entry point takes, with an output tensor given and no stream, it makes the call and returns the output. Everything else, and
-// a call that the library refuses, returns None: binding.py then goes through it step by step, allocates, or raises.
+// the entry point takes, with an output tensor given and no stream, it makes the call and returns the output, or raises what
+// the library's status stands for: the call is made once (a second one could succeed after a launch error that an
+// earlier call had left, and an accumulating GEMM would have added twice). Everything else returns None: binding.py then goes
+// through it step by step, allocates, or raises.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -20,6 +22,7 @@ decltype(&mlt_gemm_bias_act) call_gemm_bias_act;
 decltype(&mlt_gemm_acc) call_gemm_acc;
 decltype(&mlt_mha_fwd) call_mha_fwd;
 decltype(&mlt_paged_attn_decode) call_paged;
+PyObject* error_class;      // binding.MltError(status, where)
 
 // A plain tensor with memory of its own kind on GPU `device` (-1: the first one sets it), or null
 const at::Tensor* plain(PyObject* o, int& device) {
@@ -74,10 +77,16 @@ bool gemm_operands(PyObject* A, PyObject* B, PyObject* C, bool transB, bool c_is
   return true;
 }
 
-PyObject* result(int rc, PyObject* out) {
-  PyObject* r = rc == MLT_OK ? out : Py_None;
-  Py_INCREF(r);
-  return r;
+PyObject* result(int rc, PyObject* out, const char* where) {
+  if (rc != MLT_OK) {
+    if (PyObject* e = PyObject_CallFunction(error_class, "is", rc, where)) {
+      PyErr_SetObject(error_class, e);
+      Py_DECREF(e);
+    }
+    return nullptr;
+  }
+  Py_INCREF(out);
+  return out;
 }
 
 // gemm(A, B, C, transB, stream)
@@ -88,7 +97,7 @@ PyObject* py_gemm(PyObject*, PyObject* const* v, Py_ssize_t n) {
   Py_BEGIN_ALLOW_THREADS
   rc = call_gemm(g.M, g.N, g.K, g.a, g.lda, g.b, g.ldb, v[3] == Py_True, g.c, g.ldc, g.dtype, g.stream);
   Py_END_ALLOW_THREADS
-  return result(rc, v[2]);
+  return result(rc, v[2], "mlt_gemm");
 }
 
 // gemm_acc(A, B, C, transB, stream)
@@ -99,7 +108,7 @@ PyObject* py_gemm_acc(PyObject*, PyObject* const* v, Py_ssize_t n) {
   Py_BEGIN_ALLOW_THREADS
   rc = call_gemm_acc(g.M, g.N, g.K, g.a, g.lda, g.b, g.ldb, v[3] == Py_True, (float*)g.c, g.ldc, g.dtype, g.stream);
   Py_END_ALLOW_THREADS
-  return result(rc, v[2]);
+  return result(rc, v[2], "mlt_gemm_acc");
 }
 
 // gemm_bias_act(A, B, bias, act, C, transB, stream)
@@ -119,7 +128,7 @@ PyObject* py_gemm_bias_act(PyObject*, PyObject* const* v, Py_ssize_t n) {
   Py_BEGIN_ALLOW_THREADS
   rc = call_gemm_bias_act(g.M, g.N, g.K, g.a, g.lda, g.b, g.ldb, v[5] == Py_True, bias, (int)act, g.c, g.ldc, g.dtype, g.stream);
   Py_END_ALLOW_THREADS
-  return result(rc, v[4]);
+  return result(rc, v[4], "mlt_gemm_bias_act");
 }
 
 // mha_fwd(Q, K, V, scale, causal, O, stream)
@@ -146,7 +155,7 @@ PyObject* py_mha_fwd(PyObject*, PyObject* const* v, Py_ssize_t n) {
   Py_BEGIN_ALLOW_THREADS
   rc = call_mha_fwd(B, H, Sq, Sk, D, p[0], p[1], p[2], p[3], scale, v[4] == Py_True, dtype, stream);
   Py_END_ALLOW_THREADS
-  return result(rc, v[5]);
+  return result(rc, v[5], "mlt_mha_fwd");
 }
 
 // paged_attn_decode(Q, Kc, Vc, block_table, seq_lens, scale, O)
@@ -176,7 +185,7 @@ PyObject* py_paged(PyObject*, PyObject* const* v, Py_ssize_t n) {
   Py_BEGIN_ALLOW_THREADS
   rc = call_paged(B, H, D, block, blocks, num, p[0], p[1], p[2], (const int32_t*)p[3], (const int32_t*)p[4], p[5], scale, dtype, stream);
   Py_END_ALLOW_THREADS
-  return result(rc, v[6]);
+  return result(rc, v[6], "mlt_paged_attn_decode");
 }
 
 // A torch error in here (a tensor without memory behind it, say) is binding.py's to meet again
@@ -190,10 +199,13 @@ PyObject* guarded(PyObject* self, PyObject* const* v, Py_ssize_t n) {
   }
 }
 
-// bind(gemm, gemm_bias_act, gemm_acc, mha_fwd, paged_attn_decode): the library functions' addresses
+// bind(error class, gemm, gemm_bias_act, gemm_acc, mha_fwd, paged_attn_decode): the library functions' addresses
 PyObject* py_bind(PyObject*, PyObject* args) {
   Py_ssize_t a[5];
-  if (!PyArg_ParseTuple(args, "nnnnn", &a[0], &a[1], &a[2], &a[3], &a[4])) return nullptr;
+  PyObject* err;
+  if (!PyArg_ParseTuple(args, "Onnnnn", &err, &a[0], &a[1], &a[2], &a[3], &a[4])) return nullptr;
+  Py_INCREF(err);
+  error_class = err;
   call_gemm = reinterpret_cast<decltype(call_gemm)>(a[0]);
   call_gemm_bias_act = reinterpret_cast<decltype(call_gemm_bias_act)>(a[1]);
   call_gemm_acc = reinterpret_cast<decltype(call_gemm_acc)>(a[2]);

@@ -499,7 +499,8 @@ int run_gemm(const GemmArgs& g_in, GemmPlan& p, hipStream_t s) {
   if (p.parts > 1 && !g.scratch) {
     g.scratch = cached_scratch(p.scratch_bytes, s);
     if (g.scratch) {
-      g.counters = scratch_counters(g.scratch);
+      // (hipStreamPerThread is another stream in each thread: calls that overlap would leave the counters in disorder)
+      if (s != hipStreamPerThread) g.counters = scratch_counters(g.scratch);
     } else {
       void* ws = nullptr;
       if (!stream_is_capturing(s) && hipMallocAsync(&ws, (size_t)p.scratch_bytes, s) == hipSuccess && ws) {

@@ -73,7 +73,8 @@ def test_what_the_native_path_leaves_alone():
     assert f.gemm_bias_act(t["A"], t["B"], t["bias"], 7, C, False, None) is None
     assert f.gemm_acc(t["A"], t["B"], C, False, None) is None
     assert f.mha_fwd(t["Q"], t["K"], t["V"], 1, False, O, None) is None                       # an int scale
-    assert f.mha_fwd(t["Q"], t["K"], t["V"], float("nan"), False, O, None) is None             # the library's refusal
+    with pytest.raises(b.MltError):
+        f.mha_fwd(t["Q"], t["K"], t["V"], float("nan"), False, O, None)                        # the library's refusal
     assert f.mha_fwd(t["Q"].transpose(1, 2), t["K"], t["V"], 1.0, False, O, None) is None
     assert f.paged_attn_decode(t["q"], t["Kc"], t["Vc"], t["table"].long(), t["lens"], 1.0, torch.empty_like(t["q"])) is None
     with pytest.raises(b.MltError):
@@ -87,3 +88,22 @@ def test_what_the_native_path_leaves_alone():
         b.mlt_gemm(A2, t["B"], C=C)
     side.synchronize()
     assert torch.equal(C, b.mlt_gemm(A2, t["B"]))
+
+
+def test_a_failed_call_is_made_once():
+    import ctypes
+    from paper_2503_14985_amd import binding as b
+    t = _tensors(torch.device("cuda:0"), torch.bfloat16)
+    C = torch.zeros(33, 48, device="cuda:0")
+    calls = []
+    refuse = ctypes.CFUNCTYPE(ctypes.c_int, *b.raw().mlt_gemm_acc.argtypes)(lambda *a: calls.append(a) or b.MLT_ERR_LAUNCH)
+    names = ("mlt_gemm", "mlt_gemm_bias_act", "mlt_gemm_acc", "mlt_mha_fwd", "mlt_paged_attn_decode")
+    own = {f: ctypes.cast(getattr(b.raw(), f), ctypes.c_void_p).value for f in names}
+    try:
+        b._fast.bind(b.MltError, *({**own, "mlt_gemm_acc": ctypes.cast(refuse, ctypes.c_void_p).value}[f] for f in names))
+        with pytest.raises(b.MltError) as e:
+            b.mlt_gemm_acc(t["A"], t["B"], C)
+    finally:
+        b._fast.bind(b.MltError, *(own[f] for f in names))
+    assert e.value.status == b.MLT_ERR_LAUNCH and str(e.value).startswith("mlt_gemm_acc:")
+    assert len(calls) == 1 and not C.any()
