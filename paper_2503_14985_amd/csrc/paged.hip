@@ -16,8 +16,9 @@
 // With fewer (sequence, head) pairs than the chip needs workgroups, the same split goes one level
 // up as well: the units of a sequence are cut into `nsplit` contiguous ranges, one workgroup per
 // (sequence, head, range); each leaves its maximum, sum and unnormalised output slice (fp32) in a
-// scratch buffer, and a second small kernel merges the ranges of a pair in index order, the way
-// the workgroup merges its own partial results.
+// scratch buffer. Up to 8 ranges of a short launch are merged by the workgroup of the pair that comes last at a
+// counter, more of them by a second small kernel, in the same fixed order, the way a workgroup merges its own
+// partial results.
 //
 // The operation is bound by reading the cache once from HBM (2 * seq_len * D * 2 bytes per
 // sequence and head), so there is no MFMA here (a 1-row product would waste it) and no LDS staging:
@@ -82,6 +83,51 @@ __device__ __forceinline__ int sequence_of_rank(const int32_t* seq_lens, int B, 
   return b;
 }
 
+// O of one pair from its `nsplit` (at most MAXS) ranges at p, by all NT threads of a workgroup: group g of D threads adds the ranges
+// g, g + 4, ... and the four sums meet in LDS in the order 0, 1, 2, 3. A sequence has at least one key, so range 0 is never
+// empty and the maximum is finite. All of a thread's loads are requested at once: this is the memory round trips
+// that it waits for (as a kernel of its own: a plain loop over 32 ranges 16 us, eight loads in flight 3.9; 64 ranges so 4.5).
+// SHARED: the ranges come from workgroups of the same launch.
+constexpr int PG_MAX_SPLIT = 64;
+constexpr int PG_LAST_SPLIT = 8;    // ranges that the last of their workgroups merges, at most
+template <typename Tag, int D, int MAXS, int NT, bool SHARED>
+__device__ __forceinline__ void merge_ranges(const float* p, uint16_t* __restrict__ out, int nsplit, float* buf) {
+  constexpr int NR = MAXS / 4, NG = 4 * D / NT;           // ranges of a group; groups of a thread
+  float *sm = buf, *sl = sm + MAXS, *acc4 = sl + MAXS, *l4 = acc4 + 4 * D;
+  const int tid = threadIdx.x, g0 = tid / D * NG, d = tid % D;
+  auto get = [&](int i) __attribute__((always_inline)) { return SHARED ? load_shared(p + i) : p[i]; };
+  float v[NG][NR];
+#pragma unroll
+  for (int i = 0; i < NR; ++i)
+#pragma unroll
+    for (int n = 0; n < NG; ++n) v[n][i] = g0 + n + 4 * i < nsplit ? get((g0 + n + 4 * i) * (2 + D) + 2 + d) : 0.f;
+  if (tid < MAXS) {
+    sm[tid] = tid < nsplit ? get(tid * (2 + D)) : -__builtin_inff();
+    sl[tid] = tid < nsplit ? get(tid * (2 + D) + 1) : 0.f;
+  }
+  __syncthreads();
+  float M = sm[0];
+#pragma unroll
+  for (int s = 1; s < MAXS; ++s) M = __builtin_fmaxf(M, sm[s]);
+#pragma unroll
+  for (int n = 0; n < NG; ++n) {
+    const int g = g0 + n;
+    float acc = 0.f, L = 0.f;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const float wgt = __builtin_amdgcn_exp2f(sm[g + 4 * i] - M);         // empty ranges: exp2(-inf) = 0
+      acc += v[n][i] * wgt;
+      L += sl[g + 4 * i] * wgt;
+    }
+    acc4[g * D + d] = acc;
+    if (d == 0) l4[g] = L;
+  }
+  __syncthreads();
+  if (tid < D) out[d] = Elem<Tag>::from_f32((acc4[d] + acc4[D + d] + acc4[2 * D + d] + acc4[3 * D + d]) / (l4[0] + l4[1] + l4[2] + l4[3]));
+}
+// floats of LDS that it needs
+constexpr int merge_floats(int maxs, int D) { return 2 * maxs + 4 * D + 4; }
+
 // Which workgroup takes which sequence: hardware deals the workgroups of a launch to the CUs in turn, all of
 // them at once up to 8 per CU, and with the batch in its own order the CUs' shares of keys differ by
 // chance. A batch of 2 to PG_NT sequences with more workgroups than CUs is therefore dealt from the
@@ -91,13 +137,14 @@ __device__ __forceinline__ int sequence_of_rank(const int32_t* seq_lens, int B, 
 // keys, 32 heads, D = 128, shuffled: 456 -> 421 us (6.4 TB/s, as for equal lengths).
 //
 // SPLIT: blockIdx.y is the range of units this workgroup takes, and the result goes to `part`
-// ([pair][range][2 + D] floats: maximum (log2 domain), sum, unnormalised outputs) instead of O.
+// ([pair][range][2 + D] floats: maximum (log2 domain), sum, unnormalised outputs) instead of O; counters: a zero for each
+// pair (left as zero), at which the last of its workgroups finds out that it is to merge them, or null: another kernel does.
 // ORDER: by length, see above (ncu, B: only then).
 template <typename Tag, int D, bool SPLIT, bool ORDER>
 __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ Kc,
     const uint16_t* __restrict__ Vc, const int32_t* __restrict__ block_table,
-    const int32_t* __restrict__ seq_lens, uint16_t* __restrict__ O, float* __restrict__ part, int H,
+    const int32_t* __restrict__ seq_lens, uint16_t* __restrict__ O, float* part, uint32_t* __restrict__ counters, int H,
     int block_size, int max_blocks, int num_blocks, int B, int ncu, float c) {
   constexpr int LPR = D / 8;                 // lanes per key row (16 bytes each)
   constexpr int RPI = 64 / LPR;              // key rows per load instruction
@@ -234,50 +281,30 @@ __global__ __launch_bounds__(PG_NT) void paged_decode_kernel(
     }
     if (SPLIT) {
       float* out = part + ((int64_t)bh * nsplit + range) * (2 + D);
-      if (tid == 0) { out[0] = M; out[1] = L; }
-      out[2 + tid] = acc;
+      if (!ORDER && counters) {
+        if (tid == 0) { store_shared(out, M); store_shared(out + 1, L); }
+        store_shared(out + 2 + tid, acc);
+      } else {
+        if (tid == 0) { out[0] = M; out[1] = L; }
+        out[2 + tid] = acc;
+      }
     } else {
       O[(int64_t)bh * D + tid] = Elem<Tag>::from_f32(acc / L);
     }
   }
+  if (!SPLIT || ORDER || !counters) return;
+  static_assert(merge_floats(PG_LAST_SPLIT, D) <= NSPLIT * D, "the merge works in so");
+  if (!last_to_arrive(counters + bh, (uint32_t)nsplit, reinterpret_cast<uint32_t*>(sm))) return;
+  merge_ranges<Tag, D, PG_LAST_SPLIT, PG_NT, true>(part + (int64_t)bh * nsplit * (2 + D), O + (int64_t)bh * D, nsplit, &so[0][0]);
 }
 
-// One workgroup per (sequence, head), D x 4 threads: group g adds the ranges g, g + 4, ... (at most MAXS in all)
-// and the four sums meet in LDS in the order 0, 1, 2, 3. A sequence has at least one key, so range 0 is never
-// empty and the maximum is finite.
-constexpr int PG_MAX_SPLIT = 64;
+// The merge as a kernel of its own, one workgroup per (sequence, head)
 template <typename Tag, int D, int MAXS>
 __global__ __launch_bounds__(4 * D) void paged_merge_kernel(const float* __restrict__ part,
                                                             uint16_t* __restrict__ O, int nsplit) {
-  // All of a thread's loads are requested at once: this kernel is the memory round trips that it waits
-  // for (a plain loop over 32 ranges: 16 us, eight loads in flight 3.9; 64 ranges here: 4.5).
-  constexpr int NR = MAXS / 4;
-  __shared__ float sm[MAXS], sl[MAXS], acc4[4][D], l4[4];
-  const int bh = blockIdx.x, tid = threadIdx.x, g = tid / D, d = tid % D;
-  const float* p = part + (int64_t)bh * nsplit * (2 + D);
-  float v[NR];
-#pragma unroll
-  for (int i = 0; i < NR; ++i) v[i] = g + 4 * i < nsplit ? p[(g + 4 * i) * (2 + D) + 2 + d] : 0.f;
-  if (tid < MAXS) {
-    sm[tid] = tid < nsplit ? p[tid * (2 + D)] : -__builtin_inff();
-    sl[tid] = tid < nsplit ? p[tid * (2 + D) + 1] : 0.f;
-  }
-  __syncthreads();
-  float M = sm[0];
-#pragma unroll
-  for (int s = 1; s < MAXS; ++s) M = __builtin_fmaxf(M, sm[s]);
-  float acc = 0.f, L = 0.f;
-#pragma unroll
-  for (int i = 0; i < NR; ++i) {
-    const float wgt = __builtin_amdgcn_exp2f(sm[g + 4 * i] - M);           // empty ranges: exp2(-inf) = 0
-    acc += v[i] * wgt;
-    L += sl[g + 4 * i] * wgt;
-  }
-  acc4[g][d] = acc;
-  if (d == 0) l4[g] = L;
-  __syncthreads();
-  if (g == 0)
-    O[(int64_t)bh * D + d] = Elem<Tag>::from_f32((acc4[0][d] + acc4[1][d] + acc4[2][d] + acc4[3][d]) / (l4[0] + l4[1] + l4[2] + l4[3]));
+  __shared__ float buf[merge_floats(MAXS, D)];
+  const int64_t bh = blockIdx.x;
+  merge_ranges<Tag, D, MAXS, 4 * D, false>(part + bh * nsplit * (2 + D), O + bh * D, nsplit, buf);
 }
 
 template <typename Tag, int D>
@@ -287,13 +314,21 @@ int launch_paged(const PagedArgs& a, int nsplit, float* part, hipStream_t s) {
   DeviceInfo di;
   const int64_t ncu = device_info(di) ? di.ncu : 0;
   const bool order = paged_by_length(a, nsplit, ncu);
+  // Up to 8 ranges, and not by length: the last workgroup of a pair merges them, which saves the second launch (us, second
+  // kernel / last workgroup: 1 x 8 pairs of 700 keys, D = 64, 4 ranges 7.8 / 6.0; 4 x 32 of 1024, D = 128, 4 ranges 14.5 / 13.9; 16 x 16 of 600, D = 64,
+  // 2 ranges 11.8 / 11.1; 4 x 16 of 5440 in 8 equal). Its three trips to memory, one after the other (the written values, the counter, all the
+  // ranges), cost as much as the launch with more ranges or where the CUs are still busy with other pieces (1 x 8, 32768 in
+  // 64: 27.1 / 29.1; 1 x 32, 4096 in 32: 15.6 / 18.0; by length: 8 x 16, 32768 in 16 206 / 222, 10 x 32, 4096 in 6 67.9 / 71.0).
+  // (hipStreamPerThread is another stream in each thread: calls that overlap would leave the counters in disorder)
+  uint32_t* counters = nsplit > 1 && nsplit <= PG_LAST_SPLIT && !order && pairs <= (unsigned)kScratchCounters && s != hipStreamPerThread
+                           ? scratch_counters(part) : nullptr;
   auto kern = nsplit > 1 ? (order ? paged_decode_kernel<Tag, D, true, true> : paged_decode_kernel<Tag, D, true, false>)
                          : (order ? paged_decode_kernel<Tag, D, false, true> : paged_decode_kernel<Tag, D, false, false>);
   hipLaunchKernelGGL(kern, dim3(pairs, nsplit > 1 ? (unsigned)nsplit : 1u), dim3(PG_NT), 0, s, a.Q, a.Kc, a.Vc,
-                     a.block_table, a.seq_lens, a.O, nsplit > 1 ? part : (float*)nullptr, (int)a.H, (int)a.block_size,
+                     a.block_table, a.seq_lens, a.O, nsplit > 1 ? part : (float*)nullptr, counters, (int)a.H, (int)a.block_size,
                      (int)a.max_blocks, (int)a.num_blocks, (int)a.B, (int)ncu, c);
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
-  if (nsplit <= 1) return MLT_OK;
+  if (nsplit <= 1 || counters) return MLT_OK;
   auto merge = nsplit <= 8 ? paged_merge_kernel<Tag, D, 8> : nsplit <= 32 ? paged_merge_kernel<Tag, D, 32>
                                                                           : paged_merge_kernel<Tag, D, PG_MAX_SPLIT>;
   hipLaunchKernelGGL(merge, dim3(pairs), dim3(4 * D), 0, s, part, a.O, nsplit);

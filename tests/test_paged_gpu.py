@@ -167,7 +167,7 @@ def key_split():
 @pytest.mark.parametrize("nsplit", [2, 3, 7, 64])
 @pytest.mark.parametrize("dtype,D", [(BF16, 128), (FP16, 64)])
 def test_key_split_across_workgroups(key_split, nsplit, dtype, D):
-    """Keys cut into ranges over several workgroups, merged by the second kernel: lengths from one
+    """Keys cut into ranges over several workgroups, merged by the last of them or by the second kernel: lengths from one
     key (every range but the first empty) to ranges that end inside a unit, a block and a wavefront
     round."""
     from paper_2503_14985_amd import binding
@@ -205,3 +205,25 @@ def test_key_split_single_key_and_block_placement(key_split):
     inv = np.argsort(perm)
     O3 = _run(q, kc[perm], vc[perm], inv[table].astype(np.int32), lens, 0.2, BF16)
     assert torch.equal(O3, O)
+
+
+@pytest.mark.parametrize("nsplit", [2, 5, 8])
+@pytest.mark.parametrize("dtype,D", [(BF16, 64), (FP16, 128)])
+def test_last_workgroup_and_second_kernel_merge_alike(key_split, nsplit, dtype, D):
+    """More pairs than there are counters (16384): a second kernel merges the ranges. The same sequences in calls
+    of fewer pairs: the workgroup that comes last at its pair's counter does, in the same order. Repeated with other values, so
+    that a range which the merge read before it was there (or from an earlier call) would show."""
+    from paper_2503_14985_amd import binding
+    key_split(nsplit)
+    dev = torch.device("cuda:0")
+    B, H, keys = 520, 32, 48
+    g = torch.Generator(device=dev).manual_seed(nsplit)
+    dt = torch.bfloat16 if dtype == BF16 else torch.float16
+    table = torch.randperm(64, generator=g, device=dev).to(torch.int32)[:keys // 16].repeat(B, 1).contiguous()
+    lens = torch.randint(1, keys + 1, (B,), generator=g, device=dev, dtype=torch.int32)
+    for _ in range(3):
+        q, kc, vc = (torch.randn(s, generator=g, device=dev, dtype=dt) for s in ((B, H, D), (64, H, 16, D), (64, H, 16, D)))
+        whole = binding.mlt_paged_attn_decode(q, kc, vc, table, lens, 0.1)
+        for b0, n in ((0, 1), (1, 7), (8, 200), (208, 312)):
+            part = binding.mlt_paged_attn_decode(q[b0:b0 + n].contiguous(), kc, vc, table[b0:b0 + n].contiguous(), lens[b0:b0 + n].contiguous(), 0.1)
+            assert torch.equal(part.view(torch.int16), whole[b0:b0 + n].view(torch.int16)), (b0, n)
