@@ -23,7 +23,7 @@
  *     scratch buffer, one per (device, stream), allocated with hipMalloc at the first call that
  *     needs it, grown by doubling from 4 MiB (32 MiB covers every split the library chooses by
  *     itself) and kept until the process ends. Calls on one stream are ordered by the stream; calls
- *     on different streams use different buffers. If the allocation fails, or the stream is
+ *     on different streams use different buffers (on hipStreamPerThread: of different threads). If the allocation fails, or the stream is
  *     recording into a graph (which may be replayed at any time and on any stream, so that it must
  *     not share the stream's buffer), the call runs without the split (same result up to summation
  *     order). mlt_gemm_noalloc never allocates.

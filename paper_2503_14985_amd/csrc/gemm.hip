@@ -11,6 +11,7 @@
 // tiles are staged through LDS: each byte is fetched from global memory once per workgroup and
 // read by the wavefronts that share it (the rows/columns of the warp grid that Section 2.2 notes
 // work on the same sub-block of A or B).
+#include <atomic>
 #include <mutex>
 
 #include "gemm_tile.h"
@@ -416,20 +417,28 @@ static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
 }
 
 // Scratch for the partial results of a split across workgroups: one buffer per (device, stream)
-// pair, so that calls on different streams never share one; allocated at the first call that needs
+// pair, so that calls on different streams never share one (hipStreamPerThread is one handle for a stream of each
+// thread's own, and has a buffer per thread); allocated at the first call that needs
 // it (hipMalloc; no device synchronisation), grown by doubling (the smaller buffer is kept until the
-// process ends: work already enqueued may still use it), used in stream order. The table is
-// small and fixed; when it is full, or an allocation fails, a GEMM gets a stream-ordered
+// process ends: work already enqueued may still use it), used in stream order. The tables, one for streams and one for
+// threads, are small and fixed; when one is full, or an allocation fails, a GEMM gets a stream-ordered
 // allocation of its own (or, if that fails too, runs without the split). A call that is being recorded
 // into a graph gets none, also where the stream has a buffer: the graph would go on using it whenever
 // and on whatever stream it is replayed, beside the stream's own calls and beside other graphs recorded
 // on it, in no order with either.
 namespace {
-struct ScratchSlot { int dev; hipStream_t stream; float* ptr; int64_t bytes; };
+struct ScratchSlot { int dev; hipStream_t stream; uint64_t thread; float* ptr; int64_t bytes; };
 constexpr int kScratchSlots = 32;
-ScratchSlot g_scratch[kScratchSlots];
-int g_scratch_used = 0;
+struct ScratchTable { ScratchSlot slot[kScratchSlots]; int used; };
+ScratchTable g_scratch, g_thread_scratch;
 std::mutex g_scratch_mu;
+
+// a number that no other thread has or had (a thread's id is used again after its end, when its calls may still run)
+uint64_t this_thread() {
+  static std::atomic<uint64_t> last{0};
+  static thread_local const uint64_t id = ++last;
+  return id;
+}
 
 }  // namespace
 
@@ -445,15 +454,17 @@ float* cached_scratch(int64_t bytes, hipStream_t s) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); return nullptr; }
   if (stream_is_capturing(s)) return nullptr;
+  const uint64_t thread = s == hipStreamPerThread ? this_thread() : 0;
+  ScratchTable& table = thread ? g_thread_scratch : g_scratch;
   std::lock_guard<std::mutex> lock(g_scratch_mu);
   ScratchSlot* slot = nullptr;
-  for (int i = 0; i < g_scratch_used; ++i)
-    if (g_scratch[i].dev == dev && g_scratch[i].stream == s) slot = &g_scratch[i];
+  for (int i = 0; i < table.used; ++i)
+    if (table.slot[i].dev == dev && table.slot[i].stream == s && table.slot[i].thread == thread) slot = &table.slot[i];
   if (slot && slot->bytes >= bytes) return slot->ptr;
   if (!slot) {
-    if (g_scratch_used == kScratchSlots) return nullptr;
-    slot = &g_scratch[g_scratch_used];
-    *slot = ScratchSlot{dev, s, nullptr, 0};
+    if (table.used == kScratchSlots) return nullptr;
+    slot = &table.slot[table.used];
+    *slot = ScratchSlot{dev, s, thread, nullptr, 0};
   }
   int64_t want = slot->bytes > 0 ? 2 * slot->bytes : (int64_t)4 << 20;
   while (want < bytes) want *= 2;
@@ -461,7 +472,7 @@ float* cached_scratch(int64_t bytes, hipStream_t s) {
   if (hipMalloc(&p, (size_t)want + kScratchCounters * 4) != hipSuccess || !p) { (void)hipGetLastError(); return nullptr; }
   hipLaunchKernelGGL(zero_counters_kernel, dim3(kScratchCounters / 256), dim3(256), 0, s, static_cast<uint32_t*>(p));
   if (hipGetLastError() != hipSuccess) { (void)hipFree(p); return nullptr; }
-  if (slot == &g_scratch[g_scratch_used]) ++g_scratch_used;
+  if (slot == &table.slot[table.used]) ++table.used;
   slot->ptr = reinterpret_cast<float*>(static_cast<uint32_t*>(p) + kScratchCounters);
   slot->bytes = want;
   return slot->ptr;
@@ -499,8 +510,7 @@ int run_gemm(const GemmArgs& g_in, GemmPlan& p, hipStream_t s) {
   if (p.parts > 1 && !g.scratch) {
     g.scratch = cached_scratch(p.scratch_bytes, s);
     if (g.scratch) {
-      // (hipStreamPerThread is another stream in each thread: calls that overlap would leave the counters in disorder)
-      if (s != hipStreamPerThread) g.counters = scratch_counters(g.scratch);
+      g.counters = scratch_counters(g.scratch);
     } else {
       void* ws = nullptr;
       if (!stream_is_capturing(s) && hipMallocAsync(&ws, (size_t)p.scratch_bytes, s) == hipSuccess && ws) {

@@ -319,9 +319,7 @@ int launch_paged(const PagedArgs& a, int nsplit, float* part, hipStream_t s) {
   // 2 ranges 11.8 / 11.1; 4 x 16 of 5440 in 8 equal). Its three trips to memory, one after the other (the written values, the counter, all the
   // ranges), cost as much as the launch with more ranges or where the CUs are still busy with other pieces (1 x 8, 32768 in
   // 64: 27.1 / 29.1; 1 x 32, 4096 in 32: 15.6 / 18.0; by length: 8 x 16, 32768 in 16 206 / 222, 10 x 32, 4096 in 6 67.9 / 71.0).
-  // (hipStreamPerThread is another stream in each thread: calls that overlap would leave the counters in disorder)
-  uint32_t* counters = nsplit > 1 && nsplit <= PG_LAST_SPLIT && !order && pairs <= (unsigned)kScratchCounters && s != hipStreamPerThread
-                           ? scratch_counters(part) : nullptr;
+  uint32_t* counters = nsplit > 1 && nsplit <= PG_LAST_SPLIT && !order && pairs <= (unsigned)kScratchCounters ? scratch_counters(part) : nullptr;
   auto kern = nsplit > 1 ? (order ? paged_decode_kernel<Tag, D, true, true> : paged_decode_kernel<Tag, D, true, false>)
                          : (order ? paged_decode_kernel<Tag, D, false, true> : paged_decode_kernel<Tag, D, false, false>);
   hipLaunchKernelGGL(kern, dim3(pairs, nsplit > 1 ? (unsigned)nsplit : 1u), dim3(PG_NT), 0, s, a.Q, a.Kc, a.Vc,
