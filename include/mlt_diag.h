@@ -77,7 +77,7 @@ int mlt_query_tiling(int op, const int64_t dims[4], int dtype, int32_t out[10]);
  * choice as it is; "" or "auto" restores the automatic choice. A forced kernel that cannot take a
  * problem (alignment, shape) falls back to one that can, as the automatic choice would.
  *   gemm_variant  "general", "256", "256w8", "256pp16", "128pp16", "128pp16k128", "256x128kp", "128kp", "256w4", "256w8x1",
- *                 "256w1x8", "128w8", "64x128", "64", "128k2", "64x128k2", "64k4", "skinny", "skinnydma"
+ *                 "256w1x8", "128w8", "64x128", "64", "128k2", "64x128k2", "64k4", "skinny" (or its older name "skinnydma")
  *   mha_variant   "pp32", "pp16", "ps", "k2", "k4"
  * The initial values come from the environment variables MLT_GEMM_VARIANT and MLT_MHA_VARIANT,
  * which are read once, at the first call that needs them. Not synchronised with compute calls
@@ -87,9 +87,10 @@ int mlt_query_tiling(int op, const int64_t dims[4], int dtype, int32_t out[10]);
 int mlt_diag_force_variant(const char* gemm_variant, const char* mha_variant);
 
 /*
- * Number of parts the GEMM entry points split K into across workgroups (the small-tile kernels and
- * those with two K groups; partial products through an fp32 scratch, added in a fixed order by a second kernel): 0 = the
- * cost model's choice (the default), 1 = never split, 2 / 4 / 8 = that many parts wherever every
+ * Number of parts the GEMM entry points split K into across workgroups (the small-tile kernels,
+ * those with two K groups and the skinny kernel; partial products through an fp32 scratch, added in a fixed order by a second kernel,
+ * in the skinny kernel by the workgroup that comes last): 0 = the
+ * cost model's choice (the default), 1 = never split, 2 / 4 / 8 = that many parts, in the tile kernels wherever every
  * part keeps at least 8 K steps of 64. Process-wide, like mlt_diag_force_variant. Returns MLT_OK
  * or MLT_ERR_INVALID_ARG.
  */

@@ -142,7 +142,7 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   // long that splitting K pays for itself (64 x 4096 x 4096 12.8 on tiles, 13.9 here; 61 x 2976 x 16192 26.4, 29.5; but 64 x 1024 x 28672 24.8, 19.9),
   // and for tall A against a few steps of K (64 x 5512 x 72 4.4, 5.8).
   const bool tiles_win = (g.M > 48 && g.N <= 16 * NCU && KT >= 64 && KT < 256) || (g.M > 32 && KT < 8);
-  if ((g.forced == GEMM_SKINNY || g.forced == GEMM_SKINNY_DMA || (g.forced == GEMM_AUTO && !tiles_win)) && gemm_skinny_ok(g)) {
+  if ((g.forced == GEMM_SKINNY || (g.forced == GEMM_AUTO && !tiles_win)) && gemm_skinny_ok(g)) {
     // K over 1, 2, 4 or 8 workgroups: B's arrival + what a CU fetches of A (at 100 GB/s) + the price of the partial
     // results (a fit to the times of 175 problems: the choice is 1.2 % behind the best one on average, 26 % at worst)
     auto time = [&](int64_t parts) {
@@ -154,11 +154,9 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
       for (int n = 2; n <= 8; n *= 2)
         if (n * g.M * g.N * 4 <= kStaticScratchBytes && time(n) < time(p.parts)) p.parts = n;
     p.scratch_bytes = p.parts > 1 ? (int64_t)p.parts * g.M * g.N * 4 : 0;
-    // (the first name for a single column block per workgroup and whole rounds of 128-k pieces over its wavefronts)
-    const bool one_block = !g.fused() && g.M <= 32 && g.N > 14 * NCU && g.N <= 16 * NCU && g.K % 2048 == 0 && g.N * g.K < ((int64_t)1 << 25);
-    p.variant = g.forced == GEMM_SKINNY || (g.forced == GEMM_AUTO && one_block) ? GEMM_SKINNY : GEMM_SKINNY_DMA;
-    p.name = p.variant == GEMM_SKINNY ? "gemm_nt_skinny_16cols_ksplit8" : "gemm_nt_decode_k8_16cols_stream";
-    p.bm = (int)((g.M + 15) / 16) * 16; p.bn = 16; p.bk = 128;
+    p.variant = GEMM_SKINNY;
+    p.name = "gemm_nt_skinny_stream";
+    p.bm = (int)((g.M + 15) / 16) * 16; p.bn = gemm_skinny_cols(g.N, p.parts, NCU); p.bk = 128;
     p.wm = 1; p.wn = 1;
     p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
     return p;
@@ -325,7 +323,7 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   }
   int v = pick.variant;
   const int best_parts = pick.parts;
-  if (g.forced >= GEMM_256 && g.forced < GEMM_NUM_VARIANTS && g.forced != GEMM_SKINNY && g.forced != GEMM_SKINNY_DMA) v = g.forced;
+  if (g.forced >= GEMM_256 && g.forced < GEMM_NUM_VARIANTS && g.forced != GEMM_SKINNY) v = g.forced;
   if (v == GEMM_256_PP16 && !gemm_pp_ok(g)) v = GEMM_256_W8;
   if ((v == GEMM_256X128_KP || v == GEMM_128_KP) && !pp) v = v == GEMM_128_KP ? GEMM_128_W8 : GEMM_256_W8;
   if (v == GEMM_256_W4 && !gemm_w4_ok(g)) v = GEMM_256_W8;
@@ -409,8 +407,7 @@ static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     case GEMM_256X128_KP: return run_gemm_kp(g, 256, s);
     case GEMM_128_KP: return run_gemm_kp(g, 128, s);
     case GEMM_256_W4: return run_gemm_w4(g, s);
-    case GEMM_SKINNY:
-    case GEMM_SKINNY_DMA: return run_gemm_skinny(g, s);
+    case GEMM_SKINNY: return run_gemm_skinny(g, s);
   }
   const int rc = launch_small_tile<Tag, true>(g, p.variant, s);
   return rc == -1 ? MLT_ERR_UNSUPPORTED : rc;

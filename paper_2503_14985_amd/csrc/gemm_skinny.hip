@@ -282,8 +282,10 @@ int run_skinny_cols(const GemmArgs& g, hipStream_t s) {
   DeviceInfo di;
   const int64_t ncu = device_info(di) && di.ncu > 0 ? di.ncu : 256;
   if (g.parts > 1) return launch_skinny<Tag, MT, AU, 4, true>(g, ncu, s);
-  if (g.N <= 4 * ncu) return launch_skinny<Tag, MT, AU, 1, false>(g, ncu, s);
-  if (g.N <= 8 * ncu) return launch_skinny<Tag, MT, AU, 2, false>(g, ncu, s);
+  switch (gemm_skinny_cols(g.N, g.parts, ncu)) {
+    case 4: return launch_skinny<Tag, MT, AU, 1, false>(g, ncu, s);
+    case 8: return launch_skinny<Tag, MT, AU, 2, false>(g, ncu, s);
+  }
   return launch_skinny<Tag, MT, AU, 4, false>(g, ncu, s);
 }
 

@@ -32,8 +32,7 @@ const VariantName kGemmVariants[] = {
     {"general", GEMM_GENERAL}, {"256", GEMM_256}, {"256w8", GEMM_256_W8}, {"256pp16", GEMM_256_PP16}, {"256x128kp", GEMM_256X128_KP}, {"128kp", GEMM_128_KP}, {"128pp16", GEMM_128_PP16}, {"128pp16k128", GEMM_128_PP16_K128},
     {"256w4", GEMM_256_W4}, {"256w8x1", GEMM_256_W8X1}, {"256w1x8", GEMM_256_W1X8},
     {"128w8", GEMM_128_W8}, {"64x128", GEMM_64X128_W8}, {"64", GEMM_64_W4}, {"128k2", GEMM_128_K2},
-    {"64x128k2", GEMM_64X128_K2}, {"64k4", GEMM_64_K4}, {"skinny", GEMM_SKINNY},
-    {"skinnydma", GEMM_SKINNY_DMA}};
+    {"64x128k2", GEMM_64X128_K2}, {"64k4", GEMM_64_K4}, {"skinny", GEMM_SKINNY}, {"skinnydma", GEMM_SKINNY}};
 const VariantName kMhaVariants[] = {{"pp32", MHA_PP32}, {"pp16", MHA_PP16}, {"ps", MHA_PS}, {"k2", MHA_K2}, {"k4", MHA_K4}};
 
 // name -> id; "" and "auto" mean the automatic choice; -2 for an unknown name

@@ -10,8 +10,7 @@ enum GemmVariant {
   GEMM_AUTO = -1, GEMM_ZERO = 0, GEMM_GENERAL = 1,
   GEMM_256 = 2,       // 256x256x64, 4 wavefronts (2x2) of 128x128 (tiling hint "square" with a ragged K)
   GEMM_256_W8 = 4,    // 256x256x64, 8 wavefronts (2x4) of 128x64 (big tiles when the direct loads do not apply)
-  GEMM_SKINNY = 7,    // M <= 64, B stored N x K: K split over 8 wavefronts, LDS rings (one column block per workgroup)
-  GEMM_SKINNY_DMA = 8,  // the same kernel, any number of column blocks
+  GEMM_SKINNY = 7,    // M <= 64, B stored N x K: B streamed through an LDS ring per wavefront, K split over 8 wavefronts
   GEMM_256_W4 = 10,   // 256x256x64, 4 wavefronts (2x2) of 128x128, software-pipelined, direct-to-LDS loads
   GEMM_256_PP16 = 11, // 256x256x64, 8 wavefronts (2x4), two-group schedule, direct-to-LDS loads, 16x16x32 MFMAs
   GEMM_256_W8X1 = 12, // 256x256x64, 8 wavefronts as 8x1: row strips of 32 x 256 ("horizontal")
@@ -80,6 +79,8 @@ int run_gemm_any(const GemmArgs& g, int variant, hipStream_t s);
 bool gemm_w4_ok(const GemmArgs& g);            // gemm_w4.hip: whole K steps only
 int run_gemm_w4(const GemmArgs& g, hipStream_t s);
 bool gemm_skinny_ok(const GemmArgs& g);        // gemm_skinny.hip
+// its columns per block: 16, or without a K split across workgroups the 4 or 8 that a CU has of a narrow matrix
+inline int gemm_skinny_cols(int64_t N, int64_t parts, int64_t ncu) { return parts > 1 || N > 8 * ncu ? 16 : N > 4 * ncu ? 8 : 4; }
 int run_gemm_skinny(const GemmArgs& g, hipStream_t s);
 
 enum MhaVariant {

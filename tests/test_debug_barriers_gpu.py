@@ -46,9 +46,9 @@ GEMM_CASES = [
     (1024, 1024, 1024, True, "auto", 3),
     (300, 520, 1000, False, "auto", None),        # register-staged tile kernels
     (64, 4096, 64 * 200, True, "auto", None),     # K split across workgroups
-    (16, 8192, 4096, True, "auto", None),         # streaming skinny kernel (LDS ring)
-    (16, 4096, 4096, True, "auto", None),         # skinny kernel, K split inside the workgroup
-    (32, 8192, 4096, True, "skinnydma", None),
+    (16, 8192, 4096, True, "auto", None),         # skinny kernel, two column blocks per workgroup
+    (16, 4096, 4096, True, "auto", None),         # one
+    (32, 8192, 4096, True, "skinny", None),
 ]
 
 

@@ -1,5 +1,5 @@
-"""GPU parity of the decode GEMM kernels (K split over wavefronts; streaming) around the sizes of their batches
-and rings, and of the streaming kernel's fused epilogue, against the fp64 oracle."""
+"""GPU parity of the decode GEMM kernel around the sizes of its pieces of K, rings and column blocks, with K in parts, and with
+bias and activation, against the fp64 oracle."""
 import pytest
 
 from paper_2503_14985_amd import inputs
@@ -17,8 +17,8 @@ def _announce(request):
     binding.mlt_diag_force_variant(gemm="auto")
 
 
-# fewer chunks of 32 than wavefronts, one batch (4 or 8 chunks of a wavefront), one more, two, an odd and an
-# even count, a chunk that ends inside K; up to one column block per CU, and more
+# fewer pieces of 128 k than wavefronts, one for each, one more, two and three rounds of them, pieces that end inside K; up to one column
+# block per workgroup, and more
 @pytest.mark.parametrize("M", [1, 16, 17, 33, 64])
 @pytest.mark.parametrize("N", [1032, 4112, 16400, 32776])
 def test_k_split_over_wavefronts(M, N):
@@ -30,7 +30,7 @@ def test_k_split_over_wavefronts(M, N):
         A, B = inputs.gemm_inputs(M, N, K, FP16 if i % 2 else BF16, i, transB=True)
         C = pu.run_gemm(A, B, FP16 if i % 2 else BF16, transB=True)
         pu.check_gemm(A, B, C, FP16 if i % 2 else BF16, True, seed=i)
-        assert binding.mlt_last_kernel().endswith("ksplit8")
+        assert binding.mlt_last_kernel() == "gemm_nt_skinny_stream"
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 2048, 1024), (16, 4104, 520), (13, 1032, 4096), (24, 14336, 2048)])
@@ -40,7 +40,7 @@ def test_streaming_with_bias_and_activation(M, N, K, act):
     for dtype in (BF16, FP16):
         A, B = inputs.gemm_inputs(M, N, K, dtype, 4, transB=True)
         pu.run_check_gemm_bias_act(A, B, inputs.bias_input(N, dtype, 4, std=4.0), act, dtype, transB=True)
-        assert binding.mlt_last_kernel().endswith("16cols_stream")
+        assert binding.mlt_last_kernel() == "gemm_nt_skinny_stream"
 
 
 # columns per workgroup that make blocks of 4, 8 and 16 (one block, a ragged second one, more than a group of 8 or 4 takes),
@@ -56,12 +56,12 @@ def test_streaming_with_k_in_parts(M, N):
             dtype = (BF16, FP16)[i % 2]
             A, B = inputs.gemm_inputs(M, N, K, dtype, 5 + i, transB=True)
             for parts in (1, 2, 4, 8):
-                binding.mlt_diag_force_variant(gemm="skinnydma")
+                binding.mlt_diag_force_variant(gemm="skinny")
                 binding.mlt_diag_force_k_parts(parts)
                 C = pu.run_gemm(A, B, dtype, transB=True)
                 pu.check_gemm(A, B, C, dtype, True, seed=i)
                 name = binding.mlt_last_kernel()
-                assert name.endswith("16cols_stream" if parts == 1 else "16cols_stream_splitk%d" % parts)
+                assert name == "gemm_nt_skinny_stream" + ("" if parts == 1 else "_splitk%d" % parts)
                 for _ in range(2):
                     assert torch.equal(pu.run_gemm(A, B, dtype, transB=True).view(torch.int16), C.view(torch.int16))
                 if parts > 1 and parts * M * N * 4 <= 32 << 20:   # the fixed scratch: a second kernel adds the parts, in the same order

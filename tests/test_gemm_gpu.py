@@ -107,17 +107,17 @@ def test_four_wavefront_pipelined_kernel(shape, transB, dtype):
 @pytest.mark.parametrize("dtype", [BF16, FP16])
 @pytest.mark.parametrize("shape", [(16, 1024, 4096), (1, 1040, 512), (7, 1500, 264), (33, 2048, 8200),
                                    (64, 1024, 1000), (48, 1031, 4096 + 32),
-                                   (16, 16400, 520), (40, 32 * 1024 + 8, 264)])   # 32 / 64 columns per workgroup
+                                   (16, 16400, 520), (40, 32 * 1024 + 8, 264)])   # 65 and 129 columns per workgroup
 def test_skinny_kernel(shape, dtype):
     # M <= 64 with B stored N x K: one to four 16-row tiles, ragged N, K with and without a partial
-    # last batch (K % 4096 != 0) and a partial last chunk (K % 32 != 0)
+    # last round of the wavefronts (K % 1024 != 0) and a partial last piece (K % 128 != 0)
     M, N, K = shape
     name, _ = _go(M, N, K, dtype, True, std=0.02, seed=7, variant="skinny")
-    assert "skinny" in name
+    assert name == "gemm_nt_skinny_stream"
     # the same problem through the tile kernel must agree with the oracle too (and is what a
     # row-major B or a larger M gets)
     name, _ = _go(M, N, K, dtype, True, std=0.02, seed=7, variant="128w8")
-    assert "skinny" not in name
+    assert name.startswith("gemm_nt_128x128x64_w2x4")      # (K in parts or not)
 
 
 @pytest.mark.parametrize("dtype", [BF16, FP16])
@@ -125,15 +125,12 @@ def test_skinny_kernel(shape, dtype):
                                    (33, 4096, 8), (48, 1500, 7000), (16, 16 * 300 + 5, 1536),
                                    (20, 64 * 300 + 21, 1160), (16, 40965, 520), (8, 36880, 1536)])
 def test_skinny_streaming_kernel(shape, dtype, form="skinnydma"):
-    # B streamed through the LDS ring by persistent workgroups (stages of 16 columns x 512 k): one
-    # to four 16-row tiles of A, ragged N (clamped rows), K below /
-    # equal to / not a multiple of the stage, a single 8-wide K, and more column blocks than CUs
-    # (several blocks per workgroup, the ring wrapping across block ends; the last two shapes give
-    # a workgroup more blocks than one group holds: full and partial groups, odd and even numbers
-    # of k stages)
+    # the same kernel by its other name, more shapes: one to four 16-row tiles of A, ragged N (an uneven share of columns, a last
+    # block that is not full), K below / equal to / not a multiple of a piece of 128, a single 8-wide K, and more column
+    # blocks than workgroups (the last two shapes give a workgroup more blocks than one group holds: full and partial groups)
     M, N, K = shape
     name, _ = _go(M, N, K, dtype, True, std=0.02, seed=8, variant=form)
-    assert name.endswith("cols_stream")
+    assert name == "gemm_nt_skinny_stream"
 
 
 @pytest.mark.parametrize("parts", [2, 4, 8])
@@ -203,26 +200,17 @@ def test_k_split_is_chosen_for_few_tiles_against_a_long_k(shape):
     assert "splitk" in name, name
 
 
-def test_skinny_routing():
-    # one 16-row tile of A and B of 2^25 elements: the streaming kernel without any override
-    name, _ = _go(16, 8192, 4096, BF16, True, std=0.02, seed=9)
-    assert name.endswith("16cols_stream")
-    name, _ = _go(16, 4096, 4096, BF16, True, std=0.02, seed=9)       # smaller B: K split over the wavefronts
-    assert name.endswith("skinny_16cols_ksplit8")
-    name, _ = _go(30, 4096, 2048, BF16, True, std=0.02, seed=9)
-    assert name.endswith("skinny_16cols_ksplit8")
-    # two row tiles against a large B: whichever of the streaming kernel and the tile kernels the
-    # estimate favours (a long K with few columns goes to the tile kernels with K split across
-    # workgroups, many columns stay with the streaming kernel or unsplit tiles)
-    name, _ = _go(17, 8192, 4096, BF16, True, std=0.02, seed=9)
-    assert "16cols_stream" in name or "_k" in name
-    name, _ = _go(32, 4096, 28672, BF16, True, std=0.02, seed=9)
-    assert "splitk" in name
-    # taller A: the tile kernels (small tiles, K split inside the workgroup)
-    name, _ = _go(40, 16384, 2048, FP16, True, std=0.02, seed=9)
-    assert "skinny" not in name and "_k" in name
-    name, _ = _go(64, 4096, 4096, BF16, True, std=0.02, seed=9)
-    assert "64x64x64_w2x2_k4" in name
+@pytest.mark.parametrize("shape,kernel", [
+    ((16, 8192, 4096), "gemm_nt_skinny_stream"), ((16, 4096, 4096), "gemm_nt_skinny_stream"), ((30, 4096, 2048), "gemm_nt_skinny_stream"),
+    ((17, 8192, 4096), "gemm_nt_skinny_stream"), ((40, 16384, 2048), "gemm_nt_skinny_stream"),
+    # a long K against few columns: K over several workgroups as well
+    ((32, 4096, 28672), "gemm_nt_skinny_stream_splitk4"),
+    # four row tiles against a K that is neither short nor long enough for that: the tile kernels
+    ((64, 4096, 4096), "gemm_nt_64x64x64_w2x2_k4_splitk4")])
+def test_skinny_routing(shape, kernel):
+    M, N, K = shape
+    name, _ = _go(M, N, K, BF16, True, std=0.02, seed=9)
+    assert name == kernel
 
 
 @pytest.mark.parametrize("variant", ["128k2", "64x128k2", "64k4"])
@@ -280,8 +268,8 @@ def test_padded_leading_dimensions(transB):
                                                   ("128pp16", (300, 264, 192), False), ("128pp16", (300, 264, 192), True),
                                                   ("128pp16k128", (300, 264, 256), False), ("128pp16k128", (300, 264, 256), True),
                                                   ("256w4", (300, 264, 192), False),
-                                                  ("256w4", (300, 264, 192), True), ("skinnydma", (16, 1100, 1032), True),
-                                                  ("skinnydma", (40, 1100, 1032), True), ("skinny", (16, 1100, 1032), True)])
+                                                  ("256w4", (300, 264, 192), True), ("skinny", (16, 1100, 1032), True),
+                                                  ("skinny", (40, 1100, 1032), True)])
 def test_padded_leading_dimensions_direct_load_kernels(variant, shape, transB):
     # row strides larger than the rows (NaN-filled padding that must never be read into a result
     # or written) through the kernels that address global memory with per-lane byte offsets
@@ -343,15 +331,14 @@ def test_config3_llm_shapes_transB(shape):
     _go(M, N, K, BF16, True, std=0.02, seed=0)
 
 
-@pytest.mark.parametrize("shape,suffix", [((16, 28672, 8192), "16cols_stream"), ((1, 28672, 8192), "16cols_stream"),
-                                          ((64, 28672, 4096), "_k"), ((16, 131072, 4096), "16cols_stream"),
-                                          ((32, 8192, 28672), "_splitk4"), ((64, 8192, 28672), "_splitk4")])
-def test_decode_shapes_streaming_kernels_full_size(shape, suffix):
+@pytest.mark.parametrize("shape,parts", [((16, 28672, 8192), ""), ((1, 28672, 8192), ""), ((64, 28672, 4096), ""), ((16, 131072, 4096), ""),
+                                         ((32, 8192, 28672), "_splitk4"), ((64, 8192, 28672), "_splitk4")])
+def test_decode_shapes_streaming_kernels_full_size(shape, parts):
     # the memory-bound decode GEMMs at their real sizes, in the launch configuration the library
-    # picks (persistent workgroups, several column blocks each); sampled against the oracle
+    # picks (several column blocks per workgroup; K in parts); sampled against the oracle
     M, N, K = shape
     name, _ = _go(M, N, K, BF16, True, std=0.02, seed=0)
-    assert suffix in name
+    assert name == "gemm_nt_skinny_stream" + parts
 
 
 @pytest.mark.parametrize("variant", [None, "256pp16", "128pp16", "128w8", "general"])
@@ -421,7 +408,7 @@ def test_accumulate_edge_cases():
                          torch.empty((0, 7), dtype=torch.bfloat16, device=dev), C)
     torch.cuda.synchronize()
     assert torch.all(C == 3.25)                                # K = 0: C += 0
-    # a skinny shape must not take the 16-bit-output skinny kernel
+    # a skinny shape must not take the skinny kernel, whose output is 16 bits
     A = torch.ones((4, 64), dtype=torch.bfloat16, device=dev)
     B = torch.ones((2048, 64), dtype=torch.bfloat16, device=dev)
     C = torch.zeros((4, 2048), dtype=torch.float32, device=dev)
@@ -439,7 +426,7 @@ def test_accumulate_edge_cases():
                                            (None, (16, 2048, 512))])
 def test_fused_bias_activation(variant, shape, with_bias, act):
     """C = act(A*B + bias) through every kernel family's epilogue (several tiles, ragged edges);
-    the last shape would take the skinny kernel, which has no fused epilogue, and must not."""
+    the last shape takes the skinny kernel where B is stored N x K."""
     from paper_2503_14985_amd import binding
     M, N, K = shape
     for dtype, transB in ((BF16, False), (FP16, True)):
@@ -449,8 +436,7 @@ def test_fused_bias_activation(variant, shape, with_bias, act):
         st = pu.run_check_gemm_bias_act(A, B, bias, act, dtype, transB=transB)
         name = binding.mlt_last_kernel()
         print("   kernel=%s %s" % (name, st), flush=True)
-        if with_bias or act:
-            assert "skinny" not in name
+        assert ("skinny" in name) == (variant is None and transB), name
         if variant in ("256pp16", "128pp16"):
             assert name.endswith("_pp16")
 

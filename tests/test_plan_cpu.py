@@ -122,17 +122,20 @@ def test_paged_decode_is_cut_finer_only_where_that_gains(plan):
                 (6, 32, 64, 64, 36)]) == [64, 32, 6, 16, 3, 2, 4]
 
 
-def test_decode_gemms_weigh_the_streaming_kernels_walk_through_k(plan):
-    """A fused epilogue or 17 to 32 rows: long K against few columns belongs to the tiles that split K; with many
-    columns, and always with up to 16 rows and no fused epilogue, B is streamed."""
-    name = lambda M, N, K, fused=0: plan([gemm_line(M, N, K, 1, fused=fused)])[0].split()[0]
-    for c in ((15, 1656, 11200, 1), (16, 1024, 28672, 1), (1, 1024, 28672, 1), (32, 2048, 8192), (24, 1024, 11200), (32, 1024, 28672)):
-        assert "skinny" not in name(*c), c
-    for c in ((17, 6456, 5544), (17, 5120, 8192), (24, 14336, 4096), (24, 14336, 4096, 1), (16, 1024, 28672), (1, 1024, 8192), (24, 4096, 2880),
-              (16, 3584, 2048), (1, 4096, 2880), (1, 3072, 4096), (1, 5120, 5120, 1)):
-        assert name(*c).endswith("16cols_stream"), c
-    for c in ((1, 4096, 4096), (16, 4096, 4096), (30, 4096, 2048), (2, 3592, 4096)):
-        assert name(*c).endswith("ksplit8"), c
+def test_routing_of_decode_gemms(plan):
+    """Up to 64 rows against B stored N x K: B is streamed, with K over several workgroups where their few columns stand against
+    a long K; but not by 33 rows and more against less than 8 steps of 64 k, nor by 49 and more where few columns meet 64 to
+    255 steps."""
+    ask = lambda M, N, K, fused=0: plan([gemm_line(M, N, K, 1, fused=fused)])[0].rsplit(" ", 1)[0]
+    for c in ((17, 6456, 5544), (24, 14336, 4096), (24, 14336, 4096, 1), (24, 4096, 2880), (16, 3584, 2048), (1, 4096, 2880), (1, 3072, 4096),
+              (1, 1024, 8192), (1, 5120, 5120, 1), (1, 4096, 4096), (16, 4096, 4096), (30, 4096, 2048), (2, 3592, 4096), (40, 16384, 2048),
+              (64, 28672, 4096), (33, 4096, 456), (64, 4096, 512), (48, 4096, 4096), (49, 4104, 4096), (64, 4096, 4032)):
+        assert ask(*c) == "gemm_nt_skinny_stream 1", c
+    for c, parts in (((17, 5120, 8192), 4), ((15, 1656, 11200, 1), 4), ((32, 2048, 8192), 4), ((24, 1024, 11200), 8), ((16, 1024, 28672), 8),
+                     ((16, 1024, 28672, 1), 8), ((1, 1024, 28672, 1), 8), ((32, 1024, 28672), 8), ((64, 4096, 16384), 4)):
+        assert ask(*c) == "gemm_nt_skinny_stream %d" % parts, c
+    for c in ((33, 4096, 448), (64, 5512, 72), (49, 4096, 4096), (64, 4096, 4096), (64, 1024, 16320)):
+        assert ask(*c).startswith("gemm_nt_64x"), c
 
 
 def test_a_tiling_hint_on_unaligned_operands_is_the_automatic_choice(plan):
