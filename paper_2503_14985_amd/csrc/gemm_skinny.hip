@@ -142,7 +142,10 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
     uint32_t slot = ring;
     auto take = [&](u32x4 (&f)[4], int n) __attribute__((always_inline)) {
       need += n;
-      const int later = issued - need;
+      int later = issued - need;
+#ifdef MLT_DEBUG_BARRIERS
+      later = 0;                                         // waits for all of them, so that a count that is too lax shows
+#endif
       if (L::LU == 4 && later >= 16) __builtin_amdgcn_s_waitcnt(wait_imm(16, 15));
       else if (L::LU == 4 && later >= 12) __builtin_amdgcn_s_waitcnt(wait_imm(12, 15));
       else if (later >= 10) __builtin_amdgcn_s_waitcnt(wait_imm(10, 15));

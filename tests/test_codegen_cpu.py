@@ -62,15 +62,15 @@ def test_persistent_attention_q_registers_are_left_alone_while_loading(tmp_path)
             assert back, "%s: no vmcnt wait between the Q loads and their first use" % name[-30:]
 
 
-def _compile_to_asm(src, tmp_path):
+def _compile_to_asm(src, tmp_path, extra=()):
     import __graft_entry__ as entry
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     if not (os.path.exists(hipcc) or shutil.which(hipcc)):
         pytest.skip("no hipcc here")
     out = tmp_path / (src + ".s")
     flags = [f for f in entry.HIPCC_FLAGS if f != "-fPIC"]
-    subprocess.check_call([hipcc] + flags + ["-S", "--cuda-device-only", "-o", str(out),
-                                             os.path.join(entry.CSRC, src)], stderr=subprocess.DEVNULL)
+    subprocess.check_call([hipcc] + flags + list(extra) + ["-S", "--cuda-device-only", "-o", str(out),
+                                                           os.path.join(entry.CSRC, src)], stderr=subprocess.DEVNULL)
     return out.read_text()
 
 
@@ -88,3 +88,17 @@ def test_headline_kernels_keep_their_registers(tmp_path):
             assert vgprs <= 256
             found += 1
         assert found >= 4, (src, found)
+
+
+def test_debug_build_waits_for_every_load_of_the_decode_gemm(tmp_path):
+    """The decode GEMM kernel has no pipeline barrier: a wavefront waits by count for the loads of its own ring. The debug build, against
+    which its results are compared, has to wait for all of them instead, or it is the same kernel."""
+    counted = {}
+    for flag in ((), ("-DMLT_DEBUG_BARRIERS",)):
+        asm = _compile_to_asm("gemm_skinny.hip", tmp_path, flag)
+        for name, body in re.findall(r"^(_Z\S*gemm_skinny_kernel\S*):.*?\n(.*?)\.end_amdhsa_kernel", asm, re.S | re.M):
+            counted.setdefault(name, []).append(sum(int(n) > 0 for n in re.findall(r"s_waitcnt[^\n]*vmcnt\((\d+)\)", body)))
+    assert len(counted) >= 20
+    for name, (product, debug) in counted.items():
+        split = "Lb1E" in name                # K in parts: counted waits for the parts of the others, at the end, are the compiler's
+        assert product >= 6 and (debug < product - 5 if split else debug == 0), (name, product, debug)

@@ -1,6 +1,6 @@
 """Race check of the pipelined kernels: libmlt_dbg.so is the library compiled with
 -DMLT_DEBUG_BARRIERS (every pipeline barrier first waits for all outstanding memory operations and
-is taken twice). Every result of the library is a fixed function of its inputs, so the two builds
+is taken twice; the decode GEMM kernel, which has none, waits for all its loads instead of by count). Every result of the library is a fixed function of its inputs, so the two builds
 must agree bit for bit on every kernel family; a tile consumed before its load has landed, or a
 ring slot refilled while a slower wavefront still reads it, would show as a difference."""
 import ctypes
@@ -86,6 +86,38 @@ def test_gemm_kernels_agree_with_the_debug_build(dbg, dt):
                 want = binding.mlt_gemm(A, B, transB=tb) if tiling is None else binding.mlt_gemm_tiled(A, B, tiling, transB=tb)
     finally:
         binding.mlt_diag_force_variant(gemm="auto")
+
+
+@pytest.mark.parametrize("M", [1, 16, 32, 47, 64])
+def test_decode_gemm_agrees_with_the_debug_build(dbg, M):
+    """One to four row tiles (and fewer than 4 rows); blocks of 4, 8 and 16 columns, one and several of them; whole pieces of K and a
+    ragged last one; K in parts."""
+    from paper_2503_14985_amd import binding
+    dev = torch.device("cuda:0")
+    g = torch.Generator(device=dev)
+    g.manual_seed(M)
+    dt, code = ((torch.bfloat16, 0), (torch.float16, 1))[M % 2]
+    try:
+        for lib in (binding.raw(), dbg):
+            lib.mlt_diag_force_variant(b"skinny", None)
+        for N, K, parts in ((1024, 4232, 1), (2048, 4096, 1), (4096, 8192, 1), (8200, 4232, 1), (34000, 1160, 1), (1024, 8192, 8), (4104, 4232, 4), (9000, 2048, 2)):
+            print("\n[case] %s" % ((M, N, K, parts),), flush=True)
+            A = torch.randn((M, K), generator=g, device=dev, dtype=torch.float32).to(dt)
+            B = torch.randn((N, K), generator=g, device=dev, dtype=torch.float32).to(dt)
+            for lib in (binding.raw(), dbg):
+                lib.mlt_diag_force_k_parts(parts)
+            got = torch.full((M, N), float("nan"), dtype=dt, device=dev)
+            for _ in range(3):
+                want = binding.mlt_gemm(A, B, transB=True)
+                assert dbg.mlt_gemm(M, N, K, A.data_ptr(), K, B.data_ptr(), K, 1, got.data_ptr(), N, code, _stream()) == 0
+                torch.cuda.synchronize()
+                name = "gemm_nt_skinny_stream" + ("_splitk%d" % parts if parts > 1 else "")
+                assert dbg.mlt_last_kernel().decode() == binding.mlt_last_kernel() == name
+                assert torch.equal(got.view(torch.int16), want.view(torch.int16)), name
+    finally:
+        for lib in (binding.raw(), dbg):
+            lib.mlt_diag_force_variant(b"auto", None)
+            lib.mlt_diag_force_k_parts(0)
 
 
 @pytest.mark.parametrize("variant", ["pp32", "pp16", "ps"])
