@@ -26,11 +26,10 @@ DIAG_EXPORTS = ("mlt_probe_mfma", "mlt_probe_mfma16", "mlt_probe_hbm_read", "mlt
                 "mlt_last_kernel", "mlt_query_tiling", "mlt_diag_force_variant",
                 "mlt_diag_force_k_parts", "mlt_diag_force_key_split", "mlt_diag_set_persistent_grid")
 
-FASTCALL_PATH = os.path.join(_HERE, "_fastcall.so")
-if not (os.path.exists(LIB_PATH) and os.path.exists(FASTCALL_PATH)):
+if not os.path.exists(LIB_PATH):
     raise ImportError(
-        "libmlt.so and _fastcall.so are not built (%s). Run `python -c 'import __graft_entry__ as g; g.build_lib()'` "
-        "from the repository root; there is no CPU fallback." % _HERE)
+        "libmlt.so is not built (%s). Run `python -c 'import __graft_entry__ as g; g.build_lib()'` "
+        "from the repository root; there is no CPU fallback." % LIB_PATH)
 
 _lib = ctypes.CDLL(LIB_PATH)
 # What torch.cuda.current_stream(i).cuda_stream and torch.cuda.current_device() return, without the objects
@@ -87,9 +86,21 @@ class MltError(RuntimeError):
 # The usual case of a call (plain GPU tensors, an output given, no stream) goes through native code (csrc/fastcall.cpp), which returns
 # None for everything else: the functions below then marshal, allocate or raise. A call that the library refuses raises there.
 # (us per mlt_gemm call of 16 x 64 x 64 back to back: 7.5 without, 3.8 with; the library's and the runtime's own part is 3.1.)
-from . import _fastcall as _fast  # noqa: E402
-_fast.bind(MltError, *(ctypes.cast(getattr(_lib, _f), _p).value for _f in ("mlt_gemm", "mlt_gemm_bias_act", "mlt_gemm_acc", "mlt_mha_fwd",
-                                                                          "mlt_paged_attn_decode")))
+# It is built against one torch, whose tensors it looks into; with another one, with a torch without ROCm, or where it has not been built,
+# every call goes through the functions below.
+class _PythonOnly:
+    gemm = gemm_acc = gemm_bias_act = mha_fwd = paged_attn_decode = staticmethod(lambda *args: None)
+
+
+_fast = _PythonOnly
+try:
+    from . import _fastcall
+    if _fastcall.torch_version == torch.__version__:
+        _fastcall.bind(MltError, *(ctypes.cast(getattr(_lib, _f), _p).value for _f in (
+            "mlt_gemm", "mlt_gemm_bias_act", "mlt_gemm_acc", "mlt_mha_fwd", "mlt_paged_attn_decode")))
+        _fast = _fastcall
+except ImportError:
+    pass
 
 
 def raw():
