@@ -13,6 +13,10 @@
 //   * the rows of a piece are stored permuted (16-byte chunk c of row r at position c ^ r): the source
 //     address of a lane is free, its LDS position is not, and the 16 lanes that read 16 rows at one k
 //     position must hit 16 distinct bank groups;
+//   * a wavefront starts some pieces into its share and goes round, each at another place: all of them walk through K
+//     in step, and where the rows of B are a power of two long (K = 4096: 8 KB) the whole chip would read the same 2 KB
+//     out of every 8 at a time, a part of the memory's channels (us, from the first piece / going round: 1 x 8192 x 4096 17.9 / 12.5, 16 x 8192 x
+//     8192 28.8 / 25.4, 32 x 4096 x 8192 19.6 / 16.9, 16 x 28672 x 4096 39.6 / 36.7; 16 x 9000 x 2880 12.6 / 12.7);
 //   * with more than 16 columns a piece of A is fetched once for a group of up to 8 column blocks (4 from three row
 //     tiles on), whose accumulators stay in registers;
 //   * at the end the 8 partial tiles of a column block meet in LDS and are added in wavefront order.
@@ -24,7 +28,7 @@
 //
 // What bounds it: what a CU's memory path takes (about 64 bytes per clock, A and B together: 1 x 4096 x 4096 8.3 us,
 // 16 rows 9.2, 32 10.7, 64 13.7, where a kernel that only reads B takes 6.4 and an empty one 2.0), and for large B the
-// memory (16 x 28672 x 8192 74 us = 6.4 TB/s). The kernels before it, one with direct loads of 64 bytes per row into the
+// memory (16 x 28672 x 8192 71 us = 6.6 TB/s). The kernels before it, one with direct loads of 64 bytes per row into the
 // operand registers, one with four fetching and four computing wavefronts and a barrier per 16 KB: 16 x 4096 x 4096
 // 11.5 and 10.7 us, 16 x 28672 x 8192 123 and 83, 32 x 5120 x 5120 37 and 21.
 #include "mlt_common.h"
@@ -68,7 +72,7 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
   const int r16 = lane & 15, q = lane >> 4;
   const int bid = (int)blockIdx.x, c0 = bid * share + (bid < rest ? bid : rest), c1 = c0 + share + (bid < rest ? 1 : 0);
   const int nblk = (c1 - c0 + CB - 1) / CB;
-  // pieces p0 .. p1 - 1, of them p0 + wave, p0 + wave + 8, ...
+  // pieces p0 .. p1 - 1, of them first = p0 + wave, first + 8, ..., from `start` on and then from the first again
   int p0 = 0, p1 = (K + SK_KP - 1) / SK_KP;
   if (PARTS) {
     const int per = (p1 + (int)gridDim.y - 1) / (int)gridDim.y;
@@ -76,6 +80,7 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
     p1 = p0 + per < p1 ? p0 + per : p1;
   }
   const int first = p0 + wave, mine = p1 > first ? (p1 - first + SK_NW - 1) / SK_NW : 0;
+  const int start = first + (wave & (mine >= 8 ? 7 : mine >= 4 ? 3 : mine >= 2 ? 1 : 0)) * SK_NW;
   const uint32_t ring = (uint32_t)(uintptr_t)(lptr_t)smem + (uint32_t)wave * SK_RING;
 
   // load instruction i of a slot: rows 4 i .. 4 i + 3, lane l the chunk at position l % 16 of row 4 i + l / 16
@@ -97,7 +102,7 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
       for (int mt = 0; mt < MT; ++mt) acc[gb][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // the cursor: the next slot of the stream to fetch, f_s of piece f_p, and its place
-    int f_t = 0, f_s = 0, f_p = first;
+    int f_t = 0, f_s = 0, f_p = start;
     uint32_t f_slot = ring;
     int issued = 0, need = 0;                            // load instructions issued; up to the end of the slot in hand
     auto fetch = [&]() __attribute__((always_inline)) {
@@ -132,7 +137,10 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
       }
       ++f_t;
       f_slot = f_slot == ring + (R - 1) * L::SLOT ? ring : f_slot + L::SLOT;
-      if (++f_s == S) { f_s = 0; f_p += SK_NW; }
+      if (++f_s == S) {
+        f_s = 0;
+        f_p = f_p + SK_NW < p1 ? f_p + SK_NW : first;
+      }
     };
 #pragma unroll
     for (int i = 0; i < R; ++i) fetch();
@@ -167,8 +175,8 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
       slot = slot == ring + (R - 1) * L::SLOT ? ring : slot + L::SLOT;
     };
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    for (int i = 0; i < mine; ++i) {
-      const int k0 = (first + i * SK_NW) * SK_KP;
+    for (int i = 0, piece = start; i < mine; ++i, piece = piece + SK_NW < p1 ? piece + SK_NW : first) {
+      const int k0 = piece * SK_KP;
       const bool tail = k0 + SK_KP > K;                  // chunks past K: zeros in both operands
       u32x4 af[MT][4];
 #pragma unroll

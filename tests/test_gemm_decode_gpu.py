@@ -17,14 +17,14 @@ def _announce(request):
     binding.mlt_diag_force_variant(gemm="auto")
 
 
-# fewer pieces of 128 k than wavefronts, one for each, one more, two and three rounds of them, pieces that end inside K; up to one column
-# block per workgroup, and more
+# fewer pieces of 128 k than wavefronts, one for each, one more, two and more rounds of them (a wavefront starts at its share's first piece, or one
+# of the first 2, 4 or 8, and goes round), pieces that end inside K; up to one column block per workgroup, and more
 @pytest.mark.parametrize("M", [1, 16, 17, 33, 64])
 @pytest.mark.parametrize("N", [1032, 4112, 16400, 32776])
 def test_k_split_over_wavefronts(M, N):
     from paper_2503_14985_amd import binding
     binding.mlt_diag_force_variant(gemm="skinny")
-    for i, K in enumerate((8, 72, 256, 1024, 1056, 2048, 2088, 3104, 4128)):
+    for i, K in enumerate((8, 72, 256, 1024, 1056, 2048, 2088, 3104, 4128, 5008, 9352)):
         if N > 4112 and i % 3:
             continue
         A, B = inputs.gemm_inputs(M, N, K, FP16 if i % 2 else BF16, i, transB=True)
