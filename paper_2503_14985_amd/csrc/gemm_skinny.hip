@@ -26,9 +26,12 @@
 // beside 128 KB of B). The parts leave fp32 partial results in a scratch, and the one that comes last at a
 // counter adds them in the order of the parts: no second launch, no atomics on values, the same bits on every run.
 //
-// What bounds it: what a CU's memory path takes (about 64 bytes per clock, A and B together: 1 x 4096 x 4096 8.3 us,
-// 16 rows 9.2, 32 10.7, 64 13.7, where a kernel that only reads B takes 6.4 and an empty one 2.0), and for large B the
-// memory (16 x 28672 x 8192 71 us = 6.6 TB/s). The kernels before it, one with direct loads of 64 bytes per row into the
+// What bounds it: what a CU's memory path takes (about 64 bytes per clock, A and B together: 1 x 4096 x 4096 7.4 us,
+// 16 rows 8.3, 32 9.7, where a kernel that only reads B takes 6.4 and an empty one 2.0), for large B the
+// memory (16 x 28672 x 8192 71 us = 6.6 TB/s), and for short calls the way to the first load and what follows the last one. Hence the
+// order of the arguments (what the first loads need lies in their first 64 bytes and is read at once: 8 x 4096 x 1024 4.15 -> 3.93 us) and
+// instances for one and for two column blocks, whose code is not spread over eight (4 x 3392 x 128 3.3 -> 3.1, 8 x 8192 x 1024 5.54 -> 5.43).
+// The kernels before it, one with direct loads of 64 bytes per row into the
 // operand registers, one with four fetching and four computing wavefronts and a barrier per 16 KB: 16 x 4096 x 4096
 // 11.5 and 10.7 us, 16 x 28672 x 8192 123 and 83, 32 x 5120 x 5120 37 and 21.
 #include "mlt_common.h"
@@ -51,27 +54,29 @@ template <int MT, int AU, int BU> struct SkCfg {
   static constexpr int SLOT = LU * 1024;
   static constexpr int R = SK_RING / SLOT < 12 ? SK_RING / SLOT : 12;     // slots
   static constexpr int CB = 4 * BU;                                       // columns per block
-  static constexpr int GB = BU < 4 ? 1 : MT <= 2 ? 8 : 4;                 // blocks per group
-  static_assert(GB * MT * 1024 <= SK_RING, "a wavefront's partial tiles lie in its own ring");
+  static constexpr int MAX_GB = BU < 4 ? 1 : MT <= 2 ? 8 : 4;             // blocks per group, at most
+  static_assert(MAX_GB * MT * 1024 <= SK_RING, "a wavefront's partial tiles lie in its own ring");
   static_assert((R - 1) * LU < 63, "loads in flight are counted");
 };
 
-// share, rest: columns per workgroup, and how many of them have one more. PARTS: blockIdx.y is the part of K; `part` holds
+// share, rest: columns per workgroup, and how many of them have one more. GB: column blocks per group, at least those that a workgroup
+// has or MAX_GB. PARTS: blockIdx.y is the part of K; `part` holds
 // [part][M][N] floats, `counter` one zero per blockIdx.x (left as zero); without counters (null) another kernel adds the parts.
-template <typename Tag, int MT, int AU, int BU, bool PARTS>
+template <typename Tag, int MT, int AU, int BU, bool PARTS, int GB>
 __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
-    int M, int N, int K, const uint16_t* __restrict__ A, int64_t lda,
-    const uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ C, int64_t ldc, int act,
-    const uint16_t* __restrict__ bias, int share, int rest, float* __restrict__ part, uint32_t* __restrict__ counter) {
+    int M, int N, int K, int share, int rest, int lda, int ldb, int act, const uint16_t* __restrict__ A,
+    const uint16_t* __restrict__ B, uint16_t* __restrict__ C, int64_t ldc, const uint16_t* __restrict__ bias,
+    float* __restrict__ part, uint32_t* __restrict__ counter) {
+  asm volatile("" : : "s"(M), "s"(K), "s"(share), "s"(rest), "s"(lda), "s"(ldb), "s"(A), "s"(B));   // all read here, not one behind the other
   typedef typename Elem<Tag>::vec8 V8;
   typedef SkCfg<MT, AU, BU> L;
-  constexpr int GB = L::GB, CB = L::CB, R = L::R;
+  constexpr int CB = L::CB, R = L::R;
   extern __shared__ __align__(16) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, q = lane >> 4;
   const int bid = (int)blockIdx.x, c0 = bid * share + (bid < rest ? bid : rest), c1 = c0 + share + (bid < rest ? 1 : 0);
-  const int nblk = (c1 - c0 + CB - 1) / CB;
+  const int nblk = GB == 1 ? 1 : (c1 - c0 + CB - 1) / CB;
   // pieces p0 .. p1 - 1, of them first = p0 + wave, first + 8, ..., from `start` on and then from the first again
   int p0 = 0, p1 = (K + SK_KP - 1) / SK_KP;
   if (PARTS) {
@@ -93,7 +98,7 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
     vb[i] = (uint32_t)(i * 4 + lane / 16) * (uint32_t)ldb * 2u + (uint32_t)((lane % 16) ^ (i * 4 + lane / 16)) * 16u;
 
   for (int base = 0; base < nblk; base += GB) {
-    const int nb = nblk - base < GB ? nblk - base : GB;
+    const int nb = GB == 1 ? 1 : nblk - base < GB ? nblk - base : GB;
     const int S = MT + nb, T = mine * S;                 // slots per piece (row tiles, then column blocks), in all
     f32x4 acc[GB][MT];
 #pragma unroll
@@ -112,7 +117,7 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
       // rows past the matrix (past this workgroup's columns) and chunks past K: the piece's first chunk for all such
       // lanes, never stored or zeroed later; the instruction stays, and with it the count of loads in flight
       if (f_s < MT) {
-        const char* src = reinterpret_cast<const char*>(A + (int64_t)(f_s * 16) * lda + k0);
+        const char* src = reinterpret_cast<const char*>(A + (int64_t)(f_s * 16) * (uint32_t)lda + k0);
         const int rows = M - f_s * 16;
 #pragma unroll
         for (int i = 0; i < AU; ++i) {
@@ -124,7 +129,7 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
         issued += AU;
       } else {
         const int n0 = c0 + (base + f_s - MT) * CB;
-        const char* src = reinterpret_cast<const char*>(B + (int64_t)n0 * ldb + k0);
+        const char* src = reinterpret_cast<const char*>(B + (int64_t)n0 * (uint32_t)ldb + k0);
         const int rows = c1 - n0;
 #pragma unroll
         for (int i = 0; i < BU; ++i) {
@@ -267,9 +272,9 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
   }
 }
 
-template <typename Tag, int MT, int AU, int BU, bool PARTS>
-int launch_skinny(const GemmArgs& g, int64_t ncu, hipStream_t s) {
-  auto kern = gemm_skinny_kernel<Tag, MT, AU, BU, PARTS>;
+template <typename Tag, int MT, int AU, int BU, bool PARTS, int GB>
+int launch_skinny_blocks(const GemmArgs& g, unsigned nwg, hipStream_t s) {
+  auto kern = gemm_skinny_kernel<Tag, MT, AU, BU, PARTS, GB>;
   static thread_local int configured_dev = -1;            // opt in to > 64 KB LDS once per device
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MLT_ERR_DEVICE;
@@ -280,12 +285,22 @@ int launch_skinny(const GemmArgs& g, int64_t ncu, hipStream_t s) {
     }
     configured_dev = dev;
   }
-  const int64_t parts = PARTS ? g.parts : 1, want = ncu / parts > 0 ? ncu / parts : 1;
-  const unsigned nwg = (unsigned)(g.N < want ? g.N : want);   // one workgroup per CU, every one with columns
+  const int parts = PARTS ? g.parts : 1;
   hipLaunchKernelGGL(kern, dim3(nwg, (unsigned)parts), dim3(SK_NT), SK_SMEM, s, (int)g.M, (int)g.N, (int)g.K,
-                     g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.act, g.bias, (int)(g.N / nwg), (int)(g.N % nwg), g.scratch, g.counters);
+                     (int)(g.N / nwg), (int)(g.N % nwg), (int)g.lda, (int)g.ldb, g.act, g.A, g.B, g.C, g.ldc, g.bias, g.scratch, g.counters);
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
-  return PARTS && !g.counters ? run_splitk_reduce(g, (int)parts, g.M * g.N, s) : MLT_OK;
+  return PARTS && !g.counters ? run_splitk_reduce(g, parts, g.M * g.N, s) : MLT_OK;
+}
+
+template <typename Tag, int MT, int AU, int BU, bool PARTS>
+int launch_skinny(const GemmArgs& g, int64_t ncu, hipStream_t s) {
+  constexpr int MAX_GB = SkCfg<MT, AU, BU>::MAX_GB;
+  const int64_t want = ncu / (PARTS ? g.parts : 1) > 0 ? ncu / (PARTS ? g.parts : 1) : 1;
+  const unsigned nwg = (unsigned)(g.N < want ? g.N : want);   // one workgroup per CU, every one with columns
+  const int64_t blocks = ((g.N + nwg - 1) / nwg + 4 * BU - 1) / (4 * BU);
+  if (blocks == 1) return launch_skinny_blocks<Tag, MT, AU, BU, PARTS, 1>(g, nwg, s);
+  if (blocks == 2 && MAX_GB == 8) return launch_skinny_blocks<Tag, MT, AU, BU, PARTS, MAX_GB == 8 ? 2 : MAX_GB>(g, nwg, s);
+  return launch_skinny_blocks<Tag, MT, AU, BU, PARTS, MAX_GB>(g, nwg, s);
 }
 
 template <typename Tag, int MT, int AU>
@@ -319,7 +334,7 @@ bool gemm_skinny_ok(const GemmArgs& g) {
   if (!g.transB || g.acc32 || g.M > 64 || g.N < 1024) return false;
   if (!al16(g.A) || !al16(g.B)) return false;
   if (g.K % 8 || g.lda % 8 || g.ldb % 8) return false;
-  // 32-bit byte offsets from a block's first row
+  // 32-bit byte offsets from a block's first row (and with them 32-bit row strides)
   return g.lda * 2 * 16 + g.K * 2 < ((int64_t)1 << 32) && g.ldb * 2 * 16 + g.K * 2 < ((int64_t)1 << 32);
 }
 
