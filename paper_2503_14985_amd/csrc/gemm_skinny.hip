@@ -16,7 +16,9 @@
 //   * a wavefront starts some pieces into its share and goes round, each at another place: all of them walk through K
 //     in step, and where the rows of B are a power of two long (K = 4096: 8 KB) the whole chip would read the same 2 KB
 //     out of every 8 at a time, a part of the memory's channels (us, from the first piece / going round: 1 x 8192 x 4096 17.9 / 12.5, 16 x 8192 x
-//     8192 28.8 / 25.4, 32 x 4096 x 8192 19.6 / 16.9, 16 x 28672 x 4096 39.6 / 36.7; 16 x 9000 x 2880 12.6 / 12.7);
+//     8192 28.8 / 25.4, 32 x 4096 x 8192 19.6 / 16.9, 16 x 28672 x 4096 39.6 / 36.7; 16 x 9000 x 2880 12.6 / 12.7). Not where rows do not start on
+//     64 bytes: two wavefronts' neighbouring pieces then share a line, which comes from memory once only if both ask for it at the same
+//     time (1 x 22912 x 7768 64.3 / 73.4, 15 x 8192 x 4104 14.8 / 16.5; but rows of 64 bytes' multiples, 1 x 8192 x 4128 16.4 / 15.3);
 //   * with more than 16 columns a piece of A is fetched once for a group of up to 8 column blocks (4 from three row
 //     tiles on), whose accumulators stay in registers;
 //   * at the end the 8 partial tiles of a column block meet in LDS and are added in wavefront order.
@@ -85,7 +87,8 @@ __global__ __launch_bounds__(SK_NT, 2) void gemm_skinny_kernel(
     p1 = p0 + per < p1 ? p0 + per : p1;
   }
   const int first = p0 + wave, mine = p1 > first ? (p1 - first + SK_NW - 1) / SK_NW : 0;
-  const int start = first + (wave & (mine >= 8 ? 7 : mine >= 4 ? 3 : mine >= 2 ? 1 : 0)) * SK_NW;
+  const bool shared_lines = ((reinterpret_cast<uintptr_t>(B) | (uintptr_t)((uint32_t)ldb * 2u)) & 63) != 0;
+  const int start = first + (shared_lines ? 0 : wave & (mine >= 8 ? 7 : mine >= 4 ? 3 : mine >= 2 ? 1 : 0)) * SK_NW;
   const uint32_t ring = (uint32_t)(uintptr_t)(lptr_t)smem + (uint32_t)wave * SK_RING;
 
   // load instruction i of a slot: rows 4 i .. 4 i + 3, lane l the chunk at position l % 16 of row 4 i + l / 16
