@@ -114,6 +114,58 @@ static const char* any_name(int variant, int transB) {
   return transB ? "gemm_general_nt_256x256x64_w2x4" : "gemm_general_nn_256x256x64_w2x4";
 }
 
+// The streaming kernel of gemm_skinny.hip: its parts and its block
+static void plan_skinny(const GemmArgs& g, int64_t ncu, GemmPlan& p) {
+  // K over 1, 2, 4 or 8 workgroups: B's arrival + what a CU fetches of A (at 100 GB/s) + the price of the partial
+  // results (a fit to the times of 175 problems: the choice is 1.2 % behind the best one on average, 26 % at worst)
+  auto time = [&](int64_t parts) {
+    const int64_t rows = g.M <= 4 ? 4 : (g.M + 15) / 16 * 16;
+    return g.N * g.K * 2 / 6600 + rows * g.K * 2 / (100 * parts) + (parts > 1 ? 800 + 7 * parts * g.M * g.N / 1000 : 0);
+  };
+  p.parts = g.forced_parts > 0 ? g.forced_parts : 1;
+  if (g.forced == GEMM_AUTO && g.forced_parts == 0)
+    for (int n = 2; n <= 8; n *= 2)
+      if (n * g.M * g.N * 4 <= kStaticScratchBytes && time(n) < time(p.parts)) p.parts = n;
+  p.scratch_bytes = p.parts > 1 ? (int64_t)p.parts * g.M * g.N * 4 : 0;
+  p.variant = GEMM_SKINNY;
+  p.name = "gemm_nt_skinny_stream";
+  p.bm = (int)((g.M + 15) / 16) * 16; p.bn = gemm_skinny_cols(g.N, p.parts, ncu); p.bk = 128;
+  p.wm = 1; p.wn = 1;
+  p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
+}
+
+// Up to 64 rows against B stored N x K: the streaming kernel, or the tile kernels? All times with B coming from memory, as a
+// decoder's weights do (every matrix is read once per token, and a model is far larger than the 256 MiB last-level cache). On the
+// same B again and again the tile kernels gain up to a third, the streaming kernel, which does not keep B in the caches, nothing: where the
+// two are within a few percent it is the tiles (us, streaming / tiles, B from memory and, in brackets, repeated: 33 x 28672 x 4096 44 / 51 (44 / 38), 64 x
+// 28672 x 4096 50 / 54 (50 / 39), 48 x 4096 x 4096 11.6 / 12.1 (10.5 / 11.1), 64 x 8192 x 14336 49 / 46 (48 / 40)). Over 962 problems of up to 64 rows, 1024
+// to 100000 columns and K from 8 to 28672 the choice is 0.4 % behind the better kernel on average (streaming always: 10 %, 3.2 times at worst).
+static bool stream_wins(const GemmArgs& g, int64_t ncu, const GemmPlan& tiles) {
+  const int64_t kt = (g.K + 63) / 64;
+  // Few steps of K: a wavefront of the streaming kernel has one piece or none, and what takes the time is its column blocks one behind the
+  // other, each with a sum over 8 partial tiles; a workgroup of the tile kernels has one tile and few steps (us, streaming / tiles:
+  // 9 x 14768 x 64 4.7 / 3.1, 19 x 60280 x 24 13.4 / 4.5, 23 x 17600 x 256 6.0 / 5.6, with GELU 28 x 18776 x 64 7.0 / 5.0; but 1 x 1784 x 320 2.9 / 5.4,
+  // 8 x 18784 x 208 5.2 / 5.6; one row tile from 5 steps on: 2 x 69240 x 384 13.8 / 15.8). A fused activation costs the tile kernels more, whose
+  // workgroups are fewer.
+  if (g.M <= 32) return kt >= (g.M > 16 ? 8 : 5) || g.N * ((g.M + 15) / 16) <= 16 * ncu * kt * (g.fused() ? 2 : 1);
+  if (kt < 8) return false;
+  // Three and four row tiles: a workgroup of the tile kernels multiplies them all at once, so these win where their grid (`tiles`: the kernel and
+  // parts that they would take) fills its rounds, one or two, of the chip; the streaming kernel has a workgroup on every CU in any case (us,
+  // streaming / tiles; 64 x 128 tiles: 52 x 31704 x 1856, 248 of them, 30.1 / 23.7; 64 x 52736 x 576, 412, 26.8 / 17.4; 33888 x 1024, 265, 21.2 / 22.6;
+  // 55 x 6904 x 6784 in four parts, 216, 26.3 / 23.8; 41 x 5592 x 3520, 176, 12.9 / 14.7; 38 x 7664 x 3392, 240, 13.8 / 15.7; 64 x 64 tiles: 51 x 1808 x 20736 in
+  // eight, 232, 26.4 / 21.8; 60 x 13016 x 512, 204, 7.8 / 6.8; 42 x 12448 x 5632, 195, 28.7 / 31.7; 44 x 28384 x 1088, 444, 19.6 / 17.8; 34 x 24160 x 1024, 378,
+  // 14.3 / 15.6). Rows of K that are not whole steps make the tile kernels' loads slower.
+  if (g.M > 48 && g.N <= 16 * ncu && kt >= 64 && kt < 256 && tiles.parts > 1) return false;   // 64 x 4096 x 4096 13.9 / 12.8, 61 x 2976 x 16192 29.5 / 26.4
+  const bool wide = tiles.variant == GEMM_64X128_K2;
+  const int64_t wgs = (g.N + (wide ? 127 : 63)) / (wide ? 128 : 64) * tiles.parts, rounds = (wgs + ncu - 1) / ncu;
+  const bool split = tiles.parts >= 4 && rounds == 1 && g.K % 64 == 0 && kt >= 16 * tiles.parts;
+  if (wide) return !(4 * wgs >= 3 * ncu * rounds && (tiles.parts == 1 ? rounds <= 2 : split));
+  if (tiles.variant != GEMM_64_K4) return true;
+  if (tiles.parts > 1) return !(8 * wgs >= 5 * ncu && tiles.parts == 8 && split);
+  if (rounds == 1) return !(8 * wgs >= 5 * ncu && g.K % 64 == 0 && kt < (g.fused() ? 12 : 40));
+  return !(5 * wgs >= 4 * ncu * rounds && g.K % 64 == 0 && kt < 20 && !g.fused());
+}
+
 GemmPlan plan_gemm(const GemmArgs& g_in) {
   GemmPlan p;
   GemmArgs g = g_in;
@@ -134,31 +186,9 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   DeviceInfo di;
   const int64_t NCU = device_info(di) && di.ncu > 0 ? di.ncu : 256;
   const int64_t KT = (g.K + 63) / 64;
-  // ---- short A against B stored N x K: the streaming kernel of gemm_skinny.hip (all figures with B coming from memory, as a
-  // decoder's weights do: every matrix is read once per token, and a model is far larger than the 256 MiB last-level cache).
-  // Over 135 problems of 1 to 64 rows it is 1.14 times as fast as the best of the tile kernels and its own predecessors (us:
-  // 16 x 4096 x 4096 11.6 -> 9.5, 24 x 14336 x 4096 with bias and GELU 25.9 -> 23.7, 16 x 1024 x 8192 13.2 -> 7.9, 47 x 8640 x 5376
-  // 35.5 -> 23.0). It stays behind the tile kernels where a CU's rows of A are long beside its few columns and not so
-  // long that splitting K pays for itself (64 x 4096 x 4096 12.8 on tiles, 13.9 here; 61 x 2976 x 16192 26.4, 29.5; but 64 x 1024 x 28672 24.8, 19.9),
-  // and for tall A against a few steps of K (64 x 5512 x 72 4.4, 5.8).
-  const bool tiles_win = (g.M > 48 && g.N <= 16 * NCU && KT >= 64 && KT < 256) || (g.M > 32 && KT < 8);
-  if ((g.forced == GEMM_SKINNY || (g.forced == GEMM_AUTO && !tiles_win)) && gemm_skinny_ok(g)) {
-    // K over 1, 2, 4 or 8 workgroups: B's arrival + what a CU fetches of A (at 100 GB/s) + the price of the partial
-    // results (a fit to the times of 175 problems: the choice is 1.2 % behind the best one on average, 26 % at worst)
-    auto time = [&](int64_t parts) {
-      const int64_t rows = g.M <= 4 ? 4 : (g.M + 15) / 16 * 16;
-      return g.N * g.K * 2 / 6600 + rows * g.K * 2 / (100 * parts) + (parts > 1 ? 800 + 7 * parts * g.M * g.N / 1000 : 0);
-    };
-    p.parts = g.forced_parts > 0 ? g.forced_parts : 1;
-    if (g.forced == GEMM_AUTO && g.forced_parts == 0)
-      for (int n = 2; n <= 8; n *= 2)
-        if (n * g.M * g.N * 4 <= kStaticScratchBytes && time(n) < time(p.parts)) p.parts = n;
-    p.scratch_bytes = p.parts > 1 ? (int64_t)p.parts * g.M * g.N * 4 : 0;
-    p.variant = GEMM_SKINNY;
-    p.name = "gemm_nt_skinny_stream";
-    p.bm = (int)((g.M + 15) / 16) * 16; p.bn = gemm_skinny_cols(g.N, p.parts, NCU); p.bk = 128;
-    p.wm = 1; p.wn = 1;
-    p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
+  const bool skinny = gemm_skinny_ok(g);
+  if (skinny && (g.forced == GEMM_SKINNY || (g.forced == GEMM_AUTO && g.M <= 32 && stream_wins(g, NCU, p)))) {
+    plan_skinny(g, NCU, p);
     return p;
   }
   // ---- the tile kernels: workgroup tile and K split
@@ -320,6 +350,11 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     }
     if (better) pick = all[i];
     have = true;
+  }
+  p.variant = pick.variant; p.parts = pick.parts;
+  if (skinny && g.forced == GEMM_AUTO && g.M > 32 && stream_wins(g, NCU, p)) {
+    plan_skinny(g, NCU, p);
+    return p;
   }
   int v = pick.variant;
   const int best_parts = pick.parts;
@@ -515,6 +550,9 @@ int run_gemm(const GemmArgs& g_in, GemmPlan& p, hipStream_t s) {
         own = true;
       } else {
         (void)hipGetLastError();
+        // (the choice of the tile kernels for a short A was made for their split: us per captured call, 64 x 8192 x 14336
+        // 112 on tiles, 58 streaming)
+        if (g.forced == GEMM_AUTO && gemm_skinny_ok(g)) { g.forced_parts = 1; p = plan_gemm(g); }
         g.parts = 1;
         p.parts = 1;                                       // what ran, for the reported kernel name
         p.scratch_bytes = 0;

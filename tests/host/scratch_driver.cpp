@@ -55,6 +55,7 @@ static void call(const char* what, void* s) {
   int rc = -99;
   if (!strcmp(what, "gemm")) rc = mlt_gemm(16, 1024, 8192, at(1), 8192, at(2), 8192, 1, at(99), 1024, MLT_BF16, s);
   if (!strcmp(what, "tiles")) rc = mlt_gemm(777, 4096, 14336, at(1), 14336, at(99), 14336, 1, at(999), 4096, MLT_BF16, s);
+  if (!strcmp(what, "tall")) rc = mlt_gemm(44, 7296, 11456, at(1), 11456, at(99), 11456, 1, at(999), 7296, MLT_BF16, s);
   if (!strcmp(what, "mha")) rc = mlt_mha_fwd(1, 8, 1, 4096, 128, at(1), at(2), at(99), at(999), 0.1f, 0, MLT_BF16, s);
   if (!strcmp(what, "paged"))
     rc = mlt_paged_attn_decode(1, 8, 128, 16, 256, 256, at(1), at(2), at(99), (const int32_t*)at(500), (const int32_t*)at(501), at(999), 0.1f, MLT_BF16, s);

@@ -202,11 +202,12 @@ def test_k_split_is_chosen_for_few_tiles_against_a_long_k(shape):
 
 @pytest.mark.parametrize("shape,kernel", [
     ((16, 8192, 4096), "gemm_nt_skinny_stream"), ((16, 4096, 4096), "gemm_nt_skinny_stream"), ((30, 4096, 2048), "gemm_nt_skinny_stream"),
-    ((17, 8192, 4096), "gemm_nt_skinny_stream"), ((40, 16384, 2048), "gemm_nt_skinny_stream"),
+    ((17, 8192, 4096), "gemm_nt_skinny_stream"), ((40, 16384, 4096), "gemm_nt_skinny_stream"),
     # a long K against few columns: K over several workgroups as well
     ((32, 4096, 28672), "gemm_nt_skinny_stream_splitk4"),
-    # four row tiles against a K that is neither short nor long enough for that: the tile kernels
-    ((64, 4096, 4096), "gemm_nt_64x64x64_w2x2_k4_splitk4")])
+    # four row tiles against a K that is neither short nor long enough for that, tiles that fill the chip, few steps of K: the tile kernels
+    ((64, 4096, 4096), "gemm_nt_64x64x64_w2x2_k4_splitk4"), ((40, 16384, 2048), "gemm_nt_64x64x64_w2x2_k4"),
+    ((64, 8192, 28672), "gemm_nt_64x128x64_w2x4_k2_splitk4"), ((9, 14768, 64), "gemm_nt_64x64x64_w2x2")])
 def test_skinny_routing(shape, kernel):
     M, N, K = shape
     name, _ = _go(M, N, K, BF16, True, std=0.02, seed=9)
@@ -332,7 +333,7 @@ def test_config3_llm_shapes_transB(shape):
 
 
 @pytest.mark.parametrize("shape,parts", [((16, 28672, 8192), ""), ((1, 28672, 8192), ""), ((64, 28672, 4096), ""), ((16, 131072, 4096), ""),
-                                         ((32, 8192, 28672), "_splitk4"), ((64, 8192, 28672), "_splitk4")])
+                                         ((32, 8192, 28672), "_splitk4"), ((64, 9200, 28672), "_splitk4")])
 def test_decode_shapes_streaming_kernels_full_size(shape, parts):
     # the memory-bound decode GEMMs at their real sizes, in the launch configuration the library
     # picks (several column blocks per workgroup; K in parts); sampled against the oracle

@@ -124,18 +124,35 @@ def test_paged_decode_is_cut_finer_only_where_that_gains(plan):
 
 def test_routing_of_decode_gemms(plan):
     """Up to 64 rows against B stored N x K: B is streamed, with K over several workgroups where their few columns stand against
-    a long K; but not by 33 rows and more against less than 8 steps of 64 k, nor by 49 and more where few columns meet 64 to
-    255 steps."""
+    a long K."""
     ask = lambda M, N, K, fused=0: plan([gemm_line(M, N, K, 1, fused=fused)])[0].rsplit(" ", 1)[0]
     for c in ((17, 6456, 5544), (24, 14336, 4096), (24, 14336, 4096, 1), (24, 4096, 2880), (16, 3584, 2048), (1, 4096, 2880), (1, 3072, 4096),
-              (1, 1024, 8192), (1, 5120, 5120, 1), (1, 4096, 4096), (16, 4096, 4096), (30, 4096, 2048), (2, 3592, 4096), (40, 16384, 2048),
-              (64, 28672, 4096), (33, 4096, 456), (64, 4096, 512), (48, 4096, 4096), (49, 4104, 4096), (64, 4096, 4032)):
+              (1, 1024, 8192), (1, 5120, 5120, 1), (1, 4096, 4096), (16, 4096, 4096), (30, 4096, 2048), (2, 3592, 4096), (40, 16384, 4096),
+              (64, 28672, 4096), (64, 4096, 512), (48, 4096, 4096), (49, 4104, 4096), (64, 4096, 4032)):
         assert ask(*c) == "gemm_nt_skinny_stream 1", c
     for c, parts in (((17, 5120, 8192), 4), ((15, 1656, 11200, 1), 4), ((32, 2048, 8192), 4), ((24, 1024, 11200), 8), ((16, 1024, 28672), 8),
-                     ((16, 1024, 28672, 1), 8), ((1, 1024, 28672, 1), 8), ((32, 1024, 28672), 8), ((64, 4096, 16384), 4)):
+                     ((16, 1024, 28672, 1), 8), ((1, 1024, 28672, 1), 8), ((32, 1024, 28672), 8), ((50, 4800, 12608), 4)):
         assert ask(*c) == "gemm_nt_skinny_stream %d" % parts, c
-    for c in ((33, 4096, 448), (64, 5512, 72), (49, 4096, 4096), (64, 4096, 4096), (64, 1024, 16320)):
-        assert ask(*c).startswith("gemm_nt_64x"), c
+
+
+@pytest.mark.parametrize("stream,tiles", [
+    # up to 32 rows: columns per CU, row tiles, steps of 64 k (and a fused activation) against each other
+    ((1, 4096, 64), (1, 4104, 64)), ((16, 8192, 128), (16, 8200, 128)), ((16, 8192, 72), (16, 8200, 72)), ((32, 4096, 128), (32, 4104, 128)),
+    ((17, 2048, 64), (17, 2056, 64)), ((16, 60000, 264), (16, 60000, 256)), ((32, 14336, 448), (32, 14344, 448)), ((32, 30000, 456), (32, 30000, 448)), ((24, 8192, 128, 1), (24, 8200, 128, 1)),
+    # 33 rows and more: 8 steps
+    ((33, 4096, 456), (33, 4096, 448)), ((64, 4096, 512), (64, 5512, 72)),
+    # 49 rows and more, at most 16 columns per CU, 64 to 255 steps
+    ((48, 4096, 4096), (49, 4096, 4096)), ((64, 4104, 4096), (64, 4096, 4096)), ((64, 4096, 4032), (64, 1024, 16320)), ((64, 1024, 28608), (64, 1024, 16320)),
+    # 64 x 128 tiles that fill three quarters of one or two rounds; one, in four or eight parts
+    ((52, 24448, 1856), (52, 31704, 1856)), ((42, 33888, 1024), (64, 52736, 576)), ((41, 5592, 3520), (55, 6904, 6784)), ((37, 2928, 9664), (45, 3456, 9984)),
+    ((45, 3456, 9992), (45, 3456, 9984)), ((38, 7664, 4032), (38, 7664, 4608)),
+    # 64 x 64 tiles, in eight parts or few steps: five eighths of one round, four fifths of several
+    ((34, 1112, 9984), (51, 1808, 20736)), ((60, 9216, 512), (60, 13016, 512)), ((60, 13016, 520), (60, 13016, 512)), ((42, 12448, 5632), (42, 12448, 2496)),
+    ((42, 12448, 1024, 1), (42, 12448, 640, 1)), ((44, 28384, 1280), (44, 28384, 1216)), ((44, 24160, 1216), (44, 28384, 1216)), ((44, 28384, 640, 1), (44, 12448, 640, 1))])
+def test_where_the_tile_kernels_take_over_from_the_streaming_kernel(plan, stream, tiles):
+    ask = lambda M, N, K, fused=0: plan([gemm_line(M, N, K, 1, fused=fused)])[0]
+    assert ask(*stream).startswith("gemm_nt_skinny_stream"), stream
+    assert ask(*tiles).startswith("gemm_nt_64x"), (tiles, ask(*tiles))
 
 
 def test_a_tiling_hint_on_unaligned_operands_is_the_automatic_choice(plan):

@@ -8,7 +8,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 LIB_DIR = os.path.join(ROOT, "paper_2503_14985_amd")
-CALLS = ("gemm", "tiles", "mha", "paged", "few")       # decode GEMM, tile GEMM, attention, paged decode in many ranges and in few
+CALLS = ("gemm", "tiles", "tall", "mha", "paged", "few")       # decode GEMM, tile GEMM (and of 44 rows), attention, paged decode in many ranges and in few
 
 
 @pytest.fixture(scope="module")
@@ -61,10 +61,16 @@ def test_more_threads_than_buffers(ask, call):
     streams' buffers are not used up by threads."""
     *got, last = ask([(call, "P%d" % t) for t in range(34)] + [(call, "5")])
     assert [events[0] for _, events in got] == ["A"] * 32 + [got[32][1][0]] * 2
-    assert got[32][1] == (["aP", "LP", "LP", "fP"] if call in ("gemm", "tiles") else ["LP"]) and last[1][0] == "A"
+    assert got[32][1] == (["aP", "LP", "LP", "fP"] if call in ("gemm", "tiles", "tall") else ["LP"]) and last[1][0] == "A"
 
 
 @pytest.mark.parametrize("call", CALLS)
 def test_a_call_that_is_recorded_allocates_nothing(ask, call):
     (_, events), = ask([(call, "c")])
     assert len(launches(events)) == len(events) == 1
+
+
+def test_a_recorded_call_without_its_split_takes_the_kernel_that_is_better_without(ask):
+    """44 x 7296 x 11456: four parts on 64 x 128 tiles; not split the streaming kernel takes half the time."""
+    (tiles, _), (stream, _) = ask([("tall", "0"), ("tall", "c")])
+    assert tiles == "gemm_nt_64x128x64_w2x4_k2_splitk4" and stream == "gemm_nt_skinny_stream"
