@@ -154,7 +154,7 @@ int mlt_mha_fwd(int64_t B, int64_t H, int64_t Sq, int64_t Sk, int64_t D, const v
  * The keys are split over the wavefronts of a workgroup and the partial maxima, sums and outputs
  * are reduced through LDS (the paper's warp-level decomposition, Listing 6); with too few
  * sequences x heads to fill the chip the keys are split over several workgroups as well, whose
- * partial results a second kernel merges in a fixed order. Weights are rounded
+ * partial results are merged in a fixed order, by the one that comes last or by a second kernel. Weights are rounded
  * to `dtype` before they multiply V (Listing 5). The paper fixes no storage layout; this one is
  *   Q, O          device, contiguous [B, H, D]
  *   Kc, Vc        device, contiguous [num_blocks, H, block_size, D]: the cache, physical blocks

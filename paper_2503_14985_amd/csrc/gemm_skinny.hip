@@ -32,7 +32,7 @@
 // 16 rows 8.3, 32 9.7, where a kernel that only reads B takes 6.4 and an empty one 2.0), for large B the
 // memory (16 x 28672 x 8192 71 us = 6.6 TB/s), and for short calls the way to the first load and what follows the last one. Hence the
 // order of the arguments (what the first loads need lies in their first 64 bytes and is read at once: 8 x 4096 x 1024 4.15 -> 3.93 us) and
-// instances for one and for two column blocks, whose code is not spread over eight (4 x 3392 x 128 3.3 -> 3.1, 8 x 8192 x 1024 5.54 -> 5.43).
+// instances for one and for two column blocks, whose code is not spread over eight (3 x 3392 x 128 3.3 -> 3.1, 8 x 8192 x 1024 5.54 -> 5.43).
 // The kernels before it, one with direct loads of 64 bytes per row into the
 // operand registers, one with four fetching and four computing wavefronts and a barrier per 16 KB: 16 x 4096 x 4096
 // 11.5 and 10.7 us, 16 x 28672 x 8192 123 and 83, 32 x 5120 x 5120 37 and 21.

@@ -55,11 +55,12 @@ static void plan_key_groups(const MhaArgs& a, MhaPlan& p) {
     else if (a.causal) t = wgs * (rounds > 2 ? avg * 5 / 4 : avg) / ncu + (rounds + 1) / 2 * (ends - 1000) + 4000;
     else t = rounds * (avg + 3000) + 4000;
     if (t < longest + 7000) t = longest + 7000;
-    // Masked items in a second, partly filled round of 128-row tiles, where the 256-row kernel needs one round: a long item
-    // may start behind another one (D = 64: shares its CU with it). An XCD's range ends with the last tiles of its
-    // last head when it has whole heads; then the `extra` items behind the first round are the shorter ones of that head.
-    // 128 / 256 rows, us: D = 128, 12 heads x 3403 82 / 72, 22 x 1574 42 / 38, but 24 x 1536 30 / 37; D = 64, 29 x 1809 38 / 35, 40 x 998
-    // 26 / 23, but 16 x 2202 33 / 41. (A full second round of D = 64 is evened out by block_map_masked.)
+    // Masked items in a second, partly filled round of 128-row tiles, where the 256-row kernel needs one round. The term was fitted to
+    // workgroups that went through the heads one by one, so that a long item could start behind another one; the figures are those of the order
+    // of today, longest first (block_map_masked), in which the two share little. us, 64 / 128 / 256 rows: D = 128, 15 heads x
+    // 3566 87 / 102 / 77, 9 x 5585 124 / 145 / 115, but 24 x 1290 26 / 27 / 32, 32 x 1055 28 / 23 / 28 and 24 x 2029 48 / 40 / 46; D = 64, 24 x 1394 18 / 22 / 27, 8 x
+    // 4647 41 / 61 / 78, 16 x 2688 31 / 37 / 47, but 56 x 671 15 / 13 / 17, 48 x 1110 20 / 19 / 24. Over 260 such problems the choice is 4 % (D = 128) and
+    // 14 % (D = 64) behind the best one; without the term 5 and 9 %, but half as long again at worst, where 64 rows are right.
     if (a.causal && groups == 2 && rounds == 2 && one_round_of_256 && (a.D == 128 || wgs < 2 * ncu)) {
       const int64_t extra = (wgs - ncu + nxcd - 1) / nxcd;
       if (heads % nxcd != 0 || (a.D == 128 && 4 * extra >= 3 * nq)) t += longest / 2;
