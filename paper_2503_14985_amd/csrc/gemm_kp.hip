@@ -286,16 +286,20 @@ __global__ __launch_bounds__(KP_NT, 2) void gemm_kp_kernel(
       constexpr int CPT = BN / 8, NI = RPP * CPT / KP_NT;
       const int c = tid % CPT * 8, col = n0 + c;
       __syncthreads();
+      auto rows = [&](auto STREAM) __attribute__((always_inline)) {
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const int r = tid / CPT + i * (KP_NT / CPT);
-        const float* src = img + r * S + c;
-        f32x4 lo = *reinterpret_cast<const f32x4_mem*>(src), hi = *reinterpret_cast<const f32x4_mem*>(src + 4);
-        add4(lo, *reinterpret_cast<const f32x4_mem*>(src + RPP * S));
-        add4(hi, *reinterpret_cast<const f32x4_mem*>(src + RPP * S + 4));
-        if (row0 + r < M && col < N)
-          store_row8<Tag>(lo, hi, C + (int64_t)(row0 + r) * ldc + col, N - col, epi, bias ? bias + col : nullptr);
-      }
+        for (int i = 0; i < NI; ++i) {
+          const int r = tid / CPT + i * (KP_NT / CPT);
+          const float* src = img + r * S + c;
+          f32x4 lo = *reinterpret_cast<const f32x4_mem*>(src), hi = *reinterpret_cast<const f32x4_mem*>(src + 4);
+          add4(lo, *reinterpret_cast<const f32x4_mem*>(src + RPP * S));
+          add4(hi, *reinterpret_cast<const f32x4_mem*>(src + RPP * S + 4));
+          if (row0 + r < M && col < N)
+            store_row8<Tag, STREAM.value>(lo, hi, C + (int64_t)(row0 + r) * ldc + col, N - col, epi, bias ? bias + col : nullptr);
+        }
+      };
+      if (epi & EPI_STREAM) rows(std::true_type{});
+      else rows(std::false_type{});
     }
   }
 }

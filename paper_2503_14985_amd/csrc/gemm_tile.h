@@ -347,18 +347,22 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
       }
     } else {
       constexpr int CPT = BN / 8;
-      for (int it = threadIdx.x; it < BM * CPT; it += NTHR) {
-        const int r = it / CPT, c = it % CPT * 8;
-        const float* src = red + r * S + c;
-        f32x4 lo = *reinterpret_cast<const f32x4_mem*>(src), hi = *reinterpret_cast<const f32x4_mem*>(src + 4);
+      auto rows = [&](auto STREAM) __attribute__((always_inline)) {
+        for (int it = threadIdx.x; it < BM * CPT; it += NTHR) {
+          const int r = it / CPT, c = it % CPT * 8;
+          const float* src = red + r * S + c;
+          f32x4 lo = *reinterpret_cast<const f32x4_mem*>(src), hi = *reinterpret_cast<const f32x4_mem*>(src + 4);
 #pragma unroll
-        for (int g2 = 1; g2 < KS; ++g2) {
-          add4(lo, *reinterpret_cast<const f32x4_mem*>(src + g2 * BM * S));
-          add4(hi, *reinterpret_cast<const f32x4_mem*>(src + g2 * BM * S + 4));
+          for (int g2 = 1; g2 < KS; ++g2) {
+            add4(lo, *reinterpret_cast<const f32x4_mem*>(src + g2 * BM * S));
+            add4(hi, *reinterpret_cast<const f32x4_mem*>(src + g2 * BM * S + 4));
+          }
+          if (m0 + r < M && n0 + c < N)
+            store_row8<Tag, STREAM.value>(lo, hi, C + (int64_t)(m0 + r) * ldc + n0 + c, N - n0 - c, epi, bias ? bias + n0 + c : nullptr);
         }
-        if (m0 + r < M && n0 + c < N)
-          store_row8<Tag>(lo, hi, C + (int64_t)(m0 + r) * ldc + n0 + c, N - n0 - c, epi, bias ? bias + n0 + c : nullptr);
-      }
+      };
+      if (epi & EPI_STREAM) rows(std::true_type{});
+      else rows(std::false_type{});
     }
   } else {
     static_assert(KS == 1, "the large tiles have no K split inside the workgroup");

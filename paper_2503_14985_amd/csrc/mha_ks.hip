@@ -362,9 +362,9 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void mha_ks_kernel(
       *reinterpret_cast<f32x4_mem*>(po + prow * D + d + 4) = hi;
     } else {
       const float inv = 1.f / sum;
-      *reinterpret_cast<u32x4_mem*>(O + row * D + d) =
-          u32x4{Elem<Tag>::pack2(lo[0] * inv, lo[1] * inv), Elem<Tag>::pack2(lo[2] * inv, lo[3] * inv),
-                Elem<Tag>::pack2(hi[0] * inv, hi[1] * inv), Elem<Tag>::pack2(hi[2] * inv, hi[3] * inv)};
+      const u32x4 o = {Elem<Tag>::pack2(lo[0] * inv, lo[1] * inv), Elem<Tag>::pack2(lo[2] * inv, lo[3] * inv),
+                       Elem<Tag>::pack2(hi[0] * inv, hi[1] * inv), Elem<Tag>::pack2(hi[2] * inv, hi[3] * inv)};
+      __builtin_nontemporal_store(o, reinterpret_cast<u32x4_mem*>(O + row * D + d));
     }
   }
 }

@@ -173,8 +173,8 @@ __device__ __forceinline__ void store_c(uint16_t* C, int64_t idx, float v, int a
 // Epilogue word of the GEMM kernels: bit 0 = add into an fp32 C (no bias, no activation);
 // bit 3 = store the fp32 accumulator as it is (a partial product of a K split across workgroups:
 // C then points at this part's slice of the fp32 scratch); otherwise bits 1..2 = activation
-// applied to acc + bias[col] before rounding to the 16-bit C.
-enum { EPI_ACC32 = 1, EPI_ACT_SHIFT = 1, EPI_ACT_MASK = 3, EPI_PART32 = 8, ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2 };
+// applied to acc + bias[col] before rounding to the 16-bit C. Bit 4: see stream_c16.
+enum { EPI_ACC32 = 1, EPI_ACT_SHIFT = 1, EPI_ACT_MASK = 3, EPI_PART32 = 8, EPI_STREAM = 16, ACT_NONE = 0, ACT_RELU = 1, ACT_GELU = 2 };
 __device__ __forceinline__ float epi_act(float v, int act) {
   if (act == ACT_RELU) return v > 0.f ? v : 0.f;
   if (act == ACT_GELU) return 0.5f * v * (1.f + erff(v * 0.70710678118654752f));   // v * Phi(v)
@@ -188,7 +188,7 @@ __device__ __forceinline__ void gemm_epilogue(Each&& each, uint16_t* C, int epi,
     each([&](int64_t idx, int, float v) { reinterpret_cast<float*>(C)[idx] = v; });
   } else if (epi & EPI_ACC32) {
     each([&](int64_t idx, int, float v) { reinterpret_cast<float*>(C)[idx] += v; });
-  } else if (epi == 0 && bias == nullptr) {
+  } else if ((epi & ~EPI_STREAM) == 0 && bias == nullptr) {
     each([&](int64_t idx, int, float v) { C[idx] = Elem<Tag>::from_f32(v); });
   } else {
     const int act = (epi >> EPI_ACT_SHIFT) & EPI_ACT_MASK;
@@ -204,6 +204,11 @@ typedef f32x4 __attribute__((may_alias, aligned(4))) f32x4_mem4;
 typedef float __attribute__((may_alias)) f32_mem;
 
 __device__ __forceinline__ void add4(f32x4& a, const f32x4& b) { a[0] += b[0]; a[1] += b[1]; a[2] += b[2]; a[3] += b[3]; }
+
+// EPI_STREAM: the 16-bit result leaves in the non-temporal form, in whole lines (GemmArgs::stream_c). Such an access and a plain one
+// must not meet in the two arms of one branch (the compiler would merge them into a plain one), so the form is chosen
+// around the loops.
+__device__ __forceinline__ void stream_c16(const u32x4& v, uint16_t* dst) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4_mem2*>(dst)); }
 
 // Up to four consecutive fp32 elements of a row (`left` of them lie inside the matrix), stored or
 // added to what is there.
@@ -222,7 +227,7 @@ __device__ __forceinline__ void store_row4(f32x4 v, float* dst, int left, bool a
 
 // Up to eight consecutive 16-bit elements of a row (`left` >= 1 of them inside the matrix): bias and
 // activation (bias: of the first element, or null), rounding, one 16-byte store.
-template <typename Tag>
+template <typename Tag, bool STREAM>
 __device__ __forceinline__ void store_row8(const f32x4& lo, const f32x4& hi, uint16_t* dst, int left, int epi, const uint16_t* bias) {
   float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   if (bias) {
@@ -242,7 +247,8 @@ __device__ __forceinline__ void store_row8(const f32x4& lo, const f32x4& hi, uin
   }
   const u32x4 w = {Elem<Tag>::pack2(v[0], v[1]), Elem<Tag>::pack2(v[2], v[3]), Elem<Tag>::pack2(v[4], v[5]), Elem<Tag>::pack2(v[6], v[7])};
   if (left >= 8) {
-    *reinterpret_cast<u32x4_mem2*>(dst) = w;
+    if constexpr (STREAM) stream_c16(w, dst);
+    else *reinterpret_cast<u32x4_mem2*>(dst) = w;
   } else {
     for (int e = 0; e < 8; ++e)
       if (e < left) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
@@ -267,7 +273,13 @@ template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
   static constexpr int STRIDE = COLS + PAD;
   static constexpr int BYTES = ROWS * STRIDE * 4;
   template <typename Put>
-  static __device__ __forceinline__ void run(Put&& put, float* park, int lane, int row0, int col0, int M, int N,
+  static __device__ __forceinline__ void run(Put&& put, float* park, int lane, int row0, int col0, int M, int N, uint16_t* C, int64_t ldc,
+                                             int epi, const uint16_t* bias) {
+    if (epi & EPI_STREAM) run_form<true>(put, park, lane, row0, col0, M, N, C, ldc, epi, bias);
+    else run_form<false>(put, park, lane, row0, col0, M, N, C, ldc, epi, bias);
+  }
+  template <bool STREAM, typename Put>
+  static __device__ __forceinline__ void run_form(Put&& put, float* park, int lane, int row0, int col0, int M, int N,
                                              uint16_t* __restrict__ C, int64_t ldc, int epi,
                                              const uint16_t* __restrict__ bias) {
     if (epi & (EPI_PART32 | EPI_ACC32)) {
@@ -308,7 +320,7 @@ template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
     constexpr int LPR = COLS / 8, RPI = 64 / LPR, NI = ROWS / RPI;
     const int r = lane / LPR, c = (lane % LPR) * 8, col = col0 + c;
     uint16_t* cp = C + (int64_t)(row0 + r) * ldc + col;
-    const bool whole = col + 8 <= N, plain = epi == 0 && bias == nullptr;
+    const bool whole = col + 8 <= N, plain = (epi & ~EPI_STREAM) == 0 && bias == nullptr;
     const int act = (epi >> EPI_ACT_SHIFT) & EPI_ACT_MASK;
     float b[8];
 #pragma unroll
@@ -327,8 +339,10 @@ template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
                        Elem<Tag>::pack2(v[6], v[7])};
       if (row0 + r + i * RPI < M) {
         uint16_t* dst = cp + (int64_t)i * RPI * ldc;
-        if (whole) *reinterpret_cast<u32x4_mem2*>(dst) = w;
-        else
+        if (whole) {
+          if constexpr (STREAM) stream_c16(w, dst);
+          else *reinterpret_cast<u32x4_mem2*>(dst) = w;
+        } else
           for (int e = 0; e < 8; ++e)
             if (col + e < N) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
       }

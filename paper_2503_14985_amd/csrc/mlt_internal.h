@@ -44,7 +44,14 @@ struct GemmArgs {
   uint32_t* counters = nullptr;    // the scratch's kScratchCounters zeros (left as zeros), or null: a second kernel adds the parts
   int parts = 1;
   int forced_parts = 0;            // plan_gemm: 0 = the cost model's choice, 1 / 2 / 4 / 8 = forced
-  int epi() const { return acc32 ? 1 : (act << 1); }   // the kernels' epilogue word
+  // Rows of whole 128-byte lines leave in the non-temporal form. Lines that a kernel leaves dirty in the L2s, up to 32 MB of them,
+  // are written back behind its end, and on the way there they push out operands (bf16, us, plain / non-temporal: 3000 x 4096 x 1024
+  // 29.0 / 24.8, 2048 x 4096 x 1024 20.9 / 17.7, 4000 x 6144 x 1024 58.7 / 53.7, 5410 x 11200 x 512 77.9 / 71.0, 8192^2 x 1024 126 / 117,
+  // 8192^3 750 / 739, 1024 x 2048 x 512 6.9 / 6.7; of 60 such problems two lost, 1700 x 10816 x 3584 by 1 % and 4096 x 8192 x 512 to 2048 by
+  // 1 to 5 %). Rows that share lines lose: 7000 x 7000 x 1024 114 / 121, 14336 x 3000 x 512 61 / 67. An fp32 C that is accumulated
+  // into gains nothing (4096 x 4096 x 2048 73.7 / 74.1) and may still be in the last-level cache (3072 x 912 x 416 11.6 / 13.8).
+  bool stream_c() const { return !acc32 && (reinterpret_cast<uintptr_t>(C) & 127) == 0 && ldc % 64 == 0; }
+  int epi() const { return (acc32 ? 1 : act << 1) | (stream_c() ? 16 : 0); }   // the kernels' epilogue word
   bool fused() const { return bias != nullptr || act != 0; }
 };
 
