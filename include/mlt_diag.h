@@ -76,7 +76,7 @@ int mlt_query_tiling(int op, const int64_t dims[4], int dtype, int32_t out[10]);
  * process, for tuning and for tests that have to reach every kernel. A NULL argument leaves that
  * choice as it is; "" or "auto" restores the automatic choice. A forced kernel that cannot take a
  * problem (alignment, shape) falls back to one that can, as the automatic choice would.
- *   gemm_variant  "general", "256", "256w8", "256pp16", "128pp16", "128pp16k128", "256x128kp", "128kp", "256w4", "256w8x1",
+ *   gemm_variant  "general", "256", "256w8", "256pp16", "128pp16", "128pp16k128", "256x128kp", "224x128kp", "192x128kp", "160x128kp", "128kp", "256w4", "256w8x1",
  *                 "256w1x8", "128w8", "64x128", "64", "128k2", "64x128k2", "64k4", "skinny" (or its older name "skinnydma")
  *   mha_variant   "pp32", "pp16", "ps", "k2", "k4"
  * The initial values come from the environment variables MLT_GEMM_VARIANT and MLT_MHA_VARIANT,

@@ -166,6 +166,18 @@ static bool stream_wins(const GemmArgs& g, int64_t ncu, const GemmPlan& tiles) {
   return !(5 * wgs >= 4 * ncu * rounds && g.K % 64 == 0 && kt < 20 && !g.fused());
 }
 
+// rows of a tile of gemm_kp.hip; 0: another kernel's
+static int kp_rows(int variant) {
+  switch (variant) {
+    case GEMM_256X128_KP: return 256;
+    case GEMM_224X128_KP: return 224;
+    case GEMM_192X128_KP: return 192;
+    case GEMM_160X128_KP: return 160;
+    case GEMM_128_KP: return 128;
+  }
+  return 0;
+}
+
 GemmPlan plan_gemm(const GemmArgs& g_in) {
   GemmPlan p;
   GemmArgs g = g_in;
@@ -311,12 +323,16 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     const int64_t wgs = ((g.M + bm - 1) / bm) * ((g.N + 127) / 128) * parts;
     const int64_t rounds = (wgs + NCU - 1) / NCU, steps = (KT + parts - 1) / parts;
     const int64_t share = wgs < NCU ? wgs * 1000 / NCU : 1000;
-    int64_t t_step = parts > 1 ? (bm == 256 ? 425 + 195 * share / 1000 : 206 + 190 * share / 1000) : bm == 256 ? 615 : 345 + 50 * share / 1000;
+    int64_t t_step = parts > 1 ? (bm > 128 ? 425 + 195 * share / 1000 : 206 + 190 * share / 1000) : bm > 128 ? 615 : 345 + 50 * share / 1000;
+    if (bm > 128) t_step -= t_step * (256 - bm) / 512;     // 224 rows 0.94, 192 0.88, 160 0.81 of a step of 256
     if (g.K % 64) t_step += t_step * 15 / 100;
-    const int64_t compute = rounds * (steps * t_step + (bm == 256 ? 6000 : 5700));
+    const int64_t compute = rounds * (steps * t_step + (bm > 128 ? 6000 : 5700));
     const int64_t base = (g.M + g.N) * g.K * 2 / 5200, need = 6 * NCU / 10;
     const int64_t arrive = wgs >= need ? base : base * need / wgs;
-    return (compute > arrive ? compute : arrive) + (parts > 1 ? 4000 + 2 * parts * g.M * g.N / 1000 : 0);
+    // an fp32 C comes and goes when all K steps are done, with nothing to hide behind (2232 x 2752 x 968: 30 us on the two-group kernel of
+    // 128 x 128, two workgroups per CU, 38 on 224 x 128)
+    const int64_t c32 = g.acc32 && parts == 1 ? g.M * g.N * 8 / 5200 : 0;
+    return (compute > arrive ? compute : arrive) + c32 + (parts > 1 ? 4000 + 2 * parts * g.M * g.N / 1000 : 0);
   };
   for (int parts = g.forced_parts > 0 ? g.forced_parts : 1; !small_tiles && parts <= (g.forced_parts > 0 ? g.forced_parts : 8); parts *= 2) {
     // every part keeps at least 8 K steps, and all parts' tiles fit the scratch that mlt_gemm_noalloc has
@@ -326,7 +342,15 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     if (pp && KT >= 8 * parts) {
       // (256 x 128 in 8 parts for one row of tiles only: 138 x 3840 x 14928 40 us, 51 in 4 parts of 128 x 128; but 852 x 920 x
       // 14784 50 in 8, 43 on the other tiles, 2375 x 272 x 16256 67, 60)
-      if (g.M > 128 && (parts < 8 || g.M <= 256) && fits(64, 128)) all[n_all++] = Choice{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
+      if (g.M > 128 && (parts < 8 || g.M <= 256) && fits(64, 128)) {
+        // the height that multiplies the least padding in the same number of rounds
+        Choice kp{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
+        for (int v : {GEMM_224X128_KP, GEMM_192X128_KP, GEMM_160X128_KP}) {
+          const int64_t t = cost_kp(kp_rows(v), parts);
+          if (t < kp.t) kp = Choice{v, parts, kp_rows(v) * 128, t};
+        }
+        all[n_all++] = kp;
+      }
       if (fits(128, 128)) all[n_all++] = Choice{GEMM_128_KP, parts, 128 * 128, cost_kp(128, parts)};
     }
     for (const auto& c : KT / parts < 8 ? whole : p.aligned ? split : any) {
@@ -360,13 +384,13 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   const int best_parts = pick.parts;
   if (g.forced >= GEMM_256 && g.forced < GEMM_NUM_VARIANTS && g.forced != GEMM_SKINNY) v = g.forced;
   if (v == GEMM_256_PP16 && !gemm_pp_ok(g)) v = GEMM_256_W8;
-  if ((v == GEMM_256X128_KP || v == GEMM_128_KP) && !pp) v = v == GEMM_128_KP ? GEMM_128_W8 : GEMM_256_W8;
+  if (kp_rows(v) && !pp) v = v == GEMM_128_KP ? GEMM_128_W8 : GEMM_256_W8;
   if (v == GEMM_256_W4 && !gemm_w4_ok(g)) v = GEMM_256_W8;
   if (v == GEMM_128_PP16_K128 && (!pp || g.K % 128)) v = GEMM_128_PP16;
   if (v == GEMM_128_PP16 && !pp) v = GEMM_128_W8;
   // a forced kernel keeps the split only if it is one of the kernels that can run it
   const bool can_split = v == GEMM_128_K2 || v == GEMM_64X128_K2 || v == GEMM_64_K4 || v == GEMM_128_W8 ||
-                         v == GEMM_64X128_W8 || v == GEMM_64_W4 || v == GEMM_256X128_KP || v == GEMM_128_KP;
+                         v == GEMM_64X128_W8 || v == GEMM_64_W4 || kp_rows(v);
   p.parts = can_split ? best_parts : 1;
   p.scratch_bytes = p.parts > 1 ? (int64_t)p.parts * g.M * g.N * 4 : 0;
   p.variant = v;
@@ -386,6 +410,15 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     case GEMM_256X128_KP: p.bm = 256; p.bn = 128; p.wm = 2; p.wn = 2;
       p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
       p.name = g.transB ? "gemm_nt_256x128x64_w2x2_kp2" : "gemm_nn_256x128x64_w2x2_kp2"; break;
+    case GEMM_224X128_KP: p.bm = 224; p.bn = 128; p.wm = 2; p.wn = 2;
+      p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
+      p.name = g.transB ? "gemm_nt_256x128x64_w2x2_kp2" : "gemm_nn_256x128x64_w2x2_kp2"; p.suffix = "_rows224"; break;
+    case GEMM_192X128_KP: p.bm = 192; p.bn = 128; p.wm = 2; p.wn = 2;
+      p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
+      p.name = g.transB ? "gemm_nt_256x128x64_w2x2_kp2" : "gemm_nn_256x128x64_w2x2_kp2"; p.suffix = "_rows192"; break;
+    case GEMM_160X128_KP: p.bm = 160; p.bn = 128; p.wm = 2; p.wn = 2;
+      p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
+      p.name = g.transB ? "gemm_nt_256x128x64_w2x2_kp2" : "gemm_nn_256x128x64_w2x2_kp2"; p.suffix = "_rows160"; break;
     case GEMM_128_KP: p.bm = p.bn = 128; p.wm = 2; p.wn = 2;
       p.mfma_m = 16; p.mfma_n = 16; p.mfma_k = 32;
       p.name = g.transB ? "gemm_nt_128x128x64_w2x2_kp2" : "gemm_nn_128x128x64_w2x2_kp2"; break;
@@ -439,8 +472,8 @@ static int run_gemm_t(const GemmArgs& g, const GemmPlan& p, hipStream_t s) {
     case GEMM_256_PP16: return run_gemm_pp(g, 256, 64, s);
     case GEMM_128_PP16: return run_gemm_pp(g, 128, 64, s);
     case GEMM_128_PP16_K128: return run_gemm_pp(g, 128, 128, s);
-    case GEMM_256X128_KP: return run_gemm_kp(g, 256, s);
-    case GEMM_128_KP: return run_gemm_kp(g, 128, s);
+    case GEMM_256X128_KP: case GEMM_224X128_KP: case GEMM_192X128_KP: case GEMM_160X128_KP: case GEMM_128_KP:
+      return run_gemm_kp(g, kp_rows(p.variant), s);
     case GEMM_256_W4: return run_gemm_w4(g, s);
     case GEMM_SKINNY: return run_gemm_skinny(g, s);
   }

@@ -1,6 +1,6 @@
 // GEMM C = A*B for gfx950, two groups of wavefronts on alternate K steps, direct global->LDS loads.
 //
-// The tiles between the 256 x 256 of gemm_pp.hip and the small ones of gemm.hip: 256 x 128 and 128 x 128. Same
+// The tiles between the 256 x 256 of gemm_pp.hip and the small ones of gemm.hip: 128 columns by 128 to 256 rows. Same
 // three levels as the paper's GEMM (arXiv 2503.14985, Sections 2.1-2.3); what differs from gemm_pp.hip
 // is what the two wavefronts of a SIMD share. There each owns half of the tile's rows and works on every
 // K step. Here four wavefronts (2 x 2, of 128 x 64 or 64 x 64 each) cover the whole tile, group 0 takes the even K
@@ -14,7 +14,12 @@
 // 128 x 64. The two-group kernels' phases took what that predicts plus 230 clocks of barrier and latency:
 // 0.436 us per 64 of K and 128 x 128 tile, 0.72 us for 256 x 128 as 4 x 2 wavefronts of 64 x 64 (built first).
 //
-// LDS: a ring of R whole K steps (3 of 48 KB, 5 of 32 KB), operand tiles unpadded with the XOR swizzles of
+// The tall tile also comes with 224, 192 and 160 rows (112, 96, 80 per wavefront): on a grid that fits one round of the chip, what is
+// spent on padding rows is time (one round of 240 workgroups, 64 K steps, us, 256 / 224 / 192 / 160 rows: 51.6 / 48.7 / 47.4 / 44.5;
+// 777 x 4096 x 14336 in two parts, four rows of tiles: 106.3 -> 99.0; 316 x 6784 x 10368 81.5 -> 66.2; 1142 x 4624 x 5480 97 -> 81;
+// 708 x 7552 x 832 17.2 -> 13.1).
+//
+// LDS: a ring of R whole K steps (3 of 48 KB or less, 5 of 32 KB), operand tiles unpadded with the XOR swizzles of
 // gemm_pp.hip. Step s lies in stage s % R and is read in phase s, by group s % 2, which is also the group
 // that fetches it: step s + R - 1 in phase s, into the stage that the other group has read in phase s - 1.
 //
@@ -33,11 +38,11 @@ constexpr int KP_GROUP_M = 4;                            // bands of 4 tile rows
 
 template <int BM, int BN> struct KpTile {
   static constexpr int A_B = BM * KP_BK * 2, B_B = BN * KP_BK * 2, STAGE = A_B + B_B;
-  static constexpr int R = BM == 256 ? 3 : 5;            // stages: as many as fit, odd (a group's steps are two apart)
+  static constexpr int R = BM > 128 ? 3 : 5;             // stages: as many as fit, odd (a group's steps are two apart)
   static constexpr int NL = STAGE / 1024 / 4;            // 1 KB loads per wavefront and step of its group
   static constexpr int NLA = A_B / 1024 / 4;             // of them from A
   static constexpr int S = BN + 4;                       // floats per row of a group's image of the result
-  static constexpr int RPP = 128;                        // rows per pass of the epilogue: what two images leave room for
+  static constexpr int RPP = BM > 128 ? BM / 2 : 128;    // rows per pass of the epilogue: what two images leave room for
   static constexpr int IMG_B = 2 * RPP * S * 4;
   static constexpr int SMEM = R * STAGE > IMG_B ? R * STAGE : IMG_B;
 };
@@ -60,13 +65,28 @@ __global__ __launch_bounds__(KP_NT, 2) void gemm_kp_kernel(
   const uint16_t* B = B_;
   uint16_t* C = C_;
   int K = K_;
+  // K split: an XCD takes the tiles of one part, or, where a part has a single row of tiles (no panel of B to share),
+  // the same tiles of all parts (us, tiles / parts first: 777 x 4096 x 14336 108.2 / 106.2, 512 x 4096 x 14336 70.5 / 68.7, 1000 x 2048 x
+  // 8192 45.1 / 43.5; 138 x 3840 x 14928 47.7 / 50.3)
+  const int tiles = nbm * nbn;
+  int logical;
   if (part_steps > 0) {
-    const int part = blockIdx.y;
+    int part;
+    if (nbm > 1) {
+      logical = logical_block(blockIdx.x, gridDim.x, nxcd);
+      part = logical / tiles;
+      logical -= part * tiles;
+    } else {
+      part = blockIdx.x / tiles;
+      logical = logical_block(blockIdx.x - part * tiles, tiles, nxcd);
+    }
     const int k_begin = part * part_steps * BK;            // < K_: the host launches no empty part
     A += k_begin;
     B += TRANSB ? (int64_t)k_begin : (int64_t)k_begin * ldb;
     K = K_ - k_begin < part_steps * BK ? K_ - k_begin : part_steps * BK;
     C = reinterpret_cast<uint16_t*>(reinterpret_cast<float*>(C_) + (int64_t)part * part_stride);
+  } else {
+    logical = logical_block(blockIdx.x, tiles, nxcd);
   }
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -74,7 +94,7 @@ __global__ __launch_bounds__(KP_NT, 2) void gemm_kp_kernel(
   const int grp = wave >> 2, w = wave & 3;               // waves 0-3 / 4-7: one of each per SIMD
   const int wm = w >> 1, wn = w & 1;
   int tile_m, tile_n;
-  tile_of_block<KP_GROUP_M>(blockIdx.x, nbm, nbn, nxcd, tile_m, tile_n);
+  tile_of_logical<KP_GROUP_M>(logical, nbm, nbn, tile_m, tile_n);
   const int m0 = tile_m * BM, n0 = tile_n * BN;
   const int KT = (K + BK - 1) / BK;
   const int k_tail = K - (KT - 1) * BK;                  // k values in the last step
@@ -259,6 +279,7 @@ __global__ __launch_bounds__(KP_NT, 2) void gemm_kp_kernel(
     const int row0 = m0 + p * RPP;
     if (epi & (EPI_PART32 | EPI_ACC32)) {
       constexpr int CPT = BN / 4, NI = RPP * CPT / KP_NT;
+      static_assert(RPP * CPT % KP_NT == 0, "whole passes");
       const int c = tid % CPT * 4, col = n0 + c;
       float* cp = reinterpret_cast<float*>(C) + (int64_t)(row0 + tid / CPT) * ldc + col;
       f32x4 old[NI];
@@ -283,7 +304,7 @@ __global__ __launch_bounds__(KP_NT, 2) void gemm_kp_kernel(
         if (row0 + r < M) store_row4(v, cp + (int64_t)i * (KP_NT / CPT) * ldc, N - col, false);
       }
     } else {
-      constexpr int CPT = BN / 8, NI = RPP * CPT / KP_NT;
+      constexpr int CPT = BN / 8, NI = (RPP * CPT + KP_NT - 1) / KP_NT;
       const int c = tid % CPT * 8, col = n0 + c;
       __syncthreads();
       auto rows = [&](auto STREAM) __attribute__((always_inline)) {
@@ -294,7 +315,7 @@ __global__ __launch_bounds__(KP_NT, 2) void gemm_kp_kernel(
           f32x4 lo = *reinterpret_cast<const f32x4_mem*>(src), hi = *reinterpret_cast<const f32x4_mem*>(src + 4);
           add4(lo, *reinterpret_cast<const f32x4_mem*>(src + RPP * S));
           add4(hi, *reinterpret_cast<const f32x4_mem*>(src + RPP * S + 4));
-          if (row0 + r < M && col < N)
+          if ((RPP * CPT % KP_NT == 0 || r < RPP) && row0 + r < M && col < N)
             store_row8<Tag, STREAM.value>(lo, hi, C + (int64_t)(row0 + r) * ldc + col, N - col, epi, bias ? bias + col : nullptr);
         }
       };
@@ -328,7 +349,7 @@ static int launch_kp(const GemmArgs& g, hipStream_t s) {
   const int KT = (int)((g.K + KP_BK - 1) / KP_BK);
   const int part_steps = (KT + g.parts - 1) / g.parts;
   const int parts = (KT + part_steps - 1) / part_steps;    // no empty part
-  hipLaunchKernelGGL(kern, dim3(nbm * nbn, parts), dim3(KP_NT), SMEM, s, (int)g.M, (int)g.N, (int)g.K, g.A, g.lda, g.B,
+  hipLaunchKernelGGL(kern, dim3(nbm * nbn * parts), dim3(KP_NT), SMEM, s, (int)g.M, (int)g.N, (int)g.K, g.A, g.lda, g.B,
                      g.ldb, reinterpret_cast<uint16_t*>(g.scratch), g.N, nbm, nbn, device_xcds(), (int)EPI_PART32,
                      (const uint16_t*)nullptr, part_steps, g.M * g.N);
   if (hipGetLastError() != hipSuccess) return MLT_ERR_LAUNCH;
@@ -341,9 +362,19 @@ static int run_kp_t(const GemmArgs& g, hipStream_t s) {
   return g.transB ? launch_kp<Tag, true, BM, 128, true>(g, s) : launch_kp<Tag, false, BM, 128, true>(g, s);
 }
 
+template <typename Tag>
+static int run_kp(const GemmArgs& g, int bm, hipStream_t s) {
+  switch (bm) {
+    case 256: return run_kp_t<Tag, 256>(g, s);
+    case 224: return run_kp_t<Tag, 224>(g, s);
+    case 192: return run_kp_t<Tag, 192>(g, s);
+    case 160: return run_kp_t<Tag, 160>(g, s);
+  }
+  return run_kp_t<Tag, 128>(g, s);
+}
+
 int run_gemm_kp(const GemmArgs& g, int bm, hipStream_t s) {
-  if (g.dtype == MLT_BF16) return bm == 256 ? run_kp_t<bf16_tag, 256>(g, s) : run_kp_t<bf16_tag, 128>(g, s);
-  return bm == 256 ? run_kp_t<f16_tag, 256>(g, s) : run_kp_t<f16_tag, 128>(g, s);
+  return g.dtype == MLT_BF16 ? run_kp<bf16_tag>(g, bm, s) : run_kp<f16_tag>(g, bm, s);
 }
 
 }  // namespace mlt

@@ -20,7 +20,10 @@ thread_local char g_name_buf[96];
 // The selected kernel's name; a K split across workgroups shows as a suffix (_splitk2 / 4 / 8).
 void note_gemm_kernel(const GemmPlan& p) {
   if (p.parts > 1) {
-    snprintf(g_name_buf, sizeof(g_name_buf), "%s_splitk%d", p.name, p.parts);
+    snprintf(g_name_buf, sizeof(g_name_buf), "%s_splitk%d%s", p.name, p.parts, p.suffix);
+    g_last_kernel = g_name_buf;
+  } else if (*p.suffix) {
+    snprintf(g_name_buf, sizeof(g_name_buf), "%s%s", p.name, p.suffix);
     g_last_kernel = g_name_buf;
   } else {
     g_last_kernel = p.name;
@@ -29,7 +32,7 @@ void note_gemm_kernel(const GemmPlan& p) {
 
 struct VariantName { const char* name; int id; };
 const VariantName kGemmVariants[] = {
-    {"general", GEMM_GENERAL}, {"256", GEMM_256}, {"256w8", GEMM_256_W8}, {"256pp16", GEMM_256_PP16}, {"256x128kp", GEMM_256X128_KP}, {"128kp", GEMM_128_KP}, {"128pp16", GEMM_128_PP16}, {"128pp16k128", GEMM_128_PP16_K128},
+    {"general", GEMM_GENERAL}, {"256", GEMM_256}, {"256w8", GEMM_256_W8}, {"256pp16", GEMM_256_PP16}, {"256x128kp", GEMM_256X128_KP}, {"224x128kp", GEMM_224X128_KP}, {"192x128kp", GEMM_192X128_KP}, {"160x128kp", GEMM_160X128_KP}, {"128kp", GEMM_128_KP}, {"128pp16", GEMM_128_PP16}, {"128pp16k128", GEMM_128_PP16_K128},
     {"256w4", GEMM_256_W4}, {"256w8x1", GEMM_256_W8X1}, {"256w1x8", GEMM_256_W1X8},
     {"128w8", GEMM_128_W8}, {"64x128", GEMM_64X128_W8}, {"64", GEMM_64_W4}, {"128k2", GEMM_128_K2},
     {"64x128k2", GEMM_64X128_K2}, {"64k4", GEMM_64_K4}, {"skinny", GEMM_SKINNY}, {"skinnydma", GEMM_SKINNY}};

@@ -94,12 +94,11 @@ __device__ __forceinline__ int logical_block(int bid, int total, int nxcd) {
   return xcd * q + (xcd < rem ? xcd : rem) + idx;
 }
 
-// Workgroup id -> C tile: logical ids walk the tiles in column-major order inside bands of GROUP_M
+// Logical id -> C tile: the ids walk the tiles in column-major order inside bands of GROUP_M
 // tile rows, so that the workgroups resident on one XCD at a time share A row panels and B column
 // panels.
 template <int GROUP_M>
-__device__ __forceinline__ void tile_of_block(int bid, int nbm, int nbn, int nxcd, int& tm, int& tn) {
-  const int logical = logical_block(bid, nbm * nbn, nxcd);
+__device__ __forceinline__ void tile_of_logical(int logical, int nbm, int nbn, int& tm, int& tn) {
   const int per_group = GROUP_M * nbn;
   const int g = logical / per_group;
   const int first_m = g * GROUP_M;
@@ -107,6 +106,10 @@ __device__ __forceinline__ void tile_of_block(int bid, int nbm, int nbn, int nxc
   const int in_g = logical % per_group;
   tm = first_m + in_g % rows;
   tn = in_g / rows;
+}
+template <int GROUP_M>
+__device__ __forceinline__ void tile_of_block(int bid, int nbm, int nbn, int nxcd, int& tm, int& tn) {
+  tile_of_logical<GROUP_M>(logical_block(bid, nbm * nbn, nxcd), nbm, nbn, tm, tn);
 }
 
 struct bf16_tag {};

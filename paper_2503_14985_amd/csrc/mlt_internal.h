@@ -25,6 +25,9 @@ enum GemmVariant {
   GEMM_128_PP16_K128 = 21, // the same tile with K steps of 128 (one workgroup per CU, phases of twice the length)
   GEMM_256X128_KP = 22, // 256x128x64, two groups of 4 wavefronts (2x2) of 128x64 on alternate K steps, direct-to-LDS loads
   GEMM_128_KP = 23,   // 128x128x64, the same with 64x64 per wavefront
+  GEMM_224X128_KP = 24, // 256x128 with 112, 96 or 80 rows per wavefront instead of 128
+  GEMM_192X128_KP = 25,
+  GEMM_160X128_KP = 26,
   GEMM_NUM_VARIANTS
 };
 
@@ -61,6 +64,7 @@ struct GemmPlan {
   int parts = 1;                   // > 1: K split across workgroups, partial products through a scratch
   int64_t scratch_bytes = 0;       // parts * M * N * 4 when parts > 1
   const char* name = "";
+  const char* suffix = "";         // of the reported name: a tile with fewer rows than the kernel's name says
   int bm = 0, bn = 0, bk = 0, wm = 0, wn = 0;
   int mfma_m = 32, mfma_n = 32, mfma_k = 16;
 };
@@ -79,7 +83,7 @@ GemmPlan plan_gemm(const GemmArgs& g);
 int run_gemm(const GemmArgs& g, GemmPlan& p, hipStream_t s);
 bool gemm_pp_ok(const GemmArgs& g);            // gemm_pp.hip: can the two-group kernel take this problem?
 int run_gemm_pp(const GemmArgs& g, int tile, int kstep, hipStream_t s);   // tile: 256 or 128; K step 64 or (tile 128 only) 128
-int run_gemm_kp(const GemmArgs& g, int bm, hipStream_t s);   // gemm_kp.hip (where gemm_pp_ok): bm x 128, bm 256 or 128; g.parts > 1: K split across workgroups
+int run_gemm_kp(const GemmArgs& g, int bm, hipStream_t s);   // gemm_kp.hip (where gemm_pp_ok): bm x 128, bm 256, 224, 192, 160 or 128; g.parts > 1: K split across workgroups
 int run_splitk_reduce(const GemmArgs& g, int parts, int64_t part_stride, hipStream_t s);   // gemm.hip: the sum of the parts, with the epilogue
 bool gemm_any_ok(const GemmArgs& g);           // gemm_any.hip: the tile kernels on operands of any alignment
 int run_gemm_any(const GemmArgs& g, int variant, hipStream_t s);
