@@ -276,7 +276,9 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   // that a larger one is granted (350 a step against 410 or more, and more workgroups to fetch the operands), so the others
   // are not priced (0.2 us of a call of 6.5).
   const bool small_tiles = KT < 8 && g.forced_parts <= 1 && ((g.M + 63) / 64) * ((g.N + 63) / 64) <= NCU;
-  if (small_tiles) all[n_all++] = Choice{GEMM_64_W4, 1, 64 * 64, cost(64, 64, 350, 0, 1, 1)};
+  // (an fp32 C that is read and written: four times the threads, K steps split over them, from 4 steps on; us, 440 x 928 x 440 7.2 / 6.1,
+  // 1208 x 560 x 320 6.7 / 5.9, 328 x 2032 x 432 7.3 / 6.7)
+  if (small_tiles) all[n_all++] = Choice{g.acc32 && p.aligned && KT >= 4 ? GEMM_64_K4 : GEMM_64_W4, 1, 64 * 64, cost(64, 64, 350, 0, 1, 1)};
   else if (g.forced_parts <= 1 && fits(256, 256)) all[n_all++] = Choice{big.variant, 1, 256 * 256, cost(256, 256, big.t, 0, 1, 1)};
   // The two-group kernel on 128 x 128 tiles, no K split across workgroups, in its two forms (fits
   // over K at 256 and 512 tiles, kernel time without the call):

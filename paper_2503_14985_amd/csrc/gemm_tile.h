@@ -257,6 +257,26 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
   // The barrier sits where every wavefront has issued its last read of stage s and its writes
   // of tile kt+1, so after it stage s may be overwritten (in step kt+1) and tile kt+1 may be
   // read; its latency and that of the first fragment reads hide behind the MFMAs of slice 3.
+  // An fp32 C that is added to: with several K groups a thread has few pieces of it, which are on their way through the whole K loop
+  // (us, with loads behind the last step before: 440 x 928 x 440 6.1 / 5.7, 1024 x 1024 x 384 6.0 / 5.6, 328 x 2032 x 256 5.8 / 5.4). Without groups
+  // the next tiles' pieces would wait for them (264 x 4000 x 256 6.3 / 6.7).
+  constexpr int NTHR = Cfg::NT * KS, CPT4 = BN / 4, NC4 = BM * BN <= 128 * 128 ? (BM * CPT4 + NTHR - 1) / NTHR : 1;
+  constexpr bool EARLY = KS > 1 && NC4 <= 4;
+  f32x4 c32[EARLY ? NC4 : 1];
+  auto load_c32 = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < (EARLY ? NC4 : 0); ++i) {
+      const int it = (int)threadIdx.x + i * NTHR, r = it / CPT4, col = n0 + it % CPT4 * 4;
+      c32[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (r >= BM || m0 + r >= M) continue;
+      const float* src = reinterpret_cast<const float*>(C) + (int64_t)(m0 + r) * ldc + col;
+      if (col + 4 <= N) c32[i] = *reinterpret_cast<const f32x4_mem4*>(src);
+      else
+        for (int e = 0; e < 4; ++e)
+          if (col + e < N) c32[i][e] = src[e];
+    }
+  };
+
   const bool any = kt_begin < kt_end;
   if (any) {
     if (tail_first) load_global_tail((KT - 1) * BK); else load_global_full(kt_begin * BK);
@@ -264,6 +284,7 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
     store_lds(0);
     if (kt_begin + KS < kt_end) load_global_full((kt_begin + KS) * BK - k_shift);
   }
+  if (EARLY && (epi & EPI_ACC32)) load_c32();
   __syncthreads();
 
   V8 af[2][Cfg::TM], bf[2][Cfg::TN];
@@ -323,7 +344,7 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
     // banks), and all threads of the workgroup then add the KS images in the order 0, 1, ... and store.
     // (The sum by group 0 alone, its partial values read one float at a time, and the store from
     // its registers took 0.9 us longer on 512 x 4096 x 4096.)
-    constexpr int S = BN + 8, NTHR = Cfg::NT * KS;
+    constexpr int S = BN + 8;
     static_assert(KS * BM * S * 4 <= KS * Cfg::SMEM, "the images fit the stages");
     float* const red = reinterpret_cast<float*>(smem_all);
     if (KS > 1) __syncthreads();                          // (KS == 1: no stage is read after the loop's last barrier)
@@ -337,13 +358,22 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
                                       wn * (BN / WN) + j * 32 + (lane & 31)) = acc[i][j][r];
     __syncthreads();
     if (epi & (EPI_PART32 | EPI_ACC32)) {
-      constexpr int CPT = BN / 4;                         // 4-column pieces per row
-      for (int it = threadIdx.x; it < BM * CPT; it += NTHR) {
-        const int r = it / CPT, c = it % CPT * 4;
+      auto piece = [&](int it, const f32x4& old, bool load) __attribute__((always_inline)) {
+        const int r = it / CPT4, c = it % CPT4 * 4;
         f32x4 v = *reinterpret_cast<const f32x4_mem*>(red + r * S + c);
 #pragma unroll
         for (int g2 = 1; g2 < KS; ++g2) add4(v, *reinterpret_cast<const f32x4_mem*>(red + (g2 * BM + r) * S + c));
-        if (m0 + r < M) store_row4(v, reinterpret_cast<float*>(C) + (int64_t)(m0 + r) * ldc + n0 + c, N - n0 - c, epi & EPI_ACC32);
+        if (!load && (epi & EPI_ACC32)) add4(v, old);
+        if (m0 + r < M) store_row4(v, reinterpret_cast<float*>(C) + (int64_t)(m0 + r) * ldc + n0 + c, N - n0 - c, load && (epi & EPI_ACC32));
+      };
+      if constexpr (EARLY) {
+#pragma unroll
+        for (int i = 0; i < NC4; ++i) {
+          const int it = (int)threadIdx.x + i * NTHR;
+          if (BM * CPT4 % NTHR == 0 || it < BM * CPT4) piece(it, c32[i], false);
+        }
+      } else {
+        for (int it = threadIdx.x; it < BM * CPT4; it += NTHR) piece(it, c32[0], true);
       }
     } else {
       constexpr int CPT = BN / 8;

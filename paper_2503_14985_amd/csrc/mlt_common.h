@@ -276,13 +276,7 @@ template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
   static constexpr int STRIDE = COLS + PAD;
   static constexpr int BYTES = ROWS * STRIDE * 4;
   template <typename Put>
-  static __device__ __forceinline__ void run(Put&& put, float* park, int lane, int row0, int col0, int M, int N, uint16_t* C, int64_t ldc,
-                                             int epi, const uint16_t* bias) {
-    if (epi & EPI_STREAM) run_form<true>(put, park, lane, row0, col0, M, N, C, ldc, epi, bias);
-    else run_form<false>(put, park, lane, row0, col0, M, N, C, ldc, epi, bias);
-  }
-  template <bool STREAM, typename Put>
-  static __device__ __forceinline__ void run_form(Put&& put, float* park, int lane, int row0, int col0, int M, int N,
+  static __device__ __forceinline__ void run(Put&& put, float* park, int lane, int row0, int col0, int M, int N,
                                              uint16_t* __restrict__ C, int64_t ldc, int epi,
                                              const uint16_t* __restrict__ bias) {
     if (epi & (EPI_PART32 | EPI_ACC32)) {
@@ -318,8 +312,16 @@ template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
               if (col + e < N) cp[(int64_t)i * RPI * ldc + e] = v[e];
         }
       }
-      return;
+    } else if (epi & EPI_STREAM) {
+      run16<true>(put, park, lane, row0, col0, M, N, C, ldc, epi, bias);
+    } else {
+      run16<false>(put, park, lane, row0, col0, M, N, C, ldc, epi, bias);
     }
+  }
+  template <bool STREAM, typename Put>
+  static __device__ __forceinline__ void run16(Put&& put, float* park, int lane, int row0, int col0, int M, int N,
+                                             uint16_t* __restrict__ C, int64_t ldc, int epi,
+                                             const uint16_t* __restrict__ bias) {
     constexpr int LPR = COLS / 8, RPI = 64 / LPR, NI = ROWS / RPI;
     const int r = lane / LPR, c = (lane % LPR) * 8, col = col0 + c;
     uint16_t* cp = C + (int64_t)(row0 + r) * ldc + col;
