@@ -58,7 +58,8 @@ struct GemmTile {
 // steps p * part_steps .. of the problem and stores its fp32 partial tile (epi = EPI_PART32) into
 // slice p of the scratch that C_ then points at (slices part_stride floats apart, row stride ldc);
 // gemm_splitk_reduce_kernel adds the slices in a fixed order and applies the real epilogue.
-template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB, int KS, bool AL>
+// ACC: the form for an fp32 C that is added to (where there is one; the others can do it too).
+template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB, int KS, bool AL, bool ACC>
 __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
     int M, int N, int K_, const uint16_t* __restrict__ A_, int64_t lda,
     const uint16_t* __restrict__ B_, int64_t ldb, uint16_t* __restrict__ C_, int64_t ldc, int nbm,
@@ -259,9 +260,11 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
   // read; its latency and that of the first fragment reads hide behind the MFMAs of slice 3.
   // An fp32 C that is added to: with several K groups a thread has few pieces of it, which are on their way through the whole K loop
   // (us, with loads behind the last step before: 440 x 928 x 440 6.1 / 5.7, 1024 x 1024 x 384 6.0 / 5.6, 328 x 2032 x 256 5.8 / 5.4). Without groups
-  // the next tiles' pieces would wait for them (264 x 4000 x 256 6.3 / 6.7).
+  // the next tiles' pieces would wait for them (264 x 4000 x 256 6.3 / 6.7). A form of its own, because code that a small launch does not
+  // reach costs it time too (512^3, 16-bit C, 4.87 / 4.95).
   constexpr int NTHR = Cfg::NT * KS, CPT4 = BN / 4, NC4 = BM * BN <= 128 * 128 ? (BM * CPT4 + NTHR - 1) / NTHR : 1;
-  constexpr bool EARLY = KS > 1 && NC4 <= 4;
+  constexpr bool EARLY = ACC;
+  static_assert(!ACC || (KS > 1 && NC4 <= 4), "few pieces of C per thread");
   f32x4 c32[EARLY ? NC4 : 1];
   auto load_c32 = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -284,7 +287,7 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
     store_lds(0);
     if (kt_begin + KS < kt_end) load_global_full((kt_begin + KS) * BK - k_shift);
   }
-  if (EARLY && (epi & EPI_ACC32)) load_c32();
+  if (EARLY) load_c32();
   __syncthreads();
 
   V8 af[2][Cfg::TM], bf[2][Cfg::TN];
@@ -363,7 +366,7 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
         f32x4 v = *reinterpret_cast<const f32x4_mem*>(red + r * S + c);
 #pragma unroll
         for (int g2 = 1; g2 < KS; ++g2) add4(v, *reinterpret_cast<const f32x4_mem*>(red + (g2 * BM + r) * S + c));
-        if (!load && (epi & EPI_ACC32)) add4(v, old);
+        if (!load) add4(v, old);
         if (m0 + r < M) store_row4(v, reinterpret_cast<float*>(C) + (int64_t)(m0 + r) * ldc + n0 + c, N - n0 - c, load && (epi & EPI_ACC32));
       };
       if constexpr (EARLY) {
@@ -471,11 +474,11 @@ static int launch_splitk_reduce(const GemmArgs& g, int parts, int64_t part_strid
   return hipGetLastError() == hipSuccess ? MLT_OK : MLT_ERR_LAUNCH;
 }
 
-template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB, int KS, bool AL>
+template <typename Tag, int BM, int BN, int BK, int WM, int WN, bool TRANSB, int KS, bool AL, bool ACC = false>
 static int launch_tile(const GemmArgs& g, hipStream_t s) {
   typedef GemmTile<Tag, BM, BN, BK, WM, WN, TRANSB> Cfg;
   static_assert(Cfg::NT * KS <= 1024 && KS * Cfg::SMEM <= 160 * 1024, "one workgroup, one CU's LDS");
-  auto kern = gemm_tile_kernel<Tag, BM, BN, BK, WM, WN, TRANSB, KS, AL>;
+  auto kern = gemm_tile_kernel<Tag, BM, BN, BK, WM, WN, TRANSB, KS, AL, ACC>;
   static thread_local int configured_dev = -1;          // opt in to > 64 KB LDS once per device
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MLT_ERR_DEVICE;
@@ -510,6 +513,11 @@ static int launch_tile(const GemmArgs& g, hipStream_t s) {
 // padded stage is larger, so fewer groups fit the LDS).
 template <typename Tag, bool AL, int BM, int BN, int BK, int WM, int WN, int KS = 1, int KS_NN = KS>
 static int launch_tile_tb(const GemmArgs& g, hipStream_t s) {
+  if constexpr (AL && KS > 1) {
+    if (g.acc32 && g.parts <= 1)
+      return g.transB ? launch_tile<Tag, BM, BN, BK, WM, WN, true, KS, AL, true>(g, s)
+                      : launch_tile<Tag, BM, BN, BK, WM, WN, false, KS_NN, AL, true>(g, s);
+  }
   return g.transB ? launch_tile<Tag, BM, BN, BK, WM, WN, true, KS, AL>(g, s)
                   : launch_tile<Tag, BM, BN, BK, WM, WN, false, KS_NN, AL>(g, s);
 }
