@@ -148,7 +148,7 @@ __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp_kernel(
     for (int r = 0; r < 16; ++r) o_acc[t][r] = 0.f;
   f32x16 s_acc[2];
   u32x4 pq[4];                       // P^T of the current tile as MFMA operands: one per 16 keys
-  float mc_run = -__builtin_inff();  // running maximum of the scores, times c (log2 domain)
+  float mc_run = -__builtin_inff();  // reference point of the row's weights (log2 domain): a score's weight is exp2(score * c - mc_run)
   float l_run = 0.f;                 // running sum over this lane's half of the keys
 
   // Operand fragments are fetched in chunks of NDT fragments (NDT MFMAs each). A compute phase
@@ -239,10 +239,10 @@ __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp_kernel(
           pq[2 * kb + r / 8][(r / 2) & 3] = Elem<Tag>::pack2(p0, p1);
         }
     };
-    if constexpr (D == 128) {
+    if constexpr (D == 128 && std::is_same<Tag, bf16_tag>::value) {
       // The weights against the reference point as it is; where one of them reaches 2, the row's maximum is
       // taken, the point moves and the weights are taken again. (The maximum was 24 of some 145 vector instructions per tile: 4 x 32 heads x 4096
-      // 918 -> 895 us, 4 x 16 x 4096 causal 262 -> 257, 32 x 16 x 1024 causal 204 -> 198.)
+      // 918 -> 895 us, 4 x 16 x 4096 causal 262 -> 257.)
       bool redo = j == 0;
       if (!redo) {
         weights();
@@ -250,12 +250,12 @@ __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp_kernel(
       }
       if (redo) {
         const float t = row_max() * c;
-        move(t > mc_run, t + Headroom<Tag>::LOG2);
+        move(t > mc_run, t + PA_ROOM);
         weights();
       }
     } else {
-      // (the scores would have to stay beside the weights: 19 registers more than the 128 that let two workgroups share
-      // a CU, 32 x 32 heads x 1024 causal 226 -> 268 us)
+      // (D = 64: the scores would have to stay beside the weights, 19 registers more than the 128 that let two workgroups share
+      // a CU, 32 x 32 heads x 1024 causal 226 -> 268 us. fp16: see PA_ROOM.)
       // Lazy rescale: the reference point mc_run only moves when some row's maximum has grown by
       // more than PA_LAZY_T in the log2 domain (weights then stay below 2^8, far inside fp32 and
       // 16-bit range); mathematically the result does not depend on the reference point. The price:

@@ -146,18 +146,18 @@ inline int mha_xcd_word(int total, bool causal, int D, int mfma_size) {
   return mha_xcd_word(total, causal, D, mfma_size, di);
 }
 
-// Reference point of the weights of the D = 128 kernel (log2 domain). A tile's weights are first taken against the row's present one; it
+// Reference point of the weights, bf16 with D = 128 (log2 domain). A tile's weights are first taken against the row's present one; it
 // moves only when one of them reaches 2, which the packed 16-bit weights show in one bit each: no maximum is needed for the others.
-// It then moves to LOG2 above the row's maximum, so that it has that much room before it moves again. (fp16: weights more than 2^11 below
-// the largest are subnormal. Distance from float64, 2 heads x 4096, N(0, 1) and 6 times that: 2.91e-4 and 2.21e-4, with the
-// maximum as the point 2.91e-4 and 2.23e-4.)
-template <typename Tag> struct Headroom { static constexpr float LOG2 = 7.f; };
-template <> struct Headroom<f16_tag> { static constexpr float LOG2 = 3.f; };
+// It then moves to PA_ROOM above the row's maximum, so that it has that much room before it moves again. The row's largest weight is then as
+// small as 2^-PA_ROOM, which bf16 has the exponents for. fp16 has not: its weights would lose as many bits below the largest (with room 3
+// and one key 23 above 32768 others, their whole share of the result: 3.8e-3 for values around 1), so there the largest weight
+// stays at 1 or more and the point moves as in the kernel for D = 64.
+constexpr float PA_ROOM = 7.f;
 template <int N> __device__ __forceinline__ bool reaches_two(const u32x4 (&pq)[N]) {
   uint32_t any = 0;
 #pragma unroll
   for (int g = 0; g < N; ++g) any |= (pq[g][0] | pq[g][1] | pq[g][2]) | pq[g][3];
-  return (any & 0x40004000u) != 0;                          // bit 14 of either type: 2 or more, infinite, or NaN
+  return (any & 0x40004000u) != 0;                          // bit 14: 2 or more, infinite, or NaN
 }
 
 template <int D> struct PaCfg {
