@@ -148,7 +148,7 @@ __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp_kernel(
     for (int r = 0; r < 16; ++r) o_acc[t][r] = 0.f;
   f32x16 s_acc[2];
   u32x4 pq[4];                       // P^T of the current tile as MFMA operands: one per 16 keys
-  float mc_run = -__builtin_inff();  // reference point of the row's weights (log2 domain): a score's weight is exp2(score * c - mc_run)
+  float mc_run = -__builtin_inff();  // reference point of the weights: a running maximum of the scores, times c (log2 domain)
   float l_run = 0.f;                 // running sum over this lane's half of the keys
 
   // Operand fragments are fetched in chunks of NDT fragments (NDT MFMAs each). A compute phase
@@ -209,27 +209,31 @@ __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp_kernel(
         for (int r = 0; r < 16; ++r)
           if (32 * kb + 8 * (r >> 2) + (r & 3) > rel) s_acc[kb][r] = -__builtin_inff();
     }
-    auto row_max = [&]() __attribute__((always_inline)) {
-      float mx = max3(s_acc[0][0], s_acc[0][1], s_acc[0][2]);
+    float mx = max3(s_acc[0][0], s_acc[0][1], s_acc[0][2]);
 #pragma unroll
-      for (int r = 3; r < 15; r += 2) mx = max3(mx, s_acc[0][r], s_acc[0][r + 1]);
-      mx = max3(mx, s_acc[0][15], s_acc[1][0]);
+    for (int r = 3; r < 15; r += 2) mx = max3(mx, s_acc[0][r], s_acc[0][r + 1]);
+    mx = max3(mx, s_acc[0][15], s_acc[1][0]);
 #pragma unroll
-      for (int r = 1; r < 15; r += 2) mx = max3(mx, s_acc[1][r], s_acc[1][r + 1]);
-      mx = __builtin_fmaxf(mx, s_acc[1][15]);
-      return both_halves_max(mx);
-    };
-    // rows that `grow` get the reference point mc_new
-    auto move = [&](bool grow, float mc_new) __attribute__((always_inline)) {
-      const float alpha = grow ? __builtin_amdgcn_exp2f(mc_run - mc_new) : 1.f;   // 0 on the first tile
+    for (int r = 1; r < 15; r += 2) mx = max3(mx, s_acc[1][r], s_acc[1][r + 1]);
+    mx = __builtin_fmaxf(mx, s_acc[1][15]);
+    mx = both_halves_max(mx);
+    // Lazy rescale: the reference point mc_run only moves when some row's maximum has grown by
+    // more than PA_LAZY_T in the log2 domain (weights then stay below 2^8, far inside fp32 and
+    // 16-bit range); mathematically the result does not depend on the reference point. The price:
+    // the largest weight of a row is no longer exactly 1, so it is rounded to 16 bit like the rest.
+    const float t = mx * c;
+    const bool grow = t - mc_run > PA_LAZY_T;                    // true on the first tile (mc_run = -inf)
+    if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+      const float mc_new = grow ? t : mc_run;
+      const float alpha = grow ? __builtin_amdgcn_exp2f(mc_run - t) : 1.f;   // 0 on the first tile
       l_run *= alpha;
 #pragma unroll
       for (int tt = 0; tt < NDT; ++tt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o_acc[tt][r] *= alpha;
-      mc_run = grow ? mc_new : mc_run;
-    };
-    auto weights = [&]() __attribute__((always_inline)) {
+      mc_run = mc_new;
+    }
+    {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -238,32 +242,6 @@ __global__ __launch_bounds__(PA_NT, D == 64 ? 4 : 1) void mha_pp_kernel(
           const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s_acc[kb][r + 1], c, -mc_run));
           pq[2 * kb + r / 8][(r / 2) & 3] = Elem<Tag>::pack2(p0, p1);
         }
-    };
-    if constexpr (D == 128 && std::is_same<Tag, bf16_tag>::value) {
-      // The weights against the reference point as it is; where one of them reaches 2, the row's maximum is
-      // taken, the point moves and the weights are taken again. (The maximum was 24 of some 145 vector instructions per tile: 4 x 32 heads x 4096
-      // 918 -> 895 us, 4 x 16 x 4096 causal 262 -> 257.)
-      bool redo = j == 0;
-      if (!redo) {
-        weights();
-        redo = __builtin_amdgcn_ballot_w64(reaches_two(pq)) != 0;
-      }
-      if (redo) {
-        const float t = row_max() * c;
-        move(t > mc_run, t + PA_ROOM);
-        weights();
-      }
-    } else {
-      // (D = 64: the scores would have to stay beside the weights, 19 registers more than the 128 that let two workgroups share
-      // a CU, 32 x 32 heads x 1024 causal 226 -> 268 us. fp16: see PA_ROOM.)
-      // Lazy rescale: the reference point mc_run only moves when some row's maximum has grown by
-      // more than PA_LAZY_T in the log2 domain (weights then stay below 2^8, far inside fp32 and
-      // 16-bit range); mathematically the result does not depend on the reference point. The price:
-      // the largest weight of a row is no longer exactly 1, so it is rounded to 16 bit like the rest.
-      const float t = row_max() * c;
-      const bool grow = t - mc_run > PA_LAZY_T;                  // true on the first tile (mc_run = -inf)
-      if (__builtin_amdgcn_ballot_w64(grow) != 0) move(grow, t);
-      weights();
     }
   };
 

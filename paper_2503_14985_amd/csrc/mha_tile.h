@@ -146,20 +146,6 @@ inline int mha_xcd_word(int total, bool causal, int D, int mfma_size) {
   return mha_xcd_word(total, causal, D, mfma_size, di);
 }
 
-// Reference point of the weights, bf16 with D = 128 (log2 domain). A tile's weights are first taken against the row's present one; it
-// moves only when one of them reaches 2, which the packed 16-bit weights show in one bit each: no maximum is needed for the others.
-// It then moves to PA_ROOM above the row's maximum, so that it has that much room before it moves again. The row's largest weight is then as
-// small as 2^-PA_ROOM, which bf16 has the exponents for. fp16 has not: its weights would lose as many bits below the largest (with room 3
-// and one key 23 above 32768 others, their whole share of the result: 3.8e-3 for values around 1), so there the largest weight
-// stays at 1 or more and the point moves as in the kernel for D = 64.
-constexpr float PA_ROOM = 7.f;
-template <int N> __device__ __forceinline__ bool reaches_two(const u32x4 (&pq)[N]) {
-  uint32_t any = 0;
-#pragma unroll
-  for (int g = 0; g < N; ++g) any |= (pq[g][0] | pq[g][1] | pq[g][2]) | pq[g][3];
-  return (any & 0x40004000u) != 0;                          // bit 14: 2 or more, infinite, or NaN
-}
-
 template <int D> struct PaCfg {
   static constexpr int ROWB = D * 2;               // bytes per key row
   static constexpr int TILE_B = PA_BN * ROWB;      // one K or V tile

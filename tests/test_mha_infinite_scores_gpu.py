@@ -1,5 +1,5 @@
 """Attention with an infinite key element: where it makes a score -inf the key has no weight, where +inf the row is NaN. In the first
-key tile and in later ones, whose weights are taken before their maximum is known."""
+key tile and in later ones."""
 import numpy as np
 import pytest
 import torch
