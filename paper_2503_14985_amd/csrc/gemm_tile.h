@@ -403,11 +403,14 @@ __global__ __launch_bounds__(WM* WN * 64 * KS) void gemm_tile_kernel(
     typedef RowStore<Tag, 32, TJ * 32, 8> Rows;
     static_assert(WM * WN * Rows::BYTES <= Cfg::SMEM, "the parking areas fit the LDS");
     float* park = reinterpret_cast<float*>(smem + wave * Rows::BYTES);
+    // With 16 tiles per wavefront, code for both forms of the store is more than the compiler unrolls, and an accumulator with a
+    // run-time index keeps all 256 in memory (4096 x 4096 x 4104 182 -> 1837 us): plain stores there.
+    constexpr bool STREAMS = Cfg::TM * Cfg::TN < 16;
 #pragma unroll
     for (int i = 0; i < Cfg::TM; ++i)
 #pragma unroll
       for (int j0 = 0; j0 < Cfg::TN; j0 += TJ)
-        Rows::run([&](float* lds) {
+        Rows::template run<STREAMS>([&](float* lds) {
 #pragma unroll
           for (int j = 0; j < TJ; ++j)
 #pragma unroll

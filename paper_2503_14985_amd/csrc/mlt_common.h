@@ -275,7 +275,8 @@ __device__ __forceinline__ void store_row8(const f32x4& lo, const f32x4& hi, uin
 template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
   static constexpr int STRIDE = COLS + PAD;
   static constexpr int BYTES = ROWS * STRIDE * 4;
-  template <typename Put>
+  // STREAMS: honours EPI_STREAM
+  template <bool STREAMS = true, typename Put>
   static __device__ __forceinline__ void run(Put&& put, float* park, int lane, int row0, int col0, int M, int N,
                                              uint16_t* __restrict__ C, int64_t ldc, int epi,
                                              const uint16_t* __restrict__ bias) {
@@ -312,7 +313,7 @@ template <typename Tag, int ROWS, int COLS, int PAD> struct RowStore {
               if (col + e < N) cp[(int64_t)i * RPI * ldc + e] = v[e];
         }
       }
-    } else if (epi & EPI_STREAM) {
+    } else if (STREAMS && (epi & EPI_STREAM)) {
       run16<true>(put, park, lane, row0, col0, M, N, C, ldc, epi, bias);
     } else {
       run16<false>(put, park, lane, row0, col0, M, N, C, ldc, epi, bias);
