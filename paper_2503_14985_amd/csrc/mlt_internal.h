@@ -47,13 +47,23 @@ struct GemmArgs {
   uint32_t* counters = nullptr;    // the scratch's kScratchCounters zeros (left as zeros), or null: a second kernel adds the parts
   int parts = 1;
   int forced_parts = 0;            // plan_gemm: 0 = the cost model's choice, 1 / 2 / 4 / 8 = forced
-  // Rows of whole 128-byte lines leave in the non-temporal form. Lines that a kernel leaves dirty in the L2s, up to 32 MB of them,
-  // are written back behind its end, and on the way there they push out operands (bf16, us, plain / non-temporal: 3000 x 4096 x 1024
-  // 29.0 / 24.8, 2048 x 4096 x 1024 20.9 / 17.7, 4000 x 6144 x 1024 58.7 / 53.7, 5410 x 11200 x 512 77.9 / 71.0, 8192^2 x 1024 126 / 117,
-  // 8192^3 750 / 739, 1024 x 2048 x 512 6.9 / 6.7; of 60 such problems two lost, 1700 x 10816 x 3584 by 1 % and 4096 x 8192 x 512 to 2048 by
-  // 1 to 5 %). Rows that share lines lose: 7000 x 7000 x 1024 114 / 121, 14336 x 3000 x 512 61 / 67. An fp32 C that is accumulated
+  // A result of 8 MB up to the 32 MB of the L2s, in rows of whole 128-byte lines, leaves in the non-temporal form. Plain, its lines stay dirty in
+  // the L2s, are written back behind the kernel's end, and push out operands on the way there. What counts is the call and the one
+  // that reads C next (bf16, us, plain / non-temporal: the call; with a product of N x 1024 behind it; with C + R, element by element, behind it):
+  //   4 MB,   1024 x 2048 x 1024    9.4 / 9.5      19.9 / 20.7    13.2 / 13.3     lines that the next call had still found in a cache
+  //   6.4 MB,  777 x 4096 x 4096   36.6 / 35.8     68.0 / 71.3 *  41.2 / 40.9     (* N x 4096)
+  //   12 MB,  6144 x 1024 x 1024   18.5 / 15.4     37.4 / 34.4    26.5 / 26.0
+  //   16 MB,  4096 x 2048 x 1024   22.3 / 19.7     47.2 / 44.7    31.9 / 31.4
+  //   24 MB,  3072 x 4096 x 3072   69.0 / 66.1    103.6 / 101.9   81.3 / 80.0
+  //   32 MB,  2048 x 8192 x 4096   98.8 / 99.1    139.4 / 141.9  113.4 / 115.1
+  //   64 MB,  4096 x 8192 x 2048  108.3 / 106.0   212.2 / 223.2  133.5 / 140.7    the last-level cache does not keep it
+  //   128 MB, 8192 x 8192 x 1024  124.7 / 115.8   233.9 / 240.6  187.3 / 191.3
+  // Rows that share lines lose: 7000 x 7000 x 1024 114 / 121, 14336 x 3000 x 512 61 / 67. An fp32 C that is accumulated
   // into gains nothing (4096 x 4096 x 2048 73.7 / 74.1) and may still be in the last-level cache (3072 x 912 x 416 11.6 / 13.8).
-  bool stream_c() const { return !acc32 && (reinterpret_cast<uintptr_t>(C) & 127) == 0 && ldc % 64 == 0; }
+  bool stream_c() const {
+    const int64_t bytes = M * N * 2;
+    return !acc32 && bytes >= 8 << 20 && bytes < 32 << 20 && (reinterpret_cast<uintptr_t>(C) & 127) == 0 && ldc % 64 == 0;
+  }
   int epi() const { return (acc32 ? 1 : act << 1) | (stream_c() ? 16 : 0); }   // the kernels' epilogue word
   bool fused() const { return bias != nullptr || act != 0; }
 };

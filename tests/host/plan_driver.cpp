@@ -2,6 +2,7 @@
 // XCDs). One problem per line on stdin, one answer per line on stdout:
 //   gemm M N K transB lda ldb fp32_accumulate fused noncontiguous_base   ->  name parts scratch_bytes
 // (noncontiguous_base != 0: A starts on an odd element; "hint1", "hint2" instead of "gemm": with that tiling hint)
+//   store M N ldc C fp32_accumulate   ->  1 if the result leaves in the non-temporal form
 //   mha B H Sq Sk D causal   ->  name ranges
 //   paged B H D block_size max_blocks   ->  ranges dealt_by_length ("paged_split": and a forced number of ranges)
 //   xcdword workgroups causal D mfma_size   ->  what an attention launch passes as its XCD count
@@ -32,6 +33,13 @@ int main() {
       if (fused) g.bias = (const uint16_t*)0x400000;
       const GemmPlan p = plan_gemm(g);
       printf("%s %d %lld\n", p.name, p.parts, (long long)p.scratch_bytes);
+    } else if (!strcmp(op, "store")) {
+      long long M, N, ldc, C;
+      int acc;
+      if (scanf("%lld %lld %lld %lld %d", &M, &N, &ldc, &C, &acc) != 5) return 1;
+      GemmArgs g{};
+      g.M = M; g.N = N; g.K = 1024; g.C = (uint16_t*)(uintptr_t)C; g.ldc = ldc; g.acc32 = acc;
+      printf("%d\n", g.epi() & 16 ? 1 : 0);
     } else if (!strcmp(op, "mha")) {
       long long B, H, Sq, Sk, D;
       int causal;
