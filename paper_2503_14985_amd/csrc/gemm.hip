@@ -326,7 +326,10 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     const int64_t rounds = (wgs + NCU - 1) / NCU, steps = (KT + parts - 1) / parts;
     const int64_t share = wgs < NCU ? wgs * 1000 / NCU : 1000;
     int64_t t_step = parts > 1 ? (bm > 128 ? 425 + 195 * share / 1000 : 206 + 190 * share / 1000) : bm > 128 ? 615 : 345 + 50 * share / 1000;
-    if (bm > 128) t_step -= t_step * (256 - bm) / 512;     // 224 rows 0.94, 192 0.88, 160 0.81 of a step of 256
+    // fewer rows: 224 0.94, 192 0.88, 160 0.81 of a step of 256. (One round of 240 workgroups measures 0.94, 0.91, 0.84. With those
+    // the choice is worse: of 31 problems that they move to other tiles 16 lose, 303 x 11328 x 1280 19.8 / 23.7 us, 2624 x 6912 x 2304 90 / 107,
+    // 822 x 4736 x 1280 17.1 / 21.1, and no more than 5 % is gained, 1532 x 6400 x 14016 276 / 263.)
+    if (bm > 128) t_step -= t_step * (256 - bm) / 512;
     if (g.K % 64) t_step += t_step * 15 / 100;
     const int64_t compute = rounds * (steps * t_step + (bm > 128 ? 6000 : 5700));
     const int64_t base = (g.M + g.N) * g.K * 2 / 5200, need = 6 * NCU / 10;
@@ -345,11 +348,13 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
       // (256 x 128 in 8 parts for one row of tiles only: 138 x 3840 x 14928 40 us, 51 in 4 parts of 128 x 128; but 852 x 920 x
       // 14784 50 in 8, 43 on the other tiles, 2375 x 272 x 16256 67, 60)
       if (g.M > 128 && (parts < 8 || g.M <= 256) && fits(64, 128)) {
-        // the height that multiplies the least padding in the same number of rounds
+        // the height with the least estimate; of equal ones with as many tiles the smaller, which multiplies less padding (150 x 8192 x 28672 in
+        // four parts, bound by the operands' arrival: 110 us on 256 rows, 99 on 160)
+        const auto tiles = [&](int64_t rows) { return (g.M + rows - 1) / rows; };
         Choice kp{GEMM_256X128_KP, parts, 256 * 128, cost_kp(256, parts)};
         for (int v : {GEMM_224X128_KP, GEMM_192X128_KP, GEMM_160X128_KP}) {
           const int64_t t = cost_kp(kp_rows(v), parts);
-          if (t < kp.t) kp = Choice{v, parts, kp_rows(v) * 128, t};
+          if (t < kp.t || (t == kp.t && tiles(kp_rows(v)) == tiles(kp_rows(kp.variant)))) kp = Choice{v, parts, kp_rows(v) * 128, t};
         }
         all[n_all++] = kp;
       }

@@ -2,6 +2,7 @@
 // XCDs). One problem per line on stdin, one answer per line on stdout:
 //   gemm M N K transB lda ldb fp32_accumulate fused noncontiguous_base   ->  name parts scratch_bytes
 // (noncontiguous_base != 0: A starts on an odd element; "hint1", "hint2" instead of "gemm": with that tiling hint)
+//   tile (as gemm)   ->  the same with the rows and columns of its workgroup tile in front
 //   store M N ldc C fp32_accumulate   ->  1 if the result leaves in the non-temporal form
 //   mha B H Sq Sk D causal   ->  name ranges
 //   paged B H D block_size max_blocks   ->  ranges dealt_by_length ("paged_split": and a forced number of ranges)
@@ -18,7 +19,7 @@ using namespace mlt;
 int main() {
   char op[16];
   while (scanf("%15s", op) == 1) {
-    if (!strcmp(op, "gemm") || !strcmp(op, "hint1") || !strcmp(op, "hint2")) {
+    if (!strcmp(op, "gemm") || !strcmp(op, "tile") || !strcmp(op, "hint1") || !strcmp(op, "hint2")) {
       long long M, N, K, lda, ldb;
       int tb, acc, fused, odd, forced = GEMM_AUTO;
       if (scanf("%lld %lld %lld %d %lld %lld %d %d %d", &M, &N, &K, &tb, &lda, &ldb, &acc, &fused, &odd) != 9) return 1;
@@ -32,6 +33,7 @@ int main() {
       g.forced = forced; g.acc32 = acc;
       if (fused) g.bias = (const uint16_t*)0x400000;
       const GemmPlan p = plan_gemm(g);
+      if (!strcmp(op, "tile")) printf("%d %d ", p.bm, p.bn);
       printf("%s %d %lld\n", p.name, p.parts, (long long)p.scratch_bytes);
     } else if (!strcmp(op, "store")) {
       long long M, N, ldc, C;
