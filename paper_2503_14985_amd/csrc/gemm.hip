@@ -219,6 +219,12 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   // an fp32 partial tile to a scratch and a second kernel adds the parts in a fixed order
   // (deterministic; no atomics). Its price in the same units: a launch (4 us) plus writing and
   // reading parts * M * N floats at about 4 TB/s.
+  // An fp32 C that is accumulated into comes and goes when all K steps are done: half of its traffic is added for gemm_kp.hip, and for the two-group 128 x 128
+  // kernel where that has one workgroup per CU (with two, one works while the other waits). The split kernels have their pieces of C in flight from the start,
+  // and the sum of a K split and 256 x 256 do better than that. Over 190 accumulated problems the choice is then 1.4 % behind the best
+  // tile on average, 2.0 % with nothing added and with all of the traffic added to gemm_kp.hip alone (us, 680 x 3200 x 3200 27.4, there
+  // 31.2 on K steps of 128; 2912 x 1344 x 3904 38.9 / 43.8; 2232 x 2752 x 968 27.9, with nothing added 36.7 on 224 x 128).
+  const int64_t c32 = g.acc32 ? g.M * g.N * 4 / 5200 : 0;
   auto cost = [&](int64_t bm, int64_t bn, int64_t t_step, int64_t fixed, int parts, int kgroups) {
     const int64_t wgs = ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * parts;
     const int64_t rounds = (wgs + NCU - 1) / NCU;
@@ -303,10 +309,10 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     // (with at most one tile per CU and K a multiple of 128 the 128-deep form is never slower, also
     // where both are bound by operand arrival: 128 x 28672 x 8192 116 against 134 us)
     if (wgs > NCU || g.K % 128 != 0)
-      all[n_all++] = Choice{GEMM_128_PP16, 1, 128 * 128, own64 > arrive ? own64 : arrive};
+      all[n_all++] = Choice{GEMM_128_PP16, 1, 128 * 128, (own64 > arrive ? own64 : arrive) + (wgs <= NCU ? c32 : 0)};
     if (g.K % 128 == 0) {
       const int64_t own128 = ((wgs + NCU - 1) / NCU) * (KT * 436 + 4300);
-      all[n_all++] = Choice{GEMM_128_PP16_K128, 1, 128 * 128, own128 > arrive ? own128 : arrive};
+      all[n_all++] = Choice{GEMM_128_PP16_K128, 1, 128 * 128, (own128 > arrive ? own128 : arrive) + c32};
     }
   }
   // The kernels with two groups on alternate K steps (gemm_kp.hip). On a full chip their step is bound by what
@@ -334,10 +340,7 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     const int64_t compute = rounds * (steps * t_step + (bm > 128 ? 6000 : 5700));
     const int64_t base = (g.M + g.N) * g.K * 2 / 5200, need = 6 * NCU / 10;
     const int64_t arrive = wgs >= need ? base : base * need / wgs;
-    // an fp32 C comes and goes when all K steps are done, with nothing to hide behind (2232 x 2752 x 968: 30 us on the two-group kernel of
-    // 128 x 128, two workgroups per CU, 38 on 224 x 128)
-    const int64_t c32 = g.acc32 && parts == 1 ? g.M * g.N * 8 / 5200 : 0;
-    return (compute > arrive ? compute : arrive) + c32 + (parts > 1 ? 4000 + 2 * parts * g.M * g.N / 1000 : 0);
+    return (compute > arrive ? compute : arrive) + (parts > 1 ? 4000 + 2 * parts * g.M * g.N / 1000 : c32);
   };
   for (int parts = g.forced_parts > 0 ? g.forced_parts : 1; !small_tiles && parts <= (g.forced_parts > 0 ? g.forced_parts : 8); parts *= 2) {
     // every part keeps at least 8 K steps, and all parts' tiles fit the scratch that mlt_gemm_noalloc has

@@ -21,3 +21,11 @@ def test_heights(plan):  # noqa: F811
                                   (171, 7744, 9408, 1, (192, 128, 4)), (1700, 10816, 3584, 1, (192, 128, 1)), (1024, 8192, 2048, 1, (256, 128, 1)),
                                   (2048, 4096, 4096, 1, (256, 128, 1)), (8192, 8192, 8192, 0, (256, 256, 1))):
         assert tile(plan, M, N, K, transB) == want, (M, N, K)
+
+
+def test_fp32_accumulate(plan):  # noqa: F811
+    """C's traffic counts in every kernel that is alone on its CU and has nothing to hide it behind, not in one of them only."""
+    for M, N, K, transB, want in ((680, 3200, 3200, 0, "nn_128x128x64_w2x2_kp2"), (720, 3968, 4608, 0, "nn_128x128x64_w2x2_kp2"),
+                                  (2912, 1344, 3904, 0, "nn_128x128x64_w2x2_kp2"), (792, 4688, 352, 1, "nt_64x128x64_w2x4"),
+                                  (2232, 2752, 968, 0, "nn_128x128x64_w2x4_pp16"), (4096, 4096, 2048, 0, "nn_256x256x64_w2x4_pp16")):
+        assert plan([gemm_line(M, N, K, transB, acc=1)])[0].split()[0] == "gemm_" + want, (M, N, K)
