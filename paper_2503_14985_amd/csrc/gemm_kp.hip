@@ -260,7 +260,7 @@ __global__ __launch_bounds__(KP_NT, 2) void gemm_kp_kernel(
   }
   if ((KT & 1) == grp) MLT_BARRIER();                     // KT + 1 phases for both groups
 
-  // ---- epilogue: 128 rows at a time both groups park their accumulators in images of their own, and all
+  // ---- epilogue: RPP rows at a time both groups park their accumulators in images of their own, and all
   // threads add the two and store row-contiguous pieces (see RowStore for what that is worth)
   float* const img = reinterpret_cast<float*>(smem);
   constexpr int S = T::S, RPP = T::RPP;

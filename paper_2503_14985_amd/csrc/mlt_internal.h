@@ -48,7 +48,7 @@ struct GemmArgs {
   int parts = 1;
   int forced_parts = 0;            // plan_gemm: 0 = the cost model's choice, 1 / 2 / 4 / 8 = forced
   // A result of 8 MB up to the 32 MB of the L2s, in rows of whole 128-byte lines, leaves in the non-temporal form. Plain, its lines stay dirty in
-  // the L2s, are written back behind the kernel's end, and push out operands on the way there. What counts is the call and the one
+  // the L2s and are written back behind the kernel's end (the same bytes cross the L2 boundary either way). What counts is the call and the one
   // that reads C next (bf16, us, plain / non-temporal: the call; with a product of N x 1024 behind it; with C + R, element by element, behind it):
   //   4 MB,   1024 x 2048 x 1024    9.4 / 9.5      19.9 / 20.7    13.2 / 13.3     lines that the next call had still found in a cache
   //   6.4 MB,  777 x 4096 x 4096   36.6 / 35.8     68.0 / 71.3 *  41.2 / 40.9     (* N x 4096)
