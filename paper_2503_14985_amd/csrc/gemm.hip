@@ -225,11 +225,19 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   // tile on average, 2.0 % with nothing added and with all of the traffic added to gemm_kp.hip alone (us, 680 x 3200 x 3200 27.4, there
   // 31.2 on K steps of 128; 2912 x 1344 x 3904 38.9 / 43.8; 2232 x 2752 x 968 27.9, with nothing added 36.7 on 224 x 128).
   const int64_t c32 = g.acc32 ? g.M * g.N * 4 / 5200 : 0;
+  const bool pp = gemm_pp_ok(g);
+  // GELU in the epilogue takes some 3 us a round on the 128-row tiles (us, without / with it: 2181 x 1792 x 576 two-group 12.0 / 15.0, split 10.9 / 13.6) and
+  // more on the tall ones, whose wavefronts hold more of the result each and have nothing to hide it behind (970 x 7936 x 1088, 256 x 128 20.8 / 30.6, two-group
+  // 128 x 128 in pairs 21.8 / 26.5; 2024 x 8640 x 704, two rounds of 256 x 256, 51.7 / 75.8); 64-row tiles pay in every round (651 x 3392 x 576, three rounds of
+  // 64 x 64 18.8, 128 x 128 12.2). What is more than on the 128-row tiles is added. Without it 1607 x 3840 x 768 took 224 x 128, 25.0 us, 20.7 on 128 x 128;
+  // over 78 such problems the choice was 3.8 % behind the best tile, now 0.6 %. (With K in parts the sum has the GELU, at less than a microsecond.)
+  const bool gelu = g.act == ACT_GELU && pp && g.M > 128 && KT >= 8;
   auto cost = [&](int64_t bm, int64_t bn, int64_t t_step, int64_t fixed, int parts, int kgroups) {
     const int64_t wgs = ((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * parts;
     const int64_t rounds = (wgs + NCU - 1) / NCU;
     const int64_t steps = (KT + parts - 1) / parts;
-    const int64_t compute = rounds * (steps * t_step + fixed);
+    const int64_t act = !gelu || parts > 1 ? 0 : bm == 256 ? rounds * 9000 : bm == 64 ? (rounds - 1) * 1200 : 0;
+    const int64_t compute = rounds * (steps * t_step + fixed) + act;
     // operand arrival: both operands once at 5.2 TB/s, which about 0.6 workgroups per CU already
     // draw (measured 37 GB/s per streaming workgroup: 64 of them 2.4 TB/s, 128 4.2, 224 5.7);
     // beyond one workgroup per CU the last round's idle CUs count (448 workgroups take the time
@@ -255,7 +263,6 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
   // re-reads its operands from L2 less often, which the estimate leaves out: 64 x 8192 x 28672
   // measured 90 us on 64x128 tiles in four parts, 100-110 us on 64x64 tiles in two); for one tile
   // size, the fewer parts unless more parts are estimated more than 5 % faster.
-  const bool pp = gemm_pp_ok(g);
   // t: ns per K step of 64; fixed: ns per round before the first and after the last step, where a
   // fit over K gave one (2048 x 2048 x K on the split 128 x 128 kernel: 0.56 us per step + 2 us)
   struct Cand { int variant; int bm, bn; int64_t t, fixed; int kgroups; };
@@ -337,7 +344,8 @@ GemmPlan plan_gemm(const GemmArgs& g_in) {
     // 822 x 4736 x 1280 17.1 / 21.1, and no more than 5 % is gained, 1532 x 6400 x 14016 276 / 263.)
     if (bm > 128) t_step -= t_step * (256 - bm) / 512;
     if (g.K % 64) t_step += t_step * 15 / 100;
-    const int64_t compute = rounds * (steps * t_step + (bm > 128 ? 6000 : 5700));
+    const int64_t act = gelu && parts == 1 && bm > 128 ? rounds * (34 * bm - 3000) : 0;
+    const int64_t compute = rounds * (steps * t_step + (bm > 128 ? 6000 : 5700)) + act;
     const int64_t base = (g.M + g.N) * g.K * 2 / 5200, need = 6 * NCU / 10;
     const int64_t arrive = wgs >= need ? base : base * need / wgs;
     return (compute > arrive ? compute : arrive) + (parts > 1 ? 4000 + 2 * parts * g.M * g.N / 1000 : c32);

@@ -1,7 +1,7 @@
 // Prints what the library's planning functions choose, without a device (they then assume 256 CUs, 8
 // XCDs). One problem per line on stdin, one answer per line on stdout:
 //   gemm M N K transB lda ldb fp32_accumulate fused noncontiguous_base   ->  name parts scratch_bytes
-// (noncontiguous_base != 0: A starts on an odd element; "hint1", "hint2" instead of "gemm": with that tiling hint)
+// (fused: 1 bias, 2 and ReLU, 3 and GELU; noncontiguous_base != 0: A starts on an odd element; "hint1", "hint2" instead of "gemm": with that tiling hint)
 //   tile (as gemm)   ->  the same with the rows and columns of its workgroup tile in front
 //   store M N ldc C fp32_accumulate   ->  1 if the result leaves in the non-temporal form
 //   mha B H Sq Sk D causal   ->  name ranges
@@ -32,6 +32,7 @@ int main() {
       if (!strcmp(op, "hint2")) forced = GEMM_256_W1X8;
       g.forced = forced; g.acc32 = acc;
       if (fused) g.bias = (const uint16_t*)0x400000;
+      g.act = fused > 1 ? fused - 1 : 0;
       const GemmPlan p = plan_gemm(g);
       if (!strcmp(op, "tile")) printf("%d %d ", p.bm, p.bn);
       printf("%s %d %lld\n", p.name, p.parts, (long long)p.scratch_bytes);

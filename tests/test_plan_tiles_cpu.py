@@ -29,3 +29,13 @@ def test_fp32_accumulate(plan):  # noqa: F811
                                   (2912, 1344, 3904, 0, "nn_128x128x64_w2x2_kp2"), (792, 4688, 352, 1, "nt_64x128x64_w2x4"),
                                   (2232, 2752, 968, 0, "nn_128x128x64_w2x4_pp16"), (4096, 4096, 2048, 0, "nn_256x256x64_w2x4_pp16")):
         assert plan([gemm_line(M, N, K, transB, acc=1)])[0].split()[0] == "gemm_" + want, (M, N, K)
+
+
+def test_gelu(plan):  # noqa: F811
+    """Problems of few K steps that the tall tiles take without GELU and not with it, and one of many that they take with it too."""
+    for M, N, K, transB, plain, gelu in ((1607, 3840, 768, 1, "nt_256x128x64_w2x2_kp2", "nt_128x128x64_w2x4_pp16"),
+                                         (805, 6272, 704, 1, "nt_256x128x64_w2x2_kp2", "nt_128x128x64_w2x4_pp16"),
+                                         (5274, 960, 768, 1, "nt_256x128x64_w2x2_kp2", "nt_128x128x64_w2x4_pp16"),
+                                         (2024, 8640, 704, 0, "nn_256x256x64_w2x4_pp16", "nn_128x128x64_w2x4_pp16"),
+                                         (2048, 4096, 4096, 1, "nt_256x128x64_w2x2_kp2", "nt_256x128x64_w2x2_kp2")):
+        assert [x.split()[0] for x in plan([gemm_line(M, N, K, transB, fused=f) for f in (1, 3)])] == ["gemm_" + plain, "gemm_" + gelu], (M, N, K)
